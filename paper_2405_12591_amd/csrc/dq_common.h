@@ -85,26 +85,21 @@ __device__ inline uint16_t f2h_rne(float x) {
   return __builtin_bit_cast(uint16_t, (_Float16)x);
 }
 
-// fp64 -> fp16 bits with a single round-to-nearest-even; saturating variant clamps to +-65504.
+// fp64 -> fp16 bits with a single round-to-nearest-even; saturating variant clamps to +-65504.  The value
+// is first rounded to odd in fp32 (13 more bits than fp16), which makes the second rounding land
+// where a single one would.
 __device__ inline uint16_t f64_to_f16_rne(double x, bool saturate, bool* saturated) {
-  const uint64_t bits = __builtin_bit_cast(uint64_t, x);
-  const uint16_t sign = (uint16_t)((bits >> 48) & 0x8000u);
-  const double ax = __builtin_fabs(x);
-  if (!(ax == ax)) return (uint16_t)(sign | 0x7E00u);
-  if (ax >= 65520.0) {  // rounds to infinity
+  const float f = (float)x;
+  const double e = x - (double)f;                       // what the first rounding dropped
+  uint32_t bits = __builtin_bit_cast(uint32_t, f);
+  const bool away = (e > 0.0) == (f > 0.f);             // x lies further from zero than f
+  if (e != 0.0 && f != 0.f && !(bits & 1u)) bits += away ? 1u : 0xFFFFFFFFu;
+  const float odd = __builtin_bit_cast(float, bits);
+  if (saturate && __builtin_fabsf(odd) >= 65520.f) {    // rounds to infinity
     if (saturated) *saturated = true;
-    return (uint16_t)(sign | (saturate ? 0x7BFFu : 0x7C00u));
+    return (uint16_t)(((bits >> 16) & 0x8000u) | 0x7BFFu);
   }
-  if (ax < 6.103515625e-05) {  // below 2^-14: subnormal grid of 2^-24
-    const double r = __builtin_rint(ax * 16777216.0);
-    return (uint16_t)(sign | (uint16_t)r);
-  }
-  const int e = (int)((bits >> 52) & 0x7FF) - 1023;  // floor(log2(ax)), -14 <= e <= 15
-  // 2^(10-e) as a double, exact scaling so that one fp16 ulp becomes 1.0
-  const double scale = __builtin_bit_cast(double, (uint64_t)(1023 + 10 - e) << 52);
-  const double r = __builtin_rint(ax * scale);  // in [1024, 2048]
-  const uint32_t h = ((uint32_t)(e + 15) << 10) + ((uint32_t)r - 1024u);
-  return (uint16_t)(sign | h);
+  return f2h_rne(odd);
 }
 
 }  // namespace dq

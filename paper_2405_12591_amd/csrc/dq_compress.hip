@@ -592,8 +592,8 @@ __global__ __launch_bounds__(64) void decompose_kernel(dq_format fmt, dq_cache c
 
 // ------------------------------------------------------------------------------------------
 // Fast decomposition for the common shape d = 128, j1 = 16, j2 = 8: one wave per block, the two
-// dense contractions (Gram matrix, projection) on the fp64 matrix cores, the Jacobi solver with the
-// 16 x 16 matrices cut into 64 blocks of 2 x 2, one per lane.
+// dense contractions (Gram matrix, projection) on the fp64 matrix cores, the eigen-solver in
+// registers.
 //
 // v_mfma_f64_16x16x4_f64 operand layout (one double per lane for A and B, four for D):
 //   A[m][k]: lane l -> m = l % 16, k = l / 16;  B[k][n]: lane l -> n = l % 16, k = l / 16;
@@ -625,11 +625,255 @@ __device__ __forceinline__ void jacobi_rotation(double app, double aqq, double a
   big = live && apq * apq > kSettled2 * fabs(app * aqq);
 }
 
-// Pair `k` (0..7) of round `round` (0..14) of the round-robin schedule over 16 indices.
-__device__ __forceinline__ void pair16(int round, int k, int& p, int& q) {
-  if (k == 0) { p = 15; q = round; return; }
-  p = round + k; if (p >= 15) p -= 15;
-  q = round - k; if (q < 0) q += 15;
+// ---- eigen-decomposition of the 16 x 16 Gram matrix: one-sided Jacobi in registers ----
+// Columns of G are rotated against each other until they are orthogonal: G Q = U Lambda, so the
+// normalised columns are the eigenvectors and the columns' norms the eigenvalues; no matrix of
+// accumulated rotations is needed.  A lane holds a pair of columns (x, y) and derives their
+// rotation once; eight lanes hold the sixteen columns.  ROWS of the sixteen rows sit in a lane:
+// ROWS = 2 spreads one block over the wave (lane = pair + 8 * row group; the shortest chain),
+// ROWS = 16 works eight blocks per wave (lane = pair + 8 * block; no sum over lanes, every
+// rotation derived once per block).  Between rounds the y columns move to another lane of the eight
+// by a data-parallel-primitive pattern, so a round touches no LDS at all: on one wave per SIMD, which
+// issues an instruction every 5.3 cycles whatever it is, a round of about 55 instructions takes 320
+// cycles, against 550 for a two-sided iteration in LDS (100 instructions, two LDS round trips and a lane
+// exchange through LDS).  Whole call on one block per compute unit (256 blocks): 40 -> 30 us; on 320: 61
+// -> 38 us (four waves per block instead of two in the latter, now that the solver is shorter).
+// All sums over rows run over the same tree whatever ROWS is, so every build of the kernels that
+// calls this gets the same bits.
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppXor3 = 0x1B, kDppXor7 = 0x141, kDppXor8 = 0x128;
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double v) {
+  u32x2 w = __builtin_bit_cast(u32x2, v);
+  w.x = (unsigned)__builtin_amdgcn_update_dpp(0, (int)w.x, CTRL, 0xF, 0xF, true);
+  w.y = (unsigned)__builtin_amdgcn_update_dpp(0, (int)w.y, CTRL, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, w);
+}
+// v of this lane plus v of the lane 16 (32) further on or back
+__device__ __forceinline__ double add_xor16(double v) {
+  const u32x2 w = __builtin_bit_cast(u32x2, v);
+  const auto lo = __builtin_amdgcn_permlane16_swap(w.x, w.x, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(w.y, w.y, false, false);
+  return __builtin_bit_cast(double, u32x2{lo[0], hi[0]}) + __builtin_bit_cast(double, u32x2{lo[1], hi[1]});
+}
+__device__ __forceinline__ double add_xor32(double v) {
+  const u32x2 w = __builtin_bit_cast(u32x2, v);
+  const auto lo = __builtin_amdgcn_permlane32_swap(w.x, w.x, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(w.y, w.y, false, false);
+  return __builtin_bit_cast(double, u32x2{lo[0], hi[0]}) + __builtin_bit_cast(double, u32x2{lo[1], hi[1]});
+}
+
+// sum over the sixteen rows of u * v: products in pairs of rows, then a balanced tree over the
+// eight pairs, whose upper levels are lanes when ROWS < 16
+template <int ROWS>
+__device__ __forceinline__ double dot16(const double (&u)[ROWS], const double (&v)[ROWS]) {
+  double s[ROWS / 2];
+#pragma unroll
+  for (int i = 0; i < ROWS / 2; ++i) s[i] = fma(u[2 * i + 1], v[2 * i + 1], u[2 * i] * v[2 * i]);
+#pragma unroll
+  for (int n = ROWS / 4; n >= 1; n >>= 1)
+#pragma unroll
+    for (int i = 0; i < n; ++i) s[i] = s[2 * i] + s[2 * i + 1];
+  double r = s[0];
+  if (ROWS <= 8) r += dpp_d<kDppXor8>(r);
+  if (ROWS <= 4) r = add_xor16(r);
+  if (ROWS <= 2) r = add_xor32(r);
+  return r;
+}
+
+template <int ROWS>
+struct Jacobi16 {
+  double x[ROWS], y[ROWS];   // the lane's rows of its two columns
+  double a, b;               // their squared norms
+  int ix, iy;                // which columns they are
+
+  template <int CTRL>
+  __device__ __forceinline__ void move() {   // the y columns to lane ^ mask
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) y[i] = dpp_d<CTRL>(y[i]);
+    b = dpp_d<CTRL>(b);
+    iy = __builtin_amdgcn_update_dpp(0, iy, CTRL, 0xF, 0xF, true);
+  }
+  // The lanes whose `upper` is false collect the x columns of both partners (lane, lane ^ mask), the
+  // others the y columns.
+  template <int CTRL>
+  __device__ __forceinline__ void split(bool upper) {
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+      const double xo = dpp_d<CTRL>(x[i]), yo = dpp_d<CTRL>(y[i]);
+      x[i] = upper ? yo : x[i];
+      y[i] = upper ? y[i] : xo;
+    }
+    const double ao = dpp_d<CTRL>(a), bo = dpp_d<CTRL>(b);
+    a = upper ? bo : a;
+    b = upper ? b : ao;
+    const int ixo = __builtin_amdgcn_update_dpp(0, ix, CTRL, 0xF, 0xF, true);
+    const int iyo = __builtin_amdgcn_update_dpp(0, iy, CTRL, 0xF, 0xF, true);
+    ix = upper ? iyo : ix;
+    iy = upper ? iy : ixo;
+  }
+
+  // Make the pair's columns orthogonal.  tan of the angle is 2 x.y over d + sign(d) sqrt(d^2 + (2 x.y)^2)
+  // with d the difference of the squared norms; hardware estimates (about 1e-7) do for it: what is
+  // left of x.y shrinks by that factor and the next sweep deals with it.  cos gets a Newton step, so that
+  // rotations stay orthogonal to 1e-14.  The tiny addend keeps a pair of zero columns (0 / 0) from
+  // producing a NaN and is far below any pair that matters.  TEST: report whether the pair was
+  // still apart (the first sweeps do not ask).
+  template <bool TEST>
+  __device__ __forceinline__ void rotate(double floor_ab, bool& unsettled) {
+    const double g = dot16<ROWS>(x, y);
+    if (TEST) unsettled |= (g * g > kSettled2 * (a * b)) && (fmin(a, b) > floor_ab);
+    const double d = b - a, g2 = g + g;
+    const double root = __builtin_amdgcn_sqrt(fma(g2, g2, fma(d, d, 1e-240)));
+    const double t = g2 * __builtin_amdgcn_rcp(d + copysign(root, d));
+    const double w = fma(t, t, 1.0);
+    const double r0 = __builtin_amdgcn_rsq(w);
+    const double c = r0 * fma(-0.5 * w, r0 * r0, 1.5);
+    const double tc = t * c;
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+      const double xi = x[i], yi = y[i];
+      x[i] = fma(-tc, yi, c * xi);
+      y[i] = fma(tc, xi, c * yi);
+    }
+    a = fma(-t, g, a);
+    b = fma(t, g, b);
+  }
+
+  // Fifteen rounds of eight disjoint pairs: x columns against y columns, then the two halves of each
+  // among themselves, and so on; every exchange is one data-parallel-primitive pattern.  Of the orders
+  // that leave the columns where the next sweep can start from them, this one converges soonest (5.9
+  // sweeps on the synthetic workloads' blocks; with the first eight rounds the other way round, 6.9).
+  template <bool TEST>
+  __device__ __forceinline__ void sweep(int j, double floor_ab, bool& unsettled) {
+    move<kDppXor7>(); rotate<TEST>(floor_ab, unsettled);
+    move<kDppXor3>(); rotate<TEST>(floor_ab, unsettled);
+    move<kDppXor1>(); rotate<TEST>(floor_ab, unsettled);
+    move<kDppXor3>(); rotate<TEST>(floor_ab, unsettled);
+    move<kDppXor7>(); rotate<TEST>(floor_ab, unsettled);
+    move<kDppXor3>(); rotate<TEST>(floor_ab, unsettled);
+    move<kDppXor1>(); rotate<TEST>(floor_ab, unsettled);
+    move<kDppXor3>(); rotate<TEST>(floor_ab, unsettled);
+    split<kDppXor7>((j & 4) != 0); rotate<TEST>(floor_ab, unsettled);
+    move<kDppXor1>(); rotate<TEST>(floor_ab, unsettled);
+    move<kDppXor2>(); rotate<TEST>(floor_ab, unsettled);
+    move<kDppXor1>(); rotate<TEST>(floor_ab, unsettled);
+    split<kDppXor3>((j & 2) != 0); move<kDppXor1>(); rotate<TEST>(floor_ab, unsettled);
+    move<kDppXor1>(); rotate<TEST>(floor_ab, unsettled);
+    split<kDppXor1>((j & 1) != 0); rotate<TEST>(floor_ab, unsettled);
+  }
+
+  // Called with x = column j, y = column j + 8 of the matrix, j = lane % 8.  Returns the sweeps used.  All
+  // eight lanes of a block (and, for ROWS < 16, all its row groups) leave together.
+  __device__ __forceinline__ int run() {
+    const int lane = threadIdx.x & 63, j = lane & 7;
+    ix = j; iy = j + 8;
+    a = dot16<ROWS>(x, x);
+    b = dot16<ROWS>(y, y);
+    // columns of eigenvalues below 1e-14 of the largest are dropped later: whether they have settled
+    // does not matter
+    double tr = a + b;
+    tr += dpp_d<kDppXor1>(tr);
+    tr += dpp_d<kDppXor2>(tr);
+    tr += dpp_d<kDppXor7>(tr);
+    const double floor_ab = tr * 1e-28;
+    bool unsettled = true;
+    int sweeps = 0;
+    // no block with anything off the diagonal settles in three sweeps: they do not test
+    while (sweeps < 3) {
+      ++sweeps;
+      sweep<false>(j, floor_ab, unsettled);
+      a = dot16<ROWS>(x, x);
+      b = dot16<ROWS>(y, y);
+    }
+    while (unsettled && sweeps < 16) {
+      ++sweeps;
+      unsettled = false;
+      sweep<true>(j, floor_ab, unsettled);
+      a = dot16<ROWS>(x, x);
+      b = dot16<ROWS>(y, y);
+      // every pair of this sweep was within 3e-5 of orthogonal when it was rotated, so the sweep (one
+      // more quadratic step) has left them near 1e-9, two orders under the fp32 rounding of T_L
+      const unsigned long long open = __ballot(unsettled);
+      if (ROWS == 2) {
+        unsettled = open != 0;
+      } else {
+        constexpr int LPB = 128 / (ROWS == 2 ? 4 : ROWS);   // lanes per block
+        unsettled = ((open >> (lane & ~(LPB - 1))) & ((1ull << LPB) - 1)) != 0;
+      }
+    }
+    return sweeps;
+  }
+
+  // The columns' places in descending order of eigenvalue, and the factors of the two results: column
+  // times rx (ry) is the column of T_S = U Sigma, times rx^3 the row of W = Sigma^-1 U^T; 0 if the
+  // direction is dropped.  `lam`: sixteen doubles of LDS of this block.  PAIR: the columns of each half
+  // are ranked among themselves.
+  template <bool PAIR>
+  __device__ __forceinline__ void order(double* lam, int& px, int& py, double& rx, double& ry, double& lx, double& ly) {
+    const int lane = threadIdx.x & 63;
+    lx = a > 0.0 ? a * fast_rsqrt(a) : a;   // (a NaN stays one)
+    ly = b > 0.0 ? b * fast_rsqrt(b) : b;
+    lam[ix] = lx;
+    lam[iy] = ly;
+    __builtin_amdgcn_wave_barrier();
+    int places = 0;                        // of x in the low half, of y in the high half
+    double mx = 0.0, my = 0.0;
+    const int row0 = first_row(lane);
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {       // the lane's share of the sixteen columns
+      const int s = row0 + i;
+      const double o = lam[s];
+      const bool sx = !PAIR || (s >> 3) == (ix >> 3), sy = !PAIR || (s >> 3) == (iy >> 3);
+      places += (sx && (o > lx || (o == lx && s < ix))) ? 1 : 0;
+      places += (sy && (o > ly || (o == ly && s < iy))) ? 0x10000 : 0;
+      mx = sx ? fmax(mx, o) : mx;
+      if (PAIR) my = sy ? fmax(my, o) : my;
+    }
+    if (ROWS <= 8) {
+      places += __builtin_amdgcn_update_dpp(0, places, kDppXor8, 0xF, 0xF, true);
+      mx = fmax(mx, dpp_d<kDppXor8>(mx));
+      if (PAIR) my = fmax(my, dpp_d<kDppXor8>(my));
+    }
+    if (ROWS <= 4) {
+      places += __shfl_xor(places, 16);
+      mx = fmax(mx, __shfl_xor(mx, 16));
+      if (PAIR) my = fmax(my, __shfl_xor(my, 16));
+    }
+    if (ROWS <= 2) {
+      places += __shfl_xor(places, 32);
+      mx = fmax(mx, __shfl_xor(mx, 32));
+      if (PAIR) my = fmax(my, __shfl_xor(my, 32));
+    }
+    if (!PAIR) my = mx;
+    px = (places & 0xFFFF) + (PAIR ? (ix & 8) : 0);
+    py = (places >> 16) + (PAIR ? (iy & 8) : 0);
+    const bool kx = lx > 1e-12 * mx && lx > 0.0, ky = ly > 1e-12 * my && ly > 0.0;
+    rx = kx ? fast_rsqrt(lx) : 0.0;
+    ry = ky ? fast_rsqrt(ly) : 0.0;
+    if (!kx) lx = 0.0;
+    if (!ky) ly = 0.0;
+  }
+  static __device__ __forceinline__ int first_row(int lane) { return ROWS == 16 ? 0 : ROWS * ((lane >> 3) & (16 / ROWS - 1)); }
+};
+
+// W[r][b1] from the solver's registers (lam2[r]: the eigenvalue, 0 if the direction is dropped)
+template <int ROWS, bool PAIR, int LD>
+__device__ __forceinline__ void store_factors(Jacobi16<ROWS>& jac, double* lam, double* lam2, double* W) {
+  int px, py;
+  double rx, ry, lx, ly;
+  jac.template order<PAIR>(lam, px, py, rx, ry, lx, ly);
+  const int row0 = jac.first_row(threadIdx.x & 63);
+  lam2[px] = lx;
+  lam2[py] = ly;
+  const double fx = rx * rx * rx, fy = ry * ry * ry;
+#pragma unroll
+  for (int i = 0; i < ROWS; ++i) {
+    W[px * LD + row0 + i] = rx > 0.0 ? jac.x[i] * fx : 0.0;
+    W[py * LD + row0 + i] = ry > 0.0 ? jac.y[i] * fy : 0.0;
+  }
+  __builtin_amdgcn_wave_barrier();
 }
 
 // NWV waves per block: the two contractions are split over the waves by token, the eigen-solver
@@ -731,7 +975,7 @@ __global__ __launch_bounds__(64 * NWV, LEAN ? ((PAIR || N3) ? 3 : 4) : 1) void d
   static_assert(!LEAN || NWV == 1, "the lean build is one wave per block");
   static_assert(!N3 || (LEAN && !PAIR && QB != 0), "three tensors: lean build with the quantizer, d = 128");
   constexpr int kMat = j1 * ld;                              // doubles per 16 x 16 matrix (padded rows)
-  constexpr int kMatBytes = (3 + (NWV > 1 ? NWV - 1 : 1)) * kMat * (int)sizeof(double);
+  constexpr int kMatBytes = (2 + NWV - 1) * kMat * (int)sizeof(double);
   // fused quantizer: one byte per element of QT token rows, then the value layout's staging
   // (a pair: one such area per head, of 64 channels each)
   constexpr int QT = LEAN ? 32 : kTileTokens;                // rows quantized and packed at a time
@@ -742,12 +986,10 @@ __global__ __launch_bounds__(64 * NWV, LEAN ? ((PAIR || N3) ? 3 : 4) : 1) void d
   constexpr int kPoolBytes = LEAN ? (kMatBytes > kFieldBytes ? kMatBytes : kFieldBytes) : kMatBytes + kFieldBytes;
   __shared__ __attribute__((aligned(16))) unsigned char pool[kPoolBytes];
   double* const A = reinterpret_cast<double*>(pool);
-  double* const V = A + kMat;
-  double* const W = V + kMat;
+  double* const W = A + kMat;
   double* const P = W + kMat;                                // Gram partials of the other waves
   uint8_t* const lds_u = LEAN ? pool : pool + kMatBytes;
-  __shared__ double lam[j1], sigma[j1];
-  __shared__ int order[j1];
+  __shared__ double lam[j1], lam2[j1];
 
   // ---- Gram matrix G[p][q] = sum_{t, b2} X[t, p*8+b2] X[t, q*8+b2] ----
   // A and B operand of one MFMA are the same register: lane (b1 = l%16, k = l/16) holds
@@ -791,8 +1033,6 @@ __global__ __launch_bounds__(64 * NWV, LEAN ? ((PAIR || N3) ? 3 : 4) : 1) void d
       const double sum = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
       dst[row * ld + col] = (PAIR && (row >> 3) != (col >> 3)) ? 0.0 : sum;   // no products across heads
     }
-    for (int idx = threadIdx.x; idx < j1 * j1; idx += 64 * NWV)
-      V[(idx >> 4) * ld + (idx & 15)] = ((idx >> 4) == (idx & 15)) ? 1.0 : 0.0;
   }
   __syncthreads();
   if (NWV > 1) {
@@ -807,104 +1047,35 @@ __global__ __launch_bounds__(64 * NWV, LEAN ? ((PAIR || N3) ? 3 : 4) : 1) void d
   }
 
   if (wv == solver) {
-    // ---- parallel cyclic Jacobi: 15 rounds of 8 disjoint rotations per sweep ----
-    // Lane (I, J) owns the 2 x 2 block rows(pair I) x columns(pair J) of the matrix and rows
-    // {2I, 2I+1} x columns(pair J) of the accumulated rotations; it derives the rotation of pair I
-    // from that pair's three entries and takes the one of pair J from lane (J, I).
-    const int I = l >> 3, J = l & 7;
-    // (a pair: each head's entries are measured against its own trace)
-    double trace_lo = 0.0, trace_hi = 0.0;
+    // lane (pair j = l % 8, row group l / 8) holds rows 2 (l / 8) + i of columns j and j + 8
+    Jacobi16<2> jac;
 #pragma unroll
-    for (int i = 0; i < j1 / 2; ++i) { trace_lo += A[i * ld + i]; trace_hi += A[(i + 8) * ld + i + 8]; }
-    const double floor_lo = fmax((PAIR ? trace_lo : trace_lo + trace_hi) * 1e-17, 1e-300);
-    const double floor_hi = PAIR ? fmax(trace_hi * 1e-17, 1e-300) : floor_lo;
-    int sweeps = 0;
-    for (int sweep = 0; sweep < 16; ++sweep) {
-      ++sweeps;
-      bool unsettled = false;
-      auto one_round = [&](const int round) __attribute__((always_inline)) {
-        int p, q, u, v;
-        pair16(round, I, p, q);
-        pair16(round, J, u, v);
-        const double app = A[p * ld + p], aqq = A[q * ld + q], apq = A[p * ld + q];
-        const double b00 = A[p * ld + u], b01 = A[p * ld + v], b10 = A[q * ld + u], b11 = A[q * ld + v];
-        const int r0 = 2 * I * ld, r1 = r0 + ld;
-        const double v00 = V[r0 + u], v01 = V[r0 + v], v10 = V[r1 + u], v11 = V[r1 + v];
-        // the rotation of the row pair is computed here; that of the column pair J is the row-pair
-        // rotation of the transposed lane (J, I)
-        double cI, sI;
-        bool big;
-        jacobi_rotation(app, aqq, apq, (PAIR && (p >> 3)) ? floor_hi : floor_lo, cI, sI, big);
-        const double cJ = __shfl(cI, 8 * J + I), sJ = __shfl(sI, 8 * J + I);
-        unsettled |= big;
-        // Jm has Jm[p][p] = c, Jm[p][q] = s, Jm[q][p] = -s, Jm[q][q] = c;  A' = Jm^T A Jm,  V' = V Jm
-        const double x00 = b00 * cJ - b01 * sJ, x01 = b00 * sJ + b01 * cJ;
-        const double x10 = b10 * cJ - b11 * sJ, x11 = b10 * sJ + b11 * cJ;
-        A[p * ld + u] = cI * x00 - sI * x10;
-        A[p * ld + v] = cI * x01 - sI * x11;
-        A[q * ld + u] = sI * x00 + cI * x10;
-        A[q * ld + v] = sI * x01 + cI * x11;
-        V[r0 + u] = v00 * cJ - v01 * sJ;
-        V[r0 + v] = v00 * sJ + v01 * cJ;
-        V[r1 + u] = v10 * cJ - v11 * sJ;
-        V[r1 + v] = v10 * sJ + v11 * cJ;
-        // One wave: its LDS operations execute in program order, so the next round's reads see these
-        // writes without waiting for them; the compiler only has to keep the order.
-        __builtin_amdgcn_wave_barrier();
-      };
-      if constexpr (LEAN) {
-        // (the round number stays a run-time value: fifteen rounds' worth of addresses would cost
-        // the registers that let several blocks share a SIMD)
-#pragma unroll 1
-        for (int round = 0; round < 15; ++round) one_round(round);
-      } else {
-        // unrolled: the LDS addresses of a round depend only on the lane and are computed once
-#pragma unroll
-        for (int round = 0; round < 15; ++round) one_round(round);
-      }
-      // every entry rotated in this sweep was below 3e-5 of its diagonal pair, so the sweep (one
-      // more quadratic step) has left them near 1e-9, two orders under the fp32 rounding of T_L
-      if (!__any(unsettled)) break;
+    for (int i = 0; i < 2; ++i) {
+      jac.x[i] = A[(2 * (l >> 3) + i) * ld + (l & 7)];
+      jac.y[i] = A[(2 * (l >> 3) + i) * ld + (l & 7) + 8];
     }
+    const int sweeps = jac.run();
 
     // ---- singular values, ordering, small tensor ----
-    if (l < j1) lam[l] = A[l * ld + l];
-    __builtin_amdgcn_wave_barrier();
-    if (l < j1) {
-      // (a pair: every head's eigenvalues are ranked among themselves and stay in its half)
-      int rank = 0;
-      const double me = lam[l];
-      for (int s = 0; s < j1; ++s)
-        rank += (!PAIR || (s >> 3) == (l >> 3)) && ((lam[s] > me) || (lam[s] == me && s < l));
-      order[(PAIR ? (l & 8) : 0) + rank] = l;
-    }
-    __builtin_amdgcn_wave_barrier();
-    if (l < j1) {
-      const double lmax = fmax(lam[order[PAIR ? (l & 8) : 0]], 0.0);
-      const double lv = lam[order[l]];
-      sigma[l] = (lv > 1e-12 * lmax && lv > 0.0) ? sqrt(lv) : 0.0;
-    }
-    __builtin_amdgcn_wave_barrier();
+    store_factors<2, PAIR, ld>(jac, lam, lam2, W);
     const long blk = (long)bh * g.NB + slot;
     uint16_t* small = (which ? cache.v_small : cache.k_small) + blk * g.small_per_block;
     bool sat = false;
     for (int idx = l; idx < j1 * j1; idx += 64) {
       // neighbouring lanes write neighbouring entries of the stored array (keys are stored transposed)
       const int b1 = which ? idx >> 4 : idx & 15, r = which ? idx & 15 : idx >> 4;
-      const double uv = V[b1 * ld + order[r]];
-      const double sg = sigma[r];
-      W[r * ld + b1] = sg > 0.0 ? uv / sg : 0.0;
+      const double ts = W[r * ld + b1] * lam2[r];   // T_S = U Sigma = W Lambda
       if (PAIR) {
         // the heads' 8 x 8 small tensors are the diagonal blocks (the second head's blocks lie NB
         // blocks further on in the cache); the entries off the diagonal are zero and go nowhere
         if ((b1 >> 3) == (r >> 3)) {
-          const uint16_t hb = f64_to_f16_rne(uv * sg, true, &sat);
+          const uint16_t hb = f64_to_f16_rne(ts, true, &sat);
           uint16_t* sm = small + (long)(b1 >> 3) * g.NB * g.small_per_block;
           if (which) sm[(b1 & 7) * 8 + (r & 7)] = hb;
           else sm[(r & 7) * 8 + (b1 & 7)] = hb;
         }
       } else {
-        const uint16_t hb = f64_to_f16_rne(uv * sg, true, &sat);
+        const uint16_t hb = f64_to_f16_rne(ts, true, &sat);
         if (which) small[b1 * j1 + r] = hb;   // values: natural [b1][r]
         else small[r * j1 + b1] = hb;         // keys: transposed [r][b1]
       }
@@ -1430,6 +1601,16 @@ extern "C" int32_t dq_quantize_pack(const dq_format* fmt, const float* t_large, 
   return DQ_OK;
 }
 
+// Waves per block of the tuned decomposition kernel for a launch of `groups` workgroups (0: the lean
+// build, one wave per block).  The two contractions and the quantizer shrink with the waves, the
+// solver runs in one of them; beyond two workgroups per compute unit the waves of different blocks
+// queue for the SIMDs.  Measured, us per call with four / two waves (4-bit, d = 128): 256 blocks
+// 30 / 38, 512 blocks 40 / 51, 768 blocks 63 / 53, 1024 blocks 76 / 61.
+static int waves_per_block(int groups, int want_waves) {
+  if (want_waves) return want_waves == 1 ? 0 : want_waves;
+  return groups <= 512 ? 4 : groups <= 1024 ? 2 : 0;
+}
+
 static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16_t* k_new,
                              const uint16_t* v_new, int32_t t_new, int n_blocks, const int32_t* blk_idx,
                              const int32_t* n_valid, void* workspace, size_t workspace_bytes, uint32_t flags,
@@ -1523,8 +1704,7 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
                          *cache, job, large_ws, unit_status, status);                                           \
   } while (0)
     const int fused_groups = pair_heads ? units / 2 : units;
-    int fused_waves = fused_groups <= 256 ? 4 : fused_groups <= 512 ? 2 : fused_groups <= 1024 ? 1 : 0;   // 0: the lean build
-    if (want_waves) fused_waves = want_waves;
+    int fused_waves = waves_per_block(fused_groups, want_waves);
     if (fused_waves == 0) {
       if (fmt->bits == 2) DQ_LAUNCH_FUSED_LEAN(2);
       else if (fmt->bits == 4) DQ_LAUNCH_FUSED_LEAN(4);
@@ -1533,14 +1713,10 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
       if (fmt->bits == 2) DQ_LAUNCH_FUSED(4, 2);
       else if (fmt->bits == 4) DQ_LAUNCH_FUSED(4, 4);
       else DQ_LAUNCH_FUSED(4, 8);
-    } else if (fused_waves == 2) {
+    } else {
       if (fmt->bits == 2) DQ_LAUNCH_FUSED(2, 2);
       else if (fmt->bits == 4) DQ_LAUNCH_FUSED(2, 4);
       else DQ_LAUNCH_FUSED(2, 8);
-    } else {
-      if (fmt->bits == 2) DQ_LAUNCH_FUSED(1, 2);
-      else if (fmt->bits == 4) DQ_LAUNCH_FUSED(1, 4);
-      else DQ_LAUNCH_FUSED(1, 8);
     }
 #undef DQ_LAUNCH_FUSED
 #undef DQ_LAUNCH_FUSED_LEAN
@@ -1561,8 +1737,6 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
       else return DQ_EINVAL;
     }
   } else if (((fmt->head_dim == 128 && fmt->j1 == 16) || pair_heads) && !force_general) {
-    // At most one workgroup per compute unit (256 on the chip) gets more waves per block: the
-    // eigen-solver wave is issue-bound and slows down when two of them share a SIMD.
 #define DQ_LAUNCH_D16(N_)                                                                                     \
   do {                                                                                                        \
     if (pair_heads)                                                                                           \
@@ -1573,8 +1747,7 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
                          job, large_ws, unit_status, (int32_t*)nullptr);                                      \
   } while (0)
     const int groups16 = pair_heads ? units / 2 : units;
-    int nwv = groups16 <= 256 ? 4 : groups16 <= 512 ? 2 : groups16 <= 1024 ? 1 : 0;   // 0: the lean build
-    if (want_waves) nwv = want_waves;
+    const int nwv = waves_per_block(groups16, want_waves);
     if (nwv == 0) {
       if (pair_heads)
         hipLaunchKernelGGL((decompose16_kernel<1, true, 0, false, true>), dim3(units / 2), dim3(64), 0, st, *fmt, *cache,
@@ -1582,9 +1755,8 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
       else
         hipLaunchKernelGGL((decompose16_kernel<1, false, 0, false, true>), dim3(units), dim3(64), 0, st, *fmt, *cache,
                            job, large_ws, unit_status, (int32_t*)nullptr);
-    } else if (nwv >= 4) DQ_LAUNCH_D16(4);
-    else if (nwv >= 2) DQ_LAUNCH_D16(2);
-    else DQ_LAUNCH_D16(1);
+    } else if (nwv == 4) DQ_LAUNCH_D16(4);
+    else DQ_LAUNCH_D16(2);
 #undef DQ_LAUNCH_D16
   } else if (fmt->head_dim == 128) {
     if (fmt->j1 == 8) DQ_LAUNCH_DECOMPOSE(8, 128);
