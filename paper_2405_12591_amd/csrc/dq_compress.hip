@@ -1,7 +1,7 @@
 // Compression of K/V blocks into DecoQuant form (Section 3.1 of arXiv 2405.12591):
 //   step 1  two-site MPO split of the regrouped block, M = T_S * T_L            (Eq. 2, Eq. 3)
 //   step 2  per-group round-to-nearest quantization of T_L, T_S kept in fp16   (Eq. 1)
-// Two kernels: `decompose_kernel` (Gram matrix, Jacobi eigen-solver, projection; one wave per block) writes the
+// Plain shapes, two kernels: `decompose_kernel` (Gram matrix, Jacobi eigen-solver, projection; one wave per block) writes the
 // small tensor into the cache and the fp32 large tensor into the workspace;
 // `quantize_tiles_kernel` turns fp32 rows into packed codes and fp16 steps.
 #include "dq_common.h"
@@ -312,14 +312,15 @@ __global__ __launch_bounds__(256) void quantize_pack_kernel(const float* __restr
 }
 
 // The per-block status words of the decomposition become the call's two status words (flags OR-ed,
-// sweeps at their maximum).  One workgroup of 256 threads.
+// sweeps at their maximum).  One workgroup of NT threads.
+template <int NT>
 __device__ __forceinline__ void fold_status(const int32_t* __restrict__ unit_status, int n_units,
                                             int32_t* __restrict__ status) {
   __shared__ int red[2];
   if (threadIdx.x < 2) red[threadIdx.x] = 0;
   __syncthreads();
   int flags = 0, sweeps = 0;
-  for (int u = threadIdx.x; u < n_units; u += 256) {
+  for (int u = threadIdx.x; u < n_units; u += NT) {
     const int w = unit_status[u];
     flags |= w & 0xFF;
     sweeps = max(sweeps, w >> 8);
@@ -339,7 +340,7 @@ __global__ __launch_bounds__(256) void quantize_tiles_kernel(const float* __rest
                                                              int n_units, int32_t* __restrict__ status) {
   extern __shared__ uint8_t lds_u[];
   const Geometry g = make_geometry(fmt, cache.kv_heads, cache.block_capacity);
-  if (blockIdx.x == 0) fold_status(unit_status, n_units, status);
+  if (blockIdx.x == 0) fold_status<256>(unit_status, n_units, status);
   const int tile = blockIdx.x % g.tiles_per_block;
   const int unit = blockIdx.x / g.tiles_per_block;
   const UnitRef ur = unit_ref(g, job, unit);
@@ -893,13 +894,14 @@ __device__ __forceinline__ void store_factors(Jacobi16<ROWS>& jac, double* lam, 
 // word of the workspace header, zero between calls) folds the blocks' status words into the call's
 // two; status words travel as device-scope stores and loads, as the counter does, so no cache
 // write-back or invalidation is needed between the XCDs.
-// LEAN: the build for calls of thousands of blocks (a prompt), which are bound by throughput, not by
-// one block's latency: one wave per block, several blocks resident per SIMD so that one block's
-// eigen-solver (a chain of dependent instructions) overlaps the other blocks' contractions.  For
-// that the wave keeps fewer registers (loads in smaller batches, the solver's rounds not unrolled) and
-// less LDS (the quantizer works on 64 rows at a time in the space the solver's matrices leave).  The
-// arithmetic, and so every bit written, is that of the other builds.
-// N3 (lean build with the quantizer, d = 128): three local tensors (Eq. 2 with n = 3, factor shapes
+// PART: calls of thousands of blocks (a prompt) are bound by throughput, not by one block's latency, and
+// run as three launches, each with one wave per block or less and several waves per SIMD: PART 1 is the
+// Gram matrix alone (left in the block's region of the workspace), then solve16_kernel, eight blocks
+// per wave, then PART 3, the projection and quantizer.  In one launch every block derives each of its
+// rotations in eight lanes at once and its solver, a chain of dependent instructions, holds the
+// registers of the contractions.  The arithmetic, and so every bit written, is that of the other builds.
+// 14720 blocks (4-bit, d = 128): 670 us in one launch, 163 + 100 + 280 us in three.
+// N3 (PART 3 with the quantizer, d = 128): three local tensors (Eq. 2 with n = 3, factor shapes
 // 1 * (T_b/8) * 8 by j1 * j2 * 1) in the same kernel.  The first cut's right factor R is never
 // stored: a first pass over the rows forms it 16 tokens at a time (rounded to fp32, the precision
 // the three-kernel path keeps it in) and adds it to the 8 x 8 Gram matrix of the second cut,
@@ -908,11 +910,12 @@ __device__ __forceinline__ void store_factors(Jacobi16<ROWS>& jac, double* lam, 
 // the operand layout that lets a second matrix product contract over the eight tokens of a run
 // (T_2 = A V' diag(1/sigma')), and hands the rows of T_2 to the quantizer in the registers it
 // expects them in.  job.keep_large: the fp32 rows of T_2 also go to the workspace.
-template <int NWV, bool PAIR, int QB = 0, bool FULL = false, bool LEAN = false, bool N3 = false>
-__global__ __launch_bounds__(64 * NWV, LEAN ? ((PAIR || N3) ? 3 : 4) : 1) void decompose16_kernel(dq_format fmt, dq_cache cache, CompressJob job,
+template <int NWV, bool PAIR, int QB = 0, bool FULL = false, int PART = 0, bool N3 = false>
+__global__ __launch_bounds__(64 * NWV, PART == 1 ? 5 : PART == 3 ? ((PAIR || N3) ? 3 : 4) : 1) void decompose16_kernel(dq_format fmt, dq_cache cache, CompressJob job,
                                                                float* __restrict__ large_ws,
                                                                int32_t* __restrict__ unit_status,
                                                                int32_t* __restrict__ call_status) {
+  constexpr bool LEAN = PART != 0;
   __shared__ int s_last_block;
   auto end_call = [&]() __attribute__((always_inline)) {   // QB != 0 only; every workgroup, once, at its end
     // every wave waits for its own device-scope stores (the status words) to be acknowledged; after
@@ -952,6 +955,9 @@ __global__ __launch_bounds__(64 * NWV, LEAN ? ((PAIR || N3) ? 3 : 4) : 1) void d
   const UnitRef ur = unit_ref(g, job, unit);
   const int which = ur.which, slot = ur.slot, nv = ur.nv;
   const long bh = ur.bh;
+  // (the three launches of a prompt: the solver's launch has left the status words)
+  if (PART == 3 && QB != 0 && blockIdx.x == 0) fold_status<64>(unit_status, (PAIR ? 2 : 1) * (int)gridDim.x, call_status);
+  if (PART != 0 && slot < 0) return;
   if (slot < 0) {
     if (threadIdx.x == 0) {
       if (QB != 0) {
@@ -962,7 +968,7 @@ __global__ __launch_bounds__(64 * NWV, LEAN ? ((PAIR || N3) ? 3 : 4) : 1) void d
         if (PAIR) unit_status[unit + unit_gap] = 0;
       }
     }
-    if constexpr (QB != 0) end_call();
+    if constexpr (QB != 0 && PART == 0) end_call();
     return;
   }
   const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -972,8 +978,8 @@ __global__ __launch_bounds__(64 * NWV, LEAN ? ((PAIR || N3) ? 3 : 4) : 1) void d
   const uint16_t* X = ur.X;  // [nv, d] fp16 bits
   const long head_gap = (long)job.t_new * d;   // PAIR: from a row of the first head to the same row of the second
 
-  static_assert(!LEAN || NWV == 1, "the lean build is one wave per block");
-  static_assert(!N3 || (LEAN && !PAIR && QB != 0), "three tensors: lean build with the quantizer, d = 128");
+  static_assert(!LEAN || NWV == 1, "one wave per block");
+  static_assert(!N3 || (LEAN && !PAIR && QB != 0), "three tensors: PART 3 with the quantizer, d = 128");
   constexpr int kMat = j1 * ld;                              // doubles per 16 x 16 matrix (padded rows)
   constexpr int kMatBytes = (2 + NWV - 1) * kMat * (int)sizeof(double);
   // fused quantizer: one byte per element of QT token rows, then the value layout's staging
@@ -981,8 +987,7 @@ __global__ __launch_bounds__(64 * NWV, LEAN ? ((PAIR || N3) ? 3 : 4) : 1) void d
   constexpr int QT = LEAN ? 32 : kTileTokens;                // rows quantized and packed at a time
   constexpr int kHeadArea = QT * d + d * (pack_parts(QB ? QB : 8, QT) * QT * (QB ? QB : 8) / 32 + 1) * 4;
   constexpr int kFieldBytes = QB ? (PAIR ? 2 : 1) * kHeadArea : 16;
-  // the lean build's fields take the place of the matrices, which are dead by then (one wave: its
-  // LDS operations execute in program order)
+  // (the three launches: no matrices in LDS, but the second cut's)
   constexpr int kPoolBytes = LEAN ? (kMatBytes > kFieldBytes ? kMatBytes : kFieldBytes) : kMatBytes + kFieldBytes;
   __shared__ __attribute__((aligned(16))) unsigned char pool[kPoolBytes];
   double* const A = reinterpret_cast<double*>(pool);
@@ -991,12 +996,13 @@ __global__ __launch_bounds__(64 * NWV, LEAN ? ((PAIR || N3) ? 3 : 4) : 1) void d
   uint8_t* const lds_u = LEAN ? pool : pool + kMatBytes;
   __shared__ double lam[j1], lam2[j1];
 
+  double* const gram_ws = reinterpret_cast<double*>(large_ws + (long)unit * g.Tb * d);   // PART: G, then W, of this block
   // ---- Gram matrix G[p][q] = sum_{t, b2} X[t, p*8+b2] X[t, q*8+b2] ----
   // A and B operand of one MFMA are the same register: lane (b1 = l%16, k = l/16) holds
   // X[t0 + k][b1*8 + b2] for the 4 tokens of a group and one b2.  A lane loads the 8 b2 of its
   // (token, b1) as one 16-byte chunk; 16 lanes cover a 256-byte row.  Wave wv takes every NWV-th
   // group of 4 tokens.
-  {
+  if constexpr (PART != 3) {
     const int b1 = l & 15, tk = l >> 4;
     constexpr int NG = 32 / NWV;   // groups per wave in a chunk of 128 tokens
     f64x4 acc[4];
@@ -1031,9 +1037,13 @@ __global__ __launch_bounds__(64 * NWV, LEAN ? ((PAIR || N3) ? 3 : 4) : 1) void d
     for (int i = 0; i < 4; ++i) {
       const int row = (l >> 4) + 4 * i, col = l & 15;
       const double sum = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
-      dst[row * ld + col] = (PAIR && (row >> 3) != (col >> 3)) ? 0.0 : sum;   // no products across heads
+      const double val = (PAIR && (row >> 3) != (col >> 3)) ? 0.0 : sum;   // no products across heads
+      if (PART == 1) gram_ws[row * j1 + col] = val;
+      else dst[row * ld + col] = val;
     }
   }
+  if constexpr (PART == 1) return;
+  if constexpr (PART == 0) {
   __syncthreads();
   if (NWV > 1) {
     for (int idx = threadIdx.x; idx < j1 * j1; idx += 64 * NWV) {
@@ -1095,6 +1105,7 @@ __global__ __launch_bounds__(64 * NWV, LEAN ? ((PAIR || N3) ? 3 : 4) : 1) void d
     }
   }
   __syncthreads();
+  }
 
   // ---- projection: K'[t, r*8+b2] = sum_b1 W[r][b1] X[t, b1*8+b2], fp64 -> fp32 ----
   // One MFMA chain per b2: rows r, columns 16 tokens, contraction over b1 in 4 steps of 4.
@@ -1104,8 +1115,8 @@ __global__ __launch_bounds__(64 * NWV, LEAN ? ((PAIR || N3) ? 3 : 4) : 1) void d
     constexpr int TB = LEAN ? 1 : NT;   // groups whose rows are requested together
     double wreg[4];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) wreg[s] = W[(l & 15) * ld + 4 * s + (l >> 4)];
-    if (LEAN) __builtin_amdgcn_wave_barrier();   // W is read; the fields may take the matrices' place
+    for (int s = 0; s < 4; ++s)
+      wreg[s] = PART == 3 ? gram_ws[j1 * j1 + (l & 15) * j1 + 4 * s + (l >> 4)] : W[(l & 15) * ld + 4 * s + (l >> 4)];
     double w3reg[4] = {0.0, 0.0, 0.0, 0.0};
     if constexpr (N3) {
       // ---- second cut: Gram matrix of A[(r, a2, b2), a3] from the right factor, 16 tokens at a time ----
@@ -1386,7 +1397,85 @@ __global__ __launch_bounds__(64 * NWV, LEAN ? ((PAIR || N3) ? 3 : 4) : 1) void d
       }
     }
   }
-  if constexpr (QB != 0) end_call();
+  if constexpr (QB != 0 && PART == 0) end_call();
+}
+
+// The eigen-solver of a call of thousands of blocks: 64 * ROWS / 128 blocks per wave (eight at ROWS = 16:
+// every rotation is derived once, no sum crosses lanes, nothing touches LDS but the ordering).  Reads the
+// Gram matrices and writes W behind them, the small tensors into the cache, the blocks' status words.
+// Bound by instruction issue: about 145 instructions per round for eight blocks.
+// Workgroups of four waves, so that the waves spread evenly over the SIMDs.
+constexpr int kSolveWaves = 4;
+template <int ROWS, bool PAIR>
+__global__ __launch_bounds__(64 * kSolveWaves) void solve16_kernel(dq_format fmt, dq_cache cache, CompressJob job,
+                                                     float* __restrict__ large_ws, int32_t* __restrict__ unit_status,
+                                                     int n_groups) {
+  constexpr int LPB = 128 / ROWS, BPG = 64 * kSolveWaves / LPB;   // lanes per block, blocks per workgroup
+  constexpr int j1 = 16, d = PAIR ? 64 : 128;
+  const Geometry g = make_geometry(fmt, cache.kv_heads, cache.block_capacity);
+  __shared__ double s_lam[BPG][j1];
+  __shared__ __attribute__((aligned(16))) uint16_t s_small[BPG][j1 * j1];
+  const int lane = threadIdx.x & 63, blk = threadIdx.x / LPB, j = lane & 7;
+  const int gi = blockIdx.x * BPG + blk;
+  int unit = min(gi, n_groups - 1);
+  const int unit_gap = 2 * job.n_blocks;
+  if (PAIR) {
+    const int pb = unit >> 1, jb = pb % job.n_blocks, hp = pb / job.n_blocks, half_h = g.H >> 1;
+    unit = (((hp / half_h) * g.H + 2 * (hp % half_h)) * job.n_blocks + jb) * 2 + (unit & 1);
+  }
+  const UnitRef ur = unit_ref(g, job, unit);
+  const bool live = gi < n_groups && ur.slot >= 0;
+  double* const G = reinterpret_cast<double*>(large_ws + (long)unit * g.Tb * d);
+  Jacobi16<ROWS> jac;
+  const int row0 = jac.first_row(lane);
+#pragma unroll
+  for (int i = 0; i < ROWS; ++i) {   // (symmetric: column j is row j; a block that is skipped has no matrix)
+    jac.x[i] = live ? G[j * j1 + row0 + i] : 0.0;
+    jac.y[i] = live ? G[(j + 8) * j1 + row0 + i] : 0.0;
+  }
+  const int sweeps = jac.run();
+  int px, py;
+  double rx, ry, lx, ly;
+  jac.template order<PAIR>(s_lam[blk], px, py, rx, ry, lx, ly);
+  const double fx = rx * rx * rx, fy = ry * ry * ry;
+  bool sat = false;
+#pragma unroll
+  for (int i = 0; i < ROWS; ++i) {
+    const int b1 = row0 + i;
+    const double wx = rx > 0.0 ? jac.x[i] * fx : 0.0, wy = ry > 0.0 ? jac.y[i] * fy : 0.0;
+    if (live) {
+      G[j1 * j1 + px * j1 + b1] = wx;
+      G[j1 * j1 + py * j1 + b1] = wy;
+    }
+    auto put = [&](int r, double ts) __attribute__((always_inline)) {
+      if (PAIR) {   // the heads' 8 x 8 tensors one after the other; across heads there is nothing
+        if ((b1 >> 3) != (r >> 3)) return;
+        s_small[blk][(b1 >> 3) * 64 + (ur.which ? (b1 & 7) * 8 + (r & 7) : (r & 7) * 8 + (b1 & 7))] = f64_to_f16_rne(ts, true, &sat);
+      } else {      // values: [b1][r]; keys: transposed [r][b1]
+        s_small[blk][ur.which ? b1 * j1 + r : r * j1 + b1] = f64_to_f16_rne(ts, true, &sat);
+      }
+    };
+    put(px, wx * lx);   // T_S = U Sigma = W Lambda
+    put(py, wy * ly);
+  }
+  __builtin_amdgcn_wave_barrier();
+  const unsigned long long sat_lanes = __ballot(sat);
+  if (live) {
+    const int lb = lane % LPB;
+    uint16_t* const small = (ur.which ? cache.v_small : cache.k_small) + (ur.bh * g.NB + ur.slot) * g.small_per_block;
+    constexpr int CHUNKS = (PAIR ? 128 : j1 * j1) / 8;   // of eight entries
+#pragma unroll
+    for (int c = lb; c < CHUNKS; c += LPB) {
+      uint16_t* dst = PAIR ? small + (long)(c / 8) * g.NB * g.small_per_block + (c % 8) * 8 : small + c * 8;
+      *reinterpret_cast<u32x4*>(dst) = *reinterpret_cast<const u32x4*>(&s_small[blk][c * 8]);
+    }
+  }
+  if (gi < n_groups && lane % LPB == 0) {
+    const bool any_sat = ((sat_lanes >> (lane & ~(LPB - 1))) & ((1ull << LPB) - 1)) != 0;
+    const int word = live ? (any_sat ? 1 : 0) | (sweeps << 8) : 0;
+    unit_status[unit] = word;
+    if (PAIR) unit_status[unit + unit_gap] = word;
+  }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1601,8 +1690,8 @@ extern "C" int32_t dq_quantize_pack(const dq_format* fmt, const float* t_large, 
   return DQ_OK;
 }
 
-// Waves per block of the tuned decomposition kernel for a launch of `groups` workgroups (0: the lean
-// build, one wave per block).  The two contractions and the quantizer shrink with the waves, the
+// Waves per block of the tuned decomposition kernel for a launch of `groups` workgroups (0: the
+// three launches of a prompt).  The two contractions and the quantizer shrink with the waves, the
 // solver runs in one of them; beyond two workgroups per compute unit the waves of different blocks
 // queue for the SIMDs.  Measured, us per call with four / two waves (4-bit, d = 128): 256 blocks
 // 30 / 38, 512 blocks 40 / 51, 768 blocks 63 / 53, 1024 blocks 76 / 61.
@@ -1644,25 +1733,50 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
   // itself, which saves their trip through memory (four times the bytes the method needs) and the
   // quantizer's launch.  Calls of a few hundred blocks are bound by the latency of one block's chain
   // and give a block several waves; calls of more than 1024 blocks are bound by throughput and take
-  // the lean build (one wave per block, three blocks per SIMD).
+  // three launches.
   const bool fused = (flags & DQ_COMPRESS_NO_LARGE) && fmt->i3 == 1 && fmt->i1 == 1 && !force_general &&
                      ((fmt->head_dim == 128 && fmt->j1 == 16 && (fmt->group == 128 || fmt->group == 64)) ||
                       (pair_heads && fmt->group == 64));
-  // Three local tensors (d = 128, j1 = 16): the lean build makes both cuts and quantizes in one
-  // launch, and leaves the fp32 rows of T_2 in the workspace if the caller wants them.  It is one wave
+  // Three local tensors (d = 128, j1 = 16): the last of the three launches makes the second cut and quantizes, and leaves the fp32 rows of T_2 in the workspace if the caller wants them.  It is one wave
   // per block, so a call of a few hundred blocks, which is bound by the latency of one block's
   // chain, keeps the three launches (first cut with several waves per block, second cut,
   // quantizer); larger calls, and a forced wave count of one, take the one-kernel build.
   const bool fused3 = fmt->i3 == kRun && fmt->i1 == 1 && !force_general && fmt->head_dim == 128 && fmt->j1 == 16 &&
                       (fmt->group == 128 || fmt->group == 64) && (want_waves == 1 || (want_waves == 0 && units > 512));
+  // The first two launches of a call of thousands of blocks: Gram matrices, eigen-solver.  Eight blocks per
+  // solver wave need 8192 blocks to put a wave on every SIMD; up to there two blocks per wave are as fast
+  // or faster (whole call, two / eight blocks per wave: 1280 blocks 90 / 121 us, 2560 129 / 138, 8192
+  // 291 / 292, 16384 545 / 517).
+  auto launch_factor = [&]() {
+    const int groups = pair_heads ? units / 2 : units;
+    if (pair_heads)
+      hipLaunchKernelGGL((decompose16_kernel<1, true, 0, false, 1>), dim3(groups), dim3(64), 0, st, *fmt, *cache, job,
+                         large_ws, unit_status, (int32_t*)nullptr);
+    else
+      hipLaunchKernelGGL((decompose16_kernel<1, false, 0, false, 1>), dim3(groups), dim3(64), 0, st, *fmt, *cache, job,
+                         large_ws, unit_status, (int32_t*)nullptr);
+#define DQ_LAUNCH_SOLVE(R_, P_)                                                                                   \
+  hipLaunchKernelGGL((solve16_kernel<R_, P_>), dim3((groups + kSolveWaves * R_ / 2 - 1) / (kSolveWaves * R_ / 2)),   \
+                     dim3(64 * kSolveWaves), 0, st, *fmt,                                                         \
+                     *cache, job, large_ws, unit_status, groups)
+    if (groups > 8192) {
+      if (pair_heads) DQ_LAUNCH_SOLVE(16, true);
+      else DQ_LAUNCH_SOLVE(16, false);
+    } else {
+      if (pair_heads) DQ_LAUNCH_SOLVE(4, true);
+      else DQ_LAUNCH_SOLVE(4, false);
+    }
+#undef DQ_LAUNCH_SOLVE
+  };
   if (fused3) {
+    launch_factor();
 #define DQ_LAUNCH_FUSED3(B_)                                                                                     \
   do {                                                                                                           \
     if (fmt->levels)                                                                                             \
-      hipLaunchKernelGGL((decompose16_kernel<1, false, B_, true, true, true>), dim3(units), dim3(64), 0, st, *fmt, \
+      hipLaunchKernelGGL((decompose16_kernel<1, false, B_, true, 3, true>), dim3(units), dim3(64), 0, st, *fmt,  \
                          *cache, job, large_ws, unit_status, status);                                            \
     else                                                                                                         \
-      hipLaunchKernelGGL((decompose16_kernel<1, false, B_, false, true, true>), dim3(units), dim3(64), 0, st,    \
+      hipLaunchKernelGGL((decompose16_kernel<1, false, B_, false, 3, true>), dim3(units), dim3(64), 0, st,       \
                          *fmt, *cache, job, large_ws, unit_status, status);                                      \
   } while (0)
     if (fmt->bits == 2) DQ_LAUNCH_FUSED3(2);
@@ -1688,27 +1802,28 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
       hipLaunchKernelGGL((decompose16_kernel<N_, false, B_, false>), dim3(units), dim3(64 * N_), 0, st, *fmt,   \
                          *cache, job, large_ws, unit_status, status);                                           \
   } while (0)
-#define DQ_LAUNCH_FUSED_LEAN(B_)                                                                                \
+#define DQ_LAUNCH_FUSED_PART3(B_)                                                                                \
   do {                                                                                                          \
     if (pair_heads && fmt->levels)                                                                              \
-      hipLaunchKernelGGL((decompose16_kernel<1, true, B_, true, true>), dim3(units / 2), dim3(64), 0, st, *fmt, \
+      hipLaunchKernelGGL((decompose16_kernel<1, true, B_, true, 3>), dim3(units / 2), dim3(64), 0, st, *fmt, \
                          *cache, job, large_ws, unit_status, status);                                           \
     else if (pair_heads)                                                                                        \
-      hipLaunchKernelGGL((decompose16_kernel<1, true, B_, false, true>), dim3(units / 2), dim3(64), 0, st,      \
+      hipLaunchKernelGGL((decompose16_kernel<1, true, B_, false, 3>), dim3(units / 2), dim3(64), 0, st,      \
                          *fmt, *cache, job, large_ws, unit_status, status);                                     \
     else if (fmt->levels)                                                                                       \
-      hipLaunchKernelGGL((decompose16_kernel<1, false, B_, true, true>), dim3(units), dim3(64), 0, st, *fmt,    \
+      hipLaunchKernelGGL((decompose16_kernel<1, false, B_, true, 3>), dim3(units), dim3(64), 0, st, *fmt,    \
                          *cache, job, large_ws, unit_status, status);                                           \
     else                                                                                                        \
-      hipLaunchKernelGGL((decompose16_kernel<1, false, B_, false, true>), dim3(units), dim3(64), 0, st, *fmt,   \
+      hipLaunchKernelGGL((decompose16_kernel<1, false, B_, false, 3>), dim3(units), dim3(64), 0, st, *fmt,   \
                          *cache, job, large_ws, unit_status, status);                                           \
   } while (0)
     const int fused_groups = pair_heads ? units / 2 : units;
     int fused_waves = waves_per_block(fused_groups, want_waves);
     if (fused_waves == 0) {
-      if (fmt->bits == 2) DQ_LAUNCH_FUSED_LEAN(2);
-      else if (fmt->bits == 4) DQ_LAUNCH_FUSED_LEAN(4);
-      else DQ_LAUNCH_FUSED_LEAN(8);
+      launch_factor();
+      if (fmt->bits == 2) DQ_LAUNCH_FUSED_PART3(2);
+      else if (fmt->bits == 4) DQ_LAUNCH_FUSED_PART3(4);
+      else DQ_LAUNCH_FUSED_PART3(8);
     } else if (fused_waves == 4) {
       if (fmt->bits == 2) DQ_LAUNCH_FUSED(4, 2);
       else if (fmt->bits == 4) DQ_LAUNCH_FUSED(4, 4);
@@ -1719,7 +1834,7 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
       else DQ_LAUNCH_FUSED(2, 8);
     }
 #undef DQ_LAUNCH_FUSED
-#undef DQ_LAUNCH_FUSED_LEAN
+#undef DQ_LAUNCH_FUSED_PART3
     DQ_HIP_CHECK(hipGetLastError());
     return DQ_OK;
   }
@@ -1749,11 +1864,12 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
     const int groups16 = pair_heads ? units / 2 : units;
     const int nwv = waves_per_block(groups16, want_waves);
     if (nwv == 0) {
+      launch_factor();
       if (pair_heads)
-        hipLaunchKernelGGL((decompose16_kernel<1, true, 0, false, true>), dim3(units / 2), dim3(64), 0, st, *fmt, *cache,
+        hipLaunchKernelGGL((decompose16_kernel<1, true, 0, false, 3>), dim3(units / 2), dim3(64), 0, st, *fmt, *cache,
                            job, large_ws, unit_status, (int32_t*)nullptr);
       else
-        hipLaunchKernelGGL((decompose16_kernel<1, false, 0, false, true>), dim3(units), dim3(64), 0, st, *fmt, *cache,
+        hipLaunchKernelGGL((decompose16_kernel<1, false, 0, false, 3>), dim3(units), dim3(64), 0, st, *fmt, *cache,
                            job, large_ws, unit_status, (int32_t*)nullptr);
     } else if (nwv == 4) DQ_LAUNCH_D16(4);
     else DQ_LAUNCH_D16(2);
