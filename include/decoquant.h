@@ -141,7 +141,8 @@ int32_t dq_last_hip_error(void);
  * groups of that many (the last one takes what is left: 7 = 4 + 3), each its own workgroup reading
  * the same codes (at most 16 groups).  Heads of 64 channels are also taken when j1 = j2 = 8,
  * group = 64, two local tensors, q_heads == kv_heads and kv_heads is even: two neighbouring kv
- * heads are then worked by one workgroup as one head of 128 channels. */
+ * heads are then worked by one workgroup as one head of 128 channels.  (DQ_DECODE_AUTO also takes
+ * grouped query heads of 64 channels there, up to 32 per kv head; DQ_DECODE_FORCE_MFMA does not.) */
 int32_t dq_decode_mfma_supported(const dq_format* fmt, int32_t q_heads, int32_t kv_heads);
 
 /* Bytes of workspace dq_attn_decode needs for these sizes (0 on invalid arguments).  The

@@ -49,8 +49,8 @@ int choose_splits(const dq_format* f, int batch, int q_heads, int kv_heads, int 
     if (mfma) {
       int per_group = 1;
       const int hg = mfma_head_groups(f, q_heads, kv_heads, &per_group);   // each head group is a workgroup of its own
-      if (mfma_pair_heads(f, q_heads, kv_heads))   // two kv heads, one query head each, per workgroup
-        choose_mfma_shape(batch * kv_heads / 2, max_tiles, 2, f->bits, &n, &nw);
+      if (mfma_pair_heads(f, q_heads, kv_heads))   // two kv heads per workgroup
+        choose_mfma_shape(batch * kv_heads / 2 * hg, max_tiles, 2 * per_group, f->bits, &n, &nw);
       else
         choose_mfma_shape(batch * kv_heads * hg, max_tiles, per_group, f->bits, &n, &nw);
     } else {
@@ -186,7 +186,7 @@ static int32_t decode_impl(const dq_format* fmt, const dq_cache* cache, const ui
     return DQ_EINVAL;
   const bool can_mfma = mfma_supported(fmt, q_heads, cache->kv_heads);
   if ((flags & DQ_DECODE_FORCE_MFMA) && !can_mfma) return DQ_EINVAL;
-  const bool use_mfma = can_mfma && !(flags & DQ_DECODE_FORCE_GENERIC);
+  const bool use_mfma = mfma_takes(fmt, q_heads, cache->kv_heads) && !(flags & DQ_DECODE_FORCE_GENERIC);
 
   DecodeArgs a;
   a.fmt = *fmt;

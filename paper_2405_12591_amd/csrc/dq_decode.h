@@ -22,7 +22,7 @@ struct DecodeArgs {
   int nw;                  // waves per workgroup of the matrix-core kernel (4 or 8)
   int head_groups;         // matrix-core kernel: workgroups per (sequence, kv head, split) ...
   int heads_per_group;     // ... each with this many query heads (1, 2 or 4; the last one what is left)
-  int pair_heads;          // matrix-core kernel: 1 = two kv heads of 64 channels per workgroup (one query head each)
+  int pair_heads;          // matrix-core kernel: 1 = two kv heads of 64 channels per workgroup (heads_per_group query heads of each)
   int unit_map;            // which (sequence, kv head) a workgroup row takes: 0 = its own index, see unit_of_row()
   int rows_on_x;           // 0: grid (splits, rows); 1: grid (rows, splits), for more rows than a grid's y extent takes
   hipEvent_t ev_start;     // optional: recorded around the main kernel
@@ -70,6 +70,7 @@ int32_t launch_decode_generic(const DecodeArgs& a, hipStream_t st);
 int32_t launch_tail_partial(const DecodeArgs& a, float m_unit, hipStream_t st);
 int32_t launch_decode_mfma(const DecodeArgs& a, hipStream_t st);
 bool mfma_supported(const dq_format* f, int q_heads, int kv_heads);
+bool mfma_takes(const dq_format* f, int q_heads, int kv_heads);
 bool mfma_pair_heads(const dq_format* f, int q_heads, int kv_heads);
 int mfma_head_groups(const dq_format* f, int q_heads, int kv_heads, int* heads_per_group);
 int choose_splits(const dq_format* f, int batch, int q_heads, int kv_heads, int max_seq_len, bool mfma,

@@ -17,17 +17,26 @@ static int heads_per_workgroup(const dq_format* f, int rep) {
 }
 
 // Heads of 64 channels are worked in pairs of neighbouring kv heads (as one head of 128 channels and
-// two step groups): j1 = j2 = 8, one step per row, one query head per kv head, an even number of
-// heads, two local tensors.
+// two step groups): j1 = j2 = 8, one step per row, an even number of heads, two local tensors.  One or
+// two query heads of each of the two ride in a workgroup (four B columns each); more are served in
+// head groups of two, the last one taking what is left.
 bool mfma_pair_heads(const dq_format* f, int q_heads, int kv_heads) {
-  if (!format_ok(f) || kv_heads <= 0 || q_heads != kv_heads || (kv_heads & 1)) return false;
+  if (!format_ok(f) || kv_heads <= 0 || q_heads <= 0 || q_heads % kv_heads || (kv_heads & 1)) return false;
+  if (q_heads / kv_heads > 2 * kMaxHeadGroups) return false;
   return f->head_dim == 64 && f->j1 == 8 && f->j2 == 8 && f->group == 64 && f->i3 == 1 && f->i1 == 1;
+}
+
+// Whether the matrix-core kernel takes a call that leaves the choice to the library.  (Grouped query
+// heads of 64 channels are taken here but not where the caller names the kernel: dq_decode_mfma_supported
+// and DQ_DECODE_FORCE_MFMA keep the set they were defined with.)
+bool mfma_takes(const dq_format* f, int q_heads, int kv_heads) {
+  return mfma_supported(f, q_heads, kv_heads) || mfma_pair_heads(f, q_heads, kv_heads);
 }
 
 bool mfma_supported(const dq_format* f, int q_heads, int kv_heads) {
   if (!format_ok(f) || kv_heads <= 0 || q_heads <= 0 || q_heads % kv_heads) return false;
   if (f->i1 != 1) return false;   // a token factor on the small tensor: the plain kernel's
-  if (mfma_pair_heads(f, q_heads, kv_heads)) return true;
+  if (q_heads == kv_heads && mfma_pair_heads(f, q_heads, kv_heads)) return true;
   if (f->head_dim != 128 || f->j1 != 16 || f->j2 != 8) return false;
   if (f->bits != 8 && f->bits != 4 && f->bits != 2) return false;
   if (f->group != 128 && f->group != 64) return false;
@@ -36,8 +45,9 @@ bool mfma_supported(const dq_format* f, int q_heads, int kv_heads) {
 
 int mfma_head_groups(const dq_format* f, int q_heads, int kv_heads, int* heads_per_group) {
   if (mfma_pair_heads(f, q_heads, kv_heads)) {
-    if (heads_per_group) *heads_per_group = 1;
-    return 1;
+    const int per_kv = q_heads / kv_heads, r = per_kv >= 2 ? 2 : 1;
+    if (heads_per_group) *heads_per_group = r;
+    return (per_kv + r - 1) / r;
   }
   const int rep = q_heads / kv_heads;
   const int r = heads_per_workgroup(f, rep);

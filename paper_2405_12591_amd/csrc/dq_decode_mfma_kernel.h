@@ -3,9 +3,9 @@
 //                       group = 64  with 1 or 2
 // with head_dim = 128, j1 = 16, j2 = 8, block_tokens % 128 == 0, two or three local tensors.
 // More query heads per kv head are served by several workgroups (head groups) over the same codes.
-// Heads of 64 channels (j1 = 8, j2 = 8, group = 64, one query head per kv head) ride in pairs: two
-// neighbouring kv heads are worked as one head of 128 channels whose small tensors are block-diagonal
-// and whose two query heads are the real ones padded with zeros (see P2 below).
+// Heads of 64 channels (j1 = 8, j2 = 8, group = 64) ride in pairs: two neighbouring kv heads are
+// worked as one head of 128 channels whose small tensors are block-diagonal and whose query heads are
+// the real ones (one or two of each kv head) padded with zeros (see P2 below).
 //
 // This is the fusion of dequantization with the product of the local tensors of Section 3.2 (arXiv
 // 2405.12591) carried through the attention that follows it.  The low-bit codes never become
@@ -177,21 +177,26 @@ __device__ __forceinline__ float pow2i(int e) {
 // value rows are weighted with p'[e] = sum_a3 T_3^V[e, a3] p[a3] (signed, so these weights get a
 // signed top limb like the query's).  The lanes that hold the eight rows of a run form a quad,
 // so both products are quad broadcasts and fused multiply-adds.
-// P2: a pair of kv heads of 64 channels each (j1 = 8), one query head per kv head, as one virtual
-// head of 128 channels and two step groups (NG = 2, R = 2).  Virtual row r of the large tensors is row
+// P2: a pair of kv heads of 64 channels each (j1 = 8), R / 2 query heads of each, as one virtual
+// head of 128 channels and two step groups (NG = 2).  Virtual row r of the large tensors is row
 // r % 8 of head r / 8, a virtual token row is the two heads' rows side by side, virtual query head hd
-// is real head hd's query in its own 64 channels and zero in the other's, and the small tensors are
-// the heads' 8 x 8 ones on the diagonal of a 16 x 16 one.  Scores, softmax and the epilogue then run
-// unchanged: head hd's scores come from its own channels only, and its output sits in virtual
-// channels [64 hd, 64 hd + 64) (the other half, the other head's values under this head's weights,
-// is dropped).  Only addresses (each lane reads its own head's arrays), the masks that realise the
-// zeros, and the mapping of the output differ.
+// is a real query head in the 64 channels of its kv head hd / (R / 2) and zero in the other's, and the
+// small tensors are the heads' 8 x 8 ones on the diagonal of a 16 x 16 one.  Scores, softmax and the
+// epilogue then run unchanged: head hd's scores come from its own channels only, and its output sits
+// in the virtual channels of its own half (the other half, the other kv head's values under this
+// head's weights, is dropped).  Only addresses (each lane reads its own head's arrays), the masks that
+// realise the zeros, and the mapping of the output differ.  A head needs the four columns of one
+// step group, so two query heads of each kv head share a code stream; more come in head groups of
+// two.  Batch 8, 32 query on 8 kv heads, 2048 to 4096 tokens (15 MB): 74 + 7 us in the plain kernel
+// these shapes used to take, 12 us here.
 template <int BITS, int NG, int R, int NW, int TM, bool N3, bool P2>
 __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode_mfma_kernel(DecodeArgs a) {
-  static_assert(!P2 || (NG == 2 && R == 2 && !N3), "a pair of heads is two step groups and two query heads");
+  static_assert(!P2 || (NG == 2 && (R == 2 || R == 4) && !N3), "a pair of heads is two step groups and two or four query heads");
   typedef Codec<BITS> C;
   typedef typename C::chunk_t chunk_t;
-  constexpr int CPH = 4 * NG;                 // B columns per head: column CPH*head + 4*group + limb
+  constexpr int CG = P2 ? 1 : NG;             // column groups per head (a pair: a head has channels of one step group only)
+  constexpr int HPK = P2 ? R / 2 : R;         // query heads per kv head of the workgroup
+  constexpr int CPH = 4 * CG;                 // B columns per head: column CPH*head + 4*group + limb
   constexpr int NC = CPH * R;
   static_assert(NC <= 16, "too many heads for sixteen B columns");
   constexpr int F = (R + 1) / 2;              // fold MFMAs (two heads each)
@@ -205,7 +210,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   // first, as floats, by lane shifts (column 4*head + limb holds limb `limb`, most significant first),
   // and the joined columns of four successive b2 are packed side by side: 8 matrix instructions
   // per tile, and a quarter of the accumulators.
-  constexpr bool JOIN = (R == 4 && NG == 1 && !N3 && !P2);
+  constexpr bool JOIN = (R == 4 && CG == 1 && !N3);
   constexpr int PK = JOIN ? 4 : 4 / R, NSET = J2 / PK;
   constexpr int RD = P2 ? 64 : D;             // channels of a real head (output, partials, cache rows)
   constexpr int RJ1 = P2 ? 8 : J1;            // rows of a real head's large tensors
@@ -279,11 +284,17 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   int S = 0;  // the sequence's real length, read after the speculative loads are on their way
 
   // ---- the last workgroup of this (sequence, kv head) to finish merges the partial results ----
-  const long hq_first = (long)h * (a.q_heads / H) + (long)hgrp * R;   // this workgroup's first query head
-  // the last group may hold fewer than R heads (3 = 3, 7 = 4 + 3 query heads per kv head): the columns
-  // of the missing ones compute on a zero query and are never written out
-  const int nh = P2 ? 2 : min(R, a.q_heads / H - hgrp * R);
+  const int heads_per_kv = a.q_heads / H;
+  const long hq_first = (long)h * heads_per_kv + (long)hgrp * HPK;   // this workgroup's first query head
+  // the last group may hold fewer than HPK heads of a kv head (3 = 3, 7 = 4 + 3): the columns of the
+  // missing ones compute on a zero query and are never written out
+  const int nhk = min(HPK, heads_per_kv - hgrp * HPK);
   const long bhq0 = (long)b * a.q_heads + hq_first;
+  // virtual head hd: head hd of the group, or (a pair) head hd % HPK of kv head h + hd / HPK
+  auto head_live = [&](int hd) -> bool { return (P2 ? hd % HPK : hd) < nhk; };
+  auto head_row = [&](int hd) -> long {   // its row among all (sequence, query head) pairs; a missing one: the last one's
+    return P2 ? bhq0 + (long)(hd / HPK) * heads_per_kv + min(hd % HPK, nhk - 1) : bhq0 + min(hd, nhk - 1);
+  };
   int32_t* const ticket_counter = a.counters + (long)bh * a.head_groups + hgrp;
   const int n_contrib = a.n_split;   // workgroups that hand in partials
   auto ticket_and_merge = [&]() __attribute__((always_inline)) {
@@ -319,8 +330,8 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
     };
     float v_first[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     float m0 = -INFINITY, l0 = 0.f, m1 = -INFINITY, l1 = 0.f;
-    if (wave < nh) {
-      const float* base = a.partials + (bhq0 + wave) * ns * (RD + 2);
+    if (wave < R && head_live(wave)) {
+      const float* base = a.partials + head_row(wave) * ns * (RD + 2);
       if (lane < ns) {
         m0 = __hip_atomic_load(base + lane * (RD + 2) + RD, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         l0 = __hip_atomic_load(base + lane * (RD + 2) + RD + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -330,8 +341,8 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
         l1 = __hip_atomic_load(base + (lane + 64) * (RD + 2) + RD + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
-    if (tid < nh * RD) load_slots(a.partials + (bhq0 + tid / RD) * ns * (RD + 2) + tid % RD, 0, v_first);
-    if (wave < nh) {
+    if (tid < R * RD && head_live(tid / RD)) load_slots(a.partials + head_row(tid / RD) * ns * (RD + 2) + tid % RD, 0, v_first);
+    if (wave < R && head_live(wave)) {
       const float M = wave_allmax(fmaxf(m0, m1));
       const float w0 = (m0 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m0 - M);
       const float w1 = (m1 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m1 - M);
@@ -341,9 +352,10 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
       if (lane == 0) s_sum[wave] = L;
     }
     __syncthreads();
-    for (int idx = tid; idx < nh * RD; idx += 64 * NW) {
+    for (int idx = tid; idx < R * RD; idx += 64 * NW) {
       const int hd = idx / RD, c = idx % RD;
-      const float* col = a.partials + (bhq0 + hd) * ns * (RD + 2) + c;
+      if (!head_live(hd)) continue;
+      const float* col = a.partials + head_row(hd) * ns * (RD + 2) + c;
       float o = 0.f;
       for (int sp = 0; sp < ns; sp += 8) {
         float v[8];
@@ -361,8 +373,8 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
       }
       const float L = s_sum[hd];
       const float r = (L > 0.f) ? o / L : 0.f;
-      a.out[(bhq0 + hd) * RD + c] = f2h_rne(r);
-      if (a.out_f32) a.out_f32[(bhq0 + hd) * RD + c] = r;
+      a.out[head_row(hd) * RD + c] = f2h_rne(r);
+      if (a.out_f32) a.out_f32[head_row(hd) * RD + c] = r;
     }
   };
 
@@ -374,8 +386,8 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   const bool col_live = (n < NC) && (N3 || (n & 3) != 3);   // value side: three limbs per group of four columns (four with three local tensors)
   const bool col_live_k = n < NC;                      // key side: four
   // the epilogue's packed columns (see PK): column n holds head packed_head, slot packed_slot of its set
-  const int packed_head = (R == 1) ? 0 : (R == 4) ? (n >> 2) : (NG == 1) ? ((n >> 2) & 1) : (n >> 3);
-  const int packed_slot = JOIN ? (n & 3) : (R == 1) ? (n >> 2) : (R == 4) ? 0 : (NG == 1) ? (n >> 3) : ((n >> 2) & 1);
+  const int packed_head = (R == 1) ? 0 : (R == 4) ? (n >> 2) : (CG == 1) ? ((n >> 2) & 1) : (n >> 3);
+  const int packed_slot = JOIN ? (n & 3) : (R == 1) ? (n >> 2) : (R == 4) ? 0 : (CG == 1) ? (n >> 3) : ((n >> 2) & 1);
 
   // softmax layout: lane = 8*G16 + pi owns the two tokens of token group G16 whose weights sit in
   // B slots 2*pi and 2*pi + 1
@@ -398,11 +410,11 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
 #pragma unroll
     for (int f = 0; f < F; ++f) {
       const int hd = 2 * f + (n >> 3);
-      // no branch here (columns past the last head read head nh - 1 and are zeroed when packed):
+      // no branch here (columns past the last head read the last one and are zeroed when packed):
       // across a branch the compiler loses count of the loads in flight and waits for all of them
       // (a pair of heads: virtual row b1 = 4g + i of virtual head hd is row b1 % 8 of the real head;
       // the rows of the other head's half are zeroed when packed)
-      const uint16_t* qp = a.q + (bhq0 + min(hd, nh - 1)) * RD;
+      const uint16_t* qp = a.q + head_row(min(hd, R - 1)) * RD;
 #pragma unroll
       for (int i = 0; i < 4; ++i) q_raw[f][i] = qp[((4 * g + i) & (RJ1 - 1)) * J2 + b2];
     }
@@ -438,6 +450,9 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   SideP curP = {0, 0, 0, 0};
   // the lane's part of a block-diagonal small tensor lies on the diagonal
   const bool small_live = !P2 || (g >> 1) == (n >> 3);
+  // the kv head (0 or 1) of the head in the lane's column of fold f, and whether the lane's rows are its own
+  auto fold_half = [&](int f) -> int { return (2 * f + (n >> 3)) / HPK; };
+  auto fold_live = [&](int f) -> bool { return !P2 || (g >> 1) == fold_half(f); };
 
   auto tile_ptrs = [&](int tile, const unsigned char*& kc, const unsigned char*& vc, long& blkid, int& tib) {
     blkid = bh0 * NB + tile / tpb;
@@ -570,45 +585,45 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
     {
       const half4 aK = __builtin_bit_cast(half4, small_live ? cur.ksm : u32x2{0u, 0u});
       f32x4 fd[F];
-      float amax = 0.f;
+      float amax = 0.f, amax_second = 0.f;
 #pragma unroll
       for (int f = 0; f < F; ++f) {
         fd[f] = __builtin_amdgcn_mfma_f32_16x16x16f16(aK, bq[f], (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
         // a pair of heads: rows r = 4g + i of the other head's half are zero by construction; they
         // are set to zero outright so that nothing the other head holds (a NaN, say) gets across
-        if (P2 && !small_live) fd[f] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        if (P2 && !fold_live(f)) fd[f] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < 4; ++i) amax = fmaxf(amax, fabsf(fd[f][i]));
+        for (int i = 0; i < 4; ++i) {
+          if (P2) amax_second = fmaxf(amax_second, fold_half(f) ? fabsf(fd[f][i]) : 0.f);
+          amax = fmaxf(amax, (P2 && fold_half(f)) ? 0.f : fabsf(fd[f][i]));
+        }
       }
       auto exponent_of = [&](float m) -> int {
         int e = 0;
         if (m > 0.f && m < INFINITY) e = __builtin_amdgcn_frexp_expf(m);  // m = f * 2^e, f in [0.5, 1)
         return max(min(e, 100), -100);
       };
-      int e;
-      if (P2) {
-        // the lane's column belongs to head n / 8: one maximum per head
-        const int e_first = exponent_of(wave_allmax_nonneg((n >> 3) ? 0.f : amax) * qk_scale);
-        const int e_second = exponent_of(wave_allmax_nonneg((n >> 3) ? amax : 0.f) * qk_scale);
-        e = (n >> 3) ? e_second : e_first;
-        q_unscale = pow2i(e_first - (kQueryBits - 1));
+      const int e = exponent_of(wave_allmax_nonneg(amax) * qk_scale);
+      q_unscale = pow2i(e - (kQueryBits - 1));
+      const float qn_first = qk_scale * pow2i(kQueryBits - 1 - e);   // |q' * qn| < 2^27
+      float qn_second = 0.f;
+      if (P2) {   // one scale per kv head
+        const int e_second = exponent_of(wave_allmax_nonneg(amax_second) * qk_scale);
         q_unscale_second = pow2i(e_second - (kQueryBits - 1));
-      } else {
-        e = exponent_of(wave_allmax_nonneg(amax) * qk_scale);
-        q_unscale = pow2i(e - (kQueryBits - 1));
+        qn_second = qk_scale * pow2i(kQueryBits - 1 - e_second);
       }
-      const float qn = qk_scale * pow2i(kQueryBits - 1 - e);   // |q' * qn| < 2^27
       // the fold's D layout: lane (n' = b2 + 8*head, g) holds rows r = 4g + i.  Channel (r, b2) is
       // code number (r & 1)*8 + b2 of the 16 codes that row pair r >> 1 contributes to one MFMA.
 #pragma unroll
       for (int f = 0; f < F; ++f) {
         const int hd = 2 * f + (n >> 3);
+        const float qn = (P2 && fold_half(f)) ? qn_second : qn_first;
         if (hd < R) {
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const int vi = (int)__builtin_rintf(fd[f][i] * qn);
             const int r = 4 * g + i;
-            const int grp = (NG == 2) ? (r >> 3) : 0;
+            const int grp = (CG == 2) ? (r >> 3) : 0;
             const int pos = (r >> 1) * 16 + C::slot((r & 1) * 8 + (n & 7));
             unsigned char* dst = Qs + (CPH * hd + 4 * grp) * 128 + pos;
             dst[0] = (unsigned char)(vi >> (3 * kLimbBits));
@@ -681,8 +696,8 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
       float sA = 0.f, sB = 0.f;
 #pragma unroll
       for (int gr = 0; gr < NG; ++gr) {
-        if (P2 && gr != hd) continue;   // a head of a pair has its channels in its own step group only
-        const int* s0 = Ss + (CPH * hd + 4 * gr) * SS;
+        if (P2 && gr != hd / HPK) continue;   // a head of a pair has its channels in its own step group only
+        const int* s0 = Ss + (CPH * hd + (P2 ? 0 : 4 * gr)) * SS;
         const int* s1 = s0 + SS;
         const int* s2 = s1 + SS;
         const int* s3 = s2 + SS;
@@ -695,7 +710,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
         sA = 0.f; sB = 0.f;
         quad_mix(yA, yB, cur3.k3A, cur3.k3B, sA, sB);
       }
-      const float unscale = (P2 && hd) ? q_unscale_second : q_unscale;
+      const float unscale = (P2 && hd >= HPK) ? q_unscale_second : q_unscale;
       sA = okA ? sA * unscale : -INFINITY;
       sB = okB ? sB * unscale : -INFINITY;
       // the running maximum moves in a sequence's first tiles and rarely afterwards: the wave-wide
@@ -723,15 +738,14 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
       } else {
 #pragma unroll
         for (int gr = 0; gr < NG; ++gr) {
-          // a pair of heads: only the head's own rows are kept, so only their column gets weights
-          // (the other one stays zero from the start)
-          if (P2 && gr != hd) continue;
+          // a pair of heads: only the head's own rows are kept, so the weights carry their steps
+          if (P2 && gr != hd / HPK) continue;
           const float vsg = (P2 && gr) ? vs_second : vs;
           const float wa = okA ? pA * (dvA[gr] * vsg) : 0.f;
           const float wb = okB ? pB * (dvB[gr] * vsg) : 0.f;
           const uint32_t iA = min((uint32_t)(wa + 0.5f), (1u << kMantBits) - 1u);
           const uint32_t iB = min((uint32_t)(wb + 0.5f), (1u << kMantBits) - 1u);
-          unsigned char* dst = Ps + (CPH * hd + 4 * gr) * 128 + G16 * 16 + 2 * pi;
+          unsigned char* dst = Ps + (CPH * hd + (P2 ? 0 : 4 * gr)) * 128 + G16 * 16 + 2 * pi;
           *reinterpret_cast<uint16_t*>(dst) = (uint16_t)((iA >> 14) | ((iB >> 14) << 8));
           *reinterpret_cast<uint16_t*>(dst + 128) = (uint16_t)(((iA >> 7) & 127u) | (((iB >> 7) & 127u) << 8));
           *reinterpret_cast<uint16_t*>(dst + 256) = (uint16_t)((iA & 127u) | ((iB & 127u) << 8));
@@ -794,13 +808,13 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         int v = o[i];
-        if (NG == 2) v = __builtin_amdgcn_update_dpp(v, v, 0x104 /* row_shl:4 */, 0xC, 0x5, false);
+        if (CG == 2) v = __builtin_amdgcn_update_dpp(v, v, 0x104 /* row_shl:4 */, 0xC, 0x5, false);
         if (K == 0) {
           pk[i] = v;
         } else {
           // live banks after the merge: R = 1: {0};  R = 2: {0, 1} (one group), {0, 2} (two groups)
-          constexpr int kShift = (R == 2 && NG == 1) ? 8 * K : 4 * K;
-          constexpr int kBanks = ((R == 1) ? 0x1 : (NG == 1) ? 0x3 : 0x5) << (kShift / 4);
+          constexpr int kShift = (R == 2 && CG == 1) ? 8 * K : 4 * K;
+          constexpr int kBanks = ((R == 1) ? 0x1 : (CG == 1) ? 0x3 : 0x5) << (kShift / 4);
           pk[i] = __builtin_amdgcn_update_dpp(pk[i], v, 0x110 + kShift /* row_shr */, 0xF, kBanks, false);
         }
       }
@@ -871,7 +885,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   // off while the codes are on their way.
   Tail tb;
   const bool do_tail = (TM == 1) || (TM == 2 && split == 0);   // TM == 2: a branch, and coarser waits
-  if (do_tail) tb.issue_keys(a, b, h, hq_first, nh);
+  if (do_tail) tb.issue_keys(a, b, h, hq_first, nhk, heads_per_kv);
   issue_tile(spec_ok ? first_tile : 0);
   // Both lengths are requested only now (a scalar load that is still out holds up every wait on
   // scalar data, the addresses of the loads above among them) and before the asm statements below
@@ -881,24 +895,21 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   const int tail_len_raw = do_tail ? a.tail.tail_lens[b] : 0;
 #pragma unroll
   for (int f = 0; f < F; ++f) {
-    const bool head_live = (2 * f + (n >> 3)) < nh && (!P2 || (g >> 1) == (n >> 3));
+    const int fold_head = 2 * f + (n >> 3);
+    const bool live = fold_head < R && head_live(fold_head) && fold_live(f);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       asm volatile("" : "+v"(q_raw[f][i]));   // nothing derived from q may move above the requests
-      bq[f][i] = __builtin_bit_cast(_Float16, (uint16_t)(head_live ? q_raw[f][i] : 0u));
+      bq[f][i] = __builtin_bit_cast(_Float16, (uint16_t)(live ? q_raw[f][i] : 0u));
     }
   }
-  if (do_tail) tb.finish(tail_len_raw, nh, reinterpret_cast<float*>(smem), s_tail);
+  if (do_tail) tb.finish(tail_len_raw, nhk, reinterpret_cast<float*>(smem), s_tail);
 
-  if (NG == 2) {
+  if (CG == 2) {
     // A channel contributes nothing to the other group's columns: those bytes of the query limbs
     // are the same in every tile and are zeroed once (the fold writes only its own group's).
     static_assert(QS_BYTES % 16 == 0, "");
     for (int o = lane * 16; o < QS_BYTES; o += 64 * 16) *reinterpret_cast<i32x4*>(Qs + o) = izero;
-    if (P2) {   // the weight columns of the other head's step group are never written: zero for good
-      static_assert(PS_BYTES % 16 == 0, "");
-      for (int o = lane * 16; o < PS_BYTES; o += 64 * 16) *reinterpret_cast<i32x4*>(Ps + o) = izero;
-    }
     __builtin_amdgcn_wave_barrier();
   }
   S = min(max(seq_len_raw, 0), a.max_seq_len);
@@ -942,9 +953,10 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
     for (int hd = 0; hd < R; ++hd) { Mml[hd] = m_run[hd]; Mml[R + hd] = l_run[hd]; }
   }
   __syncthreads();
-  for (int idx = tid; idx < nh * RD; idx += 64 * NW) {
+  for (int idx = tid; idx < R * RD; idx += 64 * NW) {
     // c: the real head's channel; cv: where it sits among the 128 channels the waves worked on
-    const int hd = idx / RD, c = idx % RD, cv = P2 ? c + RD * hd : c;
+    const int hd = idx / RD, c = idx % RD, cv = P2 ? c + RD * (hd / HPK) : c;
+    if (!head_live(hd)) continue;
     float M = -INFINITY;
 #pragma unroll
     for (int w = 0; w < NW; ++w) M = fmaxf(M, reinterpret_cast<const float*>(smem + w * WAVE_LDS)[NC * D + hd]);
@@ -972,19 +984,19 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
         L = L * w0 + tp[D + 1] * w1;
       }
       const float r = (L > 0.f) ? o / L : 0.f;
-      a.out[(bhq0 + hd) * RD + c] = f2h_rne(r);
-      if (a.out_f32) a.out_f32[(bhq0 + hd) * RD + c] = r;
+      a.out[head_row(hd) * RD + c] = f2h_rne(r);
+      if (a.out_f32) a.out_f32[head_row(hd) * RD + c] = r;
     } else {
       // device-scope stores: they go through to memory, past the per-XCD L2, so that a workgroup
       // on another XCD can read them without any cache write-back or invalidation
-      float* part = a.partials + ((bhq0 + hd) * a.n_slots + split) * (RD + 2);
+      float* part = a.partials + (head_row(hd) * a.n_slots + split) * (RD + 2);
       __hip_atomic_store(part + c, o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (c == 0) {
         __hip_atomic_store(part + RD, M, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // M in log2 units
         __hip_atomic_store(part + RD + 1, L, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
       if (TM == 2 && split == 0) {   // the tail's partial travels with split 0's, in the slot after the splits
-        float* tpart = a.partials + ((bhq0 + hd) * a.n_slots + a.n_split) * (RD + 2);
+        float* tpart = a.partials + (head_row(hd) * a.n_slots + a.n_split) * (RD + 2);
         const float* tp = s_tail + hd * (D + 2);
         __hip_atomic_store(tpart + c, tp[cv], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (c == 0) {
@@ -1034,8 +1046,9 @@ inline void launch_r(const DecodeArgs& a, hipStream_t st) {
 
 template <int BITS>
 int32_t launch_bits(const DecodeArgs& a, hipStream_t st) {
-  if (a.pair_heads) {   // two kv heads of 64 channels per workgroup
-    launch_n3<BITS, 2, 2, false, true>(a, st);
+  if (a.pair_heads) {   // two kv heads of 64 channels per workgroup, one or two query heads of each
+    if (a.heads_per_group == 1) launch_n3<BITS, 2, 2, false, true>(a, st);
+    else launch_n3<BITS, 2, 4, false, true>(a, st);
     return DQ_OK;
   }
   const int rep = a.heads_per_group;   // query heads per workgroup (the last group may hold fewer)

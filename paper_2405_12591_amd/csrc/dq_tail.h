@@ -26,13 +26,14 @@ __device__ __forceinline__ float tail_dpp(float v) {
 
 // D: head dimension.  NWV: waves in the workgroup (all of them must call both functions).
 // HEADS: query heads handled together (every row read serves all of them).
-// PAIR: D = 128 stands for two neighbouring kv heads of 64 channels, each with its own query head
-// (HEADS = 2): a row is the two heads' rows side by side (the lanes of each half read their own
-// head's array), query head hd is zero outside its own half, and so result[hd] is head hd's
-// partial in channels [64 hd, 64 hd + 64); the other half of it means nothing.
+// PAIR: D = 128 stands for two neighbouring kv heads of 64 channels, each with HEADS / 2 query heads
+// of its own: a row is the two kv heads' rows side by side (the lanes of each half read their own
+// head's array), query head hd is zero outside the half p = hd / (HEADS / 2) of its kv head, and so
+// result[hd] is its partial in channels [64 p, 64 p + 64); the other half of it means nothing.
 template <int D, int NWV, int HEADS, bool PAIR = false>
 struct TailBlock {
-  static_assert(!PAIR || (D == 128 && HEADS == 2), "a pair is two heads of 64 channels");
+  static_assert(!PAIR || (D == 128 && HEADS % 2 == 0), "a pair is two heads of 64 channels");
+  static constexpr int HPK = PAIR ? HEADS / 2 : HEADS;   // query heads per kv head
   static constexpr int RD = PAIR ? D / 2 : D;   // halves per row in memory
   static constexpr int LPR = D / 8;      // lanes per row
   static constexpr int RPI = 64 / LPR;   // rows per wave-wide load
@@ -57,8 +58,9 @@ struct TailBlock {
     return batch * ROWS_PER_BATCH + RPI * (wave + NWV * it) + rsub;
   }
 
-  // heads [hq0, hq0 + nh) of sequence b are the query heads of kv head h (nh <= HB)
-  __device__ __forceinline__ void issue_keys(const DecodeArgs& a, int b, int h, long hq0, int nh) {
+  // heads [hq0, hq0 + nh) of sequence b are the query heads of kv head h (nh <= HPK); a pair: those of
+  // kv head h + 1 lie heads_per_kv further on
+  __device__ __forceinline__ void issue_keys(const DecodeArgs& a, int b, int h, long hq0, int nh, int heads_per_kv) {
     lane = threadIdx.x & 63; wave = threadIdx.x >> 6;
     chunk = lane % LPR; rsub = lane / LPR;
     cap = a.tail.capacity;
@@ -70,8 +72,10 @@ struct TailBlock {
     vt = a.tail.v_tail + ((long)b * H + h + own) * cap * RD + 8 * part;
     qk = a.scale * 1.4426950408889634f;
 #pragma unroll
-    for (int hd = 0; hd < HB; ++hd)
-      qraw[hd] = *reinterpret_cast<const tail_u4*>(a.q + ((long)b * a.q_heads + hq0 + min(hd, nh - 1)) * RD + 8 * part);
+    for (int hd = 0; hd < HB; ++hd) {
+      const long head = hq0 + (PAIR ? (hd / HPK) * heads_per_kv : 0) + min(hd % HPK, nh - 1);
+      qraw[hd] = *reinterpret_cast<const tail_u4*>(a.q + ((long)b * a.q_heads + head) * RD + 8 * part);
+    }
     // Rows below the capacity are readable whatever the tail's length, which is not known yet; rows
     // past the capacity read the last row instead.  No branches: the caller may have other loads in
     // flight whose count the compiler has to keep.
@@ -102,7 +106,7 @@ struct TailBlock {
         float v = part[hd];
         // a pair: the lanes on the other head's half of the row add an outright zero (their query is
         // zero, but zero times whatever that head's row holds need not be)
-        if (PAIR && chunk / (LPR / 2) != hd) v = 0.f;
+        if (PAIR && chunk / (LPR / 2) != hd / HPK) v = 0.f;
         v += tail_dpp<0xB1>(v);                    // lane ^ 1
         v += tail_dpp<0x4E>(v);                    // lane ^ 2
         v += tail_dpp<0x141>(v);                   // 7 - lane within 8
@@ -125,7 +129,7 @@ struct TailBlock {
       asm volatile("" : "+v"(qraw[hd].x), "+v"(qraw[hd].y), "+v"(qraw[hd].z), "+v"(qraw[hd].w));
       const tail_h8 qv = __builtin_bit_cast(tail_h8, qraw[hd]);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) qreg[hd][i] = (hd < nh && (!PAIR || chunk / (LPR / 2) == hd)) ? (float)qv[i] * qk : 0.f;
+      for (int i = 0; i < 8; ++i) qreg[hd][i] = (hd % HPK < nh && (!PAIR || chunk / (LPR / 2) == hd / HPK)) ? (float)qv[i] * qk : 0.f;
     }
     const int n_batches = (n_tail + ROWS_PER_BATCH - 1) / ROWS_PER_BATCH;
     // ---- scores ----
@@ -201,7 +205,7 @@ struct TailBlock {
     // lanes with the same chunk (different rows) add up, then the waves
 #pragma unroll
     for (int hd = 0; hd < HB; ++hd) {
-      if (hd < nh) {
+      if (hd % HPK < nh) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           float v = acc[hd][i];
@@ -211,8 +215,9 @@ struct TailBlock {
       }
     }
     __syncthreads();
-    for (int idx = tid; idx < nh * D; idx += 64 * NWV) {
+    for (int idx = tid; idx < HB * D; idx += 64 * NWV) {
       const int hd = idx / D, c = idx % D;
+      if (hd % HPK >= nh) continue;
       float o = 0.f;
 #pragma unroll
       for (int w = 0; w < NWV; ++w) o += red[(w * HB + hd) * D + c];
