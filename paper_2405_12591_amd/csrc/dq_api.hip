@@ -9,36 +9,33 @@ namespace dq {
 static std::atomic<int> g_last_hip_error{0};
 void set_last_hip_error(hipError_t e) { g_last_hip_error.store((int)e); }
 
-// Launch shape of the matrix-core kernel: n splits of every (sequence, kv head) and nw waves per
-// workgroup.  Measured on MI355X: a wave needs about eight 128-token tiles to amortise its start-up
-// and its share of the merge (four when it serves four query heads: more arithmetic per tile to
-// overlap); about 2048 resident waves (8 per CU) stream fastest when they can be had at that depth,
-// 1024 (one 4-wave workgroup per CU) otherwise; every extra split costs a partial write, a ticket
-// and a merge.  Small problems are bound by the fixed start-up and merge latencies: there one tile
-// per wave is best as long as every workgroup finds a compute unit of its own.
-static void choose_mfma_shape(int units, int max_tiles, int rep, int bits, int* n_out, int* nw_out) {
-  auto tiles_per_wave = [&](int n, int nw) { return max_tiles / (n * nw); };
-  const int deep = rep >= 4 ? 4 : 8;
-  // A: deep and wide (8-bit codes: a wave's ring of chunks is twice as large and an 8-wave
-  // workgroup would run out of registers)
-  for (int nw = (bits == 8 ? 4 : 8); nw >= 4; nw -= 4) {
-    const int cap = 256 * (8 / nw);            // workgroups resident on the chip
-    for (int n = cap / units; n >= 1; --n) {
-      if (n > kMaxSplits) continue;
-      if (tiles_per_wave(n, nw) >= deep && (long)units * n * nw >= 1536) { *n_out = n; *nw_out = nw; return; }
+// Launch shape of the matrix-core kernel: n splits of every (sequence, kv head) unit and nw waves per
+// workgroup, the pair with the least estimated time.  The estimate (in us, fitted to 533 measured
+// launches of 4 to 512 units and 2 to 128 tiles, 2, 4 and 8 bits, one to four heads per workgroup,
+// each in up to 22 shapes; the pair it picks is 1 % slower than the fastest measured one on average, the
+// rule of fixed depths this replaces was 4 % slower and up to 60 %: 128 units of 32 tiles with four
+// heads took 26.6 us in 4 splits of 4 waves, 19.2 in the 2 of 8 picked here):
+//   the busiest compute unit holds k = ceil(units n / 256) workgroups, k nw / 4 waves on each SIMD;
+//   a wave works ceil(tiles / (n nw)) tiles, each of which takes the longer of one wave's chain
+//   (requests, unpacking, two contractions, softmax) and the SIMD's issue of all its waves' tiles,
+//   which grows with the code width and the heads;
+//   every wave on a SIMD and every split (partial, ticket, merge) costs a fixed amount.
+static void choose_mfma_shape(int units, int max_tiles, int heads, int bits, int* n_out, int* nw_out) {
+  const float chain = 1.67f + 0.35f * (heads - 1), issue = 0.61f + 0.32f * bits + 0.045f * (heads - 1);
+  static const int kSplits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
+  float best = 3.0e38f;
+  for (const int n : kSplits) {
+    if (n > kMaxSplits || n > max_tiles) break;
+    // (8-bit codes: a wave's ring of chunks is twice as large and an 8-wave workgroup would run out of
+    // registers)
+    for (int nw = 4; nw <= (bits == 8 ? 4 : 8); nw += 4) {
+      const long per_cu = ((long)units * n + 255) / 256;
+      const float waves = 0.25f * (float)(per_cu * nw);                 // per SIMD
+      const int tiles = (max_tiles + n * nw - 1) / (n * nw);           // of the busiest wave
+      const float t = tiles * fmaxf(chain, waves * issue) + 1.07f * waves + (n > 1 ? 2.76f + 0.173f * n : 0.f);
+      if (t < best) { best = t; *n_out = n; *nw_out = nw; }
     }
   }
-  // B: deep, at least half the chip
-  for (int n = 512 / units; n >= 1; --n) {
-    if (n > kMaxSplits) continue;
-    if (tiles_per_wave(n, 4) >= 8 && (long)units * n * 4 >= 512) { *n_out = n; *nw_out = 4; return; }
-  }
-  // C: small problem: one tile per wave while a workgroup per compute unit is enough, else two
-  for (int n = (512 / units < kMaxSplits ? 512 / units : kMaxSplits); n >= 1; --n) {
-    const int need = (units * n <= 256) ? 1 : 2;
-    if (tiles_per_wave(n, 4) >= need) { *n_out = n; *nw_out = 4; return; }
-  }
-  *n_out = 1; *nw_out = 4;
 }
 
 int choose_splits(const dq_format* f, int batch, int q_heads, int kv_heads, int max_seq_len, bool mfma,
