@@ -210,7 +210,7 @@ static int32_t decode_impl(const dq_format* fmt, const dq_cache* cache, const ui
   a.unit_map = (a.n_split == 1 && a.head_groups == 1 && units <= 256) ? 3 : 0;
   if (const uint32_t umap = (flags >> 20) & 0xFu) a.unit_map = (int)umap - 1;   // the caller's override
   a.rows_on_x = ((long)cache->batch * q_heads > kMaxGridY) ? 1 : 0;   // rows: at most batch * q_heads of them
-  a.n_slots = a.n_split + (tail ? 1 : 0);
+  a.n_slots = a.n_split + (tail && !use_mfma ? 1 : 0);   // the matrix-core kernel's waves take the tail along
   if (tail) a.tail = *tail;
   else a.tail = dq_tail{nullptr, nullptr, nullptr, 0};
 #ifdef DQ_TIMELINE

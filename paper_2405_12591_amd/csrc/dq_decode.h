@@ -17,7 +17,7 @@ struct DecodeArgs {
   float* partials;         // [B*Hq, n_split, d + 2]
   int32_t* counters;       // [B*Hkv*head_groups] zero between calls
   int n_split;
-  int n_slots;             // partial slots per (b, head): n_split, plus one for the fp16 tail
+  int n_slots;             // partial slots per (b, head): n_split, plus one for the fp16 tail on the plain path
   dq_tail tail;            // k_tail == nullptr: no tail
   int nw;                  // waves per workgroup of the matrix-core kernel (4 or 8)
   int head_groups;         // matrix-core kernel: workgroups per (sequence, kv head, split) ...

@@ -446,7 +446,7 @@ __global__ __launch_bounds__(256) void tail_partial_kernel(DecodeArgs a, float m
     const long hq0 = (long)h * rep + hg;
     const int tail_len = a.tail.tail_lens[b];
     TB tb;
-    tb.issue_keys(a, b, h, hq0, nh, 0);
+    tb.issue_keys(a, b, h, hq0, nh);
     tb.finish(tail_len, nh, scratch, result);
     for (int idx = threadIdx.x; idx < nh * (D + 2); idx += 256) {
       const int hd = idx / (D + 2), c = idx % (D + 2);

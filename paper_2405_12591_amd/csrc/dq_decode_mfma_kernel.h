@@ -165,12 +165,10 @@ __device__ __forceinline__ float pow2i(int e) {
 
 // BITS: code width.  NG: step groups per token row (group = 128 / NG).  R: query heads per kv head.  NW: wavefronts per workgroup (4 or 8); the tiles
 // of one (sequence, kv head) are dealt round-robin to the NW waves of each of its n_split workgroups.
-// TM: what to do about the fp16 tail (tokens not yet compressed).  0: there is none.  1: the launch
-// has one workgroup per (sequence, kv head), which works the tail off while its first codes are on
-// their way.  2: the launch has several workgroups per (sequence, kv head); the one of split 0 does
-// the same and hands the tail's partial in with its own.  (A workgroup of its own for the tail was
-// tried: on a full chip its few dependent loads take tens of microseconds behind the streams, and
-// the workgroups queued behind it start that much later.)
+// TM: what to do about the fp16 tail (tokens not yet compressed).  0: there is none.  1, 2: its rows are
+// dealt over all waves of the (sequence, kv head), which work them off while their first codes are on
+// their way (1: the launch has one workgroup per (sequence, kv head); 2: several, so fewer rows per
+// wave are requested up front).
 // N3: three local tensors (format.i3 == 8).  Row a2*8 + e of the codes then belongs to the bond
 // index e of the third tensor instead of a token: the tile's 128 row sums y are computed as
 // before, the scores of the eight tokens of a run are s[a3] = sum_e T_3^K[e, a3] y[e], and the
@@ -222,11 +220,11 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   constexpr int WAVE_LDS = QS_BYTES + PS_BYTES + SS_BYTES;
   static_assert(WAVE_LDS >= NC * D * 4 + 2 * R * 4, "merge area must fit the wave's LDS");
   __shared__ __attribute__((aligned(16))) unsigned char smem[NW * WAVE_LDS];
-  // the fp16 tail's partial result (computed once per (sequence, kv head), by split 0, before the
-  // first tile; its scratch borrows the waves' areas, which are not in use yet)
-  typedef TailBlock<D, NW, R, P2> Tail;
-  static_assert(sizeof(smem) >= Tail::kScratchFloats * sizeof(float), "tail scratch must fit the waves' LDS");
-  __shared__ float s_tail[R * (D + 2)];
+  // the waves' partial results over the fp16 tail
+  // (128 rows requested up front, by two workgroups if TM == 2; fewer where the heads leave fewer registers)
+  constexpr int kTailBatch = TM == 1 ? 32 / NW : 16 / NW, kTailMost = R == 1 ? 8 : (R == 4 && (P2 || N3)) ? 2 : 4;
+  typedef TailWave<R, kTailBatch < kTailMost ? kTailBatch : kTailMost, P2> Tail;
+  __shared__ float s_tail[TM ? NW * Tail::kResultFloats : 1];
   __shared__ int s_last;
   __shared__ float s_wgt[4][kMaxSplits + 1];
   __shared__ float s_sum[4];
@@ -880,19 +878,18 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   // The first requests go out in one straight line of code, without a branch: across a branch the
   // compiler loses count of the loads in flight and makes every later wait a wait for all of them.
   // So a wave whose first tile lies past max_seq_len reads tile 0 instead (in bounds: the cache
-  // holds at least one block) and throws it away, and with TM == 1 every row of the tail below its
-  // capacity is requested whatever the tail's length.  The tail's rows go first: they are worked
-  // off while the codes are on their way.
+  // holds at least one block) and throws it away, and the tail's rows below its capacity are requested
+  // whatever its length.  The tail's rows go first: they are worked off while the codes are on
+  // their way.
   Tail tb;
-  const bool do_tail = (TM == 1) || (TM == 2 && split == 0);   // TM == 2: a branch, and coarser waits
-  if (do_tail) tb.issue_keys(a, b, h, hq_first, nhk, heads_per_kv);
+  if (TM) tb.issue(a, b, h, hq_first, nhk, heads_per_kv, first_tile, tile_stride);
   issue_tile(spec_ok ? first_tile : 0);
   // Both lengths are requested only now (a scalar load that is still out holds up every wait on
   // scalar data, the addresses of the loads above among them) and before the asm statements below
   // (after them the compiler no longer treats memory as unchanged and would fetch these with vector
   // loads, whose wait covers the requests above).
   const int seq_len_raw = a.seq_lens[b];
-  const int tail_len_raw = do_tail ? a.tail.tail_lens[b] : 0;
+  const int tail_len_raw = TM ? a.tail.tail_lens[b] : 0;
 #pragma unroll
   for (int f = 0; f < F; ++f) {
     const int fold_head = 2 * f + (n >> 3);
@@ -903,7 +900,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
       bq[f][i] = __builtin_bit_cast(_Float16, (uint16_t)(live ? q_raw[f][i] : 0u));
     }
   }
-  if (do_tail) tb.finish(tail_len_raw, nhk, reinterpret_cast<float*>(smem), s_tail);
+  if (TM) tb.finish(tail_len_raw, nhk, s_tail + wave * Tail::kResultFloats);
 
   if (CG == 2) {
     // A channel contributes nothing to the other group's columns: those bytes of the query limbs
@@ -959,7 +956,10 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
     if (!head_live(hd)) continue;
     float M = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) M = fmaxf(M, reinterpret_cast<const float*>(smem + w * WAVE_LDS)[NC * D + hd]);
+    for (int w = 0; w < NW; ++w) {
+      M = fmaxf(M, reinterpret_cast<const float*>(smem + w * WAVE_LDS)[NC * D + hd]);
+      if (TM) M = fmaxf(M, s_tail[w * Tail::kResultFloats + hd * (D + 2) + D]);
+    }
     float o = 0.f, L = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
@@ -972,17 +972,14 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
                            : col[0] * 16384.f + col[D] * 128.f + col[2 * D];
       o = fmaf(v, wgt, o);
       L = fmaf(base[NC * D + R + hd], wgt, L);
+      if (TM) {   // the wave's share of the fp16 tail
+        const float* tp = s_tail + w * Tail::kResultFloats + hd * (D + 2);
+        const float wt = (tp[D] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(tp[D] - M);
+        o = fmaf(tp[cv], wt, o);
+        L = fmaf(tp[D + 1], wt, L);
+      }
     }
     if (a.n_split == 1) {   // this workgroup saw the whole sequence: finish here
-      if (TM == 1) {  // fold in the fp16 tail's partial
-        const float* tp = s_tail + hd * (D + 2);
-        const float mt = tp[D];
-        const float Mn = fmaxf(M, mt);
-        const float w0 = (M == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(M - Mn);
-        const float w1 = (mt == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mt - Mn);
-        o = o * w0 + tp[cv] * w1;
-        L = L * w0 + tp[D + 1] * w1;
-      }
       const float r = (L > 0.f) ? o / L : 0.f;
       a.out[head_row(hd) * RD + c] = f2h_rne(r);
       if (a.out_f32) a.out_f32[head_row(hd) * RD + c] = r;
@@ -994,15 +991,6 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
       if (c == 0) {
         __hip_atomic_store(part + RD, M, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // M in log2 units
         __hip_atomic_store(part + RD + 1, L, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      if (TM == 2 && split == 0) {   // the tail's partial travels with split 0's, in the slot after the splits
-        float* tpart = a.partials + (head_row(hd) * a.n_slots + a.n_split) * (RD + 2);
-        const float* tp = s_tail + hd * (D + 2);
-        __hip_atomic_store(tpart + c, tp[cv], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (c == 0) {
-          __hip_atomic_store(tpart + RD, tp[D], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          __hip_atomic_store(tpart + RD + 1, tp[D + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
       }
     }
   }
