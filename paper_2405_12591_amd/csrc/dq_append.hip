@@ -140,8 +140,7 @@ extern "C" int32_t dq_cache_append(const dq_format* fmt, dq_cache* cache, const 
   if (flags & DQ_APPEND_NO_COMPRESS) return DQ_OK;
   // every sequence whose tail filled (a slot index in the plan; -1 skips the others) is compressed
   // from its tail buffer; the fp32 large tensors are not kept
-  const int32_t rc = dq_compress_kv_ex(fmt, cache, state->k_tail, state->v_tail, fmt->block_tokens, area.blk_idx,
-                                       nullptr, workspace, cbytes, DQ_COMPRESS_NO_LARGE, hip_stream);
+  const int32_t rc = compress_filled_tails(fmt, cache, state->k_tail, state->v_tail, area.blk_idx, workspace, cbytes, st);
   if (rc != DQ_OK) return rc;
   if (n_rows > 1) {
     if (fmt->head_dim == 128)

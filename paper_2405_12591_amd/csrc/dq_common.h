@@ -18,6 +18,12 @@ constexpr int kMaxDecodeRows = 1 << 24;   // (sequence, query head) pairs one de
 constexpr int kMaxTailRows = 1024; // rows of the fp16 tail a decode call takes per sequence and kv head
 constexpr int kRun = 8;            // side of the third local tensor: tokens per run it mixes
 
+constexpr uint32_t kCompressMostlyIdle = 1u << 31;   // internal flag of a compression call, see CompressJob
+// The compression launch of dq_cache_append (dq_compress.hip): one block per (sequence, kv head) whose
+// tail has filled, blk_idx[b] < 0 for all others.
+int32_t compress_filled_tails(const dq_format* fmt, dq_cache* cache, const uint16_t* k_tail, const uint16_t* v_tail,
+                              const int32_t* blk_idx, void* workspace, size_t workspace_bytes, hipStream_t st);
+
 // Record a failed HIP runtime call for dq_last_hip_error().
 void set_last_hip_error(hipError_t e);
 

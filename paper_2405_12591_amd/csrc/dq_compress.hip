@@ -18,6 +18,8 @@ struct CompressJob {
   const int32_t* blk_idx;    // [B]
   const int32_t* n_valid;    // [B] or null
   int keep_large;            // the one-kernel three-tensor build also leaves its fp32 rows in the workspace
+  int mostly_idle;           // most calls skip every sequence (a serving step whose tails rarely fill)
+  int batch;
 };
 
 // Work unit `unit` = (((b * H + h) * n_blocks) + j) * 2 + which.  slot < 0: nothing to do (sequence
@@ -943,6 +945,16 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 5 : PART == 3 ? ((PAIR || N3)
     }
     if (threadIdx.x == 0) { call_status[0] = flags; call_status[1] = sweeps; }
   };
+  if (QB != 0 && PART == 0 && job.mostly_idle) {
+    // A call that skips every sequence ends here, without a ticket: hundreds of workgroups drawing
+    // theirs from one counter at the same time took 4.1 us of the 6.1 such a launch cost (2.0 now).
+    bool any = false;
+    for (int i = threadIdx.x & 63; i < job.batch; i += 64) any |= job.blk_idx[i] >= 0;
+    if (!__any(any)) {
+      if (blockIdx.x == 0 && threadIdx.x < 2) call_status[threadIdx.x] = 0;
+      return;
+    }
+  }
   const Geometry g = make_geometry(fmt, cache.kv_heads, cache.block_capacity);
   // the work unit (of the pair's first head); the second head's unit lies `unit_gap` further on
   int unit = blockIdx.x;
@@ -1717,7 +1729,8 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
   float* large_ws = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + kWsHeaderBytes);
   const int units = cache->batch * cache->kv_heads * 2 * n_blocks;
   int32_t* unit_status = reinterpret_cast<int32_t*>(large_ws + (size_t)units * fmt->block_tokens * fmt->head_dim);
-  const CompressJob job = {k_new, v_new, t_new, n_blocks, blk_idx, n_valid, (flags & DQ_COMPRESS_NO_LARGE) ? 0 : 1};
+  const CompressJob job = {k_new, v_new, t_new, n_blocks, blk_idx, n_valid, (flags & DQ_COMPRESS_NO_LARGE) ? 0 : 1,
+                           (flags & kCompressMostlyIdle) ? 1 : 0, cache->batch};
   const size_t dlds = decompose_lds_bytes(fmt->i1 * fmt->j1, fmt->head_dim, fmt->i1);
 #define DQ_LAUNCH_DECOMPOSE(J, DD_)                                                                      \
   hipLaunchKernelGGL((decompose_kernel<J, DD_>), dim3(units), dim3(64), dlds, st, *fmt, *cache, job, large_ws, \
@@ -1939,6 +1952,14 @@ extern "C" int32_t dq_compress_kv_blocks(const dq_format* fmt, dq_cache* cache, 
   return compress_impl(fmt, cache, k_new, v_new, t_new, n_blocks, blk_idx, n_valid, workspace,
                        workspace_bytes, DQ_COMPRESS_KEEP_LARGE, hip_stream);
 }
+
+namespace dq {
+int32_t compress_filled_tails(const dq_format* fmt, dq_cache* cache, const uint16_t* k_tail, const uint16_t* v_tail,
+                              const int32_t* blk_idx, void* workspace, size_t workspace_bytes, hipStream_t st) {
+  return compress_impl(fmt, cache, k_tail, v_tail, fmt->block_tokens, 1, blk_idx, nullptr, workspace, workspace_bytes,
+                       DQ_COMPRESS_NO_LARGE | kCompressMostlyIdle, st);
+}
+}  // namespace dq
 
 extern "C" int32_t dq_compress_kv_ex(const dq_format* fmt, dq_cache* cache, const uint16_t* k_new,
                                      const uint16_t* v_new, int32_t t_new, const int32_t* blk_idx,
