@@ -151,6 +151,17 @@ class Format:
         return _CFormat(self.bits, self.group, self.head_dim, self.j1, self.j2, self.block_tokens, self.i3,
                         self.levels, self.i1)
 
+    def _ref(self):
+        """The C struct by reference, built once: a Format never changes."""
+        ref = self.__dict__.get("_c_ref")
+        if ref is None:
+            ref = C.byref(self.c())
+            object.__setattr__(self, "_c_ref", ref)   # (the dataclass is frozen)
+        return ref
+
+    def __getstate__(self):   # a pointer does not travel
+        return {k: v for k, v in self.__dict__.items() if k != "_c_ref"}
+
     @property
     def small_side(self) -> int:
         return self.i1 * self.j1
@@ -233,8 +244,16 @@ def cache_from_numpy(fmt: Format, arrays, device="cuda:0") -> Cache:
     return Cache(fmt, tensors, b, h, nb)
 
 
+# The current stream's handle without the Stream object around it (1.8 us of an 8 us call) where torch
+# has that call
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(device) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+    index = device.index
+    if _raw_stream is None or index is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return _raw_stream(index)
 
 
 def decode_workspace(fmt: Format, batch: int, q_heads: int, kv_heads: int, max_seq_len: int,
@@ -285,39 +304,42 @@ def attn_decode(cache: Cache, q: torch.Tensor, seq_lens: torch.Tensor, max_seq_l
         raise DQError("q must be contiguous fp16 and seq_lens int32")
     # the library sees pointers only: sizes are checked here, so that a tensor of the wrong shape
     # raises instead of sending a kernel past its end
-    if q.dim() != 3 or q.shape[0] != cache.batch or q.shape[2] != fmt.head_dim:
+    shape = q.shape
+    if len(shape) != 3 or shape[0] != cache.batch or shape[2] != fmt.head_dim:
         raise DQError("q must be [batch, q_heads, head_dim] with the cache's batch and head_dim")
-    bsz, hq, d = q.shape
+    bsz, hq, d = shape
     if seq_lens.numel() != bsz or not seq_lens.is_contiguous():
         raise DQError("seq_lens must hold one length per sequence")
     if out is None:
         out = torch.empty_like(q)
-    elif out.shape != q.shape or out.dtype != torch.float16 or not out.is_contiguous():
+    elif out.shape != shape or out.dtype != torch.float16 or not out.is_contiguous():
         raise DQError("out must be contiguous fp16 of q's shape")
-    if out_f32 is not None and (out_f32.shape != q.shape or out_f32.dtype != torch.float32 or not out_f32.is_contiguous()):
+    if out_f32 is not None and (out_f32.shape != shape or out_f32.dtype != torch.float32 or not out_f32.is_contiguous()):
         raise DQError("out_f32 must be contiguous fp32 of q's shape")
-    cf = fmt.c()
     ct = None
     if tail is not None:
         ct = _tail_struct(cache, tail, bsz)
+    fmt_ref, cache_ref, stream = fmt._ref(), C.byref(cache.c), _stream_ptr(q.device)
     if workspace is None:
         if kernel_events is not None:
             raise DQError("kernel events need a workspace call")
-        st = lib.dq_attn_decode_static(C.byref(cf), C.byref(cache.c), q.data_ptr(), hq, seq_lens.data_ptr(), max_seq_len,
+        st = lib.dq_attn_decode_static(fmt_ref, cache_ref, q.data_ptr(), hq, seq_lens.data_ptr(), max_seq_len,
                                        None if ct is None else C.byref(ct), softmax_scale, out.data_ptr(),
-                                       0 if out_f32 is None else out_f32.data_ptr(), flags, _stream_ptr(q.device))
-        _check(st, "dq_attn_decode_static")
+                                       0 if out_f32 is None else out_f32.data_ptr(), flags, stream)
+        if st:
+            _check(st, "dq_attn_decode_static")
         return out
-    args = (C.byref(cf), C.byref(cache.c), q.data_ptr(), hq, seq_lens.data_ptr(), max_seq_len,
+    args = (fmt_ref, cache_ref, q.data_ptr(), hq, seq_lens.data_ptr(), max_seq_len,
             softmax_scale, out.data_ptr(), 0 if out_f32 is None else out_f32.data_ptr(),
-            workspace.data_ptr(), workspace.numel(), flags, _stream_ptr(q.device))
+            workspace.data_ptr(), workspace.numel(), flags, stream)
     if tail is not None:
         st = lib.dq_attn_decode_tail(*args[:6], C.byref(ct), *args[6:])
     elif kernel_events is None:
         st = lib.dq_attn_decode(*args)
     else:
         st = lib.dq_attn_decode_timed(*args, kernel_events[0].cuda_event, kernel_events[1].cuda_event)
-    _check(st, "dq_attn_decode")
+    if st:
+        _check(st, "dq_attn_decode")
     return out
 
 
@@ -352,11 +374,10 @@ def compress_kv(cache: Cache, k_new: torch.Tensor, v_new: torch.Tensor, blk_idx:
     keep_large=False: the fp32 large tensors need not be left in the workspace
     (dq_compress_kv_ex with DQ_COMPRESS_NO_LARGE); waves, plain: its launch overrides."""
     _check_compress_args(cache, k_new, v_new, blk_idx, n_valid)
-    fmt_c = cache.fmt.c()
     t_new = k_new.shape[2]
     if t_new > cache.fmt.block_tokens:
         raise DQError("compress_kv takes at most one block of rows; compress_kv_blocks takes more")
-    args = (C.byref(fmt_c), C.byref(cache.c), k_new.data_ptr(), v_new.data_ptr(), t_new,
+    args = (cache.fmt._ref(), C.byref(cache.c), k_new.data_ptr(), v_new.data_ptr(), t_new,
             blk_idx.data_ptr(), 0 if n_valid is None else n_valid.data_ptr(),
             workspace.data_ptr(), workspace.numel())
     if keep_large and not waves and not plain:
@@ -372,8 +393,7 @@ def compress_kv_blocks(cache: Cache, k_new: torch.Tensor, v_new: torch.Tensor, b
     """Compress k_new, v_new [B, H, t_new, d], any t_new >= 1, into the block slots from blk_idx[b]
     on (dq_compress_kv_blocks; dq_compress_kv_ex when a flag is given)."""
     _check_compress_args(cache, k_new, v_new, blk_idx, n_valid)
-    cf = cache.fmt.c()
-    args = (C.byref(cf), C.byref(cache.c), k_new.data_ptr(), v_new.data_ptr(),
+    args = (cache.fmt._ref(), C.byref(cache.c), k_new.data_ptr(), v_new.data_ptr(),
             k_new.shape[2], blk_idx.data_ptr(), 0 if n_valid is None else n_valid.data_ptr(),
             workspace.data_ptr(), workspace.numel())
     if keep_large and not waves and not plain:
@@ -449,9 +469,8 @@ def cache_append(cache: Cache, k_tail: torch.Tensor, v_tail: torch.Tensor, tail_
     if k_rows.dim() != 4 or k_rows.shape != v_rows.shape or tuple(k_rows.shape[:2]) != want_tail[:2] \
             or k_rows.shape[3] != fmt.head_dim or not 1 <= k_rows.shape[2] <= fmt.block_tokens:
         raise DQError("k_rows/v_rows must be [batch, kv_heads, n_rows <= block_tokens, head_dim]")
-    cf = fmt.c()
     state = _CKVState(k_tail.data_ptr(), v_tail.data_ptr(), tail_lens.data_ptr(), seq_lens.data_ptr())
-    st = lib.dq_cache_append(C.byref(cf), C.byref(cache.c), C.byref(state), k_rows.data_ptr(), v_rows.data_ptr(),
+    st = lib.dq_cache_append(fmt._ref(), C.byref(cache.c), C.byref(state), k_rows.data_ptr(), v_rows.data_ptr(),
                              k_rows.shape[2], 0 if counts is None else counts.data_ptr(), workspace.data_ptr(),
                              workspace.numel(), flags, _stream_ptr(k_rows.device))
     _check(st, "dq_cache_append")
