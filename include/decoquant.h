@@ -243,7 +243,7 @@ size_t dq_compress_workspace_bytes(const dq_format* fmt, int32_t batch, int32_t 
  *   n_valid       i32 [B] device, rows >= n_valid[b] (and rows >= t_new) count as zero; may be NULL;
  *                 a sequence with no valid row is skipped like one with a negative blk_idx
  * The decomposition is an eigen-decomposition of the fp64 Gram matrix M M^T (j1 x j1) by
- * cyclic Jacobi rotations: T_S = U diag(sigma), T_L = diag(1/sigma) U^T M; directions with
+ * Jacobi rotations: T_S = U diag(sigma), T_L = diag(1/sigma) U^T M; directions with
  * sigma <= 1e-6 sigma_max are dropped (T_S column and T_L row zero).  T_S saturates to the
  * fp16 range; bit 0 of the int32 at workspace[0] is set if that happened in any block of this
  * call, cleared otherwise.  The int32 at workspace[4] receives the largest number of Jacobi
@@ -285,18 +285,17 @@ int32_t dq_compress_kv_blocks(const dq_format* fmt, dq_cache* cache, const uint1
 #define DQ_COMPRESS_NO_LARGE 1u   /* the caller will not read them: the library may skip that hand-off */
 #define DQ_COMPRESS_PLAIN 2u      /* use the plain vector-code decomposition kernel whatever the shape (for comparison) */
 #define DQ_COMPRESS_WAVES(n) (((uint32_t)(n) & 0xFu) << 8) /* wavefronts per block of the tuned decomposition
-                                     kernel: 1, 2 or 4; 0 leaves the choice to the library (for sweeps).  With three
-                                     local tensors 1 selects the build that makes both cuts and quantizes in one
-                                     launch (the library's choice above 512 blocks), 2 and 4 the three launches */
+                                     kernel: 1, 2 or 4; 0 leaves the choice to the library (for sweeps).  1 selects
+                                     the launches of a prompt (the library's choice above 1024 blocks, or 512 with
+                                     three local tensors) */
 
 /*
  * dq_compress_kv_blocks with flags (t_new <= T_b makes it dq_compress_kv): for callers that do not
  * read the fp32 large tensors back, such as a serving loop that compresses a block whenever a
  * tail fills (Section 3.2).  With DQ_COMPRESS_NO_LARGE the large-tensor region of the workspace
- * holds nothing defined after the call; where the library supports it (two local tensors, at most
- * 1024 blocks per call, keys and values counted apart; head_dim 128 with j1 16 and group 128 or 64,
+ * holds nothing defined after the call; where the library supports it (two local tensors; head_dim 128 with j1 16 and group 128 or 64,
  * or head_dim 64 with j1 8, group 64 and an even number of kv heads) the
- * large tensor is quantized inside the decomposition kernel and never goes through memory.  Cache
+ * large tensor is quantized as it is formed and never goes through memory.  Cache
  * contents and status words are the same bits either way.  The workspace is sized as before; its
  * first 256 bytes must be zero before the first call with this flag (dq_workspace_init on the
  * workspace, or on its first 256 bytes, does that) and are left so: they hold a counter of finished
