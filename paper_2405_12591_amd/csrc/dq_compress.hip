@@ -722,11 +722,12 @@ struct Jacobi16 {
   // left of x.y shrinks by that factor and the next sweep deals with it.  cos gets a Newton step, so that
   // rotations stay orthogonal to 1e-14.  The tiny addend keeps a pair of zero columns (0 / 0) from
   // producing a NaN and is far below any pair that matters.  TEST: report whether the pair was
-  // still apart (the first sweeps do not ask).
-  template <bool TEST>
-  __device__ __forceinline__ void rotate(double floor_ab, bool& unsettled) {
+  // still apart (the first sweeps do not ask).  PAIR: the floor of the columns' own head counts (two
+  // columns of different heads have no row in common: g is zero and nothing is to settle).
+  template <bool TEST, bool PAIR>
+  __device__ __forceinline__ void rotate(double floor_lo, double floor_hi, bool& unsettled) {
     const double g = dot16<ROWS>(x, y);
-    if (TEST) unsettled |= (g * g > kSettled2 * (a * b)) && (fmin(a, b) > floor_ab);
+    if (TEST) unsettled |= (g * g > kSettled2 * (a * b)) && (fmin(a, b) > ((PAIR && ix >= 8) ? floor_hi : floor_lo));
     const double d = b - a, g2 = g + g;
     const double root = __builtin_amdgcn_sqrt(fma(g2, g2, fma(d, d, 1e-240)));
     const double t = g2 * __builtin_amdgcn_rcp(d + copysign(root, d));
@@ -748,52 +749,60 @@ struct Jacobi16 {
   // among themselves, and so on; every exchange is one data-parallel-primitive pattern.  Of the orders
   // that leave the columns where the next sweep can start from them, this one converges soonest (5.9
   // sweeps on the synthetic workloads' blocks; with the first eight rounds the other way round, 6.9).
-  template <bool TEST>
-  __device__ __forceinline__ void sweep(int j, double floor_ab, bool& unsettled) {
-    move<kDppXor7>(); rotate<TEST>(floor_ab, unsettled);
-    move<kDppXor3>(); rotate<TEST>(floor_ab, unsettled);
-    move<kDppXor1>(); rotate<TEST>(floor_ab, unsettled);
-    move<kDppXor3>(); rotate<TEST>(floor_ab, unsettled);
-    move<kDppXor7>(); rotate<TEST>(floor_ab, unsettled);
-    move<kDppXor3>(); rotate<TEST>(floor_ab, unsettled);
-    move<kDppXor1>(); rotate<TEST>(floor_ab, unsettled);
-    move<kDppXor3>(); rotate<TEST>(floor_ab, unsettled);
-    split<kDppXor7>((j & 4) != 0); rotate<TEST>(floor_ab, unsettled);
-    move<kDppXor1>(); rotate<TEST>(floor_ab, unsettled);
-    move<kDppXor2>(); rotate<TEST>(floor_ab, unsettled);
-    move<kDppXor1>(); rotate<TEST>(floor_ab, unsettled);
-    split<kDppXor3>((j & 2) != 0); move<kDppXor1>(); rotate<TEST>(floor_ab, unsettled);
-    move<kDppXor1>(); rotate<TEST>(floor_ab, unsettled);
-    split<kDppXor1>((j & 1) != 0); rotate<TEST>(floor_ab, unsettled);
+  template <bool TEST, bool PAIR>
+  __device__ __forceinline__ void sweep(int j, double floor_lo, double floor_hi, bool& unsettled) {
+    move<kDppXor7>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    move<kDppXor3>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    move<kDppXor1>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    move<kDppXor3>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    move<kDppXor7>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    move<kDppXor3>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    move<kDppXor1>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    move<kDppXor3>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    split<kDppXor7>((j & 4) != 0); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    move<kDppXor1>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    move<kDppXor2>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    move<kDppXor1>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    split<kDppXor3>((j & 2) != 0); move<kDppXor1>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    move<kDppXor1>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    split<kDppXor1>((j & 1) != 0); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
   }
 
   // Called with x = column j, y = column j + 8 of the matrix, j = lane % 8.  Returns the sweeps used.  All
   // eight lanes of a block (and, for ROWS < 16, all its row groups) leave together.
+  template <bool PAIR>
   __device__ __forceinline__ int run() {
     const int lane = threadIdx.x & 63, j = lane & 7;
     ix = j; iy = j + 8;
     a = dot16<ROWS>(x, x);
     b = dot16<ROWS>(y, y);
     // columns of eigenvalues below 1e-14 of the largest are dropped later: whether they have settled
-    // does not matter
-    double tr = a + b;
-    tr += dpp_d<kDppXor1>(tr);
-    tr += dpp_d<kDppXor2>(tr);
-    tr += dpp_d<kDppXor7>(tr);
-    const double floor_ab = tr * 1e-28;
+    // does not matter.  (A pair: of the largest of the same head, as order() drops them.  x are the first
+    // head's columns here, y the second's.  One floor over both left a head a thousand times smaller
+    // than its partner unsettled: up to 88 % of its block lost where its singular values span 1e5.)
+    double tr_lo = PAIR ? a : a + b, tr_hi = b;
+    tr_lo += dpp_d<kDppXor1>(tr_lo);
+    tr_lo += dpp_d<kDppXor2>(tr_lo);
+    tr_lo += dpp_d<kDppXor7>(tr_lo);
+    if (PAIR) {
+      tr_hi += dpp_d<kDppXor1>(tr_hi);
+      tr_hi += dpp_d<kDppXor2>(tr_hi);
+      tr_hi += dpp_d<kDppXor7>(tr_hi);
+    }
+    const double floor_lo = tr_lo * 1e-28, floor_hi = tr_hi * 1e-28;
     bool unsettled = true;
     int sweeps = 0;
     // no block with anything off the diagonal settles in three sweeps: they do not test
     while (sweeps < 3) {
       ++sweeps;
-      sweep<false>(j, floor_ab, unsettled);
+      sweep<false, PAIR>(j, floor_lo, floor_hi, unsettled);
       a = dot16<ROWS>(x, x);
       b = dot16<ROWS>(y, y);
     }
     while (unsettled && sweeps < 16) {
       ++sweeps;
       unsettled = false;
-      sweep<true>(j, floor_ab, unsettled);
+      sweep<true, PAIR>(j, floor_lo, floor_hi, unsettled);
       a = dot16<ROWS>(x, x);
       b = dot16<ROWS>(y, y);
       // every pair of this sweep was within 3e-5 of orthogonal when it was rotated, so the sweep (one
@@ -1451,7 +1460,7 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 5 : PART == 3 ? ((QB == 2 || 
       jac.x[i] = A[(2 * (l >> 3) + i) * ld + (l & 7)];
       jac.y[i] = A[(2 * (l >> 3) + i) * ld + (l & 7) + 8];
     }
-    const int sweeps = jac.run();
+    const int sweeps = jac.template run<PAIR>();
 
     // ---- singular values, ordering, small tensor ----
     store_factors<2, PAIR, ld>(jac, lam, lam2, W);
@@ -1890,7 +1899,7 @@ __global__ __launch_bounds__(64 * kSolveWaves) void solve16_kernel(dq_format fmt
     jac.x[i] = live ? G[j * j1 + row0 + i] : 0.0;
     jac.y[i] = live ? G[(j + 8) * j1 + row0 + i] : 0.0;
   }
-  const int sweeps = jac.run();
+  const int sweeps = jac.template run<PAIR>();
   int px, py;
   double rx, ry, lx, ly;
   jac.template order<PAIR>(s_lam[blk], px, py, rx, ry, lx, ly);

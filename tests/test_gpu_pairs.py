@@ -174,3 +174,57 @@ def test_compress_pairs_heads_of_very_different_size():
         m = O.matricise(k[0, h].astype(np.float64), 1, 8)
         t_s = small[0, h, 0].astype(np.float64).T                                   # keys are stored transposed
         assert np.linalg.norm(t_s @ t_l - m) <= 2e-3 * np.linalg.norm(m), h         # fp16 small tensor, fp32 large
+
+
+@pytest.mark.parametrize("waves", [4, 2, 1])   # (1: the solver in a launch of its own)
+@pytest.mark.parametrize("big,small,decades,big_diagonal", [
+    (1000.0, 0.01, 5.0, False), (1000.0, 0.01, 5.0, True), (3000.0, 1e-4, 0.0, True), (30.0, 0.03, 3.0, False),
+])
+def test_compress_pairs_graded_head_beside_a_larger_one(waves, big, small, decades, big_diagonal):
+    """Every head is decomposed to its own accuracy: one whose singular values span `decades` decades,
+    beside a partner up to 3e7 times larger (whose Gram matrix may be diagonal from the start, so that
+    its share of the iteration ends at once).  Both orders of the two heads, eight draws each."""
+    _say("graded pair: %s" % ((waves, big, small, decades, big_diagonal),))
+    draws, n = 8, 128
+    r = np.random.default_rng(11)
+    x = np.zeros((draws, 2, n, 64), np.float16)
+    for i in range(draws):
+        q, _ = np.linalg.qr(r.standard_normal((8, 8)))
+        spread = 10.0 ** (-decades * np.arange(8) / 7)
+        graded = np.einsum("br,r,trc->tbc", q, spread, r.standard_normal((n, 8, 8))).reshape(n, 64) * small
+        if big_diagonal:   # every column of the regrouped matrix (a token and a b2) lies in one row b1 only
+            large = np.zeros((n, 8, 8))
+            for b2 in range(8):
+                large[np.arange(n), (np.arange(n) + b2) % 8, b2] = 0.5 * (1 + (np.arange(n) + b2) % 8)
+            large = large.reshape(n, 64) * big / 4
+        else:
+            large = r.standard_normal((n, 64)) * big
+        x[i, i & 1], x[i, 1 - (i & 1)] = large, graded
+    fmt = dq.Format(4, 64, 64, 8, 8, n)
+    cache = dq.alloc_cache(fmt, draws, 2, 1, DEV)
+    ws = dq.compress_workspace(fmt, draws, 2, DEV)
+    xd = torch.from_numpy(x).to(DEV)
+    dq.compress_kv(cache, xd, xd, torch.zeros(draws, dtype=torch.int32, device=DEV), None, ws, waves=waves)
+    torch.cuda.synchronize()
+    large = ws[256:256 + draws * 4 * 4 * n * 64].view(torch.float32).cpu().numpy().reshape(draws, 2, 2, n, 64)
+    small_t = {"k": cache.t["k_small"].cpu().numpy()[:, :, 0], "v": cache.t["v_small"].cpu().numpy()[:, :, 0]}
+    worst_gram = worst_product = 0.0
+    for i in range(draws):
+        for h in range(2):
+            m = O.matricise(x[i, h].astype(np.float64), 1, 8)
+            _, sigma, _ = np.linalg.svd(m, full_matrices=False)
+            for which, side in enumerate("kv"):
+                t_l = O.token_major_to_large(large[i, h, which].astype(np.float64), 8, 8)
+                kept = int((sigma > 1.5e-6 * sigma[0]).sum())        # (what the cut-off at 1e-6 keeps for certain)
+                gram = (t_l @ t_l.T)[:kept, :kept]
+                worst_gram = max(worst_gram, np.abs(gram - np.eye(kept)).max())
+                # T_L's rows are an orthonormal basis of M's row space: projecting onto it gives M back, to
+                # the fp32 rounding of the rows (2^-24 each) and the directions under the cut-off
+                worst_product = max(worst_product, np.linalg.norm(m @ t_l.T @ t_l - m) / np.linalg.norm(m))
+                t_s = small_t[side][i, h].astype(np.float64)
+                t_s = t_s.T if side == "k" else t_s                  # keys are stored transposed
+                # (an fp16 small tensor: half an ulp, 2^-11, of every entry, and 2^-25 under the subnormals)
+                err = np.linalg.norm(t_s @ t_l - m)
+                assert err <= 2.0 ** -11 * np.linalg.norm(m) + 8 * 2.0 ** -25 + 1e-6 * np.linalg.norm(m), (i, h, side)
+    _say("  worst |T_L T_L^T - I| %.2e, projection error %.2e" % (worst_gram, worst_product))
+    assert worst_gram <= 1e-5 and worst_product <= 1e-5
