@@ -225,7 +225,7 @@ struct TailBlock {
 //             read the last row instead: no branches, the caller may have other loads in flight whose
 //             count the compiler has to keep);
 //   finish()  leaves out[head][0..128) (unnormalised), out[head][128] = largest score in log2 units (-inf:
-//             no row) and out[head][129] = sum of weights in the wave's `result`.
+//             no row, or none that weighs anything) and out[head][129] = sum of weights in the wave's `result`.
 // HEADS query heads share every row.  PAIR: the 128 channels are two neighbouring kv heads of 64, each
 // with HEADS / 2 query heads: the lanes of each half read their own head's arrays, query head hd is zero
 // outside the half p = hd / (HEADS / 2), and its partial is channels [64 p, 64 p + 64) of result[hd].
@@ -296,7 +296,7 @@ struct TailWave {
 #pragma unroll
         for (int it = 0; it < BATCH; ++it) vreg[it] = *reinterpret_cast<const tail_u4*>(vt + (long)min(row_of(it0 + it), cap - 1) * RD);
       }
-      float sc[BATCH][HEADS];
+      float sc[BATCH][HEADS], m_ref[HEADS];
 #pragma unroll
       for (int it = 0; it < BATCH; ++it) {
         const tail_h8 kv = __builtin_bit_cast(tail_h8, kreg[it]);
@@ -321,8 +321,11 @@ struct TailWave {
         float m = sc[0][hd];
 #pragma unroll
         for (int it = 1; it < BATCH; ++it) m = fmaxf(m, sc[it][hd]);
-        m = fmaxf(over_rows_max(m), m_run[hd]);   // finite: the first row of the first load is valid
-        const float alpha = __builtin_amdgcn_exp2f(m_run[hd] - m);
+        m = fmaxf(over_rows_max(m), m_run[hd]);
+        // (-inf where every row so far scored that, as an infinite key makes it: such rows weigh nothing,
+        // whatever the other waves' rows do.  The weights are then taken against zero: exp2(-inf) = 0)
+        m_ref[hd] = m == -INFINITY ? 0.f : m;
+        const float alpha = __builtin_amdgcn_exp2f(m_run[hd] - m_ref[hd]);
         m_run[hd] = m;
         l_run[hd] *= alpha;
 #pragma unroll
@@ -335,7 +338,7 @@ struct TailWave {
         const tail_h8 vv = __builtin_bit_cast(tail_h8, live ? vreg[it] : tail_u4{0u, 0u, 0u, 0u});
 #pragma unroll
         for (int hd = 0; hd < HEADS; ++hd) {
-          const float p = __builtin_amdgcn_exp2f(sc[it][hd] - m_run[hd]);
+          const float p = __builtin_amdgcn_exp2f(sc[it][hd] - m_ref[hd]);
           l_run[hd] += p;
 #pragma unroll
           for (int i = 0; i < 8; ++i) acc[hd][i] = fmaf(p, (float)vv[i], acc[hd][i]);
