@@ -83,23 +83,24 @@ __host__ __device__ inline Geometry make_geometry(const dq_format& f, int kv_hea
   return g;
 }
 
-// ---- fp16 bit helpers (device) ----
+// ---- fp16 bit helpers ----
 __device__ inline float h2f(uint16_t h) {
   return (float)__builtin_bit_cast(_Float16, h);
 }
-__device__ inline uint16_t f2h_rne(float x) {
+__host__ __device__ inline uint16_t f2h_rne(float x) {
   return __builtin_bit_cast(uint16_t, (_Float16)x);
 }
 
 // fp64 -> fp16 bits with a single round-to-nearest-even; saturating variant clamps to +-65504.  The value
 // is first rounded to odd in fp32 (13 more bits than fp16), which makes the second rounding land
 // where a single one would.
-__device__ inline uint16_t f64_to_f16_rne(double x, bool saturate, bool* saturated) {
+__host__ __device__ inline uint16_t f64_to_f16_rne(double x, bool saturate, bool* saturated) {
   const float f = (float)x;
   const double e = x - (double)f;                       // what the first rounding dropped
   uint32_t bits = __builtin_bit_cast(uint32_t, f);
   const bool away = (e > 0.0) == (f > 0.f);             // x lies further from zero than f
-  if (e != 0.0 && f != 0.f && !(bits & 1u)) bits += away ? 1u : 0xFFFFFFFFu;
+  const bool inexact = e > 0.0 || e < 0.0;              // (false for infinities, whose e is a NaN)
+  if (inexact && f != 0.f && !(bits & 1u)) bits += away ? 1u : 0xFFFFFFFFu;
   const float odd = __builtin_bit_cast(float, bits);
   if (saturate && __builtin_fabsf(odd) >= 65520.f) {    // rounds to infinity
     if (saturated) *saturated = true;
