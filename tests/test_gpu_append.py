@@ -222,3 +222,41 @@ def test_13b_configuration_flow_at_full_size():
         nt = int(lens[b] % tb)
         assert np.array_equal(layer.k_tail[b, h, :nt].cpu().numpy(), kk[(nb + 1) * tb:(nb + 1) * tb + nt])
     _say("  worst fp16 abs err on %d pairs %.3g" % (len(pairs), worst))
+
+
+@pytest.mark.parametrize("bits,group,d,i3,batch,kvh", [
+    (4, 128, 128, 1, 9, 64),     # 1152 blocks: the launches of a prompt
+    (4, 64, 64, 1, 18, 64),      # 1152 pairs of 64-channel heads
+    (4, 128, 128, 8, 9, 32),     # 576 blocks of three local tensors
+    (4, 32, 128, 1, 9, 64),      # the quantizer in a launch of its own
+    (4, 128, 128, 1, 3, 4),      # a small call
+])
+def test_idle_and_filling_steps_of_any_size(bits, group, d, i3, batch, kvh):
+    """A step that fills no tail leaves the cache alone and zero in the status words; one that fills some
+    compresses exactly those, to the bits a compression call writes, and reports its sweeps."""
+    _say("idle and filling steps: %s" % ((bits, group, d, i3, batch, kvh),))
+    fmt = dq.Format(bits, group, d, d // 8, 8, 128, i3)
+    gen = torch.Generator(device=DEV).manual_seed(4)
+    cache, want = (dq.alloc_cache(fmt, batch, kvh, 2, DEV, fill=0xA5) for _ in range(2))
+    kt, vt = (torch.randn(batch, kvh, 128, d, device=DEV, generator=gen).half() for _ in "kv")
+    kr, vr = (torch.randn(batch, kvh, 1, d, device=DEV, generator=gen).half() for _ in "kv")
+    full = [b for b in range(batch) if b % 4 == 2]
+    tl = torch.tensor([126 if b in full else 7 * b % 100 for b in range(batch)], dtype=torch.int32, device=DEV)
+    sl = torch.zeros(batch, dtype=torch.int32, device=DEV)
+    ws = dq.cache_append_workspace(fmt, batch, kvh, DEV)
+    poisoned = cache.clone()
+    for step in range(2):
+        ws[:8] = 0x77                                    # what an earlier call may have left
+        dq.cache_append(cache, kt, vt, tl, sl, kr, vr, None, ws)
+        torch.cuda.synchronize()
+        status = ws[:8].view(torch.int32).tolist()
+        if step == 0:
+            assert status == [0, 0]
+            for name in cache.t:
+                assert torch.equal(cache.t[name].view(torch.uint8), poisoned.t[name].view(torch.uint8)), name
+    assert status[0] == 0 and 0 < status[1] <= 16
+    assert sl.tolist() == [128 if b in full else 0 for b in range(batch)]
+    slot = torch.tensor([0 if b in full else -1 for b in range(batch)], dtype=torch.int32, device=DEV)
+    dq.compress_kv(want, kt, vt, slot, None, dq.compress_workspace(fmt, batch, kvh, DEV), keep_large=False)
+    for name in cache.t:
+        assert torch.equal(cache.t[name].view(torch.uint8), want.t[name].view(torch.uint8)), name
