@@ -906,14 +906,16 @@ __device__ __forceinline__ void store_factors(Jacobi16<ROWS>& jac, double* lam, 
 // ------------------------------------------------------------------------------------------
 // Projection and quantizer on the fp16 matrix cores, for 2- and 4-bit codes of two local tensors.
 //
-// The codes and steps are those of the fp64 projection, bit for bit, but few elements need it: the
-// projection runs on fp16 matrix instructions (the rows are fp16 as they are, W is cut into three fp16
-// pieces, 33 bits; fp32 accumulation) with a known error bound, and only what lies within that bound
-// of a decision (a code's rounding boundary, a step's rounding boundary) is formed again in fp64.
+// The codes and steps are those of the fp64 projection, bit for bit, but few tokens need it: a first pass
+// projects on fp16 matrix instructions (the rows are fp16 as they are, W is cut into three fp16 pieces, 33
+// bits; fp32 accumulation) with a proven error bound, and a token with a step or a code within that bound
+// of a rounding boundary is put on a list.  The listed tokens of a tile, sixteen at a time, then go through
+// the fp64 projection itself (second pass; a block whose bound is wide goes there as a whole).
 // A 16 x 16 x 16 product takes three matrix instructions instead of four fp64 ones of 64 cycles each, and no
 // fp16 value is widened: on this chip matrix and vector instructions of a SIMD do not overlap, so both
-// count.  14720 blocks (4-bit, d = 128): 280 -> 205 us, at two waves per SIMD (199 registers, most of them
-// for the paths that settle what is in doubt; held to 168 or 128 they spill: 212 and 287 us).
+// count.  14720 blocks (4-bit, d = 128): 280 us all in fp64, 181 so, at three waves per SIMD (settling single
+// elements where they arise, under a narrower bound that was not proven, took 201: 199 registers, two waves.
+// Held to four waves the second pass spills: 205).
 //
 // Keys (W as the left operand): lane (token n = l % 16, g = l / 16) gets rows r = 4 g + i of its token, eight
 // b2 each, i.e. whole words of the key layout, which it stores as they are.  Values (operands
@@ -921,14 +923,26 @@ __device__ __forceinline__ void store_factors(Jacobi16<ROWS>& jac, double* lam, 
 // neighbours in the value layout and go through LDS once, 8 or 16 bits at a time, to be stored in rows.
 // In both a lane's elements belong to one step group per token (rows r < 8, r >= 8).
 //
-// Error bound.  T = sum W X of row r and token t, with |X_b1| <= sum_r' |T_S[b1, r']| max_r'' |T[r'']|:
-// sum |W X| <= C amax_t for the block's constant C = max_r sum_b1 |W[r, b1]| sum_r' |T_S[b1, r']|.  The
-// accumulation rounds to 2^-24 of the partial sums.  kSlack C is 2^-24 times 12 to 40 on the synthetic
-// workloads' blocks; the largest error seen there is 2^-24 times 3.7 of amax_t.
+// Error bound.  T[r] = sum_b1 W[r, b1] X[b1] of a token and a b2, S = sum |W X|, amax = the token's largest |T|.
+//  - A 16x16x16 fp16 matrix instruction adds its products in two groups of eight: each product is cut to 24
+//    bits below the group's largest exponent (an fp16 subnormal counts with exponent -14), the sum added to
+//    the accumulator, cut likewise, and rounded to fp32 (found by comparing with that model over random and
+//    adversarial operands).  A group is so within 8 * 2^-24 of its largest product plus 2^-24 of its result, and the
+//    chain of three instructions, the last of which carries all but 2^-10 of the sum, within
+//    10.1 * 2^-24 S: kRoundings = 12.  A subnormal X adds at most 16 * 2^-24 * 2^-14 max |W[r]|.
+//  - The pieces leave out what is known exactly when they are cut (`left`).
+//  - S <= C amax + sum |W[r]| d.  X = T_S T + what directions that were dropped carry, so |X[b1]| <= s[b1] amax + d,
+//    s[b1] = sum_r |T_S[b1, r]|, d <= sqrt(15e-12 lambda_max) (0 if none was dropped): C = sum |W[r, b1]| s[b1];
+//    and by Cauchy and Schwarz C = |W[r]| sqrt(sum lambda) as well.
+//  - The value that is quantized is the fp64 sum rounded to fp32, and the comparisons round, too: 4 * 2^-24 amax.
+// So |error| <= eps amax + eps_abs with the block's constants eps, eps_abs.  On the blocks of a synthetic prompt 3 to
+// 5 of a tile's 128 tokens are listed with one step per token, 8 to 10 with two.
 // ------------------------------------------------------------------------------------------
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-constexpr float kSlack = 2.f * 0x1p-24f;
+constexpr float kRoundings = 12.f;
+// eps beyond which a block skips the first pass: about half of its tokens would be listed
+constexpr float kHardEps = 0x1p-13f;
 
 __device__ __forceinline__ float max_xor16(float v) {
   const uint32_t w = __builtin_bit_cast(uint32_t, v);
@@ -952,18 +966,19 @@ struct FastProject {
   f16x4 w0, w1, w2;  // row r = l % 16 of W, columns b1 = 4 (l / 16) + j, scaled by 2^(15 - e): three pieces
   float sc;          // 2^(e - 15) of row l % 16
   float sck[4];      // ... of rows 4 (l / 16) + i
-  float eps;         // error bound relative to the token's largest |T|
-  const double* W;   // [16][ldw], in the workspace
+  float eps, eps_abs;   // the error bound (see above)
+  const double* W;   // [16][16], in the workspace
   const uint16_t* X; // the block's rows
-  int ldw, nv;
+  int nv;
   long head_gap;
   bool one_group;
+  bool hard;         // the first pass is not worth its while
 
-  // X[t][b1 * 8 + b2], the row's 16-byte pieces of b1 = 4 (l / 16) + j
+  // X[t][b1 * 8 + b2], the 16-byte piece of one b1
   __device__ __forceinline__ const uint16_t* piece(int t, int b1) const {
     return PAIR ? X + (b1 >> 3) * head_gap + (long)t * 64 + (b1 & 7) * 8 : X + (long)t * 128 + b1 * 8;
   }
-  __device__ __forceinline__ void load(u32x4 (&x)[4], int t) const {
+  __device__ __forceinline__ void load(u32x4 (&x)[4], int t) const {   // b1 = 4 (l / 16) + j
     const int g = (threadIdx.x & 63) >> 4;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -972,16 +987,30 @@ struct FastProject {
     }
   }
 
-  // lam2: the eigenvalues in the order of W's rows
-  __device__ __forceinline__ void setup(const double* W_, int ldw_, const double* lam2) {
-    W = W_; ldw = ldw_;
+  static __device__ __forceinline__ float sum16(float v) {   // over the sixteen lanes of a row (a pair: its half)
+    v += lane_exchange<0xB1>(v);
+    v += lane_exchange<0x4E>(v);
+    v += lane_exchange<0x141>(v);
+    if (!PAIR) v += lane_exchange<0x140>(v);
+    return v;
+  }
+  static __device__ __forceinline__ float max16(float v) {
+    v = fmaxf(v, lane_exchange<0xB1>(v));
+    v = fmaxf(v, lane_exchange<0x4E>(v));
+    v = fmaxf(v, lane_exchange<0x141>(v));
+    return v;
+  }
+
+  // lam2: the eigenvalues in the order of W's rows (0: dropped)
+  __device__ __forceinline__ void setup(const double* W_, const double* lam2) {
+    W = W_;
     const int l = threadIdx.x & 63, r = l & 15, g = l >> 4;
     double w[4], wm = 0.0;
-    float ab[4], s[4];
+    float ab[4], left[4], s[4];
     const float lam = (float)lam2[r];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      w[j] = W[r * ldw + 4 * g + j];
+      w[j] = W[r * 16 + 4 * g + j];
       wm = fmax(wm, fabs(w[j]));
       ab[j] = fabsf((float)w[j]);
       s[j] = ab[j] * lam;                       // |T_S[b1][r]|
@@ -996,39 +1025,51 @@ struct FastProject {
       const _Float16 h0 = (_Float16)(float)ws;
       const double r1 = ws - (double)(float)h0;
       const _Float16 h1 = (_Float16)(float)r1;
+      const double r2 = r1 - (double)(float)h1;
+      const _Float16 h2 = (_Float16)(float)r2;
       w0[j] = h0;
       w1[j] = h1;
-      w2[j] = (_Float16)(float)(r1 - (double)(float)h1);
+      w2[j] = h2;
+      // (a subnormal piece counts with exponent -14 as well: the addend)
+      left[j] = (fabsf((float)(r2 - (double)(float)h2)) + 0x1p-35f) * sc;
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) sck[i] = __shfl(sc, 4 * g + i);
-    float c = 0.f;
+    float c = 0.f, rest = 0.f, one = 0.f, two = 0.f;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {               // sums over the rows r, then over b1, then the largest row
-      float v = s[j];
-      v += lane_exchange<0xB1>(v);
-      v += lane_exchange<0x4E>(v);
-      v += lane_exchange<0x141>(v);
-      v += lane_exchange<0x140>(v);
+    for (int j = 0; j < 4; ++j) {
+      // (a pair: W is block-diagonal, so the rows of the b1's own head, which the half may not be, hold it all)
+      float v = sum16(s[j]);
+      if (PAIR) v = fmaxf(v, lane_exchange<0x140>(v));
       c = fmaf(ab[j], v, c);
+      rest = fmaf(left[j], v, rest);
+      one += ab[j];
+      two = fmaf(ab[j], ab[j], two);
     }
-    c += __shfl_xor(c, 16);
-    c += __shfl_xor(c, 32);
-    c = fmaxf(c, lane_exchange<0xB1>(c));
-    c = fmaxf(c, lane_exchange<0x4E>(c));
-    c = fmaxf(c, lane_exchange<0x141>(c));
-    c = fmaxf(c, lane_exchange<0x140>(c));
-    eps = kSlack * c;
-  }
-
-  // T[r][t][b2] in fp64, rounded to fp32 as the fp64 projection hands it to the quantizer
-  __device__ __forceinline__ float exact(int r, int t, int b2) const {
-    double a = 0.0;
-    if (t < nv) {
-#pragma unroll 2   // (rare; unrolled it would cost the registers of the common path)
-      for (int b1 = 0; b1 < 16; ++b1) a = fma(W[r * ldw + b1], (double)h2f(piece(t, b1)[b2]), a);
+#pragma unroll
+    for (int o = 16; o <= 32; o <<= 1) {
+      c += __shfl_xor(c, o);
+      rest += __shfl_xor(rest, o);
+      one += __shfl_xor(one, o);
+      two += __shfl_xor(two, o);
     }
-    return (float)a;
+    const float total = sum16(lam);
+    float most = max16(lam);
+    float least = -max16(-lam);
+    if (!PAIR) {
+      most = fmaxf(most, lane_exchange<0x140>(most));
+      least = fminf(least, lane_exchange<0x140>(least));
+    }
+    c = fminf(c, __builtin_sqrtf(two) * __builtin_sqrtf(total));
+    const float d = least > 0.f ? 0.f : 4.1e-6f * __builtin_sqrtf(most);
+    // (2 % for the rounding of these sums themselves)
+    float rel = 1.02f * (0x1p-24f * (kRoundings * c + 4.f) + rest), abs = 1.02f * (0x1p-24f * kRoundings * one * d + sc * 0x1p-19f);
+    // all of the block's rows; NaN (a block that holds one) must not get lost
+    hard = __any(!(rel + 32.f * abs <= kHardEps));
+    rel = max16(rel);
+    abs = max16(abs);
+    eps = fmaxf(rel, lane_exchange<0x140>(rel));
+    eps_abs = fmaxf(abs, lane_exchange<0x140>(abs));
   }
 
   __device__ __forceinline__ static uint16_t step_bits(float up, float dn) {
@@ -1067,9 +1108,7 @@ struct FastProject {
   template <bool VALUES>
   __device__ __forceinline__ float group_max(float v, bool both) const {
     if (VALUES) {
-      v = fmaxf(v, lane_exchange<0xB1>(v));
-      v = fmaxf(v, lane_exchange<0x4E>(v));
-      v = fmaxf(v, lane_exchange<0x141>(v));
+      v = max16(v);
       if (both) v = fmaxf(v, lane_exchange<0x140>(v));
     } else {
       v = max_xor16(v);
@@ -1079,16 +1118,14 @@ struct FastProject {
   }
 
   // Fields of NT = 1 (keys) or 4 (values) tokens of the lane: element (i, b2) belongs to row 4 g + i of token
-  // t0 + n, or to row n of token t0 + 4 g + i.  Steps come back in `sbits` (values: of token
-  // t0 + 4 g + n % 4), the fields, QB bits each, in `part`: keys: element 8 i + b2 in index order (part[i]:
-  // eight of them); values: part[b2]: the four tokens.
+  // n of the sixteen, or to row n of token 4 g + i.  Steps come back in `sbits` (values: of token 4 g + n % 4), the
+  // fields, QB bits each, in `part`: keys: element 8 i + b2 in index order (part[i]: eight of them);
+  // values: part[b2]: the four tokens.  Returns the tokens that are in doubt, one bit each, the same in all lanes.
   template <bool VALUES>
-  __device__ __forceinline__ void quantize(const f32x4 (&acc)[8], int t0, uint16_t& sbits, uint32_t (&part)[VALUES ? 8 : 4]) const {
-    const int l = threadIdx.x & 63, n = l & 15, g = l >> 4;
+  __device__ __forceinline__ uint32_t quantize(const f32x4 (&acc)[8], uint16_t& sbits, uint32_t (&part)[VALUES ? 8 : 4]) const {
+    const int l = threadIdx.x & 63, n = l & 15;
     constexpr int NT = VALUES ? 4 : 1;
     auto scale = [&](int i) -> float { return VALUES ? sc : sck[i]; };
-    auto row = [&](int i) -> int { return VALUES ? n : 4 * g + i; };
-    auto token = [&](int i) -> int { return VALUES ? t0 + 4 * g + i : t0 + n; };
     // ---- largest values per token and group, and the step ----
     float up[NT], dn[NT];
 #pragma unroll
@@ -1122,64 +1159,16 @@ struct FastProject {
         my_all = (n & 3) == k ? all[k] : my_all;
       }
     }
-    const float err = eps * my_all;
+    const float err = fmaf(eps, my_all, eps_abs);
     sbits = step_bits(my_up + err, my_dn + err);
-    const bool unsure = sbits != step_bits(fmaxf(my_up - err, 0.f), fmaxf(my_dn - err, 0.f));
-    if (__any(unsure)) {   // some step lies within the bound of a rounding boundary
-      // every element that may be the largest of its group is formed in fp64; the largest of them decides
-      uint32_t todo = 0;
-      float up_e[NT], dn_e[NT];
-#pragma unroll
-      for (int k = 0; k < NT; ++k) { up_e[k] = 0.f; dn_e[k] = 0.f; }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int k = VALUES ? i : 0;
-        float e2 = 2.f * eps * all[k], sci = scale(i);
-        asm volatile("" : "+v"(sci));
-#pragma unroll
-        for (int b2 = 0; b2 < 8; ++b2) {
-          const float v = acc[b2][i] * sci;
-          const bool may = FULL ? (v >= up[k] - e2 || -v >= dn[k] - e2) : (fabsf(v) >= up[k] - e2);
-          todo |= may ? 1u << (8 * i + b2) : 0u;
-        }
-      }
-      while (__any(todo != 0)) {
-        if (todo) {
-          const int k = __builtin_ctz(todo), i = k >> 3;
-          todo &= todo - 1;
-          const float x = exact(row(i), token(i), k & 7);
-#pragma unroll
-          for (int q = 0; q < NT; ++q) {
-            const bool mine = !VALUES || i == q;
-            up_e[q] = mine ? fmaxf(up_e[q], FULL ? x : fabsf(x)) : up_e[q];
-            if (FULL) dn_e[q] = mine ? fmaxf(dn_e[q], -x) : dn_e[q];
-          }
-        }
-      }
-#pragma unroll
-      for (int k = 0; k < NT; ++k) {
-        up_e[k] = group_max<VALUES>(up_e[k], one_group);
-        if (FULL) dn_e[k] = group_max<VALUES>(dn_e[k], one_group);
-      }
-      float u = up_e[0], m = dn_e[0];
-      if (VALUES) {
-#pragma unroll
-        for (int k = 1; k < NT; ++k) {
-          u = (n & 3) == k ? up_e[k] : u;
-          m = (n & 3) == k ? dn_e[k] : m;
-        }
-      }
-      sbits = step_bits(u, m);
-    }
+    const bool doubt = sbits != step_bits(fmaxf(my_up - err, 0.f), fmaxf(my_dn - err, 0.f));
     const float my_step = h2f(sbits);
     const float my_inv = my_step > 0.f ? __builtin_amdgcn_rcpf(my_step) : 0.f;
     // a quotient this far from a half-integer is on the right side of it: the bound above, the
     // reciprocal's error and the rounding of the product
     const float my_thr = 0.5f - (err * my_inv + (float)(QMAX + 1) * 0x1p-21f);
-    // the step of a group of subnormal size may be rounded so far down that a quotient leaves the range.
-    // (FULL: the negative end has one more code.  Held against half a code more only, every group whose
-    // step its negative end decides counted, about half of all, and the settling below ran for almost
-    // every sixteen tokens: 16384 blocks, 4-bit, all codes 565 us, 524 now.)
+    // the step of a group of subnormal size may be rounded so far down that a quotient leaves the range
+    // (FULL: whose negative end has one more code)
     const bool wide = (FULL ? fmaxf(my_up, my_dn - my_step) : my_up) * my_inv > (float)QMAX + 0.25f;
     float inv[NT], thr[NT];
 #pragma unroll
@@ -1201,14 +1190,15 @@ struct FastProject {
         thr[k] = lane_exchange<0xFF>(my_thr);
       }
     }
-    const bool clamp = __any(wide);
     // ---- fields: the integer nearest to the quotient appears in the low bits of quotient + kMagic ----
     uint32_t bias = 0;
 #pragma unroll
     for (int k = 0; k < (VALUES ? 4 : 8); ++k) bias += kMagicBits << (QB * k);
 #pragma unroll
     for (int k = 0; k < (VALUES ? 8 : 4); ++k) part[k] = 0u - bias;
-    bool near = false;
+    // bit i: token 4 g + i is in doubt (keys: bit 0).  (A field out of its range carries into those of the other
+    // tokens of its word.)
+    uint32_t near = wide ? (VALUES ? 15u : 1u) : doubt ? (VALUES ? 1u << (n & 3) : 1u) : 0u;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float f = inv[VALUES ? i : 0] * scale(i);
@@ -1222,58 +1212,95 @@ struct FastProject {
         if (VALUES) part[b2] += bits << (QB * i);
         else part[i] += bits << (QB * b2);
       }
-      near |= far > thr[VALUES ? i : 0];
+      near |= far > thr[VALUES ? i : 0] ? 1u << (VALUES ? i : 0) : 0u;
     }
-    if (clamp || __any(near)) {   // rare: settle what is in doubt in fp64
-      uint32_t todo = 0;
+    const unsigned long long any = __ballot(near != 0);
+    if (any == 0) return 0;
+    if (!VALUES) return (uint32_t)(any | (any >> 16) | (any >> 32) | (any >> 48)) & 0xFFFFu;
+    near |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)near, 0xB1, 0xF, 0xF, true);
+    near |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)near, 0x4E, 0xF, 0xF, true);
+    near |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)near, 0x141, 0xF, 0xF, true);
+    near |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)near, 0x140, 0xF, 0xF, true);
+    return (uint32_t)__builtin_amdgcn_readlane((int)near, 0) | (uint32_t)__builtin_amdgcn_readlane((int)near, 16) << 4 |
+           (uint32_t)__builtin_amdgcn_readlane((int)near, 32) << 8 | (uint32_t)__builtin_amdgcn_readlane((int)near, 48) << 12;
+  }
+
+  // ---- second pass: sixteen tokens through the fp64 projection.  The operands, their order and so every
+  // bit are those of the build that keeps the fp32 rows.  `mine`: the token of slot n = l % 16, counted from
+  // `first` (-1: none).  The lane's element (i, b2) belongs to row 4 g + i of slot n (keys: the rows of W are dealt
+  // so), or to row n of slot g + 4 i (values).  Steps: of the group that holds the lane's rows, per token; fields: a
+  // byte each, element (i, b2) in byte b2 % 4 of fields[i][b2 / 4].
+  template <bool VALUES>
+  __device__ __forceinline__ void settle(int first, int mine, uint16_t (&sbits)[VALUES ? 4 : 1], uint32_t (&fields)[4][2]) const {
+    const int l = threadIdx.x & 63, n = l & 15, g = l >> 4;
+    constexpr int NT = VALUES ? 4 : 1;
+    const int row = VALUES ? n : 4 * (n & 3) + (n >> 2);
+    double w[4];
+    u32x4 x[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float f = inv[VALUES ? i : 0] * scale(i);
-        asm volatile("" : "+v"(f));   // (the quotients are formed again: kept, they would cost 64 registers)
+    for (int s = 0; s < 4; ++s) {
+      w[s] = W[row * 16 + 4 * s + g];
+      x[s] = u32x4{0u, 0u, 0u, 0u};
+      if (mine >= 0 && first + mine < nv) x[s] = *reinterpret_cast<const u32x4*>(piece(first + mine, 4 * s + g));
+    }
+    float f[4][8];
 #pragma unroll
-        for (int b2 = 0; b2 < 8; ++b2) {
-          const float q = fmaf(acc[b2][i], f, kMagic);
-          const float e = fmaf(acc[b2][i], f, kMagic - q);
-          const float c = q - kMagic;
-          const bool doubt = fabsf(e) > thr[VALUES ? i : 0] || c > (float)QMAX || c < (float)QMIN;
-          todo |= doubt ? 1u << (8 * i + b2) : 0u;
+    for (int half = 0; half < 8; half += 4) {   // (four b2 at a time: 32 registers of sums instead of 64)
+      f64x4 acc[4];
+#pragma unroll
+      for (int b2 = 0; b2 < 4; ++b2) acc[b2] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const f16x8 h = __builtin_bit_cast(f16x8, x[s]);
+#pragma unroll
+        for (int b2 = 0; b2 < 4; ++b2) {
+          const double v = (double)(float)h[half + b2];
+          acc[b2] = VALUES ? __builtin_amdgcn_mfma_f64_16x16x4f64(v, w[s], acc[b2], 0, 0, 0)
+                           : __builtin_amdgcn_mfma_f64_16x16x4f64(w[s], v, acc[b2], 0, 0, 0);
         }
       }
-      float steps[NT];   // (values: from the lanes of the quad that settled them, while all lanes are here)
-      steps[0] = VALUES ? lane_exchange<0x00>(my_step) : my_step;
-      if (VALUES) {
-        steps[NT > 1 ? 1 : 0] = lane_exchange<0x55>(my_step);
-        steps[NT > 1 ? 2 : 0] = lane_exchange<0xAA>(my_step);
-        steps[NT > 1 ? 3 : 0] = lane_exchange<0xFF>(my_step);
-      }
-      while (__any(todo != 0)) {
-        if (todo) {
-          const int k = __builtin_ctz(todo), i = k >> 3, b2 = k & 7;
-          todo &= todo - 1;
-          // what the loop above added for this element: formed again from the same numbers
-          float v = 0.f, f = 0.f;
 #pragma unroll
-          for (int qi = 0; qi < 4; ++qi) {
-            f = i == qi ? inv[VALUES ? qi : 0] * scale(qi) : f;
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int qb = 0; qb < 8; ++qb) v = k == 8 * qi + qb ? acc[qb][qi] : v;
-          }
-          const uint32_t had = __builtin_bit_cast(uint32_t, fmaf(v, f, kMagic)) - kMagicBits;
-          const float x = exact(row(i), token(i), b2);
-          float inv_i = inv[0];
-#pragma unroll
-          for (int qi = 1; qi < NT; ++qi) inv_i = i == qi ? inv[qi] : inv_i;
-          float step = steps[0];
-#pragma unroll
-          for (int qi = 1; qi < NT; ++qi) step = i == qi ? steps[qi] : step;
-          const int c = settle_code(x, __builtin_rintf(x * inv_i), step, 0.5 * (double)step);
-          const uint32_t now = (uint32_t)(min(max(c, QMIN), QMAX) + BIAS);
-          const uint32_t delta = (now - had) << (QB * (VALUES ? i : b2));
-#pragma unroll
-          for (int q = 0; q < (VALUES ? 8 : 4); ++q) part[q] += (q == (VALUES ? b2 : i)) ? delta : 0u;
-        }
-      }
+        for (int b2 = 0; b2 < 4; ++b2) f[i][half + b2] = (float)acc[b2][i];
+      __builtin_amdgcn_sched_barrier(0);
     }
+    float up[NT], dn[NT];
+#pragma unroll
+    for (int k = 0; k < NT; ++k) { up[k] = 0.f; dn[k] = 0.f; }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int b2 = 0; b2 < 8; ++b2) {
+        up[VALUES ? i : 0] = fmaxf(up[VALUES ? i : 0], FULL ? f[i][b2] : fabsf(f[i][b2]));
+        if (FULL) dn[VALUES ? i : 0] = fmaxf(dn[VALUES ? i : 0], -f[i][b2]);
+      }
+    float step[NT], inv[NT];
+#pragma unroll
+    for (int k = 0; k < NT; ++k) {
+      up[k] = group_max<VALUES>(up[k], one_group);
+      if (FULL) dn[k] = group_max<VALUES>(dn[k], one_group);
+      sbits[k] = step_bits(up[k], dn[k]);
+      step[k] = h2f(sbits[k]);
+      inv[k] = step[k] > 0.f ? __builtin_amdgcn_rcpf(step[k]) : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int k = VALUES ? i : 0;
+      fields[i][0] = fields_of_four<QB, FULL>(f[i][0], f[i][1], f[i][2], f[i][3], step[k], inv[k]);
+      fields[i][1] = fields_of_four<QB, FULL>(f[i][4], f[i][5], f[i][6], f[i][7], step[k], inv[k]);
+    }
+  }
+  // eight fields of a byte each -> QB bits each
+  static __device__ __forceinline__ uint32_t squeeze(uint32_t lo, uint32_t hi) {
+    if (QB == 4) {
+      lo |= lo >> 4;
+      hi |= hi >> 4;
+      return (lo & 0xFFu) | ((lo >> 8) & 0xFF00u) | ((hi & 0xFFu) << 16) | ((hi & 0xFF0000u) << 8);
+    }
+    lo |= lo >> 6;
+    hi |= hi >> 6;
+    return (lo & 0xFu) | ((lo >> 12) & 0xF0u) | ((hi & 0xFu) << 8) | ((hi >> 4) & 0xF000u);
   }
 };
 
@@ -1311,7 +1338,7 @@ struct FastProject {
 // (T_2 = A V' diag(1/sigma')), and hands the rows of T_2 to the quantizer in the registers it
 // expects them in.  job.keep_large: the fp32 rows of T_2 also go to the workspace.
 template <int NWV, bool PAIR, int QB = 0, bool FULL = false, int PART = 0, bool N3 = false>
-__global__ __launch_bounds__(64 * NWV, PART == 1 ? 5 : PART == 3 ? ((QB == 2 || QB == 4) && !N3 ? 2 : (PAIR || N3) ? 3 : 4) : 1) void decompose16_kernel(dq_format fmt, dq_cache cache, CompressJob job,
+__global__ __launch_bounds__(64 * NWV, PART == 1 ? 5 : PART == 3 ? ((QB == 2 || QB == 4 || PAIR || N3) ? 3 : 4) : 1) void decompose16_kernel(dq_format fmt, dq_cache cache, CompressJob job,
                                                                float* __restrict__ large_ws,
                                                                int32_t* __restrict__ unit_status,
                                                                int32_t* __restrict__ call_status) {
@@ -1411,6 +1438,7 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 5 : PART == 3 ? ((QB == 2 || 
   double* const P = W + kMat;                                // Gram partials of the other waves
   uint8_t* const lds_u = LEAN ? pool : pool + kMatBytes;
   __shared__ double lam[j1], lam2[j1];
+  __shared__ uint8_t s_list[FAST ? kTileTokens : 1];          // the tile's tokens that are settled in fp64
 
   double* const gram_ws = reinterpret_cast<double*>(large_ws + (long)unit * g.Tb * d);   // PART: G, then W, of this block
   // ---- Gram matrix G[p][q] = sum_{t, b2} X[t, p*8+b2] X[t, q*8+b2] ----
@@ -1527,61 +1555,105 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 5 : PART == 3 ? ((QB == 2 || 
     typedef FastProject<QB, FULL, PAIR> FP;
     FP fp;
     fp.X = X; fp.nv = nv; fp.head_gap = head_gap; fp.one_group = !PAIR && g.groups == 1;
-    fp.setup(gram_ws + j1 * j1, j1, gram_ws + 2 * j1 * j1);
+    fp.setup(gram_ws + j1 * j1, gram_ws + 2 * j1 * j1);
     const int n = l & 15, q4 = l >> 4;
     const long blk = bh * g.NB + slot;
     uint8_t* const codes = (which ? cache.v_codes : cache.k_codes) + blk * g.codes_per_block;
     uint16_t* const scales = (which ? cache.v_scales : cache.k_scales) + blk * g.scales_per_block;
     const long codes_gap = (long)g.NB * g.codes_per_block, scales_gap = (long)g.NB * g.scales_per_block;   // PAIR: to the second head's
-    u32x4 x[4];
-    fp.load(x, 16 * wv + n);
-    if (!which) {
-      for (int t0 = 16 * wv; t0 < g.Tb; t0 += 16 * NWV) {
-        f32x4 acc[8];
-        fp.template project<false>(x, acc);
-        fp.load(x, t0 + 16 * NWV + n);   // (past the block: nothing is read)
-        uint16_t sb;
-        uint32_t part[4];
-        fp.template quantize<false>(acc, t0, sb, part);
-        // the lane's 32 elements of its token's row: words 4 q4 .. of 4-bit codes, 2 q4 .. of 2-bit codes
-        uint8_t* const dst = codes + (PAIR ? (q4 >> 1) * codes_gap + (long)(t0 + n) * (8 * QB) + (q4 & 1) * (4 * QB)
-                                           : (long)(t0 + n) * (16 * QB) + q4 * (4 * QB));
-        if (QB == 4) *reinterpret_cast<u32x4*>(dst) = u32x4{part[0], part[1], part[2], part[3]};
-        else *reinterpret_cast<u32x2*>(dst) = u32x2{part[0] | (part[1] << 16), part[2] | (part[3] << 16)};
-        if (PAIR) {
-          if (!(q4 & 1)) scales[(q4 >> 1) * scales_gap + t0 + n] = sb;
-        } else if (q4 == 0 || (!fp.one_group && q4 == 2)) {
-          scales[(long)(t0 + n) * g.groups + (q4 >> 1)] = sb;
+    uint8_t* const stage = lds_u;
+    // the lane's 32 elements of a key token's row: words 4 q4 .. of 4-bit codes, 2 q4 .. of 2-bit codes
+    auto store_key = [&](int t, const uint32_t (&part)[4], uint16_t sb) __attribute__((always_inline)) {
+      uint8_t* const dst = codes + (PAIR ? (q4 >> 1) * codes_gap + (long)t * (8 * QB) + (q4 & 1) * (4 * QB)
+                                         : (long)t * (16 * QB) + q4 * (4 * QB));
+      if (QB == 4) *reinterpret_cast<u32x4*>(dst) = u32x4{part[0], part[1], part[2], part[3]};
+      else *reinterpret_cast<u32x2*>(dst) = u32x2{part[0] | (part[1] << 16), part[2] | (part[3] << 16)};
+      if (PAIR) {
+        if (!(q4 & 1)) scales[(q4 >> 1) * scales_gap + t] = sb;
+      } else if (q4 == 0 || (!fp.one_group && q4 == 2)) {
+        scales[(long)t * g.groups + (q4 >> 1)] = sb;
+      }
+    };
+    // the step of a value token's group that holds the lane's row n
+    auto store_value_step = [&](int t, uint16_t sb) __attribute__((always_inline)) {
+      if (PAIR) scales[(n >> 3) * scales_gap + t] = sb;
+      else if (!fp.one_group || n < 8) scales[(long)t * g.groups + (n >> 3)] = sb;
+    };
+    for (int tile = 0; tile < g.Tb; tile += kTileTokens) {
+      int listed = fp.hard ? kTileTokens : 0;   // tokens of the tile in s_list (a hard block: all of them)
+      if (!fp.hard) {
+        auto list = [&](uint32_t tokens, int t0) __attribute__((always_inline)) {
+          if (tokens == 0) return;
+          if (l < 16 && ((tokens >> l) & 1u)) s_list[listed + __builtin_popcount(tokens & ((1u << l) - 1u))] = (uint8_t)(t0 + l);
+          listed += __builtin_popcount(tokens);
+        };
+        u32x4 x[4];
+        fp.load(x, tile + n);
+#pragma unroll 1
+        for (int t0 = 0; t0 < kTileTokens; t0 += 16) {
+          f32x4 acc[8];
+          uint16_t sb;
+          if (!which) {
+            fp.template project<false>(x, acc);
+            fp.load(x, tile + t0 + 16 + n);   // (past the tile's end: read and dropped; past the rows: nothing is read)
+            uint32_t part[4];
+            const uint32_t doubt = fp.template quantize<false>(acc, sb, part);
+            list(doubt, t0);
+            if (!((doubt >> n) & 1u)) store_key(tile + t0 + n, part, sb);
+          } else {
+            fp.template project<true>(x, acc);
+            fp.load(x, tile + t0 + 16 + n);
+            uint32_t part[8];
+            const uint32_t doubt = fp.template quantize<true>(acc, sb, part);
+            list(doubt, t0);
+            // row (b2, r = n) of the tile, tokens t0 + 4 q4 .. + 3
+#pragma unroll
+            for (int b2 = 0; b2 < 8; ++b2) {
+              uint8_t* const dst = stage + (b2 * 16 + n) * FP::STRIDE + (t0 / 4 + q4) * (QB / 2);
+              if (QB == 4) *reinterpret_cast<uint16_t*>(dst) = (uint16_t)part[b2];
+              else *dst = (uint8_t)part[b2];
+            }
+            if ((n & 4) == 0 && !((doubt >> (4 * q4 + (n & 3))) & 1u)) store_value_step(tile + t0 + 4 * q4 + (n & 3), sb);
+          }
         }
       }
-    } else {
-      uint8_t* const stage = lds_u;
-      for (int tile = 0; tile < g.Tb; tile += kTileTokens) {
-        for (int t0 = 16 * wv; t0 < kTileTokens; t0 += 16 * NWV) {
-          f32x4 acc[8];
-          fp.template project<true>(x, acc);
-          fp.load(x, tile + t0 + 16 * NWV + n);
-          uint16_t sb;
-          uint32_t part[8];
-          fp.template quantize<true>(acc, tile + t0, sb, part);
-          // row (b2, r = n) of the tile, tokens t0 + 4 q4 .. + 3
+      __builtin_amdgcn_wave_barrier();   // (one wave: its LDS operations execute in order)
+#pragma unroll 1
+      for (int base = 0; base < listed; base += 16) {
+        auto token = [&](int slot_) -> int { return base + slot_ >= listed ? -1 : fp.hard ? base + slot_ : (int)s_list[base + slot_]; };
+        uint32_t fields[4][2];
+        if (!which) {
+          const int t = token(n);
+          uint16_t sb[1];
+          fp.template settle<false>(tile, t, sb, fields);
+          uint32_t part[4];
 #pragma unroll
-          for (int b2 = 0; b2 < 8; ++b2) {
-            uint8_t* const dst = stage + (b2 * 16 + n) * FP::STRIDE + (t0 / 4 + q4) * (QB / 2);
-            if (QB == 4) *reinterpret_cast<uint16_t*>(dst) = (uint16_t)part[b2];
-            else *dst = (uint8_t)part[b2];
-          }
-          const int tok = tile + t0 + 4 * q4 + (n & 3);
-          if (PAIR) {
-            if ((n & 4) == 0) scales[(n >> 3) * scales_gap + tok] = sb;
-          } else if (n < 4 || (!fp.one_group && n >= 8 && n < 12)) {
-            scales[(long)tok * g.groups + (n >> 3)] = sb;
+          for (int i = 0; i < 4; ++i) part[i] = FP::squeeze(fields[i][0], fields[i][1]);
+          if (t >= 0) store_key(tile + t, part, sb[0]);
+        } else {
+          uint16_t sb[4];
+          fp.template settle<true>(tile, token(n), sb, fields);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int t = token(q4 + 4 * i);
+            if (t < 0) continue;
+            // the token's field in its row's word (neighbours of other tokens may be settled at the same time)
+            const int shift = (t * QB) & 31;
+            uint32_t* const word = reinterpret_cast<uint32_t*>(stage + n * FP::STRIDE) + t * QB / 32;
+#pragma unroll
+            for (int b2 = 0; b2 < 8; ++b2) {
+              atomicAnd(word + b2 * (16 * FP::STRIDE / 4), ~(((1u << QB) - 1u) << shift));
+              atomicOr(word + b2 * (16 * FP::STRIDE / 4), ((fields[i][b2 >> 2] >> (8 * (b2 & 3))) & 0xFFu) << shift);
+            }
+            if ((n & 7) == 0) store_value_step(tile + t, sb[i]);
           }
         }
+      }
+      if (which) {
         __syncthreads();
         // the tile's rows in memory: [b2][r], or per head [b2][r % 8]
         constexpr int CPR = FP::ROWB / 16;   // 16-byte pieces per row
-        for (int idx = threadIdx.x; idx < 128 * CPR; idx += 64 * NWV) {
+        for (int idx = l; idx < 128 * CPR; idx += 64) {
           const int rw = idx / CPR, pc = idx % CPR;
           const uint32_t* src = reinterpret_cast<const uint32_t*>(stage + rw * FP::STRIDE + 16 * pc);
           const u32x4 v = {src[0], src[1], src[2], src[3]};
