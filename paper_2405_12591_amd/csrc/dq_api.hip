@@ -10,35 +10,56 @@ static std::atomic<int> g_last_hip_error{0};
 void set_last_hip_error(hipError_t e) { g_last_hip_error.store((int)e); }
 
 // Launch shape of the matrix-core kernel: n splits of every (sequence, kv head) unit and nw waves per
-// workgroup, the pair with the least estimated time.  The estimate (in us, fitted to 533 measured
-// launches of 4 to 512 units and 2 to 128 tiles, 2, 4 and 8 bits, one to four heads per workgroup,
-// each in up to 22 shapes; the pair it picks is 1 % slower than the fastest measured one on average, the
-// rule of fixed depths this replaces was 4 % slower and up to 60 %: 128 units of 32 tiles with four
-// heads took 26.6 us in 4 splits of 4 waves, 19.2 in the 2 of 8 picked here):
-//   the busiest compute unit holds k = ceil(units n / 256) workgroups, k nw / 4 waves on each SIMD;
-//   a wave works ceil(tiles / (n nw)) tiles, each of which takes the longer of one wave's chain
-//   (requests, unpacking, two contractions, softmax) and the SIMD's issue of all its waves' tiles,
-//   which grows with the code width and the heads;
-//   every wave on a SIMD and every split (partial, ticket, merge) costs a fixed amount.
-static void choose_mfma_shape(int units, int max_tiles, int heads, int bits, int* n_out, int* nw_out) {
-  const float chain = 1.67f + 0.35f * (heads - 1), issue = 0.61f + 0.32f * bits + 0.045f * (heads - 1);
+// workgroup, the pair with the least estimated time.  The estimate is meant to rank shapes, not to give
+// their time; it was fitted to the kernel timestamps of 2302 launches (1 to 640 units, 1 to 256
+// tiles of 128 tokens, 2, 4 and 8 bits, one to four heads per workgroup, two and three tensors, with
+// and without a tail), each in up to 24 shapes:
+//   the busiest compute unit works k = ceil(units n / 256) workgroups, as many at a time as its registers
+//   hold, the rest in further rounds;
+//   in a round a wave works ceil(tiles / (n nw)) tiles, each of which takes the longer of one wave's
+//   chain (requests, unpacking, two contractions, softmax) and the SIMD's issue of all its waves'
+//   tiles, which grows with the code width, and something for every wave beside it;
+//   every wave on a SIMD and every split (partial, ticket, merge) costs a fixed amount, and so does the
+//   tail per wave and per load of its rows;
+//   a finer split has to promise 8.6 % to be taken.
+// The picks are 0.9 % slower than the fastest shape measured on average, 19 % at worst (96 units of 64
+// tiles with four heads: 26.5 us in 2 splits of 8 waves, 30.4 in the 8 of 4 that an estimate without
+// rounds took).  That estimate was 1.3 % off on average and 30 % at worst, and over 3 % slower in 133 of
+// the 2302 cases than the rule of fixed depths before it (35 now); that rule was 4.5 % off and 73 %.
+static void choose_mfma_shape(int units, int max_tiles, int heads, int bits, bool two_groups, bool three, bool tail,
+                              int* n_out, int* nw_out) {
   static const int kSplits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
+  // waves a SIMD's registers hold (the heads' accumulators, the ring of chunks and the tail's rows decide)
+  int resident;
+  if (bits == 8) resident = (heads == 1 || (heads == 2 && !three && !tail)) ? 2 : 1;
+  else if (bits == 4) resident = (!three && (heads == 1 || (heads == 2 && !tail && !two_groups))) ? 3 : 2;
+  else resident = heads == 1 ? (three ? 3 : 4) : heads == 2 ? (three ? 2 : 3) : 2;
+  const float h = (float)(heads - 1), n3 = three ? 1.f : 0.f;
+  const float chain = 1.955f + 0.626f * h + 2.847f * n3, issue = 0.018f + 0.483f * bits + 0.008f * h + 0.758f * n3;
+  const float per_wave = 2.172f + (tail ? 0.024f * (1 + heads) : 0.f);
   float best = 3.0e38f;
   for (const int n : kSplits) {
     if (n > kMaxSplits || n > max_tiles) break;
     // (8-bit codes: a wave's ring of chunks is twice as large and an 8-wave workgroup would run out of
     // registers)
     for (int nw = 4; nw <= (bits == 8 ? 4 : 8); nw += 4) {
-      const long per_cu = ((long)units * n + 255) / 256;
-      const float waves = 0.25f * (float)(per_cu * nw);                 // per SIMD
       const int tiles = (max_tiles + n * nw - 1) / (n * nw);           // of the busiest wave
-      const float t = tiles * fmaxf(chain, waves * issue) + 1.07f * waves + (n > 1 ? 2.76f + 0.173f * n : 0.f);
-      if (t < best) { best = t; *n_out = n; *nw_out = nw; }
+      auto round = [&](int groups) -> float {                          // so many workgroups on a compute unit at a time
+        if (groups == 0) return 0.f;
+        const float waves = 0.25f * (float)(groups * nw);               // per SIMD
+        return tiles * (fmaxf(chain, waves * issue) + 0.289f * waves) + per_wave * waves + 0.072f;
+      };
+      const int together = resident * 4 / nw > 1 ? resident * 4 / nw : 1;
+      const long per_cu = ((long)units * n + 255) / 256;
+      float t = (float)(per_cu / together) * round(together) + round((int)(per_cu % together));
+      if (n > 1) t += 1.606f + 0.112f * n;
+      if (tail) t += 0.136f * (float)((16 + n * nw - 1) / (n * nw));    // (64 rows, four a load)
+      if (t < 0.914f * best) { best = t; *n_out = n; *nw_out = nw; }
     }
   }
 }
 
-int choose_splits(const dq_format* f, int batch, int q_heads, int kv_heads, int max_seq_len, bool mfma,
+int choose_splits(const dq_format* f, int batch, int q_heads, int kv_heads, int max_seq_len, bool mfma, bool tail,
                   uint32_t flags, int* nw_out) {
   const int max_tiles = (max_seq_len + kTileTokens - 1) / kTileTokens;
   int n = 1, nw = 4;
@@ -47,9 +68,9 @@ int choose_splits(const dq_format* f, int batch, int q_heads, int kv_heads, int 
       int per_group = 1;
       const int hg = mfma_head_groups(f, q_heads, kv_heads, &per_group);   // each head group is a workgroup of its own
       if (mfma_pair_heads(f, q_heads, kv_heads))   // two kv heads per workgroup
-        choose_mfma_shape(batch * kv_heads / 2 * hg, max_tiles, 2 * per_group, f->bits, &n, &nw);
+        choose_mfma_shape(batch * kv_heads / 2 * hg, max_tiles, 2 * per_group, f->bits, true, false, tail, &n, &nw);
       else
-        choose_mfma_shape(batch * kv_heads * hg, max_tiles, per_group, f->bits, &n, &nw);
+        choose_mfma_shape(batch * kv_heads * hg, max_tiles, per_group, f->bits, f->group == 64, f->i3 == kRun, tail, &n, &nw);
     } else {
       const int units = batch * q_heads;
       n = (2048 + units - 1) / units;
@@ -200,7 +221,7 @@ static int32_t decode_impl(const dq_format* fmt, const dq_cache* cache, const ui
   a.partials = reinterpret_cast<float*>(ws + kWsHeaderBytes + decode_counter_bytes(cache->batch, q_heads));
   a.heads_per_group = q_heads / cache->kv_heads;
   a.head_groups = use_mfma ? mfma_head_groups(fmt, q_heads, cache->kv_heads, &a.heads_per_group) : 1;
-  a.n_split = choose_splits(fmt, cache->batch, q_heads, cache->kv_heads, max_seq_len, use_mfma, flags, &a.nw);
+  a.n_split = choose_splits(fmt, cache->batch, q_heads, cache->kv_heads, max_seq_len, use_mfma, tail != nullptr, flags, &a.nw);
   // With one workgroup per compute unit and equal shares, a launch ends with its slowest XCD.
   // Dealing the units so that every XCD sees every residue class of them (mod 8) brings the XCDs
   // closer together: measured 4 - 5 % faster on the 256-unit benchmark shapes (4- and 8-bit), neutral

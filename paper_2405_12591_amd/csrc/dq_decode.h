@@ -14,7 +14,7 @@ struct DecodeArgs {
   float scale;             // softmax scale (already defaulted)
   uint16_t* out;           // [B, Hq, d] fp16 bits
   float* out_f32;          // optional
-  float* partials;         // [B*Hq, n_split, d + 2]
+  float* partials;         // [B*Hq, n_slots, d + 2]
   int32_t* counters;       // [B*Hkv*head_groups] zero between calls
   int n_split;
   int n_slots;             // partial slots per (b, head): n_split, plus one for the fp16 tail on the plain path
@@ -74,6 +74,6 @@ bool mfma_takes(const dq_format* f, int q_heads, int kv_heads);
 bool mfma_pair_heads(const dq_format* f, int q_heads, int kv_heads);
 int mfma_head_groups(const dq_format* f, int q_heads, int kv_heads, int* heads_per_group);
 int choose_splits(const dq_format* f, int batch, int q_heads, int kv_heads, int max_seq_len, bool mfma,
-                  uint32_t flags, int* nw_out);
+                  bool tail, uint32_t flags, int* nw_out);
 
 }  // namespace dq
