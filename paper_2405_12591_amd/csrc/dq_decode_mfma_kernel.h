@@ -226,7 +226,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   typedef TailWave<R, kTailBatch < kTailMost ? kTailBatch : kTailMost, P2> Tail;
   __shared__ float s_tail[TM ? NW * Tail::kResultFloats : 1];
   __shared__ int s_last;
-  __shared__ float s_wgt[4][kMaxSplits + 1];
+  __shared__ float s_wgt[4][kMaxSplits];
   __shared__ float s_sum[4];
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -320,33 +320,28 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
     // each slot's weight in LDS; then every thread adds up
     // its element over the slots, eight device-scope loads at a time (slots past the last one are
     // not read and weigh nothing).
-    const int ns = a.n_slots;   // <= kMaxSplits + 1 (the tail's slot included)
+    const int ns = a.n_slots;   // the splits: <= kMaxSplits = 64, a slot per lane (the waves' shares of the tail are in them)
+    static_assert(kMaxSplits <= 64, "one slot per lane");
     auto load_slots = [&](const float* col, int sp, float (&v)[8]) __attribute__((always_inline)) {
 #pragma unroll
       for (int k = 0; k < 8; ++k)
         v[k] = (sp + k < ns) ? __hip_atomic_load(col + (sp + k) * (RD + 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.f;
     };
     float v_first[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    float m0 = -INFINITY, l0 = 0.f, m1 = -INFINITY, l1 = 0.f;
+    float m0 = -INFINITY, l0 = 0.f;
     if (wave < R && head_live(wave)) {
       const float* base = a.partials + head_row(wave) * ns * (RD + 2);
       if (lane < ns) {
         m0 = __hip_atomic_load(base + lane * (RD + 2) + RD, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         l0 = __hip_atomic_load(base + lane * (RD + 2) + RD + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
-      if (lane + 64 < ns) {
-        m1 = __hip_atomic_load(base + (lane + 64) * (RD + 2) + RD, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        l1 = __hip_atomic_load(base + (lane + 64) * (RD + 2) + RD + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
     }
     if (tid < R * RD && head_live(tid / RD)) load_slots(a.partials + head_row(tid / RD) * ns * (RD + 2) + tid % RD, 0, v_first);
     if (wave < R && head_live(wave)) {
-      const float M = wave_allmax(fmaxf(m0, m1));
+      const float M = wave_allmax(m0);
       const float w0 = (m0 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m0 - M);
-      const float w1 = (m1 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m1 - M);
       if (lane < ns) s_wgt[wave][lane] = w0;
-      if (lane + 64 < ns) s_wgt[wave][lane + 64] = w1;
-      const float L = wave_allsum(l0 * w0 + l1 * w1);
+      const float L = wave_allsum(l0 * w0);
       if (lane == 0) s_sum[wave] = L;
     }
     __syncthreads();
