@@ -273,6 +273,13 @@ def settle_clocks(dq, torch, caches, q, lens_d, max_seq, ws, out, flags, ms=150.
     return i
 
 
+def on_matrix_cores(dq, fmt, w):
+    """Whether DECODE_AUTO runs the matrix-core kernel: what DECODE_FORCE_MFMA takes, and grouped query
+    heads of 64 channels, up to 32 per kv head, where the kv heads pair up."""
+    return dq.decode_mfma_supported(fmt, w.q_heads, w.kv_heads) or (
+        fmt.head_dim == 64 and w.q_heads <= 32 * w.kv_heads and dq.decode_mfma_supported(fmt, w.kv_heads, w.kv_heads))
+
+
 def run_config(dq, torch, w, K, W, n_layers, generic, pool, dev="cuda:0", shape_tag=None, launch=(0, 0)):
     fmt, cache0, lens, comp = build_cache(dq, torch, w, dev, pool)
     caches = [cache0] + [cache0.clone() for _ in range(n_layers - 1)]
@@ -282,7 +289,7 @@ def run_config(dq, torch, w, K, W, n_layers, generic, pool, dev="cuda:0", shape_
     ws = dq.decode_workspace(fmt, w.batch, w.q_heads, w.kv_heads, max_seq, dev)
     out = torch.empty_like(q)
     flags = (dq.DECODE_FORCE_GENERIC if generic else dq.DECODE_AUTO) | dq.decode_flags(splits=launch[0], waves=launch[1])
-    path = "generic" if (generic or not dq.decode_mfma_supported(fmt, w.q_heads, w.kv_heads)) else "mfma"
+    path = "generic" if (generic or not on_matrix_cores(dq, fmt, w)) else "mfma"
 
     kev = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(K)]
     for a, b in kev:   # record once so that the handles exist

@@ -64,7 +64,7 @@ def main():
         return
     w = workloads.get_workload(args.workload)
     fmt, cache0, lens, _ = bench.build_cache(dq, torch, w, dev, bench._InProcess())
-    if not dq.decode_mfma_supported(fmt, w.q_heads, w.kv_heads):
+    if not bench.on_matrix_cores(dq, fmt, w):
         raise SystemExit("the matrix-core kernel does not take this workload")
     caches = [cache0] + [cache0.clone() for _ in range(7)]
     q = torch.from_numpy(workloads.query(w)).to(dev)
