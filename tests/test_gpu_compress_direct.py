@@ -43,11 +43,11 @@ def _both_ways(w, t_new, n_valid, blk, waves=0):
 
 @pytest.mark.parametrize("bits,group,levels,tb,batch,kvh", [
     (4, 128, 0, 128, 8, 8),      # 128 blocks: four waves per block
-    (4, 128, 0, 128, 8, 32),     # 512 blocks: two waves per block (the benchmark's call)
+    (4, 128, 0, 128, 8, 32),     # 512 blocks: the most that get four (the benchmark's call)
     (2, 64, 0, 128, 5, 8),
     (2, 64, 1, 256, 3, 4),
     (8, 128, 0, 128, 4, 40),     # 320 blocks
-    (2, 64, 0, 128, 16, 32),     # 1024 blocks: one wave per block
+    (2, 64, 0, 128, 16, 32),     # 1024 blocks: two waves per block
     (4, 64, 1, 128, 2, 6),
     (8, 64, 0, 256, 2, 2),
     (2, 128, 1, 128, 3, 3),
@@ -74,8 +74,8 @@ def test_fused_quantizer_writes_the_same_cache(bits, group, levels, tb, batch, k
 
 
 def test_calls_the_fused_kernel_does_not_cover_fall_back():
-    """More than 1024 blocks, three local tensors, 64-channel heads that do not pair up, groups of 32: the flag is a
-    permission, not a demand; the call gives the same cache as without it."""
+    """More than 1024 blocks (three launches), three local tensors, 64-channel heads that do not pair up,
+    groups of 32: the flag is a permission, not a demand; the call gives the same cache as without it."""
     base = workloads.get_workload("llama7b_4bit")
     for kw in (dict(batch=17, q_heads=32, kv_heads=32),                                   # 1088 blocks
                dict(batch=2, q_heads=4, kv_heads=4, i3=8),
@@ -138,10 +138,10 @@ def test_properties_at_the_call_sizes_that_ship(name, batch, kvh):
 
 @pytest.mark.parametrize("bits,group,levels,d", [(4, 128, 0, 128), (2, 64, 1, 128), (8, 128, 0, 128), (4, 64, 0, 64)])
 def test_the_lean_build_for_large_calls_writes_the_same_bits(bits, group, levels, d):
-    """Calls of more than 1024 blocks take a build of the decomposition kernel that keeps fewer
-    registers and less LDS (several blocks per SIMD).  Same arithmetic: with and without the fp32
-    rows kept, the cache must equal, bit for bit, what the one-wave build of the small calls writes
-    (selected through the flags word), ragged rows and skipped sequences included."""
+    """Calls of more than 1024 blocks run as three launches with one wave per block or less.  Same
+    arithmetic: with and without the fp32 rows kept, the cache must equal, bit for bit, what the builds
+    of the small calls write (four and two waves per block, selected through the flags word), ragged rows
+    and skipped sequences included."""
     batch, kvh = 9, 64 if d == 64 else 32
     w = dataclasses.replace(workloads.get_workload("llama7b_4bit"), batch=batch, q_heads=kvh, kv_heads=kvh, bits=bits,
                             group=group, levels=levels, max_seq=256, min_seq=256, head_dim=d, j1=d // 8, j2=8)
@@ -155,7 +155,7 @@ def test_the_lean_build_for_large_calls_writes_the_same_bits(bits, group, levels
     n_valid = torch.tensor([256, 130, 1, 0, 255, 128, 129, 256, 77][:batch], dtype=torch.int32, device=DEV)
     first = torch.tensor([0, 1, 0, 0, 0, -1, 0, 0, 1][:batch], dtype=torch.int32, device=DEV)
     out = []
-    for keep, waves in ((True, 0), (False, 0), (True, 1), (False, 1)):
+    for keep, waves in ((True, 4), (False, 4), (False, 2), (True, 0), (False, 0), (False, 1)):
         cache = dq.alloc_cache(fmt, batch, kvh, 2, DEV, fill=0xA5)
         ws = dq.compress_workspace(fmt, batch, kvh, DEV, t_new=256)
         dq.compress_kv_blocks(cache, kd, vd, first, n_valid, ws, keep_large=keep, waves=waves)
@@ -165,3 +165,37 @@ def test_the_lean_build_for_large_calls_writes_the_same_bits(bits, group, levels
         for name in cache.t:
             assert torch.equal(cache.t[name], out[0][0].t[name]), name
         assert torch.equal(status, out[0][1])
+
+
+@pytest.mark.parametrize("bits,group,levels,d,keep", [(4, 128, 0, 128, False), (2, 64, 1, 128, True), (4, 64, 0, 64, False)])
+def test_calls_of_more_than_8192_blocks_write_the_bits_of_small_ones(bits, group, levels, d, keep):
+    """Above 8192 blocks (pairs of 64-channel heads) the eigen-solver works eight blocks per wave.  8330 of them, not a
+    multiple of what a workgroup takes, ragged rows and skipped sequences among them: cache and status
+    words must be those of one small call per block position (four waves per block)."""
+    batch, kvh, nb = 5, 98 if d == 64 else 49, 17
+    n = nb * 128 - 50
+    _say("8330 blocks: bits=%d G=%d levels=%d d=%d keep=%s" % (bits, group, levels, d, keep))
+    fmt = dq.Format(bits, group, d, d // 8, 8, 128, 1, levels)
+    gen = torch.Generator(device=DEV).manual_seed(12)
+    k, v = (torch.randn((batch, kvh, n, d), device=DEV, generator=gen).half() for _ in "kv")
+    for x in (k, v):
+        x[..., 7] *= 20
+    rows = [n, 9 * 128 + 1, n, 3 * 128, n - 100]
+    first = [0, 1, -1, 0, 0]
+    valid, slot = (torch.tensor(t, dtype=torch.int32, device=DEV) for t in (rows, first))
+    large, small = (dq.alloc_cache(fmt, batch, kvh, nb, DEV, fill=0xA5) for _ in range(2))
+    ws = dq.compress_workspace(fmt, batch, kvh, DEV, t_new=n)
+    dq.compress_kv_blocks(large, k, v, slot, valid, ws, keep_large=keep)
+    status = ws[:8].view(torch.int32).tolist()
+    ws_small = dq.compress_workspace(fmt, batch, kvh, DEV)
+    sweeps = 0
+    for j in range(nb):
+        kj, vj = (x[:, :, 128 * j:128 * (j + 1)].contiguous() for x in (k, v))
+        sj = torch.tensor([f + j if 0 <= f < nb - j else -1 for f in first], dtype=torch.int32, device=DEV)
+        dq.compress_kv(small, kj, vj, sj, (valid - 128 * j).clamp(min=0), ws_small, keep_large=False)
+        word = ws_small[:8].view(torch.int32).tolist()
+        assert word[0] == 0
+        sweeps = max(sweeps, word[1])
+    for name in large.t:
+        assert torch.equal(large.t[name].view(torch.uint8), small.t[name].view(torch.uint8)), name
+    assert status == [0, sweeps]

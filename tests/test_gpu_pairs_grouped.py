@@ -59,6 +59,31 @@ def test_grouped_pairs_with_a_tail_match_the_plain_kernel(q_heads, kv_heads, tai
         again = dq.attn_decode(cache, q, lens, n, ws, flags=flags, tail=tuple(tail))      # tickets left clean
         assert torch.equal(first, again)
         outs.append(o32)
+    # (the two kernels round differently: had the library's choice been the plain one, the bits would agree)
+    assert not torch.equal(outs[0], outs[1])
     # both kernels are within 1e-4 of |out| < 4 of the exact result (fp32 sums over 770 rows)
     assert torch.isfinite(outs[0]).all()
     assert (outs[0] - outs[1]).abs().max().item() < 2e-4
+
+
+@pytest.mark.parametrize("bits,q_heads,kv_heads,plain", [
+    (4, 8, 4, False), (2, 6, 2, False), (8, 16, 2, False), (4, 64, 2, False), (4, 66, 2, True), (4, 6, 3, True),
+])
+def test_which_kernel_grouped_heads_get(bits, q_heads, kv_heads, plain):
+    """The library's choice gives the plain kernel's bits exactly where it is the plain kernel: more than
+    32 query heads per kv head, an odd number of kv heads."""
+    _say("kernel of grouped pairs: %s" % ((bits, q_heads, kv_heads, plain),))
+    fmt = dq.Format(bits, 64, 64, 8, 8, 128)
+    g = torch.Generator(device=DEV).manual_seed(6)
+    cache = dq.alloc_cache(fmt, 1, kv_heads, 3, DEV)
+    k, v = (torch.randn(1, kv_heads, 384, 64, device=DEV, generator=g).half() for _ in "kv")
+    dq.compress_kv_blocks(cache, k, v, torch.zeros(1, dtype=torch.int32, device=DEV), None,
+                          dq.compress_workspace(fmt, 1, kv_heads, DEV, t_new=384))
+    q = torch.randn(1, q_heads, 64, device=DEV, generator=g).half()
+    lens = torch.tensor([380], dtype=torch.int32, device=DEV)
+    outs = []
+    for flags in (dq.DECODE_AUTO, dq.DECODE_FORCE_GENERIC):
+        o32 = torch.empty(1, q_heads, 64, dtype=torch.float32, device=DEV)
+        dq.attn_decode(cache, q, lens, 384, dq.decode_workspace(fmt, 1, q_heads, kv_heads, 384, DEV), out_f32=o32, flags=flags)
+        outs.append(o32)
+    assert torch.equal(*outs) == plain

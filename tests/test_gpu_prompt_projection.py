@@ -27,7 +27,7 @@ def _rows(kind, b, h, n, d, g):
 @pytest.mark.parametrize("kind", ["normal", "sizes", "grid", "outliers"])
 @pytest.mark.parametrize("bits,group,dim,levels,tb", [
     (4, 128, 128, 0, 128), (4, 64, 128, 1, 256), (2, 64, 128, 0, 128), (2, 128, 128, 1, 128), (4, 64, 64, 0, 128),
-    (2, 64, 64, 1, 256), (4, 32, 128, 0, 128),
+    (2, 64, 64, 1, 256), (4, 128, 128, 1, 128),
 ])
 def test_prompt_projection_is_that_of_the_fp64_path(kind, bits, group, dim, levels, tb):
     print("prompt projection: %s" % ((kind, bits, group, dim, levels, tb),), flush=True)
