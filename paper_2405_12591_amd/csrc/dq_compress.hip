@@ -658,6 +658,10 @@ __device__ __forceinline__ void jacobi_rotation(double app, double aqq, double a
 // -> 38 us (four waves per block instead of two in the latter, now that the solver is shorter).
 // All sums over rows run over the same tree whatever ROWS is, so every build of the kernels that
 // calls this gets the same bits.
+// Accuracy, replayed on the CPU over blocks whose singular values span 0 to 5.8 decades (600 to 2000 each),
+// against the two-sided iteration: rows of T_L orthonormal to 3e-9 / 7e-9 on flat spectra, both at the
+// fp32 rounding of T_L once it is stored (9e-9 to 8e-8); T_S T_L before any rounding 5e-10 / 2e-15 off,
+// because the normalised columns are orthogonal to 2e-9 only, and 2.6e-8 for both with T_L in fp32.
 constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppXor3 = 0x1B, kDppXor7 = 0x141, kDppXor8 = 0x128;
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
@@ -699,6 +703,8 @@ __device__ __forceinline__ double dot16(const double (&u)[ROWS], const double (&
   if (ROWS <= 2) r = add_xor32(r);
   return r;
 }
+
+constexpr int kMostSweeps = 24;
 
 template <int ROWS>
 struct Jacobi16 {
@@ -814,7 +820,8 @@ struct Jacobi16 {
       a = dot16<ROWS>(x, x);
       b = dot16<ROWS>(y, y);
     }
-    while (unsettled && sweeps < 16) {
+    // (blocks in general position settle in 6, graded ones in up to 17: five decades and a half)
+    while (unsettled && sweeps < kMostSweeps) {
       ++sweeps;
       unsettled = false;
       sweep<true, PAIR>(j, floor_lo, floor_hi, unsettled);
