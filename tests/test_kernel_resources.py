@@ -39,3 +39,29 @@ def test_occupancy_the_launch_shapes_count_on():
             # these workgroups run two to a compute unit: two waves per SIMD share its 512 registers
             assert r["VGPRs"] + r["AGPRs"] <= 256 and r["LDS Size"] <= 80 * 1024, (name, r)
     assert seen >= 100
+
+
+def test_resident_waves_of_the_launch_shape_estimate():
+    """choose_mfma_shape (dq_api.hip) counts on so many waves of the 4-wave kernels per SIMD; the built
+    kernels must hold at least as many (launches in several splits; those in one split hold the tail's
+    rows in more registers)."""
+    import re
+
+    def resident(bits, heads, two_groups, three, tail):
+        if bits == 8:
+            return 2 if heads == 1 or (heads == 2 and not three and not tail) else 1
+        if bits == 4:
+            return 3 if not three and (heads == 1 or (heads == 2 and not tail and not two_groups)) else 2
+        return {1: 3 if three else 4, 2: 2 if three else 3, 4: 2}[heads]
+
+    seen = 0
+    for name, r in _resources().items():
+        m = re.search(r"decode_mfma_kernelILi(\d)ELi(\d)ELi(\d)ELi4ELi([02])ELb([01])ELb([01])E", name)
+        if m:
+            bits, groups, heads, tail, three, pair = (int(x) for x in m.groups())
+            seen += 1
+            want = resident(bits, heads, groups == 2, three == 1, tail == 2)
+            # (two kinds of launch with two step groups hold one wave less; the estimate does not tell them apart)
+            less = groups == 2 and ((bits, heads, tail, three, pair) == (2, 2, 2, 0, 0) or (bits, heads, three) == (8, 1, 1))
+            assert r["Occupancy"] >= want - less, (name, r, want)
+    assert seen >= 40
