@@ -916,13 +916,15 @@ __device__ __forceinline__ void store_factors(Jacobi16<ROWS>& jac, double* lam, 
 // The codes and steps are those of the fp64 projection, bit for bit, but few tokens need it: a first pass
 // projects on fp16 matrix instructions (the rows are fp16 as they are, W is cut into three fp16 pieces, 33
 // bits; fp32 accumulation) with a proven error bound, and a token with a step or a code within that bound
-// of a rounding boundary is put on a list.  The listed tokens of a tile, sixteen at a time, then go through
-// the fp64 projection itself (second pass; a block whose bound is wide goes there as a whole).
+// of a rounding boundary is put on a list.  The listed tokens of a tile then go through the fp64 projection
+// itself, two at a time, their 2 x 8 columns side by side in one product (second pass; a block whose
+// bound is wide goes there as a whole).
 // A 16 x 16 x 16 product takes three matrix instructions instead of four fp64 ones of 64 cycles each, and no
 // fp16 value is widened: on this chip matrix and vector instructions of a SIMD do not overlap, so both
-// count.  14720 blocks (4-bit, d = 128): 280 us all in fp64, 181 so, at three waves per SIMD (settling single
-// elements where they arise, under a narrower bound that was not proven, took 201: 199 registers, two waves.
-// Held to four waves the second pass spills: 205).
+// count.  14720 blocks (4-bit, d = 128): 280 us all in fp64, 181 so (settling single elements where they
+// arise, under a narrower bound that was not proven, took 201 at 199 registers; the second pass keeps nothing
+// alive during the first and 114 registers do).  The second pass does not show: 16384 blocks, 195 us with
+// it and without.
 //
 // Keys (W as the left operand): lane (token n = l % 16, g = l / 16) gets rows r = 4 g + i of its token, eight
 // b2 each, i.e. whole words of the key layout, which it stores as they are.  Values (operands
@@ -1001,7 +1003,7 @@ struct FastProject {
     if (!PAIR) v += lane_exchange<0x140>(v);
     return v;
   }
-  static __device__ __forceinline__ float max16(float v) {
+  static __device__ __forceinline__ float max8(float v) {      // over eight lanes
     v = fmaxf(v, lane_exchange<0xB1>(v));
     v = fmaxf(v, lane_exchange<0x4E>(v));
     v = fmaxf(v, lane_exchange<0x141>(v));
@@ -1061,8 +1063,8 @@ struct FastProject {
       two += __shfl_xor(two, o);
     }
     const float total = sum16(lam);
-    float most = max16(lam);
-    float least = -max16(-lam);
+    float most = max8(lam);
+    float least = -max8(-lam);
     if (!PAIR) {
       most = fmaxf(most, lane_exchange<0x140>(most));
       least = fminf(least, lane_exchange<0x140>(least));
@@ -1073,8 +1075,8 @@ struct FastProject {
     float rel = 1.02f * (0x1p-24f * (kRoundings * c + 4.f) + rest), abs = 1.02f * (0x1p-24f * kRoundings * one * d + sc * 0x1p-19f);
     // all of the block's rows; NaN (a block that holds one) must not get lost
     hard = __any(!(rel + 32.f * abs <= kHardEps));
-    rel = max16(rel);
-    abs = max16(abs);
+    rel = max8(rel);
+    abs = max8(abs);
     eps = fmaxf(rel, lane_exchange<0x140>(rel));
     eps_abs = fmaxf(abs, lane_exchange<0x140>(abs));
   }
@@ -1115,7 +1117,7 @@ struct FastProject {
   template <bool VALUES>
   __device__ __forceinline__ float group_max(float v, bool both) const {
     if (VALUES) {
-      v = max16(v);
+      v = max8(v);
       if (both) v = fmaxf(v, lane_exchange<0x140>(v));
     } else {
       v = max_xor16(v);
@@ -1232,82 +1234,40 @@ struct FastProject {
            (uint32_t)__builtin_amdgcn_readlane((int)near, 32) << 8 | (uint32_t)__builtin_amdgcn_readlane((int)near, 48) << 12;
   }
 
-  // ---- second pass: sixteen tokens through the fp64 projection.  The operands, their order and so every
-  // bit are those of the build that keeps the fp32 rows.  `mine`: the token of slot n = l % 16, counted from
-  // `first` (-1: none).  The lane's element (i, b2) belongs to row 4 g + i of slot n (keys: the rows of W are dealt
-  // so), or to row n of slot g + 4 i (values).  Steps: of the group that holds the lane's rows, per token; fields: a
-  // byte each, element (i, b2) in byte b2 % 4 of fields[i][b2 / 4].
-  template <bool VALUES>
-  __device__ __forceinline__ void settle(int first, int mine, uint16_t (&sbits)[VALUES ? 4 : 1], uint32_t (&fields)[4][2]) const {
-    const int l = threadIdx.x & 63, n = l & 15, g = l >> 4;
-    constexpr int NT = VALUES ? 4 : 1;
-    const int row = VALUES ? n : 4 * (n & 3) + (n >> 2);
-    double w[4];
-    u32x4 x[4];
+  // ---- second pass: two tokens at a time through the fp64 projection, all their 2 x 8 columns side by side in
+  // one product.  The sums, their order and so every bit are those of the build that keeps the fp32 rows.
+  // Lane (n = l % 16, g = l / 16): token n / 8 of the two, b2 = n % 8, rows r = 4 g + i (the rows of W are dealt so).
+  __device__ __forceinline__ void load_factor(double (&w)[4], int l) const {
+    const int n = l & 15, g = l >> 4;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) w[s] = W[(4 * (n & 3) + (n >> 2)) * 16 + 4 * s + g];
+  }
+  // x[s]: the lane's token's X[b1 = 4 s + g][b2] (t < 0: none)
+  __device__ __forceinline__ void load_column(uint16_t (&x)[4], int t, int l) const {
+    const int g = l >> 4;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      w[s] = W[row * 16 + 4 * s + g];
-      x[s] = u32x4{0u, 0u, 0u, 0u};
-      if (mine >= 0 && first + mine < nv) x[s] = *reinterpret_cast<const u32x4*>(piece(first + mine, 4 * s + g));
-    }
-    float f[4][8];
-#pragma unroll
-    for (int half = 0; half < 8; half += 4) {   // (four b2 at a time: 32 registers of sums instead of 64)
-      f64x4 acc[4];
-#pragma unroll
-      for (int b2 = 0; b2 < 4; ++b2) acc[b2] = f64x4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const f16x8 h = __builtin_bit_cast(f16x8, x[s]);
-#pragma unroll
-        for (int b2 = 0; b2 < 4; ++b2) {
-          const double v = (double)(float)h[half + b2];
-          acc[b2] = VALUES ? __builtin_amdgcn_mfma_f64_16x16x4f64(v, w[s], acc[b2], 0, 0, 0)
-                           : __builtin_amdgcn_mfma_f64_16x16x4f64(w[s], v, acc[b2], 0, 0, 0);
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int b2 = 0; b2 < 4; ++b2) f[i][half + b2] = (float)acc[b2][i];
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    float up[NT], dn[NT];
-#pragma unroll
-    for (int k = 0; k < NT; ++k) { up[k] = 0.f; dn[k] = 0.f; }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int b2 = 0; b2 < 8; ++b2) {
-        up[VALUES ? i : 0] = fmaxf(up[VALUES ? i : 0], FULL ? f[i][b2] : fabsf(f[i][b2]));
-        if (FULL) dn[VALUES ? i : 0] = fmaxf(dn[VALUES ? i : 0], -f[i][b2]);
-      }
-    float step[NT], inv[NT];
-#pragma unroll
-    for (int k = 0; k < NT; ++k) {
-      up[k] = group_max<VALUES>(up[k], one_group);
-      if (FULL) dn[k] = group_max<VALUES>(dn[k], one_group);
-      sbits[k] = step_bits(up[k], dn[k]);
-      step[k] = h2f(sbits[k]);
-      inv[k] = step[k] > 0.f ? __builtin_amdgcn_rcpf(step[k]) : 0.f;
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int k = VALUES ? i : 0;
-      fields[i][0] = fields_of_four<QB, FULL>(f[i][0], f[i][1], f[i][2], f[i][3], step[k], inv[k]);
-      fields[i][1] = fields_of_four<QB, FULL>(f[i][4], f[i][5], f[i][6], f[i][7], step[k], inv[k]);
+      x[s] = 0;
+      if (t >= 0 && t < nv) x[s] = piece(t, 4 * s + g)[l & 7];
     }
   }
-  // eight fields of a byte each -> QB bits each
-  static __device__ __forceinline__ uint32_t squeeze(uint32_t lo, uint32_t hi) {
-    if (QB == 4) {
-      lo |= lo >> 4;
-      hi |= hi >> 4;
-      return (lo & 0xFFu) | ((lo >> 8) & 0xFF00u) | ((hi & 0xFFu) << 16) | ((hi & 0xFF0000u) << 8);
+  // The fields of the lane's four rows, a byte each, and the step of the group that holds them.
+  __device__ __forceinline__ uint32_t settle(const double (&w)[4], const uint16_t (&x)[4], uint16_t& sbits) const {
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(w[s], (double)h2f(x[s]), acc, 0, 0, 0);
+    float f[4], up = 0.f, dn = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      f[i] = (float)acc[i];
+      up = fmaxf(up, FULL ? f[i] : fabsf(f[i]));
+      if (FULL) dn = fmaxf(dn, -f[i]);
     }
-    lo |= lo >> 6;
-    hi |= hi >> 6;
-    return (lo & 0xFu) | ((lo >> 12) & 0xF0u) | ((hi & 0xFu) << 8) | ((hi >> 4) & 0xF000u);
+    up = group_max<false>(max8(up), one_group);   // (the token's eight b2, then its rows)
+    if (FULL) dn = group_max<false>(max8(dn), one_group);
+    sbits = step_bits(up, dn);
+    const float step = h2f(sbits), inv = step > 0.f ? __builtin_amdgcn_rcpf(step) : 0.f;
+    return fields_of_four<QB, FULL>(f[0], f[1], f[2], f[3], step, inv);
   }
 };
 
@@ -1345,7 +1305,7 @@ struct FastProject {
 // (T_2 = A V' diag(1/sigma')), and hands the rows of T_2 to the quantizer in the registers it
 // expects them in.  job.keep_large: the fp32 rows of T_2 also go to the workspace.
 template <int NWV, bool PAIR, int QB = 0, bool FULL = false, int PART = 0, bool N3 = false>
-__global__ __launch_bounds__(64 * NWV, PART == 1 ? 5 : PART == 3 ? ((QB == 2 || QB == 4 || PAIR || N3) ? 3 : 4) : 1) void decompose16_kernel(dq_format fmt, dq_cache cache, CompressJob job,
+__global__ __launch_bounds__(64 * NWV, PART == 1 ? 5 : PART == 3 ? ((PAIR && QB != 2 && QB != 4) || N3 ? 3 : 4) : 1) void decompose16_kernel(dq_format fmt, dq_cache cache, CompressJob job,
                                                                float* __restrict__ large_ws,
                                                                int32_t* __restrict__ unit_status,
                                                                int32_t* __restrict__ call_status) {
@@ -1625,34 +1585,66 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 5 : PART == 3 ? ((QB == 2 || 
         }
       }
       __builtin_amdgcn_wave_barrier();   // (one wave: its LDS operations execute in order)
+      if (listed > 0) {
+        // (the lane's number anew: addresses formed from it ahead of the first pass would cost that pass its
+        // registers, 152 instead of 114)
+        int lane = l;
+        asm volatile("" : "+v"(lane));
+        const int n = lane & 15, q4 = lane >> 4;
+        double w[4];
+        fp.load_factor(w, lane);
+        constexpr int PAIRS = 2;           // pairs of tokens whose rows are requested together
 #pragma unroll 1
-      for (int base = 0; base < listed; base += 16) {
-        auto token = [&](int slot_) -> int { return base + slot_ >= listed ? -1 : fp.hard ? base + slot_ : (int)s_list[base + slot_]; };
-        uint32_t fields[4][2];
-        if (!which) {
-          const int t = token(n);
-          uint16_t sb[1];
-          fp.template settle<false>(tile, t, sb, fields);
-          uint32_t part[4];
+        for (int base = 0; base < listed; base += 2 * PAIRS) {
+          int tok[PAIRS];
+          uint16_t xc[PAIRS][4];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) part[i] = FP::squeeze(fields[i][0], fields[i][1]);
-          if (t >= 0) store_key(tile + t, part, sb[0]);
-        } else {
-          uint16_t sb[4];
-          fp.template settle<true>(tile, token(n), sb, fields);
+          for (int k = 0; k < PAIRS; ++k) {
+            const int at = base + 2 * k + (n >> 3);
+            tok[k] = at >= listed ? -1 : fp.hard ? at : (int)s_list[at];
+            fp.load_column(xc[k], tok[k] < 0 ? -1 : tile + tok[k], lane);
+          }
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int t = token(q4 + 4 * i);
-            if (t < 0) continue;
-            // the token's field in its row's word (neighbours of other tokens may be settled at the same time)
-            const int shift = (t * QB) & 31;
-            uint32_t* const word = reinterpret_cast<uint32_t*>(stage + n * FP::STRIDE) + t * QB / 32;
+          for (int k = 0; k < PAIRS; ++k) {
+            uint16_t sb;
+            const uint32_t fields = fp.settle(w, xc[k], sb);   // rows 4 q4 + i, b2 = n % 8
+            const int t = tok[k], b2 = n & 7;
+            if (which) {
+              // the token's field in its row's word (the other token's may be in the same one)
+              uint32_t* const word = reinterpret_cast<uint32_t*>(stage + (b2 * 16 + 4 * q4) * FP::STRIDE) + max(t, 0) * QB / 32;
+              const int shift = (t * QB) & 31;
 #pragma unroll
-            for (int b2 = 0; b2 < 8; ++b2) {
-              atomicAnd(word + b2 * (16 * FP::STRIDE / 4), ~(((1u << QB) - 1u) << shift));
-              atomicOr(word + b2 * (16 * FP::STRIDE / 4), ((fields[i][b2 >> 2] >> (8 * (b2 & 3))) & 0xFFu) << shift);
+              for (int i = 0; i < 4; ++i)
+                if (t >= 0) {
+                  atomicAnd(word + i * (FP::STRIDE / 4), ~(((1u << QB) - 1u) << shift));
+                  atomicOr(word + i * (FP::STRIDE / 4), ((fields >> (8 * i)) & 0xFFu) << shift);
+                }
+            } else {
+              // row r's eight b2 are neighbours: lane b2 = i collects those of row 4 q4 + i
+              uint32_t mine = 0;
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                uint32_t v = ((fields >> (8 * i)) & 0xFFu) << (QB * b2);
+                v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);
+                v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);
+                v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);
+                mine = b2 == i ? v : mine;
+              }
+              const int r = 4 * q4 + b2;
+              uint8_t* const dst = codes + (PAIR ? (q4 >> 1) * codes_gap + (long)(tile + t) * (8 * QB) + (r & 7) * QB
+                                                 : (long)(tile + t) * (16 * QB) + r * QB);
+              if (t >= 0 && b2 < 4) {
+                if (QB == 4) *reinterpret_cast<uint32_t*>(dst) = mine;
+                else *reinterpret_cast<uint16_t*>(dst) = (uint16_t)mine;
+              }
             }
-            if ((n & 7) == 0) store_value_step(tile + t, sb[i]);
+            if (t >= 0 && b2 == 0) {
+              if (PAIR) {
+                if (!(q4 & 1)) scales[(q4 >> 1) * scales_gap + tile + t] = sb;
+              } else if (q4 == 0 || (!fp.one_group && q4 == 2)) {
+                scales[(long)(tile + t) * g.groups + (q4 >> 1)] = sb;
+              }
+            }
           }
         }
       }
@@ -1660,7 +1652,9 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 5 : PART == 3 ? ((QB == 2 || 
         __syncthreads();
         // the tile's rows in memory: [b2][r], or per head [b2][r % 8]
         constexpr int CPR = FP::ROWB / 16;   // 16-byte pieces per row
-        for (int idx = l; idx < 128 * CPR; idx += 64) {
+        int lane = l;
+        asm volatile("" : "+v"(lane));
+        for (int idx = lane; idx < 128 * CPR; idx += 64) {
           const int rw = idx / CPR, pc = idx % CPR;
           const uint32_t* src = reinterpret_cast<const uint32_t*>(stage + rw * FP::STRIDE + 16 * pc);
           const u32x4 v = {src[0], src[1], src[2], src[3]};
@@ -2278,6 +2272,17 @@ static int waves_per_block(int groups, int want_waves) {
   return groups <= 512 ? 4 : groups <= 1024 ? 2 : 0;
 }
 
+// LDS that a prompt's projection (2 or 4 bits) is given beyond what it uses, to hold fewer waves than its
+// registers would let onto a SIMD: four are best where they take the whole launch at once (groups <=
+// 4096: 2048 pairs of 64-channel heads, whole call, 138 us with four, 146 with three; 8192 blocks 120 / 132),
+// beyond that their rows push each other out of the caches (projection alone, four / three / two waves
+// per SIMD: 16384 blocks 195 / 187 / 208 us, 8192 pairs 141 / 134 / 130).
+static size_t prompt_projection_pad(int groups, bool pair_heads, int bits) {
+  if (groups <= 4096 || bits == 8) return 0;
+  const size_t per_cu = pair_heads ? 8 : 12, used = 128 * (16 * bits + 4) + 1024;
+  return 160 * 1024 / per_cu - used;
+}
+
 static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16_t* k_new,
                              const uint16_t* v_new, int32_t t_new, int n_blocks, const int32_t* blk_idx,
                              const int32_t* n_valid, void* workspace, size_t workspace_bytes, uint32_t flags,
@@ -2384,20 +2389,21 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
 #define DQ_LAUNCH_FUSED_PART3(B_)                                                                                \
   do {                                                                                                          \
     if (pair_heads && fmt->levels)                                                                              \
-      hipLaunchKernelGGL((decompose16_kernel<1, true, B_, true, 3>), dim3(units / 2), dim3(64), 0, st, *fmt, \
+      hipLaunchKernelGGL((decompose16_kernel<1, true, B_, true, 3>), dim3(units / 2), dim3(64), pad, st, *fmt, \
                          *cache, job, large_ws, unit_status, status);                                           \
     else if (pair_heads)                                                                                        \
-      hipLaunchKernelGGL((decompose16_kernel<1, true, B_, false, 3>), dim3(units / 2), dim3(64), 0, st,      \
+      hipLaunchKernelGGL((decompose16_kernel<1, true, B_, false, 3>), dim3(units / 2), dim3(64), pad, st,      \
                          *fmt, *cache, job, large_ws, unit_status, status);                                     \
     else if (fmt->levels)                                                                                       \
-      hipLaunchKernelGGL((decompose16_kernel<1, false, B_, true, 3>), dim3(units), dim3(64), 0, st, *fmt,    \
+      hipLaunchKernelGGL((decompose16_kernel<1, false, B_, true, 3>), dim3(units), dim3(64), pad, st, *fmt,    \
                          *cache, job, large_ws, unit_status, status);                                           \
     else                                                                                                        \
-      hipLaunchKernelGGL((decompose16_kernel<1, false, B_, false, 3>), dim3(units), dim3(64), 0, st, *fmt,   \
+      hipLaunchKernelGGL((decompose16_kernel<1, false, B_, false, 3>), dim3(units), dim3(64), pad, st, *fmt,   \
                          *cache, job, large_ws, unit_status, status);                                           \
   } while (0)
     const int fused_groups = pair_heads ? units / 2 : units;
     int fused_waves = waves_per_block(fused_groups, want_waves);
+    const size_t pad = prompt_projection_pad(fused_groups, pair_heads, fmt->bits);
     if (fused_waves == 0) {
       launch_factor();
       if (fmt->bits == 2) DQ_LAUNCH_FUSED_PART3(2);
