@@ -18,16 +18,18 @@ void set_last_hip_error(hipError_t e) { g_last_hip_error.store((int)e); }
 //   hold, the rest in further rounds;
 //   in a round a wave works ceil(tiles / (n nw)) tiles, each of which takes the longer of one wave's
 //   chain (requests, unpacking, two contractions, softmax) and the SIMD's issue of all its waves'
-//   tiles, which grows with the code width, and something for every wave beside it;
+//   tiles, which grows with the code width, and something for every wave beside it; a pair of
+//   64-channel heads counts a chain 0.2 us shorter than two heads of 128 channels (256 units of 32 tiles
+//   in 4 bits: 26.1 us in one split of 4 waves, 27.5 in the 8 waves that are picked without it);
 //   every wave on a SIMD and every split (partial, ticket, merge) costs a fixed amount, and so does the
 //   tail per wave and per load of its rows;
 //   a finer split has to promise 8.6 % to be taken.
-// The picks are 0.9 % slower than the fastest shape measured on average, 19 % at worst (96 units of 64
-// tiles with four heads: 26.5 us in 2 splits of 8 waves, 30.4 in the 8 of 4 that an estimate without
-// rounds took).  That estimate was 1.3 % off on average and 30 % at worst, and over 3 % slower in 133 of
-// the 2302 cases than the rule of fixed depths before it (35 now); that rule was 4.5 % off and 73 %.
-static void choose_mfma_shape(int units, int max_tiles, int heads, int bits, bool two_groups, bool three, bool tail,
-                              int* n_out, int* nw_out) {
+// The picks are 0.9 % slower than the fastest shape measured on average, 19 % at worst.  An estimate
+// without rounds was 1.3 % off on average and 30 % at worst (96 units of 64 tiles, four heads and a tail:
+// 33.6 us in its 8 splits of 4 waves, 26.8 in the 2 of 8 taken here), and over 3 % slower in 133 of the
+// 2302 cases than the rule of fixed depths before it (33 now); that rule was 4.5 % off and 73 %.
+static void choose_mfma_shape(int units, int max_tiles, int heads, int bits, bool two_groups, bool three, bool pair,
+                              bool tail, int* n_out, int* nw_out) {
   static const int kSplits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
   // waves a SIMD's registers hold (the heads' accumulators, the ring of chunks and the tail's rows decide)
   int resident;
@@ -35,7 +37,8 @@ static void choose_mfma_shape(int units, int max_tiles, int heads, int bits, boo
   else if (bits == 4) resident = (!three && (heads == 1 || (heads == 2 && !tail && !two_groups))) ? 3 : 2;
   else resident = heads == 1 ? (three ? 3 : 4) : heads == 2 ? (three ? 2 : 3) : 2;
   const float h = (float)(heads - 1), n3 = three ? 1.f : 0.f;
-  const float chain = 1.955f + 0.626f * h + 2.847f * n3, issue = 0.018f + 0.483f * bits + 0.008f * h + 0.758f * n3;
+  const float chain = 1.955f + 0.626f * h + 2.847f * n3 - (pair ? 0.2f : 0.f);
+  const float issue = 0.018f + 0.483f * bits + 0.008f * h + 0.758f * n3;
   const float per_wave = 2.172f + (tail ? 0.024f * (1 + heads) : 0.f);
   float best = 3.0e38f;
   for (const int n : kSplits) {
@@ -68,9 +71,10 @@ int choose_splits(const dq_format* f, int batch, int q_heads, int kv_heads, int 
       int per_group = 1;
       const int hg = mfma_head_groups(f, q_heads, kv_heads, &per_group);   // each head group is a workgroup of its own
       if (mfma_pair_heads(f, q_heads, kv_heads))   // two kv heads per workgroup
-        choose_mfma_shape(batch * kv_heads / 2 * hg, max_tiles, 2 * per_group, f->bits, true, false, tail, &n, &nw);
+        choose_mfma_shape(batch * kv_heads / 2 * hg, max_tiles, 2 * per_group, f->bits, true, false, true, tail, &n, &nw);
       else
-        choose_mfma_shape(batch * kv_heads * hg, max_tiles, per_group, f->bits, f->group == 64, f->i3 == kRun, tail, &n, &nw);
+        choose_mfma_shape(batch * kv_heads * hg, max_tiles, per_group, f->bits, f->group == 64, f->i3 == kRun, false, tail,
+                          &n, &nw);
     } else {
       const int units = batch * q_heads;
       n = (2048 + units - 1) / units;
