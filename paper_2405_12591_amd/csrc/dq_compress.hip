@@ -921,10 +921,12 @@ __device__ __forceinline__ void store_factors(Jacobi16<ROWS>& jac, double* lam, 
 // bound is wide goes there as a whole).
 // A 16 x 16 x 16 product takes three matrix instructions instead of four fp64 ones of 64 cycles each, and no
 // fp16 value is widened: on this chip matrix and vector instructions of a SIMD do not overlap, so both
-// count.  14720 blocks (4-bit, d = 128): 280 us all in fp64, 181 so (settling single elements where they
-// arise, under a narrower bound that was not proven, took 201 at 199 registers; the second pass keeps nothing
-// alive during the first and 114 registers do).  The second pass does not show: 16384 blocks, 195 us with
-// it and without.
+// count.  14720 blocks with outlier channels (4-bit, d = 128): 280 us all in fp64, 192 so (settling single
+// elements where they arise, under a narrower bound that was not proven, took 201 at 199 registers; the second
+// pass keeps nothing alive during the first and 114 registers do).  The second pass is 20 us of it, and does not
+// show without outliers (16384 blocks, 195 us with it and without).  Sixteen tokens at a time, 32 fp64
+// instructions whatever the list holds, it takes 10 us less there, but more with few tokens and at fewer
+// waves per SIMD: whole calls of 4096 blocks 132 us instead of 121, of 8192 pairs of heads 280 instead of 262.
 //
 // Keys (W as the left operand): lane (token n = l % 16, g = l / 16) gets rows r = 4 g + i of its token, eight
 // b2 each, i.e. whole words of the key layout, which it stores as they are.  Values (operands
@@ -2276,10 +2278,12 @@ static int waves_per_block(int groups, int want_waves) {
 // registers would let onto a SIMD: four are best where they take the whole launch at once (groups <=
 // 4096: 2048 pairs of 64-channel heads, whole call, 138 us with four, 146 with three; 8192 blocks 120 / 132),
 // beyond that their rows push each other out of the caches (projection alone, four / three / two waves
-// per SIMD: 16384 blocks 195 / 187 / 208 us, 8192 pairs 141 / 134 / 130).
+// per SIMD: 16384 blocks 195 / 187 / 208 us, 8192 pairs 141 / 134 / 130).  Pairs are held to six workgroups
+// per compute unit (whole call, eight / six: 8192 pairs 266 / 262 us in 4 bits, 256 / 252 in 2, 16384 pairs
+// 511 / 502 and 501 / 493; 6000 pairs 186 / 188 and 184 / 181).
 static size_t prompt_projection_pad(int groups, bool pair_heads, int bits) {
   if (groups <= 4096 || bits == 8) return 0;
-  const size_t per_cu = pair_heads ? 8 : 12, used = 128 * (16 * bits + 4) + 1024;
+  const size_t per_cu = pair_heads ? 6 : 12, used = 128 * (16 * bits + 4) + 1024;
   return 160 * 1024 / per_cu - used;
 }
 
