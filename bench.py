@@ -49,7 +49,7 @@ PROFILED_TRAFFIC_BYTES = {
     ("gqa_long", "mfma"): (287280.5 * 1.9999 + 764.0) * 1024,
     ("gqa8_long", "mfma"): (353847.3 * 1.9999 + 256.0) * 1024,
     ("opt_d64_4bit", "mfma"): (71839.5 * 1.9994 + 64.0) * 1024,
-    ("llama7b_4bit_n3", "mfma"): (72855.0 * 1.9994 + 64.0) * 1024,
+    ("llama7b_4bit_n3", "mfma"): (72857.5 * 1.9994 + 64.0) * 1024,
 }
 TRAFFIC_SOURCE = ("profiles/decode_mfma_llama7b_4bit.md, profiles/decode_mfma_other_workloads.md: rocprofv3 --pmc "
                   "FETCH_SIZE (scaled by the read-kernel calibration) + WRITE_SIZE per launch (a constant of the "
