@@ -1273,6 +1273,242 @@ struct FastProject {
   }
 };
 
+// Gram matrix of a block's sixteen rows b1 (1024 columns (t, b2) each at 128 tokens), NWV waves, wave wv
+// taking every NWV-th group of four tokens: lane (b1 = l % 16, k = l / 16) loads the 8 b2 of token k of a group
+// as one 16-byte piece; 16 lanes cover a 256-byte row.
+//
+// The sums are exact integers: an fp16 value is a multiple of 2^-24, and x * 2^24 = 254 * 2^24 * d4 + v with v a
+// 32-bit integer, |v| <= 127.5 * 2^24.  v is cut into four signed digits d0..d3 of eight bits; d4 is zero
+// unless |x| >= 127.5, which a step of eight tokens asks of all its elements at once (one step in ten on prompts
+// with outlier channels).  A digit of the lane's sixteen elements is one operand of the int8 matrix cores; of the
+// sixteen products of digits ten are formed (the others are their transposes), those of one weight in
+// one accumulator (at most 2^29).  Low and high half of the result are joined as exact doubles and rounded
+// once, so G does not depend on the number of waves or the order of the sums (a sum of squares beyond 2^30
+// has more bits than the high half holds and takes up to three roundings more).  A block that holds values
+// beyond kMostDigits (infinities and NaN among them) takes the fp64 matrix instructions below.
+// Bound by vector instructions: six and a half an element, and 160 matrix instructions of 16 cycles a block, where
+// the fp64 matrix cores take two an element and 256 of 64 cycles (and round their sums).
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+constexpr float kPlainMost = 127.4375f;   // the largest fp16 value below 127.5
+constexpr float kMostDigits = 32256.f;
+
+// The sums of products of digits: p[w]: digits i < j <= 3, total weight w + 1; e[i]: digit i with itself; f[i]: d4
+// with digit i.
+struct GramSums {
+  i32x4 p[5], e[5], f[4];
+  f16x2 most;   // the largest |x| so far, of even and odd elements
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int i = 0; i < 5; ++i) p[i] = e[i] = i32x4{0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) f[i] = i32x4{0, 0, 0, 0};
+    most = f16x2{(_Float16)0.f, (_Float16)0.f};
+  }
+  // four 32-bit integers -> their digits, a word of four elements each
+  static __device__ __forceinline__ void cut(const int (&v)[4], int& q0, int& q1, int& q2, int& q3) {
+    constexpr uint32_t kBias = 0x00808080u;   // every lower byte of v + kBias is a digit + 128, the top one a digit
+    const uint32_t a = (uint32_t)v[0] + kBias, b = (uint32_t)v[1] + kBias, c = (uint32_t)v[2] + kBias, d = (uint32_t)v[3] + kBias;
+    const uint32_t ab_lo = __builtin_amdgcn_perm(b, a, 0x05010400u), cd_lo = __builtin_amdgcn_perm(d, c, 0x05010400u);
+    const uint32_t ab_hi = __builtin_amdgcn_perm(b, a, 0x07030602u), cd_hi = __builtin_amdgcn_perm(d, c, 0x07030602u);
+    q0 = (int)(__builtin_amdgcn_perm(cd_lo, ab_lo, 0x05040100u) ^ 0x80808080u);
+    q1 = (int)(__builtin_amdgcn_perm(cd_lo, ab_lo, 0x07060302u) ^ 0x80808080u);
+    q2 = (int)(__builtin_amdgcn_perm(cd_hi, ab_hi, 0x05040100u) ^ 0x80808080u);
+    q3 = (int)__builtin_amdgcn_perm(cd_hi, ab_hi, 0x07060302u);
+  }
+  // eight tokens: the lane's row's eight b2 of two of them
+  __device__ __forceinline__ void add(const u32x4& v0, const u32x4& v1) {
+    const u32x4 x[2] = {v0, v1};
+    f16x2 m = {(_Float16)0.f, (_Float16)0.f};
+#pragma unroll
+    for (int i = 0; i < 8; ++i)   // largest of m, x, -x; a NaN stays
+      asm("v_pk_maximum3_f16 %0, %0, %1, %1 neg_lo:[0,0,1] neg_hi:[0,0,1]" : "+v"(m) : "v"(x[i >> 2][i & 3]));
+    asm("v_pk_maximum3_f16 %0, %0, %1, %1" : "+v"(most) : "v"(m));
+    i32x4 q[4];   // digit i of the lane's sixteen elements
+    const bool plain = (float)m.x <= kPlainMost && (float)m.y <= kPlainMost;
+    if (__all(plain)) {
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        int v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          v[i] = (int)fmaf((float)__builtin_bit_cast(f16x2, (uint32_t)x[w >> 1][2 * (w & 1) + (i >> 1)])[i & 1], 0x1p24f, 0.f);
+        int d0, d1, d2, d3;
+        cut(v, d0, d1, d2, d3);
+        q[0][w] = d0; q[1][w] = d1; q[2][w] = d2; q[3][w] = d3;
+      }
+    } else {
+      i32x4 q4;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        int v[4], top[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float h = (float)__builtin_bit_cast(f16x2, (uint32_t)x[w >> 1][2 * (w & 1) + (i >> 1)])[i & 1];
+          const float t = __builtin_rintf(h * (1.f / 254.f));   // 0 up to 127, |h - 254 t| <= 127.1 beyond
+          const float big = fabsf(h) > kPlainMost ? t : 0.f;
+          v[i] = (int)(fmaf(-254.f, big, h) * 0x1p24f);
+          top[i] = (int)big;
+        }
+        int d0, d1, d2, d3;
+        cut(v, d0, d1, d2, d3);
+        q[0][w] = d0; q[1][w] = d1; q[2][w] = d2; q[3][w] = d3;
+        q4[w] = (top[0] & 0xFF) | (top[1] & 0xFF) << 8 | (top[2] & 0xFF) << 16 | top[3] << 24;
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) f[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(q4, q[i], f[i], 0, 0, 0);
+      e[4] = __builtin_amdgcn_mfma_i32_16x16x64_i8(q4, q4, e[4], 0, 0, 0);
+    }
+    p[0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(q[0], q[1], p[0], 0, 0, 0);
+    p[1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(q[0], q[2], p[1], 0, 0, 0);
+    p[2] = __builtin_amdgcn_mfma_i32_16x16x64_i8(q[0], q[3], p[2], 0, 0, 0);
+    p[3] = __builtin_amdgcn_mfma_i32_16x16x64_i8(q[1], q[3], p[3], 0, 0, 0);
+    p[4] = __builtin_amdgcn_mfma_i32_16x16x64_i8(q[2], q[3], p[4], 0, 0, 0);
+    e[0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(q[0], q[0], e[0], 0, 0, 0);
+    e[1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(q[1], q[1], e[1], 0, 0, 0);
+    e[2] = __builtin_amdgcn_mfma_i32_16x16x64_i8(q[2], q[2], e[2], 0, 0, 0);
+    e[3] = __builtin_amdgcn_mfma_i32_16x16x64_i8(q[3], q[3], e[3], 0, 0, 0);
+    p[2] = __builtin_amdgcn_mfma_i32_16x16x64_i8(q[1], q[2], p[2], 0, 0, 0);
+  }
+  __device__ __forceinline__ bool fits() const { return (float)most.x <= kMostDigits && (float)most.y <= kMostDigits; }
+  // Low and high (2^32) half.  Products of a digit with itself count half: the sum with the transpose makes them whole.
+  __device__ __forceinline__ void store(double* lo, double* hi, int ld) const {
+    const int l = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {   // lane (column l % 16) holds rows 4 (l / 16) + i
+      const int at = (4 * (l >> 4) + i) * ld + (l & 15);
+      lo[at] = fma((double)p[2][i], 0x1p24, fma((double)p[1][i], 0x1p16, (double)p[0][i] * 0x1p8)) +
+               fma((double)e[1][i], 0x1p15, (double)e[0][i] * 0.5);
+      const double h = fma((double)p[4][i], 0x1p8, (double)p[3][i]) + fma((double)e[3][i], 0x1p15, (double)e[2][i] * 0.5);
+      // (d4's weight: 254 * 2^24)
+      const double t = fma((double)f[3][i], 0x1p16, fma((double)f[2][i], 0x1p8, (double)f[1][i])) +
+                       fma((double)e[4][i], 127.0 * 0x1p16, (double)f[0][i] * 0x1p-8);
+      hi[at] = fma(t, 254.0, h);
+    }
+  }
+};
+
+// N groups of four tokens from token t0 on, wave wv of NWV taking every NWV-th
+template <int NWV, bool PAIR, int N>
+__device__ __forceinline__ void load_groups(u32x4 (&v)[N], const uint16_t* row, int t0, int nv) {
+  constexpr int d = PAIR ? 64 : 128;
+  const int t1 = t0 + 4 * (threadIdx.x >> 6) + ((threadIdx.x & 63) >> 4);
+  auto piece = [&](int u) __attribute__((always_inline)) {
+    // (a prompt's rows are not read again soon: 14720 blocks 103 us with non-temporal loads, 114 with plain ones)
+    const u32x4* p = reinterpret_cast<const u32x4*>(row + (long)(t1 + 4 * u * NWV) * d);
+    return NWV == 1 ? __builtin_nontemporal_load(p) : *p;
+  };
+  if (t0 + 4 * N * NWV <= nv) {   // (whole pieces without a branch per load)
+#pragma unroll
+    for (int u = 0; u < N; ++u) v[u] = piece(u);
+  } else {
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      v[u] = u32x4{0u, 0u, 0u, 0u};
+      if (t1 + 4 * u * NWV < nv) v[u] = piece(u);
+    }
+  }
+}
+
+// On the fp64 matrix cores: A and B operand of one instruction are the same register (lane (b1, k) holds
+// X[t0 + k][b1*8 + b2] for the 4 tokens of a group and one b2); products of fp16 values are exact, sums round.
+template <int NWV, bool PAIR>
+__device__ __forceinline__ void gram16_fp64(const uint16_t* row, int nv, double* mats, double* out, int ldo) {
+  constexpr int ld = 17, kMat = 16 * ld, GP = 4;
+  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  f64x4 acc[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) acc[i] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+  for (int t0 = 0; t0 < nv; t0 += 4 * GP * NWV) {
+    u32x4 y[GP];
+    load_groups<NWV, PAIR>(y, row, t0, nv);
+#pragma unroll
+    for (int u = 0; u < GP; ++u) {
+      const f16x8 h = __builtin_bit_cast(f16x8, y[u]);
+#pragma unroll
+      for (int b2 = 0; b2 < 8; ++b2) {
+        const double a = (double)(float)h[b2];
+        acc[b2 & 3] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, a, acc[b2 & 3], 0, 0, 0);
+      }
+    }
+  }
+  double* const dst = mats + wv * kMat;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = (l >> 4) + 4 * i, c = l & 15;
+    const double sum = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
+    dst[r * ld + c] = (PAIR && (r >> 3) != (c >> 3)) ? 0.0 : sum;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 4 / NWV; ++k) {
+    const int idx = (int)threadIdx.x + 64 * NWV * k, at = (idx >> 4) * ld + (idx & 15);
+    double sum = mats[at];
+#pragma unroll
+    for (int w = 1; w < NWV; ++w) sum += mats[w * kMat + at];   // fixed order: reproducible
+    out[(idx >> 4) * ldo + (idx & 15)] = sum;
+  }
+}
+
+// mats: 2 * NWV matrices of 16 x 17 doubles in LDS; s_fits: NWV words.  out may be mats (ldo 17).  All waves call it; it
+// ends with a barrier.
+template <int NWV, bool PAIR>
+__device__ __forceinline__ void gram16(const uint16_t* __restrict__ X, int nv, long head_gap, double* mats,
+                                       int* s_fits, double* out, int ldo) {
+  constexpr int ld = 17, kMat = 16 * ld;
+  constexpr int GP = NWV == 1 ? 4 : 8;   // groups requested together
+  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, b1 = l & 15;
+  const uint16_t* const row = PAIR ? X + (b1 >> 3) * head_gap + (b1 & 7) * 8 : X + b1 * 8;
+  GramSums sums;
+  sums.clear();
+  u32x4 x[GP], y[GP];
+  load_groups<NWV, PAIR>(x, row, 0, nv);
+#pragma unroll 1
+  for (int t0 = 4 * GP * NWV;; t0 += 4 * GP * NWV) {
+    const bool more = t0 < nv;
+    if (more) load_groups<NWV, PAIR>(y, row, t0, nv);
+#pragma unroll
+    for (int u = 0; u < GP; u += 2) sums.add(x[u], x[u + 1]);
+    if (!more) break;
+#pragma unroll
+    for (int u = 0; u < GP; ++u) x[u] = y[u];
+  }
+  sums.store(mats + 2 * wv * kMat, mats + (2 * wv + 1) * kMat, ld);
+  bool fits = __all(sums.fits());
+  if (NWV > 1 && l == 0) s_fits[wv] = fits;
+  __syncthreads();
+  if (NWV > 1) {
+#pragma unroll
+    for (int w = 0; w < NWV; ++w) fits &= s_fits[w] != 0;
+  }
+  if (fits) {   // (the same answer in every wave)
+    double val[4 / NWV];
+#pragma unroll
+    for (int k = 0; k < 4 / NWV; ++k) {
+      const int idx = (int)threadIdx.x + 64 * NWV * k, p = idx >> 4, q = idx & 15;
+      double s_lo = 0.0, s_hi = 0.0;
+#pragma unroll
+      for (int w = 0; w < NWV; ++w) {
+        const double* m = mats + 2 * w * kMat;
+        s_lo += m[p * ld + q] + m[q * ld + p];
+        s_hi += m[kMat + p * ld + q] + m[kMat + q * ld + p];
+      }
+      // (no products across the heads of a pair)
+      val[k] = (PAIR && (p >> 3) != (q >> 3)) ? 0.0 : fma(s_hi, 0x1p32, s_lo) * 0x1p-48;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4 / NWV; ++k) {
+      const int idx = (int)threadIdx.x + 64 * NWV * k;
+      out[(idx >> 4) * ldo + (idx & 15)] = val[k];
+    }
+  } else {
+    gram16_fp64<NWV, PAIR>(row, nv, mats, out, ldo);
+  }
+  __syncthreads();
+}
+
 // NWV waves per block: the two contractions are split over the waves by token, the eigen-solver
 // runs in one of them.  The host picks NWV so that the launch has about one wave per SIMD.
 // PAIR: heads of 64 channels with j1 = 8.  The same block (keys or values, same sequence and block
@@ -1307,7 +1543,7 @@ struct FastProject {
 // (T_2 = A V' diag(1/sigma')), and hands the rows of T_2 to the quantizer in the registers it
 // expects them in.  job.keep_large: the fp32 rows of T_2 also go to the workspace.
 template <int NWV, bool PAIR, int QB = 0, bool FULL = false, int PART = 0, bool N3 = false>
-__global__ __launch_bounds__(64 * NWV, PART == 1 ? 5 : PART == 3 ? ((PAIR && QB != 2 && QB != 4) || N3 ? 3 : 4) : 1) void decompose16_kernel(dq_format fmt, dq_cache cache, CompressJob job,
+__global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? ((PAIR && QB != 2 && QB != 4) || N3 ? 3 : 4) : 1) void decompose16_kernel(dq_format fmt, dq_cache cache, CompressJob job,
                                                                float* __restrict__ large_ws,
                                                                int32_t* __restrict__ unit_status,
                                                                int32_t* __restrict__ call_status) {
@@ -1393,7 +1629,7 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 5 : PART == 3 ? ((PAIR && QB 
   static_assert(!LEAN || NWV == 1, "one wave per block");
   static_assert(!N3 || (LEAN && !PAIR && QB != 0), "three tensors: PART 3 with the quantizer, d = 128");
   constexpr int kMat = j1 * ld;                              // doubles per 16 x 16 matrix (padded rows)
-  constexpr int kMatBytes = (2 + NWV - 1) * kMat * (int)sizeof(double);
+  constexpr int kMatBytes = 2 * NWV * kMat * (int)sizeof(double);   // the waves' Gram partials; then G and W
   // fused quantizer: one byte per element of QT token rows, then the value layout's staging
   // (a pair: one such area per head, of 64 channels each)
   constexpr int QT = LEAN ? 32 : kTileTokens;                // rows quantized and packed at a time
@@ -1404,71 +1640,18 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 5 : PART == 3 ? ((PAIR && QB 
   __shared__ __attribute__((aligned(16))) unsigned char pool[kPoolBytes];
   double* const A = reinterpret_cast<double*>(pool);
   double* const W = A + kMat;
-  double* const P = W + kMat;                                // Gram partials of the other waves
   uint8_t* const lds_u = LEAN ? pool : pool + kMatBytes;
   __shared__ double lam[j1], lam2[j1];
   __shared__ uint8_t s_list[FAST ? kTileTokens : 1];          // the tile's tokens that are settled in fp64
 
   double* const gram_ws = reinterpret_cast<double*>(large_ws + (long)unit * g.Tb * d);   // PART: G, then W, of this block
   // ---- Gram matrix G[p][q] = sum_{t, b2} X[t, p*8+b2] X[t, q*8+b2] ----
-  // A and B operand of one MFMA are the same register: lane (b1 = l%16, k = l/16) holds
-  // X[t0 + k][b1*8 + b2] for the 4 tokens of a group and one b2.  A lane loads the 8 b2 of its
-  // (token, b1) as one 16-byte chunk; 16 lanes cover a 256-byte row.  Wave wv takes every NWV-th
-  // group of 4 tokens.
   if constexpr (PART != 3) {
-    const int b1 = l & 15, tk = l >> 4;
-    constexpr int NG = 32 / NWV;   // groups per wave in a chunk of 128 tokens
-    f64x4 acc[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] = f64x4{0.0, 0.0, 0.0, 0.0};
-    constexpr int GC = LEAN ? 8 : NG;   // groups requested together (the same order of products either way)
-    for (int t0 = 0; t0 < nv; t0 += 128) {
-#pragma unroll 1
-      for (int u0 = 0; u0 < NG; u0 += GC) {
-        u32x4 x[GC];
-#pragma unroll
-        for (int u = 0; u < GC; ++u) {
-          const int t = t0 + 4 * ((u0 + u) * NWV + wv) + tk;
-          x[u] = u32x4{0u, 0u, 0u, 0u};
-          if (t < nv)
-            x[u] = *reinterpret_cast<const u32x4*>(PAIR ? X + (b1 >> 3) * head_gap + (long)t * d + (b1 & 7) * 8
-                                                        : X + (long)t * d + b1 * 8);
-        }
-#pragma unroll
-        for (int u = 0; u < GC; ++u) {
-          const f16x8 h = __builtin_bit_cast(f16x8, x[u]);
-#pragma unroll
-          for (int b2 = 0; b2 < 8; ++b2) {
-            const double a = (double)(float)h[b2];
-            acc[b2 & 3] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, a, acc[b2 & 3], 0, 0, 0);
-          }
-        }
-      }
-    }
-    double* dst = wv == 0 ? A : P + (wv - 1) * j1 * ld;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = (l >> 4) + 4 * i, col = l & 15;
-      const double sum = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
-      const double val = (PAIR && (row >> 3) != (col >> 3)) ? 0.0 : sum;   // no products across heads
-      if (PART == 1) gram_ws[row * j1 + col] = val;
-      else dst[row * ld + col] = val;
-    }
+    __shared__ int s_fits[NWV];
+    gram16<NWV, PAIR>(X, nv, head_gap, A, s_fits, PART == 1 ? gram_ws : A, PART == 1 ? j1 : ld);
   }
   if constexpr (PART == 1) return;
   if constexpr (PART == 0) {
-  __syncthreads();
-  if (NWV > 1) {
-    for (int idx = threadIdx.x; idx < j1 * j1; idx += 64 * NWV) {
-      const int e = (idx >> 4) * ld + (idx & 15);
-      double sum = A[e];
-#pragma unroll
-      for (int k = 0; k < NWV - 1; ++k) sum += P[k * j1 * ld + e];   // fixed order: reproducible
-      A[e] = sum;
-    }
-    __syncthreads();
-  }
-
   if (wv == solver) {
     // lane (pair j = l % 8, row group l / 8) holds rows 2 (l / 8) + i of columns j and j + 8
     Jacobi16<2> jac;
