@@ -19,11 +19,35 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kAppendThreads = 256;
 
+// The sequence's lengths move and the plan for the kernels that follow is left; one thread per sequence.
+__device__ __forceinline__ void move_lengths(int b, int tb, int tl, int slen, int c, int block_capacity, int may_compress,
+                                             int32_t* __restrict__ tail_lens, int32_t* __restrict__ seq_lens,
+                                             const AppendArea& area, int32_t* __restrict__ status) {
+  const int take = min(c, tb - tl);
+  int blk = -1, rest = 0, new_tl = tl + take;
+  if (new_tl == tb) {                             // the tail holds a whole block: compress it
+    const int slot = max(slen, 0) / tb;
+    if (!may_compress) {
+      atomicOr(status + 3, 2);                    // the caller said no tail would fill: it stays full, further rows are dropped
+    } else if (slot < block_capacity) {
+      blk = slot;
+      seq_lens[b] = (slot + 1) * tb;
+      rest = c - take;
+      new_tl = rest;                              // what is left of this call's rows restarts the tail
+    } else {
+      atomicOr(status + 3, 1);                    // no free slot: the tail stays full, further rows are dropped
+    }
+  }
+  area.blk_idx[b] = blk;
+  area.take[b] = take;
+  area.rest[b] = rest;
+  tail_lens[b] = new_tl;
+}
+
 // One workgroup per (sequence, kv head, chunk of rows): copies its rows behind the tail's current
-// end.  The last workgroup of a sequence to finish (a ticket per sequence) then moves the
-// sequence's lengths and leaves the plan for the kernels that follow.  All workgroups of a sequence
-// read its old tail length before they take their ticket, and only the holder of the last ticket
-// writes the new one.
+// end.  The last workgroup of a sequence (a ticket per sequence) then moves the sequence's lengths and
+// leaves the plan.  All workgroups of a sequence read its old tail length before they take their ticket, and
+// only the holder of the last ticket writes the new one.
 template <int D>
 __global__ __launch_bounds__(kAppendThreads) void append_rows_kernel(
     dq_format fmt, int batch, int kv_heads, int block_capacity, uint16_t* __restrict__ k_tail,
@@ -52,24 +76,43 @@ __global__ __launch_bounds__(kAppendThreads) void append_rows_kernel(
   const int ticket = __hip_atomic_fetch_add(area.tickets + b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (ticket != kv_heads * chunks - 1) return;
   __hip_atomic_store(area.tickets + b, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // clean for the next call
-  int blk = -1, rest = 0, new_tl = tl + take;
-  if (new_tl == tb) {                             // the tail holds a whole block: compress it
-    const int slot = max(seq_lens[b], 0) / tb;
-    if (!may_compress) {
-      atomicOr(status + 3, 2);                    // the caller said no tail would fill: it stays full, further rows are dropped
-    } else if (slot < block_capacity) {
-      blk = slot;
-      seq_lens[b] = (slot + 1) * tb;
-      rest = c - take;
-      new_tl = rest;                              // what is left of this call's rows restarts the tail
-    } else {
-      atomicOr(status + 3, 1);                    // no free slot: the tail stays full, further rows are dropped
-    }
+  move_lengths(b, tb, tl, seq_lens[b], c, block_capacity, may_compress, tail_lens, seq_lens, area, status);
+}
+
+// A few rows (a generated token): one workgroup per sequence copies the rows of all its heads and moves its
+// lengths, no ticket.  Bound by latency: the rows are requested together with the lengths, so the chain is
+// arguments, one round trip, stores.  16 sequences of 8 heads, one row: 3.3 us, 4.4 with a workgroup per head and the ticket.
+constexpr int kFewPieces = 8;   // 16-byte pieces of keys and of values a thread copies at most
+template <int D>
+__global__ __launch_bounds__(kAppendThreads) void append_few_kernel(
+    dq_format fmt, int kv_heads, int block_capacity, uint16_t* __restrict__ k_tail,
+    uint16_t* __restrict__ v_tail, int32_t* __restrict__ tail_lens, int32_t* __restrict__ seq_lens,
+    const uint16_t* __restrict__ k_rows, const uint16_t* __restrict__ v_rows, int n_rows,
+    const int32_t* __restrict__ counts, AppendArea area, int32_t* __restrict__ status, int may_compress) {
+  constexpr int LPR = D / 8;
+  const int b = blockIdx.x, tb = fmt.block_tokens, rows = kv_heads * n_rows;
+  const int tl_raw = tail_lens[b], slen = seq_lens[b], c_raw = counts ? counts[b] : n_rows;
+  u32x4 k[kFewPieces], v[kFewPieces];
+#pragma unroll
+  for (int i = 0; i < kFewPieces; ++i) {
+    const int piece = i * kAppendThreads + (int)threadIdx.x;
+    if (piece >= rows * LPR) break;
+    const long src = (long)b * rows * D + 8l * piece;
+    k[i] = *reinterpret_cast<const u32x4*>(k_rows + src);
+    v[i] = *reinterpret_cast<const u32x4*>(v_rows + src);
   }
-  area.blk_idx[b] = blk;
-  area.take[b] = take;
-  area.rest[b] = rest;
-  tail_lens[b] = new_tl;
+  const int tl = min(max(tl_raw, 0), tb), c = min(max(c_raw, 0), n_rows), take = min(c, tb - tl);
+#pragma unroll
+  for (int i = 0; i < kFewPieces; ++i) {
+    const int piece = i * kAppendThreads + (int)threadIdx.x, row = piece / LPR, h = row / n_rows, r = row % n_rows;
+    if (piece >= rows * LPR) break;
+    if (r >= take) continue;
+    const long dst = (((long)b * kv_heads + h) * tb + tl + r) * D + 8 * (piece % LPR);
+    *reinterpret_cast<u32x4*>(k_tail + dst) = k[i];
+    *reinterpret_cast<u32x4*>(v_tail + dst) = v[i];
+  }
+  __syncthreads();   // every thread has read the old lengths
+  if (threadIdx.x == 0) move_lengths(b, tb, tl, slen, c, block_capacity, may_compress, tail_lens, seq_lens, area, status);
 }
 
 // After the compression: the rows of this call that did not fit before the tail was compressed go
@@ -128,14 +171,26 @@ extern "C" int32_t dq_cache_append(const dq_format* fmt, dq_cache* cache, const 
   const int rpb = kAppendThreads / (fmt->head_dim / 8);
   const int chunks = (n_rows + rpb - 1) / rpb;
   const dim3 grid((unsigned)(B * H * chunks));
-  if (fmt->head_dim == 128)
+  const int may_compress = (flags & DQ_APPEND_NO_COMPRESS) ? 0 : 1;
+  // A sequence's rows in one workgroup as long as a thread's share of them fits its registers: 8 pieces each of keys
+  // and values, i.e. one row of up to 128 heads of 128 channels.
+  if ((long)H * n_rows * (fmt->head_dim / 8) <= kFewPieces * kAppendThreads) {
+    if (fmt->head_dim == 128)
+      hipLaunchKernelGGL(append_few_kernel<128>, dim3(B), dim3(kAppendThreads), 0, st, *fmt, H, cache->block_capacity,
+                         state->k_tail, state->v_tail, state->tail_lens, state->seq_lens, k_rows, v_rows, n_rows,
+                         counts, area, status, may_compress);
+    else
+      hipLaunchKernelGGL(append_few_kernel<64>, dim3(B), dim3(kAppendThreads), 0, st, *fmt, H, cache->block_capacity,
+                         state->k_tail, state->v_tail, state->tail_lens, state->seq_lens, k_rows, v_rows, n_rows,
+                         counts, area, status, may_compress);
+  } else if (fmt->head_dim == 128)
     hipLaunchKernelGGL(append_rows_kernel<128>, grid, dim3(kAppendThreads), 0, st, *fmt, B, H, cache->block_capacity,
                        state->k_tail, state->v_tail, state->tail_lens, state->seq_lens, k_rows, v_rows, n_rows,
-                       counts, area, status, chunks, (flags & DQ_APPEND_NO_COMPRESS) ? 0 : 1);
+                       counts, area, status, chunks, may_compress);
   else
     hipLaunchKernelGGL(append_rows_kernel<64>, grid, dim3(kAppendThreads), 0, st, *fmt, B, H, cache->block_capacity,
                        state->k_tail, state->v_tail, state->tail_lens, state->seq_lens, k_rows, v_rows, n_rows,
-                       counts, area, status, chunks, (flags & DQ_APPEND_NO_COMPRESS) ? 0 : 1);
+                       counts, area, status, chunks, may_compress);
   DQ_HIP_CHECK(hipGetLastError());
   if (flags & DQ_APPEND_NO_COMPRESS) return DQ_OK;
   // every sequence whose tail filled (a slot index in the plan; -1 skips the others) is compressed

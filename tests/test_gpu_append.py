@@ -260,3 +260,46 @@ def test_idle_and_filling_steps_of_any_size(bits, group, d, i3, batch, kvh):
     dq.compress_kv(want, kt, vt, slot, None, dq.compress_workspace(fmt, batch, kvh, DEV), keep_large=False)
     for name in cache.t:
         assert torch.equal(cache.t[name].view(torch.uint8), want.t[name].view(torch.uint8)), name
+
+
+@pytest.mark.parametrize("heads,n,d", [(8, 1, 128), (128, 1, 128), (130, 1, 128), (8, 16, 128), (8, 17, 128), (3, 7, 64),
+                                       (1, 1, 64), (2, 128, 64), (2, 129, 64)])
+def test_rows_and_lengths_on_both_sides_of_the_one_workgroup_limit(heads, n, d):
+    """One workgroup per sequence copies up to 2048 pieces of 16 bytes (heads * n * d / 8), larger calls take a
+    workgroup per head and chunk: tails, lengths and status of either, from empty, ordinary, nearly full and
+    full tails, with and without a free slot, against the policy written out on the host."""
+    tb, nb = 256, 2
+    _say("append: %d heads, %d rows, d=%d" % (heads, n, d))
+    fmt = dq.Format(4, 128 if d == 128 else 64, d, d // 8, 8, tb)
+    tails = [0, 17, tb - n, tb - 1, tb - n // 2 - 1, 200, tb - 1, 3]
+    slens = [0, tb, 0, tb, 2 * tb, 0, 2 * tb, tb]
+    for counts in (None, [n, 0, n, 1, n, max(n - 1, 0), n, n]):
+        b = len(tails)
+        g = torch.Generator(device=DEV).manual_seed(n)
+        make = lambda rows: torch.randn(b, heads, rows, d, device=DEV, generator=g).half()
+        kt, vt, kr, vr = make(tb), make(tb), make(n), make(n)
+        want = {x: t.clone() for x, t in (("k", kt), ("v", vt))}
+        tl, sl = (torch.tensor(x, dtype=torch.int32, device=DEV) for x in (tails, slens))
+        c = None if counts is None else torch.tensor(counts, dtype=torch.int32, device=DEV)
+        cache = dq.alloc_cache(fmt, b, heads, nb, DEV)
+        ws = dq.cache_append_workspace(fmt, b, heads, DEV)
+        dq.cache_append(cache, kt, vt, tl, sl, kr, vr, c, ws)
+        torch.cuda.synchronize()
+        end_t, end_s, full = [], [], False
+        for i in range(b):
+            m = n if counts is None else counts[i]
+            take = min(m, tb - tails[i])
+            rest, t, s = 0, tails[i] + take, slens[i]
+            if t == tb and s // tb < nb:
+                rest, s = m - take, s + tb
+                t = rest
+            elif t == tb:
+                full = True
+            for x, rows in (("k", kr), ("v", vr)):
+                want[x][i, :, tails[i]:tails[i] + take] = rows[i, :, :take]
+                want[x][i, :, :rest] = rows[i, :, take:take + rest]
+            end_t.append(t)
+            end_s.append(s)
+        assert tl.tolist() == end_t and sl.tolist() == end_s
+        assert torch.equal(kt, want["k"]) and torch.equal(vt, want["v"])
+        assert int(ws[12:16].view(torch.int32).item()) == (1 if full else 0)
