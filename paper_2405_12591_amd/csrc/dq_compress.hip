@@ -954,6 +954,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr float kRoundings = 12.f;
 // eps beyond which a block skips the first pass: about half of its tokens would be listed
 constexpr float kHardEps = 0x1p-13f;
+// Where a block's constants lie, in doubles from its Gram matrix on (behind G, W and the eigenvalues): the pieces of W,
+// then floats.
+constexpr int kFastPieces = 2 * 256 + 16, kFastScales = kFastPieces + 3 * 64;
 
 __device__ __forceinline__ float max_xor16(float v) {
   const uint32_t w = __builtin_bit_cast(uint32_t, v);
@@ -966,15 +969,26 @@ __device__ __forceinline__ float max_xor32(float v) {
   return fmaxf(__builtin_bit_cast(float, (uint32_t)x[0]), __builtin_bit_cast(float, (uint32_t)x[1]));
 }
 
+// Between steps of NWV waves that share LDS; NWV = 1: of one wave on its own, whose LDS operations execute in order.
+template <int NWV>
+__device__ __forceinline__ void team_barrier() {
+  if (NWV > 1) {
+    __syncthreads();
+  } else {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
 template <int QB, bool FULL, bool PAIR>
 struct FastProject {
   static constexpr int QMAX = (1 << (QB - 1)) - 1, QMIN = FULL ? -QMAX - 1 : -QMAX, BIAS = 1 << (QB - 1);
   static constexpr float kMagic = 12582912.f + (float)BIAS;   // 1.5 * 2^23: the code + BIAS sits in the low bits of q + kMagic
   static constexpr uint32_t kMagicBits = 0x4B400000u;
   static constexpr int ROWB = 16 * QB, STRIDE = ROWB + 4;     // bytes of a value row of a tile, and of its place in LDS
-  static constexpr int kStageBytes = 128 * STRIDE;
+  static constexpr int kStageBytes = 128 * STRIDE, kRowBytes = 16 * 256;
 
-  f16x4 w0, w1, w2;  // row r = l % 16 of W, columns b1 = 4 (l / 16) + j, scaled by 2^(15 - e): three pieces
+  f16x4 w0, w1, w2;  // row r = l % 16 of W, columns b1 = 4 j + l / 16, scaled by 2^(15 - e): three pieces
   float sc;          // 2^(e - 15) of row l % 16
   float sck[4];      // ... of rows 4 (l / 16) + i
   float eps, eps_abs;   // the error bound (see above)
@@ -989,22 +1003,32 @@ struct FastProject {
   __device__ __forceinline__ const uint16_t* piece(int t, int b1) const {
     return PAIR ? X + (b1 >> 3) * head_gap + (long)t * 64 + (b1 & 7) * 8 : X + (long)t * 128 + b1 * 8;
   }
-  __device__ __forceinline__ void load(u32x4 (&x)[4], int t) const {   // b1 = 4 (l / 16) + j
-    const int g = (threadIdx.x & 63) >> 4;
+  // Sixteen tokens' rows, as they lie in memory: lane l gets piece b1 = l % 16 of token t0 + 4 u + l / 16 (past the last row:
+  // that row again; the caller clears it).  What bounds a prompt's projection is memory: without its quantizer it
+  // takes the same time.  Requested in the matrix cores' order, lanes 256 bytes apart, the rows took four times the
+  // accesses to the first-level cache, and each of its lines was asked for four times; in memory order no line is,
+  // so that they can pass the caches by.  14720 blocks, steady clocks: 179 us in the other order (215 non-temporal),
+  // 172 so, 148 non-temporal; two groups ahead instead of one 161.
+  __device__ __forceinline__ void load(u32x4 (&x)[4], int t0) const {
+    const int l = threadIdx.x & 63;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      x[j] = u32x4{0u, 0u, 0u, 0u};
-      if (t < nv) x[j] = *reinterpret_cast<const u32x4*>(piece(t, 4 * g + j));
+    for (int u = 0; u < 4; ++u) {
+      const int t = t0 + 4 * u + (l >> 4);
+      x[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(piece(min(t, nv - 1), l & 15)));
     }
   }
-
-  static __device__ __forceinline__ float sum16(float v) {   // over the sixteen lanes of a row (a pair: its half)
-    v += lane_exchange<0xB1>(v);
-    v += lane_exchange<0x4E>(v);
-    v += lane_exchange<0x141>(v);
-    if (!PAIR) v += lane_exchange<0x140>(v);
-    return v;
+  // ... and through LDS (kRowBytes) into the matrix cores' order: lane (n = l % 16, g = l / 16) gets pieces b1 = 4 j + g
+  // of token n.  Piece b1 of token n lies at place b1 ^ n of its row, so that neither side meets a bank twice.
+  static __device__ __forceinline__ void turn(u32x4 (&x)[4], uint8_t* rows) {
+    const int l = threadIdx.x & 63, n = l & 15, g = l >> 4;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) *reinterpret_cast<u32x4*>(rows + (4 * u + g) * 256 + ((n ^ (4 * u + g)) * 16)) = x[u];
+    team_barrier<1>();
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x[j] = *reinterpret_cast<const u32x4*>(rows + n * 256 + (((4 * j + g) ^ n) * 16));
+    team_barrier<1>();
   }
+
   static __device__ __forceinline__ float max8(float v) {      // over eight lanes
     v = fmaxf(v, lane_exchange<0xB1>(v));
     v = fmaxf(v, lane_exchange<0x4E>(v));
@@ -1012,75 +1036,22 @@ struct FastProject {
     return v;
   }
 
-  // lam2: the eigenvalues in the order of W's rows (0: dropped)
-  __device__ __forceinline__ void setup(const double* W_, const double* lam2) {
-    W = W_;
+  // (what store_fast_factors left)
+  __device__ __forceinline__ void setup(const double* G) {
+    W = G + 256;
+    const uint16_t* const pieces = reinterpret_cast<const uint16_t*>(G + kFastPieces);
+    const float* const scales = reinterpret_cast<const float*>(G + kFastScales);
     const int l = threadIdx.x & 63, r = l & 15, g = l >> 4;
-    double w[4], wm = 0.0;
-    float ab[4], left[4], s[4];
-    const float lam = (float)lam2[r];
+    w0 = *reinterpret_cast<const f16x4*>(pieces + (g * 16 + r) * 4);
+    w1 = *reinterpret_cast<const f16x4*>(pieces + 256 + (g * 16 + r) * 4);
+    w2 = *reinterpret_cast<const f16x4*>(pieces + 512 + (g * 16 + r) * 4);
+    sc = scales[r];
+    const f32x4 s4 = *reinterpret_cast<const f32x4*>(scales + 4 * g);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      w[j] = W[r * 16 + 4 * g + j];
-      wm = fmax(wm, fabs(w[j]));
-      ab[j] = fabsf((float)w[j]);
-      s[j] = ab[j] * lam;                       // |T_S[b1][r]|
-    }
-    wm = fmax(wm, __shfl_xor(wm, 16));
-    wm = fmax(wm, __shfl_xor(wm, 32));
-    const int e = wm > 0.0 ? __builtin_amdgcn_frexp_exp(wm) : 0;   // |w| < 2^e
-    sc = __builtin_amdgcn_ldexpf(1.f, e - 15);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const double ws = __builtin_amdgcn_ldexp(w[j], 15 - e);
-      const _Float16 h0 = (_Float16)(float)ws;
-      const double r1 = ws - (double)(float)h0;
-      const _Float16 h1 = (_Float16)(float)r1;
-      const double r2 = r1 - (double)(float)h1;
-      const _Float16 h2 = (_Float16)(float)r2;
-      w0[j] = h0;
-      w1[j] = h1;
-      w2[j] = h2;
-      // (a subnormal piece counts with exponent -14 as well: the addend)
-      left[j] = (fabsf((float)(r2 - (double)(float)h2)) + 0x1p-35f) * sc;
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) sck[i] = __shfl(sc, 4 * g + i);
-    float c = 0.f, rest = 0.f, one = 0.f, two = 0.f;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      // (a pair: W is block-diagonal, so the rows of the b1's own head, which the half may not be, hold it all)
-      float v = sum16(s[j]);
-      if (PAIR) v = fmaxf(v, lane_exchange<0x140>(v));
-      c = fmaf(ab[j], v, c);
-      rest = fmaf(left[j], v, rest);
-      one += ab[j];
-      two = fmaf(ab[j], ab[j], two);
-    }
-#pragma unroll
-    for (int o = 16; o <= 32; o <<= 1) {
-      c += __shfl_xor(c, o);
-      rest += __shfl_xor(rest, o);
-      one += __shfl_xor(one, o);
-      two += __shfl_xor(two, o);
-    }
-    const float total = sum16(lam);
-    float most = max8(lam);
-    float least = -max8(-lam);
-    if (!PAIR) {
-      most = fmaxf(most, lane_exchange<0x140>(most));
-      least = fminf(least, lane_exchange<0x140>(least));
-    }
-    c = fminf(c, __builtin_sqrtf(two) * __builtin_sqrtf(total));
-    const float d = least > 0.f ? 0.f : 4.1e-6f * __builtin_sqrtf(most);
-    // (2 % for the rounding of these sums themselves)
-    float rel = 1.02f * (0x1p-24f * (kRoundings * c + 4.f) + rest), abs = 1.02f * (0x1p-24f * kRoundings * one * d + sc * 0x1p-19f);
-    // all of the block's rows; NaN (a block that holds one) must not get lost
-    hard = __any(!(rel + 32.f * abs <= kHardEps));
-    rel = max8(rel);
-    abs = max8(abs);
-    eps = fmaxf(rel, lane_exchange<0x140>(rel));
-    eps_abs = fmaxf(abs, lane_exchange<0x140>(abs));
+    for (int i = 0; i < 4; ++i) sck[i] = s4[i];
+    eps = scales[16];
+    eps_abs = scales[17];
+    hard = scales[18] != 0.f;
   }
 
   __device__ __forceinline__ static uint16_t step_bits(float up, float dn) {
@@ -1171,8 +1142,16 @@ struct FastProject {
       }
     }
     const float err = fmaf(eps, my_all, eps_abs);
-    sbits = step_bits(my_up + err, my_dn + err);
-    const bool doubt = sbits != step_bits(fmaxf(my_up - err, 0.f), fmaxf(my_dn - err, 0.f));
+    // The step of the exact sums lies between those of the ends of the interval: the quotients' own rounding widens
+    // it by 2^-22 (an exact division costs twenty instructions); a tie or a step that depends on it is in doubt.
+    constexpr float kDown = QMAX == 1 ? 1.f : (1.f - 0x1p-22f) / QMAX, kUp = QMAX == 1 ? 1.f : (1.f + 0x1p-22f) / QMAX;
+    float hi = (my_up + err) * kUp, lo = (my_up - err) * kDown;
+    if (FULL) {
+      hi = fmaxf(hi, (my_dn + err) * (1.f / (QMAX + 1)));
+      lo = fmaxf(lo, (my_dn - err) * (1.f / (QMAX + 1)));
+    }
+    sbits = f2h_rne(hi);
+    const bool doubt = sbits != f2h_rne(fmaxf(lo, 0.f));
     const float my_step = h2f(sbits);
     const float my_inv = my_step > 0.f ? __builtin_amdgcn_rcpf(my_step) : 0.f;
     // a quotient this far from a half-integer is on the right side of it: the bound above, the
@@ -1509,6 +1488,15 @@ __device__ __forceinline__ void gram16(const uint16_t* __restrict__ X, int nv, l
   __syncthreads();
 }
 
+// The unit of workgroup wg of n, in launches of many workgroups: they go round-robin to the eight XCDs and, in each, to
+// its four shader engines, whatever these have left to do, so workgroup wg runs on engine wg % 32.  Keys and values
+// (units 2 i and 2 i + 1), which take 25 and 32 us a wave, and the blocks past a sequence's end would each fall to the
+// same few engines; a group of 32 units is dealt five places further on than the one before it.
+// 14720 of 16384 blocks valid: Gram matrices 99 us, 103 in plain order.
+__device__ __forceinline__ int dealt_unit(int wg, int n) {
+  return wg < (n & ~31) ? (wg & ~31) | ((wg + 5 * (wg >> 5)) & 31) : wg;
+}
+
 // NWV waves per block: the two contractions are split over the waves by token, the eigen-solver
 // runs in one of them.  The host picks NWV so that the launch has about one wave per SIMD.
 // PAIR: heads of 64 channels with j1 = 8.  The same block (keys or values, same sequence and block
@@ -1543,7 +1531,7 @@ __device__ __forceinline__ void gram16(const uint16_t* __restrict__ X, int nv, l
 // (T_2 = A V' diag(1/sigma')), and hands the rows of T_2 to the quantizer in the registers it
 // expects them in.  job.keep_large: the fp32 rows of T_2 also go to the workspace.
 template <int NWV, bool PAIR, int QB = 0, bool FULL = false, int PART = 0, bool N3 = false>
-__global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? ((PAIR && QB != 2 && QB != 4) || N3 ? 3 : 4) : 1) void decompose16_kernel(dq_format fmt, dq_cache cache, CompressJob job,
+__global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? (PAIR || N3 || QB == 4 ? 3 : 4) : 1) void decompose16_kernel(dq_format fmt, dq_cache cache, CompressJob job,
                                                                float* __restrict__ large_ws,
                                                                int32_t* __restrict__ unit_status,
                                                                int32_t* __restrict__ call_status) {
@@ -1587,12 +1575,13 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? ((PAIR && QB 
   }
   const Geometry g = make_geometry(fmt, cache.kv_heads, cache.block_capacity);
   // the work unit (of the pair's first head); the second head's unit lies `unit_gap` further on
-  int unit = blockIdx.x;
+  const int wg = PART != 0 ? dealt_unit(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  int unit = wg;
   const int unit_gap = 2 * job.n_blocks;
   if (PAIR) {
-    const int pb = blockIdx.x >> 1, j = pb % job.n_blocks, hp = pb / job.n_blocks;   // hp = b * (H/2) + head pair
+    const int pb = wg >> 1, j = pb % job.n_blocks, hp = pb / job.n_blocks;   // hp = b * (H/2) + head pair
     const int half_h = g.H >> 1;
-    unit = (((hp / half_h) * g.H + 2 * (hp % half_h)) * job.n_blocks + j) * 2 + (blockIdx.x & 1);
+    unit = (((hp / half_h) * g.H + 2 * (hp % half_h)) * job.n_blocks + j) * 2 + (wg & 1);
   }
   const UnitRef ur = unit_ref(g, job, unit);
   const int which = ur.which, slot = ur.slot, nv = ur.nv;
@@ -1634,7 +1623,7 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? ((PAIR && QB 
   // (a pair: one such area per head, of 64 channels each)
   constexpr int QT = LEAN ? 32 : kTileTokens;                // rows quantized and packed at a time
   constexpr int kHeadArea = QT * d + d * (pack_parts(QB ? QB : 8, QT) * QT * (QB ? QB : 8) / 32 + 1) * 4;
-  constexpr int kFieldBytes = FAST ? FastProject<QB == 2 ? 2 : 4, FULL, PAIR>::kStageBytes : QB ? (PAIR ? 2 : 1) * kHeadArea : 16;
+  constexpr int kFieldBytes = FAST ? FastProject<QB == 2 ? 2 : 4, FULL, PAIR>::kStageBytes + FastProject<QB == 2 ? 2 : 4, FULL, PAIR>::kRowBytes : QB ? (PAIR ? 2 : 1) * kHeadArea : 16;
   // (the three launches: no matrices in LDS, but the second cut's)
   constexpr int kPoolBytes = LEAN ? (kMatBytes > kFieldBytes ? kMatBytes : kFieldBytes) : kMatBytes + kFieldBytes;
   __shared__ __attribute__((aligned(16))) unsigned char pool[kPoolBytes];
@@ -1707,7 +1696,7 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? ((PAIR && QB 
     typedef FastProject<QB, FULL, PAIR> FP;
     FP fp;
     fp.X = X; fp.nv = nv; fp.head_gap = head_gap; fp.one_group = !PAIR && g.groups == 1;
-    fp.setup(gram_ws + j1 * j1, gram_ws + 2 * j1 * j1);
+    fp.setup(gram_ws);
     const int n = l & 15, q4 = l >> 4;
     const long blk = bh * g.NB + slot;
     uint8_t* const codes = (which ? cache.v_codes : cache.k_codes) + blk * g.codes_per_block;
@@ -1718,7 +1707,7 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? ((PAIR && QB 
     auto store_key = [&](int t, const uint32_t (&part)[4], uint16_t sb) __attribute__((always_inline)) {
       uint8_t* const dst = codes + (PAIR ? (q4 >> 1) * codes_gap + (long)t * (8 * QB) + (q4 & 1) * (4 * QB)
                                          : (long)t * (16 * QB) + q4 * (4 * QB));
-      if (QB == 4) *reinterpret_cast<u32x4*>(dst) = u32x4{part[0], part[1], part[2], part[3]};
+      if (QB == 4) __builtin_nontemporal_store(u32x4{part[0], part[1], part[2], part[3]}, reinterpret_cast<u32x4*>(dst));
       else *reinterpret_cast<u32x2*>(dst) = u32x2{part[0] | (part[1] << 16), part[2] | (part[3] << 16)};
       if (PAIR) {
         if (!(q4 & 1)) scales[(q4 >> 1) * scales_gap + t] = sb;
@@ -1739,22 +1728,28 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? ((PAIR && QB 
           if (l < 16 && ((tokens >> l) & 1u)) s_list[listed + __builtin_popcount(tokens & ((1u << l) - 1u))] = (uint8_t)(t0 + l);
           listed += __builtin_popcount(tokens);
         };
-        u32x4 x[4];
-        fp.load(x, tile + n);
+        u32x4 next[4];
+        fp.load(next, tile);
 #pragma unroll 1
         for (int t0 = 0; t0 < kTileTokens; t0 += 16) {
+          u32x4 x[4] = {next[0], next[1], next[2], next[3]};
+          if (tile + t0 + 16 > nv) {   // (rows that are not there are zero)
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              if (tile + t0 + 4 * u + q4 >= nv) x[u] = u32x4{0u, 0u, 0u, 0u};
+          }
+          FP::turn(x, stage + FP::kStageBytes);
+          fp.load(next, tile + t0 + 16);   // (past the tile's end: read and dropped; past the rows: nothing is read)
           f32x4 acc[8];
           uint16_t sb;
           if (!which) {
             fp.template project<false>(x, acc);
-            fp.load(x, tile + t0 + 16 + n);   // (past the tile's end: read and dropped; past the rows: nothing is read)
             uint32_t part[4];
             const uint32_t doubt = fp.template quantize<false>(acc, sb, part);
             list(doubt, t0);
             if (!((doubt >> n) & 1u)) store_key(tile + t0 + n, part, sb);
           } else {
             fp.template project<true>(x, acc);
-            fp.load(x, tile + t0 + 16 + n);
             uint32_t part[8];
             const uint32_t doubt = fp.template quantize<true>(acc, sb, part);
             list(doubt, t0);
@@ -1845,7 +1840,7 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? ((PAIR && QB 
           const u32x4 v = {src[0], src[1], src[2], src[3]};
           uint8_t* const dst = codes + (PAIR ? ((rw >> 3) & 1) * codes_gap + (long)tile * (8 * QB) + ((rw >> 4) * 8 + (rw & 7)) * FP::ROWB + 16 * pc
                                              : (long)tile * (16 * QB) + rw * FP::ROWB + 16 * pc);
-          *reinterpret_cast<u32x4*>(dst) = v;
+          __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(dst));
         }
         __syncthreads();
       }
@@ -2144,13 +2139,138 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? ((PAIR && QB 
   if constexpr (QB != 0 && PART == 0) end_call();
 }
 
+// The constants of FastProject, from the solver's registers (a lane: ROWS of the rows b1 of two columns of W^T, places
+// px and py; their sums cross eight lanes at most, where the projection's wave, one block in 64 lanes, took 850
+// instructions for them, a fifth of its own: 14720 blocks 177 us for the projection, 193 before, and 7 more here): the three fp16 pieces
+// of W scaled by 2^(15 - e), |W[r]| < 2^e, as [piece][b1 % 4][r][b1 / 4]; 2^(e - 15) of every row; eps, eps_abs, hard.
+template <int ROWS, bool PAIR>
+__device__ __forceinline__ void store_fast_factors(const Jacobi16<ROWS>& jac, const double (&wx)[ROWS], const double (&wy)[ROWS],
+                                                   int px, int py, double lx, double ly, bool live, double* G) {
+  static_assert(ROWS % 4 == 0, "a lane's rows are whole pieces");
+  const int lane = threadIdx.x & 63, row0 = jac.first_row(lane);
+  uint16_t* const pieces = reinterpret_cast<uint16_t*>(G + kFastPieces);
+  float* const scales = reinterpret_cast<float*>(G + kFastScales);
+  auto over_rows = [&](float v, auto op) __attribute__((always_inline)) {   // the lanes that hold the column's other rows
+    if (ROWS <= 8) v = op(v, lane_exchange<kDppXor8>(v));
+    if (ROWS <= 4) v = op(v, __shfl_xor(v, 16));
+    return v;
+  };
+  auto over_columns = [&](float v, auto op) __attribute__((always_inline)) {
+    v = op(v, lane_exchange<kDppXor1>(v));
+    v = op(v, lane_exchange<kDppXor2>(v));
+    return op(v, lane_exchange<kDppXor7>(v));
+  };
+  auto add = [](float a, float b) { return a + b; };
+  auto most = [](float a, float b) { return fmaxf(a, b); };
+  const float lam[2] = {(float)lx, (float)ly};
+  // s[b1] = sum_r |T_S[b1][r]|  (a pair: W is block-diagonal, the other head's columns add nothing)
+  float s[ROWS];
+#pragma unroll
+  for (int i = 0; i < ROWS; ++i)
+    s[i] = over_columns(fabsf((float)wx[i]) * lam[0] + fabsf((float)wy[i]) * lam[1], add);
+  // sum, largest and least eigenvalue (a pair: of the column's own head)
+  float total[2], top[2], least[2];
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const int head = (c ? py : px) >> 3;
+    const bool sx = !PAIR || (px >> 3) == head, sy = !PAIR || (py >> 3) == head;
+    if (PAIR) {
+      // both heads' figures in every lane, then the column's own
+      float t[2], m[2], n[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const bool hx = (px >> 3) == h, hy = (py >> 3) == h;
+        t[h] = over_columns((hx ? lam[0] : 0.f) + (hy ? lam[1] : 0.f), add);
+        m[h] = over_columns(fmaxf(hx ? lam[0] : 0.f, hy ? lam[1] : 0.f), most);
+        n[h] = over_columns(fmaxf(hx ? -lam[0] : -INFINITY, hy ? -lam[1] : -INFINITY), most);
+      }
+      total[c] = head ? t[1] : t[0];
+      top[c] = head ? m[1] : m[0];
+      least[c] = -(head ? n[1] : n[0]);
+    } else {
+      total[c] = over_columns((sx ? lam[0] : 0.f) + (sy ? lam[1] : 0.f), add);
+      top[c] = over_columns(fmaxf(lam[0], lam[1]), most);
+      least[c] = -over_columns(fmaxf(-lam[0], -lam[1]), most);
+    }
+  }
+  float rel = 0.f, abs = 0.f;
+  bool soft = true;
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const int r = c ? py : px;
+    float wm = 0.f, one = 0.f, two = 0.f, cs = 0.f;
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+      const float ab = fabsf((float)(c ? wy[i] : wx[i]));
+      wm = fmaxf(wm, ab);
+      one += ab;
+      two = fmaf(ab, ab, two);
+      cs = fmaf(ab, s[i], cs);
+    }
+    wm = over_rows(wm, most);
+    // |w| < 2^e (the rounding of wm to fp32 may only raise it); the smallest scale keeps 2^(15 - e) a float
+    const int e = wm > 0.f ? max(__builtin_amdgcn_frexp_expf(wm * (1.f + 0x1p-22f)), -100) : 0;
+    const float scale = __builtin_amdgcn_ldexpf(1.f, e - 15);
+    float rest = 0.f;
+    _Float16 h[3][ROWS];
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+      double left = __builtin_amdgcn_ldexp(c ? wy[i] : wx[i], 15 - e);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        float f = (float)left;
+        asm("" : "+v"(f));   // (two conversions: of a double straight to fp16 there is only a long sequence)
+        h[k][i] = (_Float16)f;
+        left -= (double)(float)h[k][i];
+      }
+      // (a subnormal piece counts with exponent -14 as well: the addend)
+      rest = fmaf((fabsf((float)left) + 0x1p-35f) * scale, s[i], rest);
+    }
+    if (live) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        if (ROWS == 16) {
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+            *reinterpret_cast<f16x4*>(pieces + 256 * k + (g * 16 + r) * 4) = f16x4{h[k][g], h[k][(4 + g) % ROWS], h[k][(8 + g) % ROWS], h[k][(12 + g) % ROWS]};
+        } else {
+#pragma unroll
+          for (int i = 0; i < ROWS; ++i)
+            reinterpret_cast<_Float16*>(pieces)[256 * k + ((i & 3) * 16 + r) * 4 + ((row0 + i) >> 2)] = h[k][i];
+        }
+      }
+    }
+    one = over_rows(one, add);
+    two = over_rows(two, add);
+    cs = over_rows(cs, add);
+    rest = over_rows(rest, add);
+    cs = fminf(cs, __builtin_sqrtf(two) * __builtin_sqrtf(total[c]));
+    const float dropped = least[c] > 0.f ? 0.f : 4.1e-6f * __builtin_sqrtf(top[c]);
+    // (2 % for the rounding of these sums themselves)
+    const float re = 1.02f * (0x1p-24f * (kRoundings * cs + 4.f) + rest);
+    const float ae = 1.02f * (0x1p-24f * kRoundings * one * dropped + scale * 0x1p-19f);
+    soft = soft && re + 32.f * ae <= kHardEps;   // all of the block's rows; false for a NaN (a block that holds one)
+    rel = fmaxf(rel, re);
+    abs = fmaxf(abs, ae);
+    if (live && row0 == 0) scales[r] = scale;
+  }
+  rel = over_columns(rel, most);
+  abs = over_columns(abs, most);
+  const float all_soft = -over_columns(soft ? -1.f : 0.f, most);
+  if (live && row0 == 0 && (lane & 7) == 0) {
+    scales[16] = rel;
+    scales[17] = abs;
+    scales[18] = all_soft != 0.f ? 0.f : 1.f;
+  }
+}
+
 // The eigen-solver of a call of thousands of blocks: 64 * ROWS / 128 blocks per wave (eight at ROWS = 16:
 // every rotation is derived once, no sum crosses lanes, nothing touches LDS but the ordering).  Reads the
 // Gram matrices and writes W behind them, the small tensors into the cache, the blocks' status words.
 // Bound by instruction issue: about 145 instructions per round for eight blocks.
 // Workgroups of four waves, so that the waves spread evenly over the SIMDs.
 constexpr int kSolveWaves = 4;
-template <int ROWS, bool PAIR>
+template <int ROWS, bool PAIR, bool FAST>
 __global__ __launch_bounds__(64 * kSolveWaves) void solve16_kernel(dq_format fmt, dq_cache cache, CompressJob job,
                                                      float* __restrict__ large_ws, int32_t* __restrict__ unit_status,
                                                      int n_groups) {
@@ -2196,13 +2316,15 @@ __global__ __launch_bounds__(64 * kSolveWaves) void solve16_kernel(dq_format fmt
     G[2 * j1 * j1 + py] = ly;
   }
   bool sat = false;
+  double wx[ROWS], wy[ROWS];   // columns px and py of W^T
 #pragma unroll
   for (int i = 0; i < ROWS; ++i) {
     const int b1 = row0 + i;
-    const double wx = rx > 0.0 ? jac.x[i] * fx : 0.0, wy = ry > 0.0 ? jac.y[i] * fy : 0.0;
+    wx[i] = rx > 0.0 ? jac.x[i] * fx : 0.0;
+    wy[i] = ry > 0.0 ? jac.y[i] * fy : 0.0;
     if (live) {
-      G[j1 * j1 + px * j1 + b1] = wx;
-      G[j1 * j1 + py * j1 + b1] = wy;
+      G[j1 * j1 + px * j1 + b1] = wx[i];
+      G[j1 * j1 + py * j1 + b1] = wy[i];
     }
     auto put = [&](int r, double ts) __attribute__((always_inline)) {
       if (PAIR) {   // the heads' 8 x 8 tensors one after the other; across heads there is nothing
@@ -2212,9 +2334,10 @@ __global__ __launch_bounds__(64 * kSolveWaves) void solve16_kernel(dq_format fmt
         s_small[blk][ur.which ? b1 * j1 + r : r * j1 + b1] = f64_to_f16_rne(ts, true, &sat);
       }
     };
-    put(px, wx * lx);   // T_S = U Sigma = W Lambda
-    put(py, wy * ly);
+    put(px, wx[i] * lx);   // T_S = U Sigma = W Lambda
+    put(py, wy[i] * ly);
   }
+  if constexpr (FAST) store_fast_factors<ROWS, PAIR>(jac, wx, wy, px, py, lx, ly, live, G);
   __builtin_amdgcn_wave_barrier();
   const unsigned long long sat_lanes = __ballot(sat);
   if (live) {
@@ -2466,8 +2589,8 @@ static int waves_per_block(int groups, int want_waves) {
 // 511 / 502 and 501 / 493; 6000 pairs 186 / 188 and 184 / 181).
 static size_t prompt_projection_pad(int groups, bool pair_heads, int bits) {
   if (groups <= 4096 || bits == 8) return 0;
-  const size_t per_cu = pair_heads ? 6 : 12, used = 128 * (16 * bits + 4) + 1024;
-  return 160 * 1024 / per_cu - used;
+  const size_t per_cu = pair_heads ? 6 : 12, used = 128 * (16 * bits + 4) + 4096 + 1024;
+  return 160 * 1024 / per_cu > used ? 160 * 1024 / per_cu - used : 0;
 }
 
 static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16_t* k_new,
@@ -2518,7 +2641,8 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
   // solver wave need 8192 blocks to put a wave on every SIMD; up to there two blocks per wave are as fast
   // or faster (whole call, two / eight blocks per wave: 1280 blocks 90 / 121 us, 2560 129 / 138, 8192
   // 291 / 292, 16384 545 / 517).
-  auto launch_factor = [&]() {
+  // `fast`: the fp16 projection follows and wants its constants.
+  auto launch_factor = [&](bool fast) {
     const int groups = pair_heads ? units / 2 : units;
     if (pair_heads)
       hipLaunchKernelGGL((decompose16_kernel<1, true, 0, false, 1>), dim3(groups), dim3(64), 0, st, *fmt, *cache, job,
@@ -2526,21 +2650,27 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
     else
       hipLaunchKernelGGL((decompose16_kernel<1, false, 0, false, 1>), dim3(groups), dim3(64), 0, st, *fmt, *cache, job,
                          large_ws, unit_status, (int32_t*)nullptr);
-#define DQ_LAUNCH_SOLVE(R_, P_)                                                                                   \
-  hipLaunchKernelGGL((solve16_kernel<R_, P_>), dim3((groups + kSolveWaves * R_ / 2 - 1) / (kSolveWaves * R_ / 2)),   \
+#define DQ_LAUNCH_SOLVE(R_, P_, F_)                                                                               \
+  hipLaunchKernelGGL((solve16_kernel<R_, P_, F_>), dim3((groups + kSolveWaves * R_ / 2 - 1) / (kSolveWaves * R_ / 2)), \
                      dim3(64 * kSolveWaves), 0, st, *fmt,                                                         \
                      *cache, job, large_ws, unit_status, groups)
+#define DQ_LAUNCH_SOLVE_F(R_, P_)          \
+  do {                                     \
+    if (fast) DQ_LAUNCH_SOLVE(R_, P_, true); \
+    else DQ_LAUNCH_SOLVE(R_, P_, false);   \
+  } while (0)
     if (groups > 8192) {
-      if (pair_heads) DQ_LAUNCH_SOLVE(16, true);
-      else DQ_LAUNCH_SOLVE(16, false);
+      if (pair_heads) DQ_LAUNCH_SOLVE_F(16, true);
+      else DQ_LAUNCH_SOLVE_F(16, false);
     } else {
-      if (pair_heads) DQ_LAUNCH_SOLVE(4, true);
-      else DQ_LAUNCH_SOLVE(4, false);
+      if (pair_heads) DQ_LAUNCH_SOLVE_F(4, true);
+      else DQ_LAUNCH_SOLVE_F(4, false);
     }
+#undef DQ_LAUNCH_SOLVE_F
 #undef DQ_LAUNCH_SOLVE
   };
   if (fused3) {
-    launch_factor();
+    launch_factor(false);
 #define DQ_LAUNCH_FUSED3(B_)                                                                                     \
   do {                                                                                                           \
     if (fmt->levels)                                                                                             \
@@ -2592,7 +2722,7 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
     int fused_waves = waves_per_block(fused_groups, want_waves);
     const size_t pad = prompt_projection_pad(fused_groups, pair_heads, fmt->bits);
     if (fused_waves == 0) {
-      launch_factor();
+      launch_factor(fmt->bits != 8);
       if (fmt->bits == 2) DQ_LAUNCH_FUSED_PART3(2);
       else if (fmt->bits == 4) DQ_LAUNCH_FUSED_PART3(4);
       else DQ_LAUNCH_FUSED_PART3(8);
@@ -2638,7 +2768,7 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
     // 17.7 us against 22.5 with three)
     const int nwv = waves_per_block(groups16, (flags & kCompressMostlyIdle) && groups16 > 1024 ? 2 : want_waves);
     if (nwv == 0) {
-      launch_factor();
+      launch_factor(false);
       if (pair_heads)
         hipLaunchKernelGGL((decompose16_kernel<1, true, 0, false, 3>), dim3(units / 2), dim3(64), 0, st, *fmt, *cache,
                            job, large_ws, unit_status, (int32_t*)nullptr);
