@@ -1048,7 +1048,8 @@ __device__ __forceinline__ void store_factors(Jacobi16<ROWS>& jac, double* lam, 
 // bound is wide goes there as a whole).
 // A 16 x 16 x 16 product takes three matrix instructions instead of four fp64 ones of 64 cycles each, and no
 // fp16 value is widened: on this chip matrix and vector instructions of a SIMD do not overlap, so both
-// count.  14720 blocks with outlier channels (4-bit, d = 128): 280 us all in fp64, 192 so (settling single
+// count.  14720 blocks with outlier channels (4-bit, d = 128), before the rows were requested in memory order (148 since):
+// 280 us all in fp64, 192 so (settling single
 // elements where they arise, under a narrower bound that was not proven, took 201 at 199 registers; the second
 // pass keeps nothing alive during the first and 114 registers do).  The second pass is 20 us of it, and does not
 // show without outliers (16384 blocks, 195 us with it and without).  Sixteen tokens at a time, 32 fp64
@@ -1636,7 +1637,8 @@ __device__ __forceinline__ int dealt_unit(int wg, int n) {
 // per wave, then PART 3, the projection and quantizer.  In one launch every block derives each of its
 // rotations in eight lanes at once and its solver, a chain of dependent instructions, holds the
 // registers of the contractions.  The arithmetic, and so every bit written, is that of the other builds.
-// 14720 blocks (4-bit, d = 128): 670 us in one launch, 163 + 100 + 280 us in three.
+// 14720 blocks (4-bit, d = 128): 670 us in one launch, 163 + 100 + 280 us in three when both contractions were fp64 and the
+// sweeps double, 103 + 103 + 148 now (steady clocks).
 // N3 (PART 3 with the quantizer, d = 128): three local tensors (Eq. 2 with n = 3, factor shapes
 // 1 * (T_b/8) * 8 by j1 * j2 * 1) in the same kernel.  The first cut's right factor R is never
 // stored: a first pass over the rows forms it 16 tokens at a time (rounded to fp32, the precision
