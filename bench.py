@@ -166,9 +166,10 @@ def block_bytes(w):
 
 
 def block_flops(w):
-    """fp64 flops of one block's decomposition as the library does it: Gram matrix (j1 x j1 over
-    T_b*j2 columns), projection (the same count), and the Jacobi iteration (about six sweeps of
-    j1*(j1-1)/2 rotations over two j1 x j1 matrices, 12 flops per rotated pair of entries)."""
+    """Flops of one block's decomposition, counted as if all were fp64 (the library does most of them on
+    smaller types): Gram matrix (j1 x j1 over T_b*j2 columns), projection (the same count), and the Jacobi
+    iteration (about six sweeps of j1*(j1-1)/2 rotations over two j1 x j1 matrices, 12 flops per rotated
+    pair of entries)."""
     cols = w.block_tokens * w.j2
     return 2 * 2 * w.j1 * w.j1 * cols + 6 * (w.j1 * (w.j1 - 1) // 2) * 2 * w.j1 * 12
 

@@ -2702,12 +2702,10 @@ static int waves_per_block(int groups, int want_waves) {
 }
 
 // LDS that a prompt's projection (2 or 4 bits) is given beyond what it uses, to hold fewer waves than its
-// registers would let onto a SIMD: four are best where they take the whole launch at once (groups <=
-// 4096: 2048 pairs of 64-channel heads, whole call, 138 us with four, 146 with three; 8192 blocks 120 / 132),
-// beyond that their rows push each other out of the caches (projection alone, four / three / two waves
-// per SIMD: 16384 blocks 195 / 187 / 208 us, 8192 pairs 141 / 134 / 130).  Pairs are held to six workgroups
-// per compute unit (whole call, eight / six: 8192 pairs 266 / 262 us in 4 bits, 256 / 252 in 2, 16384 pairs
-// 511 / 502 and 501 / 493; 6000 pairs 186 / 188 and 184 / 181).
+// registers would let onto a SIMD: beyond 4096 workgroups more rows on their way are slower, not faster.  Pairs of heads
+// are held to six workgroups per compute unit (whole call, without / with: 8192 pairs 236 / 232 us in 4 bits, 231 / 225 in
+// 2; 16384 pairs 423 / 416 and 419 / 408; 6000 pairs 190 / 184), 2-bit codes of 128 channels to twelve (32768 blocks 696 /
+// 683; 4-bit ones use that much LDS as it is).
 static size_t prompt_projection_pad(int groups, bool pair_heads, int bits) {
   if (groups <= 4096 || bits == 8) return 0;
   const size_t per_cu = pair_heads ? 6 : 12, used = 128 * (16 * bits + 4) + 4096 + 1024;
