@@ -1378,9 +1378,14 @@ struct FastProject {
 // unless |x| >= 127.5, which a step of eight tokens asks of all its elements at once (one step in ten on prompts
 // with outlier channels).  A digit of the lane's sixteen elements is one operand of the int8 matrix cores; of the
 // sixteen products of digits ten are formed (the others are their transposes), those of one weight in
-// one accumulator (at most 2^29).  Low and high half of the result are joined as exact doubles and rounded
-// once, so G does not depend on the number of waves or the order of the sums (a sum of squares beyond 2^30
-// has more bits than the high half holds and takes up to three roundings more).  A block that holds values
+// one accumulator: at most 2^18 a token (eight columns, two products of 2^14), and 32 bits would wrap from 8192 tokens a
+// wave on, so every kDrainTokens tokens of a wave the accumulators are added to two doubles an entry in LDS, a low
+// and a high half.  Tokens add less than 1.04 * 2^42 each to the low half of an entry and of its transpose together, in
+// halves of one: 256 of them stay far under 2^52, and what goes beyond 2^32 is carried to the high half (2^32 a token,
+// in halves: 2^20 tokens) before more is added.  The halves are therefore exact, are joined and rounded
+// once, and G does not depend on the number of waves or the order of the sums, whatever the size of the block (a sum of
+// squares beyond 2^30 whose rows hold values of 127.5 and more has more bits than the high half holds: it takes up to
+// three roundings more each time the accumulators are drained).  A block that holds values
 // beyond kMostDigits (infinities and NaN among them) takes the fp64 matrix instructions below.
 // Bound by vector instructions: six and a half an element, and 160 matrix instructions of 16 cycles a block, where
 // the fp64 matrix cores take two an element and 256 of 64 cycles (and round their sums).
@@ -1388,18 +1393,18 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 constexpr float kPlainMost = 127.4375f;   // the largest fp16 value below 127.5
 constexpr float kMostDigits = 32256.f;
+constexpr int kDrainTokens = 256;         // tokens a wave adds up in 32 bits (see above)
 
 // The sums of products of digits: p[w]: digits i < j <= 3, total weight w + 1; e[i]: digit i with itself; f[i]: d4
 // with digit i.
 struct GramSums {
   i32x4 p[5], e[5], f[4];
-  f16x2 most;   // the largest |x| so far, of even and odd elements
+  f16x2 most = {(_Float16)0.f, (_Float16)0.f};   // the largest |x| so far, of even and odd elements
   __device__ __forceinline__ void clear() {
 #pragma unroll
     for (int i = 0; i < 5; ++i) p[i] = e[i] = i32x4{0, 0, 0, 0};
 #pragma unroll
     for (int i = 0; i < 4; ++i) f[i] = i32x4{0, 0, 0, 0};
-    most = f16x2{(_Float16)0.f, (_Float16)0.f};
   }
   // four 32-bit integers -> their digits, a word of four elements each
   static __device__ __forceinline__ void cut(const int (&v)[4], int& q0, int& q1, int& q2, int& q3) {
@@ -1467,19 +1472,28 @@ struct GramSums {
     p[2] = __builtin_amdgcn_mfma_i32_16x16x64_i8(q[1], q[2], p[2], 0, 0, 0);
   }
   __device__ __forceinline__ bool fits() const { return (float)most.x <= kMostDigits && (float)most.y <= kMostDigits; }
-  // Low and high (2^32) half.  Products of a digit with itself count half: the sum with the transpose makes them whole.
-  __device__ __forceinline__ void store(double* lo, double* hi, int ld) const {
+  // The sums so far into their low and high (2^32) half (`first`: there is nothing in these yet).  Products of a digit
+  // with itself count half: the sum with the transpose makes them whole.
+  __device__ __forceinline__ void drain(double* lo, double* hi, int ld, bool first) const {
     const int l = threadIdx.x & 63;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {   // lane (column l % 16) holds rows 4 (l / 16) + i
       const int at = (4 * (l >> 4) + i) * ld + (l & 15);
-      lo[at] = fma((double)p[2][i], 0x1p24, fma((double)p[1][i], 0x1p16, (double)p[0][i] * 0x1p8)) +
-               fma((double)e[1][i], 0x1p15, (double)e[0][i] * 0.5);
+      double w = fma((double)p[2][i], 0x1p24, fma((double)p[1][i], 0x1p16, (double)p[0][i] * 0x1p8)) +
+                 fma((double)e[1][i], 0x1p15, (double)e[0][i] * 0.5);
       const double h = fma((double)p[4][i], 0x1p8, (double)p[3][i]) + fma((double)e[3][i], 0x1p15, (double)e[2][i] * 0.5);
       // (d4's weight: 254 * 2^24)
       const double t = fma((double)f[3][i], 0x1p16, fma((double)f[2][i], 0x1p8, (double)f[1][i])) +
                        fma((double)e[4][i], 127.0 * 0x1p16, (double)f[0][i] * 0x1p-8);
-      hi[at] = fma(t, 254.0, h);
+      double v = fma(t, 254.0, h);
+      if (!first) {
+        w += lo[at];
+        const double carry = __builtin_rint(w * 0x1p-32);
+        w = fma(carry, -0x1p32, w);
+        v += hi[at] + carry;
+      }
+      lo[at] = w;
+      hi[at] = v;
     }
   }
 };
@@ -1556,21 +1570,28 @@ __device__ __forceinline__ void gram16(const uint16_t* __restrict__ X, int nv, l
   constexpr int GP = NWV == 1 ? 4 : 8;   // groups requested together
   const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, b1 = l & 15;
   const uint16_t* const row = PAIR ? X + (b1 >> 3) * head_gap + (b1 & 7) * 8 : X + b1 * 8;
+  static_assert(kDrainTokens % (4 * GP) == 0, "a wave's share is whole steps");
   GramSums sums;
-  sums.clear();
   u32x4 x[GP], y[GP];
   load_groups<NWV, PAIR>(x, row, 0, nv);
+  int t0 = 0;
+  bool more = true;
 #pragma unroll 1
-  for (int t0 = 4 * GP * NWV;; t0 += 4 * GP * NWV) {
-    const bool more = t0 < nv;
-    if (more) load_groups<NWV, PAIR>(y, row, t0, nv);
+  for (bool first = true; more; first = false) {
+    sums.clear();
+#pragma unroll 1
+    do {
+      t0 += 4 * GP * NWV;
+      more = t0 < nv;
+      if (more) load_groups<NWV, PAIR>(y, row, t0, nv);
 #pragma unroll
-    for (int u = 0; u < GP; u += 2) sums.add(x[u], x[u + 1]);
-    if (!more) break;
+      for (int u = 0; u < GP; u += 2) sums.add(x[u], x[u + 1]);
+      if (!more) break;
 #pragma unroll
-    for (int u = 0; u < GP; ++u) x[u] = y[u];
+      for (int u = 0; u < GP; ++u) x[u] = y[u];
+    } while (t0 % (kDrainTokens * NWV) != 0);
+    sums.drain(mats + 2 * wv * kMat, mats + (2 * wv + 1) * kMat, ld, first);
   }
-  sums.store(mats + 2 * wv * kMat, mats + (2 * wv + 1) * kMat, ld);
   bool fits = __all(sums.fits());
   if (NWV > 1 && l == 0) s_fits[wv] = fits;
   __syncthreads();
@@ -1639,6 +1660,8 @@ __device__ __forceinline__ int dealt_unit(int wg, int n) {
 // registers of the contractions.  The arithmetic, and so every bit written, is that of the other builds.
 // 14720 blocks (4-bit, d = 128): 670 us in one launch, 163 + 100 + 280 us in three when both contractions were fp64 and the
 // sweeps double, 103 + 103 + 148 now (steady clocks).
+// Launch bounds: one launch (PART 0) asks for two waves per SIMD, or its products' accumulators go to registers of
+// their own and calls of more than one workgroup a compute unit hold one (1024 blocks of 64 channels, 8 bits: 56 us, 37).
 // N3 (PART 3 with the quantizer, d = 128): three local tensors (Eq. 2 with n = 3, factor shapes
 // 1 * (T_b/8) * 8 by j1 * j2 * 1) in the same kernel.  The first cut's right factor R is never
 // stored: a first pass over the rows forms it 16 tokens at a time (rounded to fp32, the precision
@@ -1649,7 +1672,7 @@ __device__ __forceinline__ int dealt_unit(int wg, int n) {
 // (T_2 = A V' diag(1/sigma')), and hands the rows of T_2 to the quantizer in the registers it
 // expects them in.  job.keep_large: the fp32 rows of T_2 also go to the workspace.
 template <int NWV, bool PAIR, int QB = 0, bool FULL = false, int PART = 0, bool N3 = false>
-__global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? (PAIR || N3 || QB == 4 ? 3 : 4) : 1) void decompose16_kernel(dq_format fmt, dq_cache cache, CompressJob job,
+__global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? (PAIR || N3 || QB == 4 ? 3 : 4) : 2) void decompose16_kernel(dq_format fmt, dq_cache cache, CompressJob job,
                                                                float* __restrict__ large_ws,
                                                                int32_t* __restrict__ unit_status,
                                                                int32_t* __restrict__ call_status) {

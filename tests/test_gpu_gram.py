@@ -86,3 +86,63 @@ def test_gram_matrix_is_the_exact_sum_rounded_once(kind, dim, tb):
         for other in caches[1:]:
             for name in other.t:
                 assert torch.equal(other.t[name], caches[0].t[name]), name
+
+
+def _exact_long(x, j1):
+    """_exact for long blocks: the products of upper and lower halves of the values in 64-bit integers
+    (2^20 * 2^20 * 2^17 columns), joined as Python integers."""
+    v = (x.astype(np.float64) * 2.0 ** 24).astype(np.int64)
+    m = v.reshape(-1, j1, 8).transpose(1, 0, 2).reshape(j1, -1)
+    hi, lo = m >> 20, m & (2 ** 20 - 1)
+    top, mid, low = hi @ hi.T, hi @ lo.T, lo @ lo.T
+    mid = mid + mid.T
+    return np.array([[float((int(top[p, q]) << 40) + (int(mid[p, q]) << 20) + int(low[p, q])) * 2.0 ** -48
+                      for q in range(j1)] for p in range(j1)])
+
+
+@pytest.mark.parametrize("tokens", [257, 8191, 16512])
+@pytest.mark.parametrize("kind", ["half", "tiny", "wide", "small_by_large", "normal", "edges"])
+def test_gram_matrix_of_long_blocks(kind, tokens):
+    """The products of digits are summed in 32 bits.  One digit of -128 throughout (a half) passes 2^31 at 16384
+    tokens of a wave, other values later; a block may have any multiple of 128 tokens.  257 tokens: the first that a
+    wave alone adds up in two parts."""
+    print("gram of a long block: %s, %d tokens" % (kind, tokens), flush=True)
+    tb = -(-tokens // 128) * 128
+    fmt = dq.Format(4, 128, 128, 16, 8, tb)
+    g = torch.Generator(device=DEV).manual_seed(6)
+    shape = (1, 2, tokens, 128)
+    fill = {"half": 0.5,                      # the third digit is -128
+            "tiny": -32896 * 2.0 ** -24,      # the two lowest digits are
+            "wide": 126.5}                    # the third -128, the fourth 127
+    if kind in fill:
+        k = torch.full(shape, fill[kind], device=DEV)
+    elif kind == "small_by_large":            # the two products of the middle weight at their largest together
+        k = torch.full(shape, 126.5, device=DEV)
+        k[..., :64] = -32896 * 2.0 ** -24
+    else:
+        k = _rows(kind, shape, g)
+    k = k.half()
+    v = k * torch.randn(shape, device=DEV, generator=g).sign().half()   # (the off-diagonal sums cancel)
+    first = torch.zeros(1, dtype=torch.int32, device=DEV)
+    ws = dq.compress_workspace(fmt, 1, 2, DEV, t_new=tokens)
+    caches = []
+    for waves in (1, 2, 4):
+        cache = dq.alloc_cache(fmt, 1, 2, 1, DEV)
+        dq.compress_kv(cache, k, v, first, None, ws, keep_large=False, waves=waves)
+        torch.cuda.synchronize()
+        caches.append(cache)
+        if waves == 1:
+            part = ws[256:256 + 2 * 2 * tb * 128 * 4].view(torch.float64).view(2, 2, -1)[..., :256].cpu().numpy()
+    for h in range(2):
+        for which, src in enumerate((k, v)):
+            want = _exact_long(src[0, h].cpu().numpy(), 16)
+            got = part[h, which].reshape(16, 16)
+            if kind == "edges":   # rows with values beyond 127.5: every part of 256 tokens may round three times
+                size = np.sqrt(np.outer(np.diag(want), np.diag(want)))
+                assert (np.abs(got - want) <= (3 * -(-tokens // 256) + 1) * 2.0 ** -53 * size).all(), (h, which)
+            else:
+                assert (got == want).all(), (h, which)
+    if kind == "normal":
+        for other in caches[1:]:
+            for name in other.t:
+                assert torch.equal(other.t[name], caches[0].t[name]), name
