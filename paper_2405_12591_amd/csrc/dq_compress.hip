@@ -649,7 +649,8 @@ __device__ __forceinline__ void jacobi_rotation(double app, double aqq, double a
 // accumulated rotations is needed.  A lane holds a pair of columns (x, y) and derives their
 // rotation once; eight lanes hold the sixteen columns.  ROWS of the sixteen rows sit in a lane:
 // ROWS = 2 spreads one block over the wave (lane = pair + 8 * row group; the shortest chain),
-// ROWS = 8 works four blocks per wave (lane = pair + 8 * row half + 16 * block).  Between rounds the y columns move to another lane of the eight
+// ROWS = 16 works eight blocks per wave (lane = pair + 8 * block; no sum over lanes, every
+// rotation derived once per block).  Between rounds the y columns move to another lane of the eight
 // by a data-parallel-primitive pattern, so a round touches no LDS at all: on one wave per SIMD, which
 // issues an instruction every 5.3 cycles whatever it is, a round of about 55 instructions takes 320
 // cycles, against 550 for a two-sided iteration in LDS (100 instructions, two LDS round trips and a lane
@@ -685,59 +686,37 @@ __device__ __forceinline__ double add_xor32(double v) {
   return __builtin_bit_cast(double, u32x2{lo[0], hi[0]}) + __builtin_bit_cast(double, u32x2{lo[1], hi[1]});
 }
 
-__device__ __forceinline__ float add_xor16(float v) {
-  const uint32_t w = __builtin_bit_cast(uint32_t, v);
-  const auto x = __builtin_amdgcn_permlane16_swap(w, w, false, false);
-  return __builtin_bit_cast(float, (uint32_t)x[0]) + __builtin_bit_cast(float, (uint32_t)x[1]);
-}
-__device__ __forceinline__ float add_xor32(float v) {
-  const uint32_t w = __builtin_bit_cast(uint32_t, v);
-  const auto x = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-  return __builtin_bit_cast(float, (uint32_t)x[0]) + __builtin_bit_cast(float, (uint32_t)x[1]);
-}
-template <int CTRL> __device__ __forceinline__ double dpp_t(double v) { return dpp_d<CTRL>(v); }
-template <int CTRL> __device__ __forceinline__ float dpp_t(float v) { return lane_exchange<CTRL>(v); }
-
 // sum over the sixteen rows of u * v: products in pairs of rows, then a balanced tree over the
 // eight pairs, whose upper levels are lanes when ROWS < 16
-__device__ __forceinline__ double fma_t(double a, double b, double c) { return fma(a, b, c); }
-__device__ __forceinline__ float fma_t(float a, float b, float c) { return fmaf(a, b, c); }
-template <int ROWS, typename T>
-__device__ __forceinline__ T dot16(const T (&u)[ROWS], const T (&v)[ROWS]) {
-  T s[ROWS / 2];
+template <int ROWS>
+__device__ __forceinline__ double dot16(const double (&u)[ROWS], const double (&v)[ROWS]) {
+  double s[ROWS / 2];
 #pragma unroll
-  for (int i = 0; i < ROWS / 2; ++i) s[i] = fma_t(u[2 * i + 1], v[2 * i + 1], u[2 * i] * v[2 * i]);
+  for (int i = 0; i < ROWS / 2; ++i) s[i] = fma(u[2 * i + 1], v[2 * i + 1], u[2 * i] * v[2 * i]);
 #pragma unroll
   for (int n = ROWS / 4; n >= 1; n >>= 1)
 #pragma unroll
     for (int i = 0; i < n; ++i) s[i] = s[2 * i] + s[2 * i + 1];
-  T r = s[0];
-  if (ROWS <= 8) r += dpp_t<kDppXor8>(r);
+  double r = s[0];
+  if (ROWS <= 8) r += dpp_d<kDppXor8>(r);
   if (ROWS <= 4) r = add_xor16(r);
   if (ROWS <= 2) r = add_xor32(r);
   return r;
 }
 
 constexpr int kMostSweeps = 24;
-// Sweeps in single precision ahead of the double ones, and when they end: a pair (squared) within 1e-3 of orthogonal
-// when it was rotated leaves about 1e-6; columns of eigenvalues below 1e-6 of the largest are noise there.
-constexpr int kMostSweeps32 = 9;
-constexpr float kSettled32 = 1e-6f, kFloor32 = 1e-12f;
-// The single-precision columns V may start the double ones if V^T V = 1 + E with |E| up to this: V (1 - E/2 + 3/8 E^2) is
-// orthonormal but for 5/16 of the cube of E (in norm at most sixteen times as large): 1.6e-10 at the worst.
-constexpr double kStart32 = 5e-5;
 
-template <int ROWS, typename T = double>
+template <int ROWS>
 struct Jacobi16 {
-  T x[ROWS], y[ROWS];        // the lane's rows of its two columns
-  T a, b;                    // their squared norms
+  double x[ROWS], y[ROWS];   // the lane's rows of its two columns
+  double a, b;               // their squared norms
   int ix, iy;                // which columns they are
 
   template <int CTRL>
   __device__ __forceinline__ void move() {   // the y columns to lane ^ mask
 #pragma unroll
-    for (int i = 0; i < ROWS; ++i) y[i] = dpp_t<CTRL>(y[i]);
-    b = dpp_t<CTRL>(b);
+    for (int i = 0; i < ROWS; ++i) y[i] = dpp_d<CTRL>(y[i]);
+    b = dpp_d<CTRL>(b);
     iy = __builtin_amdgcn_update_dpp(0, iy, CTRL, 0xF, 0xF, true);
   }
   // The lanes whose `upper` is false collect the x columns of both partners (lane, lane ^ mask), the
@@ -746,11 +725,11 @@ struct Jacobi16 {
   __device__ __forceinline__ void split(bool upper) {
 #pragma unroll
     for (int i = 0; i < ROWS; ++i) {
-      const T xo = dpp_t<CTRL>(x[i]), yo = dpp_t<CTRL>(y[i]);
+      const double xo = dpp_d<CTRL>(x[i]), yo = dpp_d<CTRL>(y[i]);
       x[i] = upper ? yo : x[i];
       y[i] = upper ? y[i] : xo;
     }
-    const T ao = dpp_t<CTRL>(a), bo = dpp_t<CTRL>(b);
+    const double ao = dpp_d<CTRL>(a), bo = dpp_d<CTRL>(b);
     a = upper ? bo : a;
     b = upper ? b : ao;
     const int ixo = __builtin_amdgcn_update_dpp(0, ix, CTRL, 0xF, 0xF, true);
@@ -767,32 +746,24 @@ struct Jacobi16 {
   // still apart (the first sweeps do not ask).  PAIR: the floor of the columns' own head counts (two
   // columns of different heads have no row in common: g is zero and nothing is to settle).
   template <bool TEST, bool PAIR>
-  __device__ __forceinline__ void rotate(T floor_lo, T floor_hi, bool& unsettled) {
-    constexpr bool WIDE = sizeof(T) == 8;
-    const T g = dot16<ROWS>(x, y);
-    if (TEST) unsettled |= (g * g > (WIDE ? (T)kSettled2 : (T)kSettled32) * (a * b)) && (fmin(a, b) > ((PAIR && ix >= 8) ? floor_hi : floor_lo));
-    const T d = b - a, g2 = g + g;
-    T t, c;
-    if constexpr (WIDE) {
-      const double root = __builtin_amdgcn_sqrt(fma(g2, g2, fma(d, d, 1e-240)));
-      t = g2 * __builtin_amdgcn_rcp(d + copysign(root, d));
-      const double w = fma(t, t, 1.0);
-      const double r0 = __builtin_amdgcn_rsq(w);
-      c = r0 * fma(-0.5 * w, r0 * r0, 1.5);
-    } else {   // (the estimates are as good as the type)
-      const float root = __builtin_amdgcn_sqrtf(fmaf(g2, g2, fmaf(d, d, 1e-37f)));
-      t = g2 * __builtin_amdgcn_rcpf(d + copysignf(root, d));
-      c = __builtin_amdgcn_rsqf(fmaf(t, t, 1.f));
-    }
-    const T tc = t * c;
+  __device__ __forceinline__ void rotate(double floor_lo, double floor_hi, bool& unsettled) {
+    const double g = dot16<ROWS>(x, y);
+    if (TEST) unsettled |= (g * g > kSettled2 * (a * b)) && (fmin(a, b) > ((PAIR && ix >= 8) ? floor_hi : floor_lo));
+    const double d = b - a, g2 = g + g;
+    const double root = __builtin_amdgcn_sqrt(fma(g2, g2, fma(d, d, 1e-240)));
+    const double t = g2 * __builtin_amdgcn_rcp(d + copysign(root, d));
+    const double w = fma(t, t, 1.0);
+    const double r0 = __builtin_amdgcn_rsq(w);
+    const double c = r0 * fma(-0.5 * w, r0 * r0, 1.5);
+    const double tc = t * c;
 #pragma unroll
     for (int i = 0; i < ROWS; ++i) {
-      const T xi = x[i], yi = y[i];
-      x[i] = fma_t(-tc, yi, c * xi);
-      y[i] = fma_t(tc, xi, c * yi);
+      const double xi = x[i], yi = y[i];
+      x[i] = fma(-tc, yi, c * xi);
+      y[i] = fma(tc, xi, c * yi);
     }
-    a = fma_t(-t, g, a);
-    b = fma_t(t, g, b);
+    a = fma(-t, g, a);
+    b = fma(t, g, b);
   }
 
   // Fifteen rounds of eight disjoint pairs: x columns against y columns, then the two halves of each
@@ -800,7 +771,7 @@ struct Jacobi16 {
   // that leave the columns where the next sweep can start from them, this one converges soonest (5.9
   // sweeps on the synthetic workloads' blocks; with the first eight rounds the other way round, 6.9).
   template <bool TEST, bool PAIR>
-  __device__ __forceinline__ void sweep(int j, T floor_lo, T floor_hi, bool& unsettled) {
+  __device__ __forceinline__ void sweep(int j, double floor_lo, double floor_hi, bool& unsettled) {
     move<kDppXor7>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
     move<kDppXor3>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
     move<kDppXor1>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
@@ -818,25 +789,11 @@ struct Jacobi16 {
     split<kDppXor1>((j & 1) != 0); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
   }
 
-  // Whether some pair of the lane's block is still apart
-  static __device__ __forceinline__ bool block_any(bool mine) {
-    const unsigned long long open = __ballot(mine);
-    if (ROWS == 2) return open != 0;
-    constexpr int LPB = 128 / (ROWS == 2 ? 4 : ROWS);   // lanes per block
-    return ((open >> (threadIdx.x & 63 & ~(LPB - 1))) & ((1ull << LPB) - 1)) != 0;
-  }
-  static __device__ __forceinline__ T over_columns(T v) {   // sum over the eight lanes
-    v += dpp_t<kDppXor1>(v);
-    v += dpp_t<kDppXor2>(v);
-    return v + dpp_t<kDppXor7>(v);
-  }
-
   // Called with x = column j, y = column j + 8 of the matrix, j = lane % 8.  Returns the sweeps used.  All
   // eight lanes of a block (and, for ROWS < 16, all its row groups) leave together.
   template <bool PAIR>
   __device__ __forceinline__ int run() {
-    constexpr bool WIDE = sizeof(T) == 8;
-    const int j = threadIdx.x & 7;
+    const int lane = threadIdx.x & 63, j = lane & 7;
     ix = j; iy = j + 8;
     a = dot16<ROWS>(x, x);
     b = dot16<ROWS>(y, y);
@@ -844,21 +801,27 @@ struct Jacobi16 {
     // does not matter.  (A pair: of the largest of the same head, as order() drops them.  x are the first
     // head's columns here, y the second's.  One floor over both left a head a thousand times smaller
     // than its partner unsettled: up to 88 % of its block lost where its singular values span 1e5.)
-    const T small = WIDE ? (T)1e-28 : (T)kFloor32;
-    const T floor_lo = over_columns(PAIR ? a : a + b) * small, floor_hi = PAIR ? over_columns(b) * small : floor_lo;
+    double tr_lo = PAIR ? a : a + b, tr_hi = b;
+    tr_lo += dpp_d<kDppXor1>(tr_lo);
+    tr_lo += dpp_d<kDppXor2>(tr_lo);
+    tr_lo += dpp_d<kDppXor7>(tr_lo);
+    if (PAIR) {
+      tr_hi += dpp_d<kDppXor1>(tr_hi);
+      tr_hi += dpp_d<kDppXor2>(tr_hi);
+      tr_hi += dpp_d<kDppXor7>(tr_hi);
+    }
+    const double floor_lo = tr_lo * 1e-28, floor_hi = tr_hi * 1e-28;
     bool unsettled = true;
     int sweeps = 0;
-    if (!WIDE) {   // no block with anything off the diagonal settles in three sweeps: they do not test
-      while (sweeps < 3) {
-        ++sweeps;
-        sweep<false, PAIR>(j, floor_lo, floor_hi, unsettled);
-        a = dot16<ROWS>(x, x);
-        b = dot16<ROWS>(y, y);
-      }
+    // no block with anything off the diagonal settles in three sweeps: they do not test
+    while (sweeps < 3) {
+      ++sweeps;
+      sweep<false, PAIR>(j, floor_lo, floor_hi, unsettled);
+      a = dot16<ROWS>(x, x);
+      b = dot16<ROWS>(y, y);
     }
-    // (in double precision: one sweep after the single ones as a rule; blocks they could not start, graded over three
-    // decades and more, take up to 17)
-    while (unsettled && sweeps < (WIDE ? kMostSweeps : kMostSweeps32)) {
+    // (blocks in general position settle in 6, graded ones in up to 17: five decades and a half)
+    while (unsettled && sweeps < kMostSweeps) {
       ++sweeps;
       unsettled = false;
       sweep<true, PAIR>(j, floor_lo, floor_hi, unsettled);
@@ -866,7 +829,13 @@ struct Jacobi16 {
       b = dot16<ROWS>(y, y);
       // every pair of this sweep was within 3e-5 of orthogonal when it was rotated, so the sweep (one
       // more quadratic step) has left them near 1e-9, two orders under the fp32 rounding of T_L
-      unsettled = block_any(unsettled);
+      const unsigned long long open = __ballot(unsettled);
+      if (ROWS == 2) {
+        unsettled = open != 0;
+      } else {
+        constexpr int LPB = 128 / (ROWS == 2 ? 4 : ROWS);   // lanes per block
+        unsettled = ((open >> (lane & ~(LPB - 1))) & ((1ull << LPB) - 1)) != 0;
+      }
     }
     return sweeps;
   }
@@ -920,104 +889,8 @@ struct Jacobi16 {
     if (!kx) lx = 0.0;
     if (!ky) ly = 0.0;
   }
-  static __device__ __forceinline__ int first_row(int lane) { return ROWS * ((lane >> 3) & (16 / ROWS - 1)); }
+  static __device__ __forceinline__ int first_row(int lane) { return ROWS == 16 ? 0 : ROWS * ((lane >> 3) & (16 / ROWS - 1)); }
 };
-
-// Between steps of NWV waves that share LDS; NWV = 1: of one wave on its own, whose LDS operations execute in order.
-template <int NWV>
-__device__ __forceinline__ void team_barrier() {
-  if (NWV > 1) {
-    __syncthreads();
-  } else {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-  }
-}
-
-// The eigen-decomposition of G, in two steps.  In single precision (half the instructions of a round, or a third where
-// a block is spread over the wave) the same iteration finds the eigenvectors to about 1e-7: the normalised columns V.
-// Three terms of the series of V (V^T V)^(-1/2) make them orthogonal to 1e-13 as a rule, and the
-// columns of G V, all in double precision on the matrix cores, are what the double iteration starts from: G V Q = U
-// Lambda.  One of its sweeps then finds every pair within 3e-5 of orthogonal, where it took six to nine of them from G
-// itself.  A block whose V is further than kStart32 from orthonormal (singular values over more than two and a half
-// decades, zero columns, NaN) starts from G.  Steady clocks, with every sweep in double precision / so: calls
-// of 320 blocks 37.7 / 34.3 us, 2304 tokens of 8 heads 38.0 / 35.6, 32768 blocks 725 / 690; the solver of 14720 blocks alone
-// 97 / 103.
-// In: x, y of `jac` are columns j and j + 8 of the lane's block's matrix (j = lane % 8).  `matrix(b)`: block b of the wave's
-// G (row length ldg); `live`: bit b set if block b is there; `lds`: 272 doubles per block.
-template <int ROWS, bool PAIR, typename MATRIX>
-__device__ __forceinline__ int solve_mixed(Jacobi16<ROWS>& jac, MATRIX matrix, int ldg, unsigned live, double* lds) {
-  constexpr int LPB = ROWS == 2 ? 64 : 128 / ROWS, NB = 64 / LPB, ld = 17, kMat = 16 * ld;
-  const int lane = threadIdx.x & 63, j = lane & 7, row0 = jac.first_row(lane);
-  const int n = lane & 15, g = lane >> 4;
-  double* const mine = lds + lane / LPB * kMat;
-  // the matrices once more, for the products (requested here: one by one where they are used, each would wait for memory)
-  double gm[NB][4];
-#pragma unroll
-  for (int b = 0; b < NB; ++b)
-#pragma unroll
-    for (int s = 0; s < 4; ++s) gm[b][s] = matrix(b)[(4 * s + g) * ldg + n];   // (symmetric: G[n][4 s + g] as well)
-  {
-    Jacobi16<ROWS, float> f;
-    // scaled so that the largest columns (a pair: of each head) are near one
-    const double nx = dot16<ROWS>(jac.x, jac.x), ny = dot16<ROWS>(jac.y, jac.y);
-    const double tx = Jacobi16<ROWS>::over_columns(PAIR ? nx : nx + ny), ty = PAIR ? Jacobi16<ROWS>::over_columns(ny) : tx;
-    const int ex = -(__builtin_amdgcn_frexp_exp(tx) >> 1), ey = -(__builtin_amdgcn_frexp_exp(ty) >> 1);
-#pragma unroll
-    for (int i = 0; i < ROWS; ++i) {
-      f.x[i] = (float)__builtin_amdgcn_ldexp(jac.x[i], ex);
-      f.y[i] = (float)__builtin_amdgcn_ldexp(jac.y[i], ey);
-    }
-    f.template run<PAIR>();
-    const float sx = f.a > 1e-30f ? __builtin_amdgcn_rsqf(f.a) : 0.f, sy = f.b > 1e-30f ? __builtin_amdgcn_rsqf(f.b) : 0.f;
-#pragma unroll
-    for (int i = 0; i < ROWS; ++i) {
-      mine[(row0 + i) * ld + f.ix] = (double)(f.x[i] * sx);
-      mine[(row0 + i) * ld + f.iy] = (double)(f.y[i] * sy);
-    }
-  }
-  team_barrier<1>();
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    if (!((live >> b) & 1u)) continue;
-    double* const V = lds + b * kMat;
-    double vk[4], vm[4];
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      vk[s] = V[(4 * s + g) * ld + n];
-      vm[s] = V[n * ld + 4 * s + g];
-    }
-    f64x4 S = {0.0, 0.0, 0.0, 0.0}, E2 = S, V1 = S, B = S;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) S = __builtin_amdgcn_mfma_f64_16x16x4f64(vk[s], vk[s], S, 0, 0, 0);
-    bool near = true;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const double one = g + 4 * i == n ? 1.0 : 0.0;
-      S[i] -= one;
-      near = near && fabs(S[i]) <= kStart32;
-    }
-#pragma unroll
-    for (int s = 0; s < 4; ++s) E2 = __builtin_amdgcn_mfma_f64_16x16x4f64(S[s], S[s], E2, 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) S[i] = fma(0.375, E2[i], fma(-0.5, S[i], g + 4 * i == n ? 1.0 : 0.0));
-    // (a result's register i holds row l / 16 + 4 i: the right operand's k of step i)
-#pragma unroll
-    for (int s = 0; s < 4; ++s) V1 = __builtin_amdgcn_mfma_f64_16x16x4f64(vm[s], S[s], V1, 0, 0, 0);
-#pragma unroll
-    for (int s = 0; s < 4; ++s) B = __builtin_amdgcn_mfma_f64_16x16x4f64(gm[b][s], V1[s], B, 0, 0, 0);
-    const bool start = __all(near);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) V[(g + 4 * i) * ld + n] = start ? B[i] : gm[b][i];
-  }
-  team_barrier<1>();
-#pragma unroll
-  for (int i = 0; i < ROWS; ++i) {
-    jac.x[i] = mine[(row0 + i) * ld + j];
-    jac.y[i] = mine[(row0 + i) * ld + j + 8];
-  }
-  return jac.template run<PAIR>();
-}
 
 // W[r][b1] from the solver's registers (lam2[r]: the eigenvalue, 0 if the direction is dropped)
 template <int ROWS, bool PAIR, int LD>
@@ -1095,6 +968,17 @@ __device__ __forceinline__ float max_xor32(float v) {
   const uint32_t w = __builtin_bit_cast(uint32_t, v);
   const auto x = __builtin_amdgcn_permlane32_swap(w, w, false, false);
   return fmaxf(__builtin_bit_cast(float, (uint32_t)x[0]), __builtin_bit_cast(float, (uint32_t)x[1]));
+}
+
+// Between steps of NWV waves that share LDS; NWV = 1: of one wave on its own, whose LDS operations execute in order.
+template <int NWV>
+__device__ __forceinline__ void team_barrier() {
+  if (NWV > 1) {
+    __syncthreads();
+  } else {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
 }
 
 template <int QB, bool FULL, bool PAIR>
@@ -1654,7 +1538,7 @@ __device__ __forceinline__ int dealt_unit(int wg, int n) {
 // write-back or invalidation is needed between the XCDs.
 // PART: calls of thousands of blocks (a prompt) are bound by throughput, not by one block's latency, and
 // run as three launches, each with one wave per block or less and several waves per SIMD: PART 1 is the
-// Gram matrix alone (left in the block's region of the workspace), then solve16_kernel, two or four blocks
+// Gram matrix alone (left in the block's region of the workspace), then solve16_kernel, eight blocks
 // per wave, then PART 3, the projection and quantizer.  In one launch every block derives each of its
 // rotations in eight lanes at once and its solver, a chain of dependent instructions, holds the
 // registers of the contractions.  The arithmetic, and so every bit written, is that of the other builds.
@@ -1790,7 +1674,7 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? (PAIR || N3 |
       jac.x[i] = A[(2 * (l >> 3) + i) * ld + (l & 7)];
       jac.y[i] = A[(2 * (l >> 3) + i) * ld + (l & 7) + 8];
     }
-    const int sweeps = solve_mixed<2, PAIR>(jac, [&](int) { return A; }, ld, 1u, W);
+    const int sweeps = jac.template run<PAIR>();
 
     // ---- singular values, ordering, small tensor ----
     store_factors<2, PAIR, ld>(jac, lam, lam2, W);
@@ -2370,9 +2254,15 @@ __device__ __forceinline__ void store_fast_factors(const Jacobi16<ROWS>& jac, co
     if (live) {
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
+        if (ROWS == 16) {
 #pragma unroll
-        for (int i = 0; i < ROWS; ++i)
-          reinterpret_cast<_Float16*>(pieces)[256 * k + ((i & 3) * 16 + r) * 4 + ((row0 + i) >> 2)] = h[k][i];
+          for (int g = 0; g < 4; ++g)
+            *reinterpret_cast<f16x4*>(pieces + 256 * k + (g * 16 + r) * 4) = f16x4{h[k][g], h[k][(4 + g) % ROWS], h[k][(8 + g) % ROWS], h[k][(12 + g) % ROWS]};
+        } else {
+#pragma unroll
+          for (int i = 0; i < ROWS; ++i)
+            reinterpret_cast<_Float16*>(pieces)[256 * k + ((i & 3) * 16 + r) * 4 + ((row0 + i) >> 2)] = h[k][i];
+        }
       }
     }
     one = over_rows(one, add);
@@ -2399,9 +2289,10 @@ __device__ __forceinline__ void store_fast_factors(const Jacobi16<ROWS>& jac, co
   }
 }
 
-// The eigen-solver of a call of thousands of blocks: 64 * ROWS / 128 blocks per wave (four at ROWS = 8).  Reads the
+// The eigen-solver of a call of thousands of blocks: 64 * ROWS / 128 blocks per wave (eight at ROWS = 16:
+// every rotation is derived once, no sum crosses lanes, nothing touches LDS but the ordering).  Reads the
 // Gram matrices and writes W behind them, the small tensors into the cache, the blocks' status words.
-// Bound by instruction issue.
+// Bound by instruction issue: about 145 instructions per round for eight blocks.
 // Workgroups of four waves, so that the waves spread evenly over the SIMDs.
 constexpr int kSolveWaves = 4;
 template <int ROWS, bool PAIR, bool FAST>
@@ -2411,10 +2302,9 @@ __global__ __launch_bounds__(64 * kSolveWaves) void solve16_kernel(dq_format fmt
   constexpr int LPB = 128 / ROWS, BPG = 64 * kSolveWaves / LPB;   // lanes per block, blocks per workgroup
   constexpr int j1 = 16, d = PAIR ? 64 : 128;
   const Geometry g = make_geometry(fmt, cache.kv_heads, cache.block_capacity);
-  __shared__ __attribute__((aligned(16))) double s_mats[BPG * j1 * 17];   // of each block: V, G V; then its small tensor and eigenvalues
+  __shared__ double s_lam[BPG][j1];
+  __shared__ __attribute__((aligned(16))) uint16_t s_small[BPG][j1 * j1];
   const int lane = threadIdx.x & 63, blk = threadIdx.x / LPB, j = lane & 7;
-  uint16_t* const s_small = reinterpret_cast<uint16_t*>(s_mats + blk * (j1 * 17));
-  double* const s_lam = s_mats + blk * (j1 * 17) + 64;
   const int gi = blockIdx.x * BPG + blk;
   int unit = min(gi, n_groups - 1);
   const int unit_gap = 2 * job.n_blocks;
@@ -2441,19 +2331,10 @@ __global__ __launch_bounds__(64 * kSolveWaves) void solve16_kernel(dq_format fmt
     jac.x[i] = live ? G[j * j1 + row0 + i] : 0.0;
     jac.y[i] = live ? G[(j + 8) * j1 + row0 + i] : 0.0;
   }
-  const unsigned long long lives = __ballot(live);
-  unsigned live_blocks = 0;
-#pragma unroll
-  for (int b = 0; b < 64 / LPB; ++b) live_blocks |= (unsigned)((lives >> (b * LPB)) & 1u) << b;
-  const uint64_t at = reinterpret_cast<uint64_t>(G);
-  auto matrix = [&](int b) __attribute__((always_inline)) {
-    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)at, b * LPB), hi = __builtin_amdgcn_readlane((int)(uint32_t)(at >> 32), b * LPB);
-    return reinterpret_cast<const double*>((uint64_t)hi << 32 | lo);
-  };
-  const int sweeps = solve_mixed<ROWS, PAIR>(jac, matrix, j1, live_blocks, s_mats + (threadIdx.x >> 6) * (64 / LPB) * (j1 * 17));
+  const int sweeps = jac.template run<PAIR>();
   int px, py;
   double rx, ry, lx, ly;
-  jac.template order<PAIR>(s_lam, px, py, rx, ry, lx, ly);
+  jac.template order<PAIR>(s_lam[blk], px, py, rx, ry, lx, ly);
   const double fx = rx * rx * rx, fy = ry * ry * ry;
   if (live) {
     G[2 * j1 * j1 + px] = lx;
@@ -2473,9 +2354,9 @@ __global__ __launch_bounds__(64 * kSolveWaves) void solve16_kernel(dq_format fmt
     auto put = [&](int r, double ts) __attribute__((always_inline)) {
       if (PAIR) {   // the heads' 8 x 8 tensors one after the other; across heads there is nothing
         if ((b1 >> 3) != (r >> 3)) return;
-        s_small[(b1 >> 3) * 64 + (ur.which ? (b1 & 7) * 8 + (r & 7) : (r & 7) * 8 + (b1 & 7))] = f64_to_f16_rne(ts, true, &sat);
+        s_small[blk][(b1 >> 3) * 64 + (ur.which ? (b1 & 7) * 8 + (r & 7) : (r & 7) * 8 + (b1 & 7))] = f64_to_f16_rne(ts, true, &sat);
       } else {      // values: [b1][r]; keys: transposed [r][b1]
-        s_small[ur.which ? b1 * j1 + r : r * j1 + b1] = f64_to_f16_rne(ts, true, &sat);
+        s_small[blk][ur.which ? b1 * j1 + r : r * j1 + b1] = f64_to_f16_rne(ts, true, &sat);
       }
     };
     put(px, wx[i] * lx);   // T_S = U Sigma = W Lambda
@@ -2491,7 +2372,7 @@ __global__ __launch_bounds__(64 * kSolveWaves) void solve16_kernel(dq_format fmt
 #pragma unroll
     for (int c = lb; c < CHUNKS; c += LPB) {
       uint16_t* dst = PAIR ? small + (long)(c / 8) * g.NB * g.small_per_block + (c % 8) * 8 : small + c * 8;
-      *reinterpret_cast<u32x4*>(dst) = *reinterpret_cast<const u32x4*>(&s_small[c * 8]);
+      *reinterpret_cast<u32x4*>(dst) = *reinterpret_cast<const u32x4*>(&s_small[blk][c * 8]);
     }
   }
   if (gi < n_groups && lane % LPB == 0) {
@@ -2779,10 +2660,10 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
   // quantizer); larger calls, and a forced wave count of one, take the one-kernel build.
   const bool fused3 = fmt->i3 == kRun && fmt->i1 == 1 && !force_general && fmt->head_dim == 128 && fmt->j1 == 16 &&
                       (fmt->group == 128 || fmt->group == 64) && (want_waves == 1 || (want_waves == 0 && units > 512));
-  // The first two launches of a call of thousands of blocks: Gram matrices, eigen-solver.  Four blocks per
-  // solver wave above 8192 blocks, two up to there, where the waves would not fill the chip (solver of 14720 blocks, four /
-  // two per wave: 103 / 112 us; whole call of 32768 blocks 690 / 707.  Eight per wave: 124 us and 734: each round of
-  // the double sweep, which runs once or twice, is 145 instructions then, most of the time on their way from memory).
+  // The first two launches of a call of thousands of blocks: Gram matrices, eigen-solver.  Eight blocks per
+  // solver wave need 8192 blocks to put a wave on every SIMD; up to there two blocks per wave are as fast
+  // or faster (whole call, two / eight blocks per wave: 1280 blocks 90 / 121 us, 2560 129 / 138, 8192
+  // 291 / 292, 16384 545 / 517).
   // `fast`: the fp16 projection follows and wants its constants.
   auto launch_factor = [&](bool fast) {
     const int groups = pair_heads ? units / 2 : units;
@@ -2802,8 +2683,8 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
     else DQ_LAUNCH_SOLVE(R_, P_, false);   \
   } while (0)
     if (groups > 8192) {
-      if (pair_heads) DQ_LAUNCH_SOLVE_F(8, true);
-      else DQ_LAUNCH_SOLVE_F(8, false);
+      if (pair_heads) DQ_LAUNCH_SOLVE_F(16, true);
+      else DQ_LAUNCH_SOLVE_F(16, false);
     } else {
       if (pair_heads) DQ_LAUNCH_SOLVE_F(4, true);
       else DQ_LAUNCH_SOLVE_F(4, false);
