@@ -1383,14 +1383,13 @@ struct GramSums {
 };
 
 // N groups of four tokens from token t0 on, wave wv of NWV taking every NWV-th
-template <int NWV, bool PAIR, int N>
+template <int NWV, bool PAIR, bool CACHED, int N>
 __device__ __forceinline__ void load_groups(u32x4 (&v)[N], const uint16_t* row, int t0, int nv) {
   constexpr int d = PAIR ? 64 : 128;
   const int t1 = t0 + 4 * (threadIdx.x >> 6) + ((threadIdx.x & 63) >> 4);
   auto piece = [&](int u) __attribute__((always_inline)) {
-    // (a prompt's rows are not read again soon: 14720 blocks 103 us with non-temporal loads, 114 with plain ones)
     const u32x4* p = reinterpret_cast<const u32x4*>(row + (long)(t1 + 4 * u * NWV) * d);
-    return NWV == 1 ? __builtin_nontemporal_load(p) : *p;
+    return NWV == 1 && !CACHED ? __builtin_nontemporal_load(p) : *p;   // (see kMostCached)
   };
   if (t0 + 4 * N * NWV <= nv) {   // (whole pieces without a branch per load)
 #pragma unroll
@@ -1406,7 +1405,7 @@ __device__ __forceinline__ void load_groups(u32x4 (&v)[N], const uint16_t* row, 
 
 // On the fp64 matrix cores: A and B operand of one instruction are the same register (lane (b1, k) holds
 // X[t0 + k][b1*8 + b2] for the 4 tokens of a group and one b2); products of fp16 values are exact, sums round.
-template <int NWV, bool PAIR>
+template <int NWV, bool PAIR, bool CACHED>
 __device__ __forceinline__ void gram16_fp64(const uint16_t* row, int nv, double* mats, double* out, int ldo) {
   constexpr int ld = 17, kMat = 16 * ld, GP = 4;
   const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -1416,7 +1415,7 @@ __device__ __forceinline__ void gram16_fp64(const uint16_t* row, int nv, double*
 #pragma unroll 1
   for (int t0 = 0; t0 < nv; t0 += 4 * GP * NWV) {
     u32x4 y[GP];
-    load_groups<NWV, PAIR>(y, row, t0, nv);
+    load_groups<NWV, PAIR, CACHED>(y, row, t0, nv);
 #pragma unroll
     for (int u = 0; u < GP; ++u) {
       const f16x8 h = __builtin_bit_cast(f16x8, y[u]);
@@ -1447,7 +1446,7 @@ __device__ __forceinline__ void gram16_fp64(const uint16_t* row, int nv, double*
 
 // mats: 2 * NWV matrices of 16 x 17 doubles in LDS; s_fits: NWV words.  out may be mats (ldo 17).  All waves call it; it
 // ends with a barrier.
-template <int NWV, bool PAIR>
+template <int NWV, bool PAIR, bool CACHED>
 __device__ __forceinline__ void gram16(const uint16_t* __restrict__ X, int nv, long head_gap, double* mats,
                                        int* s_fits, double* out, int ldo) {
   constexpr int ld = 17, kMat = 16 * ld;
@@ -1457,7 +1456,7 @@ __device__ __forceinline__ void gram16(const uint16_t* __restrict__ X, int nv, l
   static_assert(kDrainTokens % (4 * GP) == 0, "a wave's share is whole steps");
   GramSums sums;
   u32x4 x[GP], y[GP];
-  load_groups<NWV, PAIR>(x, row, 0, nv);
+  load_groups<NWV, PAIR, CACHED>(x, row, 0, nv);
   int t0 = 0;
   bool more = true;
 #pragma unroll 1
@@ -1467,7 +1466,7 @@ __device__ __forceinline__ void gram16(const uint16_t* __restrict__ X, int nv, l
     do {
       t0 += 4 * GP * NWV;
       more = t0 < nv;
-      if (more) load_groups<NWV, PAIR>(y, row, t0, nv);
+      if (more) load_groups<NWV, PAIR, CACHED>(y, row, t0, nv);
 #pragma unroll
       for (int u = 0; u < GP; u += 2) sums.add(x[u], x[u + 1]);
       if (!more) break;
@@ -1505,7 +1504,7 @@ __device__ __forceinline__ void gram16(const uint16_t* __restrict__ X, int nv, l
       out[(idx >> 4) * ldo + (idx & 15)] = val[k];
     }
   } else {
-    gram16_fp64<NWV, PAIR>(row, nv, mats, out, ldo);
+    gram16_fp64<NWV, PAIR, CACHED>(row, nv, mats, out, ldo);
   }
   __syncthreads();
 }
@@ -1555,7 +1554,8 @@ __device__ __forceinline__ int dealt_unit(int wg, int n) {
 // the operand layout that lets a second matrix product contract over the eight tokens of a run
 // (T_2 = A V' diag(1/sigma')), and hands the rows of T_2 to the quantizer in the registers it
 // expects them in.  job.keep_large: the fp32 rows of T_2 also go to the workspace.
-template <int NWV, bool PAIR, int QB = 0, bool FULL = false, int PART = 0, bool N3 = false>
+// CACHED (PART 1): the rows are requested with plain loads (see kMostCached).
+template <int NWV, bool PAIR, int QB = 0, bool FULL = false, int PART = 0, bool N3 = false, bool CACHED = false>
 __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? (PAIR || N3 || QB == 4 ? 3 : 4) : 2) void decompose16_kernel(dq_format fmt, dq_cache cache, CompressJob job,
                                                                float* __restrict__ large_ws,
                                                                int32_t* __restrict__ unit_status,
@@ -1662,7 +1662,7 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? (PAIR || N3 |
   // ---- Gram matrix G[p][q] = sum_{t, b2} X[t, p*8+b2] X[t, q*8+b2] ----
   if constexpr (PART != 3) {
     __shared__ int s_fits[NWV];
-    gram16<NWV, PAIR>(X, nv, head_gap, A, s_fits, PART == 1 ? gram_ws : A, PART == 1 ? j1 : ld);
+    gram16<NWV, PAIR, CACHED>(X, nv, head_gap, A, s_fits, PART == 1 ? gram_ws : A, PART == 1 ? j1 : ld);
   }
   if constexpr (PART == 1) return;
   if constexpr (PART == 0) {
@@ -2620,6 +2620,15 @@ static int waves_per_block(int groups, int want_waves) {
   return groups <= 512 ? 4 : groups <= 1024 ? 2 : 0;
 }
 
+// Blocks (of sixteen rows of channels: pairs of 64-channel heads count once) up to which the Gram matrices' launch requests
+// its rows with plain loads: the projection then finds them in the 256 MB last-level cache, 32 KB a block (kMostCachedFast: 2- and
+// 4-bit codes).  Where the rows do not fit, or the fp32 rows, 64 KB a block, displace them (kMostCached: kept large tensors;
+// 8 bits and three tensors, bound by instructions, gain nothing), loads that pass the caches by are faster.  Whole call in us,
+// non-temporal / plain: 4 bits, 2048 blocks 70.0 / 67.2, 4096 126 / 115, 8192 214 / 202, 9216 254 / 249, 13312 324 / 324, 14720
+// 339 / 346; 4096 pairs 142 / 128; large tensors kept, 2048 blocks 138 / 128, 3072 199 / 211; 8 bits, 1152 blocks 83.1 /
+// 82.7, 8192 285 / 300.
+constexpr int kMostCachedFast = 8192, kMostCached = 2048;
+
 // LDS that a prompt's projection (2 or 4 bits) is given beyond what it uses, to hold fewer waves than its
 // registers would let onto a SIMD: beyond 4096 workgroups more rows on their way are slower, not faster.  Pairs of heads
 // are held to six workgroups per compute unit (whole call, without / with: 8192 pairs 236 / 232 us in 4 bits, 231 / 225 in
@@ -2682,12 +2691,15 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
   // `fast`: the fp16 projection follows and wants its constants.
   auto launch_factor = [&](bool fast) {
     const int groups = pair_heads ? units / 2 : units;
-    if (pair_heads)
-      hipLaunchKernelGGL((decompose16_kernel<1, true, 0, false, 1>), dim3(groups), dim3(64), 0, st, *fmt, *cache, job,
-                         large_ws, unit_status, (int32_t*)nullptr);
-    else
-      hipLaunchKernelGGL((decompose16_kernel<1, false, 0, false, 1>), dim3(groups), dim3(64), 0, st, *fmt, *cache, job,
-                         large_ws, unit_status, (int32_t*)nullptr);
+    const bool cached = groups <= (fast ? kMostCachedFast : kMostCached);
+#define DQ_LAUNCH_GRAM(P_, C_)                                                                                       \
+  hipLaunchKernelGGL((decompose16_kernel<1, P_, 0, false, 1, false, C_>), dim3(groups), dim3(64), 0, st, *fmt, *cache, \
+                     job, large_ws, unit_status, (int32_t*)nullptr)
+    if (pair_heads && cached) DQ_LAUNCH_GRAM(true, true);
+    else if (pair_heads) DQ_LAUNCH_GRAM(true, false);
+    else if (cached) DQ_LAUNCH_GRAM(false, true);
+    else DQ_LAUNCH_GRAM(false, false);
+#undef DQ_LAUNCH_GRAM
 #define DQ_LAUNCH_SOLVE(R_, P_, F_)                                                                               \
   hipLaunchKernelGGL((solve16_kernel<R_, P_, F_>), dim3((groups + kSolveWaves * R_ / 2 - 1) / (kSolveWaves * R_ / 2)), \
                      dim3(64 * kSolveWaves), 0, st, *fmt,                                                         \
