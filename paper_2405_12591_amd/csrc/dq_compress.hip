@@ -981,13 +981,13 @@ __device__ __forceinline__ void team_barrier() {
   }
 }
 
-template <int QB, bool FULL, bool PAIR>
+template <int QB, bool FULL, bool PAIR, bool DIRECT>
 struct FastProject {
   static constexpr int QMAX = (1 << (QB - 1)) - 1, QMIN = FULL ? -QMAX - 1 : -QMAX, BIAS = 1 << (QB - 1);
   static constexpr float kMagic = 12582912.f + (float)BIAS;   // 1.5 * 2^23: the code + BIAS sits in the low bits of q + kMagic
   static constexpr uint32_t kMagicBits = 0x4B400000u;
   static constexpr int ROWB = 16 * QB, STRIDE = ROWB + 4;     // bytes of a value row of a tile, and of its place in LDS
-  static constexpr int kStageBytes = 128 * STRIDE, kRowBytes = 16 * 256;
+  static constexpr int kStageBytes = 128 * STRIDE, kRowBytes = DIRECT ? 0 : 16 * 256;
 
   f16x4 w0, w1, w2;  // row r = l % 16 of W, columns b1 = 4 j + l / 16, scaled by 2^(15 - e): three pieces
   float sc;          // 2^(e - 15) of row l % 16
@@ -1010,8 +1010,18 @@ struct FastProject {
   // accesses to the first-level cache, and each of its lines was asked for four times; in memory order no line is,
   // so that they can pass the caches by.  14720 blocks, steady clocks: 179 us in the other order (215 non-temporal),
   // 172 so, 148 non-temporal; two groups ahead instead of one 161.
+  // DIRECT: in the matrix cores' order all the same, pieces b1 = 4 j + l / 16 of token t0 + l % 16 (zero past the last row).
   __device__ __forceinline__ void load(u32x4 (&x)[4], int t0) const {
     const int l = threadIdx.x & 63;
+    if (DIRECT) {
+      const int t = t0 + (l & 15);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        x[j] = u32x4{0u, 0u, 0u, 0u};
+        if (t < nv) x[j] = *reinterpret_cast<const u32x4*>(piece(t, 4 * j + (l >> 4)));
+      }
+      return;
+    }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int t = t0 + 4 * u + (l >> 4);
@@ -1554,9 +1564,10 @@ __device__ __forceinline__ int dealt_unit(int wg, int n) {
 // the operand layout that lets a second matrix product contract over the eight tokens of a run
 // (T_2 = A V' diag(1/sigma')), and hands the rows of T_2 to the quantizer in the registers it
 // expects them in.  job.keep_large: the fp32 rows of T_2 also go to the workspace.
-// CACHED (PART 1): the rows are requested with plain loads (see kMostCached).
+// CACHED: PART 1 requests the rows with plain loads (see kMostCached), PART 3 (2 or 4 bits) in the matrix cores' order (see
+// kLeastDirect).
 template <int NWV, bool PAIR, int QB = 0, bool FULL = false, int PART = 0, bool N3 = false, bool CACHED = false>
-__global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? (PAIR || N3 || QB == 4 ? 3 : 4) : 2) void decompose16_kernel(dq_format fmt, dq_cache cache, CompressJob job,
+__global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? (!CACHED && (PAIR || N3 || QB == 4) ? 3 : 4) : 2) void decompose16_kernel(dq_format fmt, dq_cache cache, CompressJob job,
                                                                float* __restrict__ large_ws,
                                                                int32_t* __restrict__ unit_status,
                                                                int32_t* __restrict__ call_status) {
@@ -1648,7 +1659,7 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? (PAIR || N3 |
   // (a pair: one such area per head, of 64 channels each)
   constexpr int QT = LEAN ? 32 : kTileTokens;                // rows quantized and packed at a time
   constexpr int kHeadArea = QT * d + d * (pack_parts(QB ? QB : 8, QT) * QT * (QB ? QB : 8) / 32 + 1) * 4;
-  constexpr int kFieldBytes = FAST ? FastProject<QB == 2 ? 2 : 4, FULL, PAIR>::kStageBytes + FastProject<QB == 2 ? 2 : 4, FULL, PAIR>::kRowBytes : QB ? (PAIR ? 2 : 1) * kHeadArea : 16;
+  constexpr int kFieldBytes = FAST ? FastProject<QB == 2 ? 2 : 4, FULL, PAIR, CACHED>::kStageBytes + FastProject<QB == 2 ? 2 : 4, FULL, PAIR, CACHED>::kRowBytes : QB ? (PAIR ? 2 : 1) * kHeadArea : 16;
   // (the three launches: no matrices in LDS, but the second cut's)
   constexpr int kPoolBytes = LEAN ? (kMatBytes > kFieldBytes ? kMatBytes : kFieldBytes) : kMatBytes + kFieldBytes;
   __shared__ __attribute__((aligned(16))) unsigned char pool[kPoolBytes];
@@ -1718,7 +1729,7 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? (PAIR || N3 |
   }
 
   if constexpr (FAST) {
-    typedef FastProject<QB, FULL, PAIR> FP;
+    typedef FastProject<QB, FULL, PAIR, CACHED> FP;
     FP fp;
     fp.X = X; fp.nv = nv; fp.head_gap = head_gap; fp.one_group = !PAIR && g.groups == 1;
     fp.setup(gram_ws);
@@ -1758,12 +1769,12 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? (PAIR || N3 |
 #pragma unroll 1
         for (int t0 = 0; t0 < kTileTokens; t0 += 16) {
           u32x4 x[4] = {next[0], next[1], next[2], next[3]};
-          if (tile + t0 + 16 > nv) {   // (rows that are not there are zero)
+          if (!CACHED && tile + t0 + 16 > nv) {   // (rows that are not there are zero)
 #pragma unroll
             for (int u = 0; u < 4; ++u)
               if (tile + t0 + 4 * u + q4 >= nv) x[u] = u32x4{0u, 0u, 0u, 0u};
           }
-          FP::turn(x, stage + FP::kStageBytes);
+          if (!CACHED) FP::turn(x, stage + FP::kStageBytes);
           fp.load(next, tile + t0 + 16);   // (past the tile's end: read and dropped; past the rows: nothing is read)
           f32x4 acc[8];
           uint16_t sb;
@@ -2629,13 +2640,22 @@ static int waves_per_block(int groups, int want_waves) {
 // 82.7, 8192 285 / 300.
 constexpr int kMostCachedFast = 8192, kMostCached = 2048;
 
+// Workgroups of a prompt's projection (2 or 4 bits) that request their rows in the matrix cores' order: of these four fit a
+// SIMD, of those that turn their rows in LDS three, which takes launches of more than 2816 in two rounds instead of one.  It
+// matters where many tokens are settled in fp64 and a wave takes long; the rows still come from the last-level cache (see
+// kMostCachedFast), whose lines are asked for four times in this order.  Whole call in us, turned / direct, blocks with outlier
+// channels and blocks graded over three decades: 2048 blocks 67.5 / 68.1 and 131 / 130, 2816 94.1 / 94.1 and 183 / 183, 3072
+// 99.3 / 98.8 and 221 / 184, 4096 117 / 116 and 252 / 213, 6144 158 / 154 and 343 / 308, 8192 202 / 211 and 439 / 398;
+// pairs of heads, 4096 135 / 132 and 238 / 201, 5120 155 / 157 and 348 / 254.
+constexpr int kLeastDirect = 2817, kMostDirect = 6144;
+
 // LDS that a prompt's projection (2 or 4 bits) is given beyond what it uses, to hold fewer waves than its
-// registers would let onto a SIMD: beyond 4096 workgroups more rows on their way are slower, not faster.  Pairs of heads
+// registers would let onto a SIMD: beyond 6144 workgroups more rows on their way are slower, not faster.  Pairs of heads
 // are held to six workgroups per compute unit (whole call, without / with: 8192 pairs 236 / 232 us in 4 bits, 231 / 225 in
 // 2; 16384 pairs 423 / 416 and 419 / 408; 6000 pairs 190 / 184), 2-bit codes of 128 channels to twelve (32768 blocks 696 /
 // 683; 4-bit ones use that much LDS as it is).
 static size_t prompt_projection_pad(int groups, bool pair_heads, int bits) {
-  if (groups <= 4096 || bits == 8) return 0;
+  if (groups <= kMostDirect || bits == 8) return 0;
   const size_t per_cu = pair_heads ? 6 : 12, used = 128 * (16 * bits + 4) + 4096 + 1024;
   return 160 * 1024 / per_cu > used ? 160 * 1024 / per_cu - used : 0;
 }
@@ -2753,19 +2773,19 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
       hipLaunchKernelGGL((decompose16_kernel<N_, false, B_, false>), dim3(units), dim3(64 * N_), 0, st, *fmt,   \
                          *cache, job, large_ws, unit_status, status);                                           \
   } while (0)
-#define DQ_LAUNCH_FUSED_PART3(B_)                                                                                \
+#define DQ_LAUNCH_FUSED_PART3(B_, D_)                                                                              \
   do {                                                                                                          \
     if (pair_heads && fmt->levels)                                                                              \
-      hipLaunchKernelGGL((decompose16_kernel<1, true, B_, true, 3>), dim3(units / 2), dim3(64), pad, st, *fmt, \
+      hipLaunchKernelGGL((decompose16_kernel<1, true, B_, true, 3, false, D_>), dim3(units / 2), dim3(64), pad, st, *fmt, \
                          *cache, job, large_ws, unit_status, status);                                           \
     else if (pair_heads)                                                                                        \
-      hipLaunchKernelGGL((decompose16_kernel<1, true, B_, false, 3>), dim3(units / 2), dim3(64), pad, st,      \
+      hipLaunchKernelGGL((decompose16_kernel<1, true, B_, false, 3, false, D_>), dim3(units / 2), dim3(64), pad, st,      \
                          *fmt, *cache, job, large_ws, unit_status, status);                                     \
     else if (fmt->levels)                                                                                       \
-      hipLaunchKernelGGL((decompose16_kernel<1, false, B_, true, 3>), dim3(units), dim3(64), pad, st, *fmt,    \
+      hipLaunchKernelGGL((decompose16_kernel<1, false, B_, true, 3, false, D_>), dim3(units), dim3(64), pad, st, *fmt,    \
                          *cache, job, large_ws, unit_status, status);                                           \
     else                                                                                                        \
-      hipLaunchKernelGGL((decompose16_kernel<1, false, B_, false, 3>), dim3(units), dim3(64), pad, st, *fmt,   \
+      hipLaunchKernelGGL((decompose16_kernel<1, false, B_, false, 3, false, D_>), dim3(units), dim3(64), pad, st, *fmt,   \
                          *cache, job, large_ws, unit_status, status);                                           \
   } while (0)
     const int fused_groups = pair_heads ? units / 2 : units;
@@ -2773,9 +2793,12 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
     const size_t pad = prompt_projection_pad(fused_groups, pair_heads, fmt->bits);
     if (fused_waves == 0) {
       launch_factor(fmt->bits != 8);
-      if (fmt->bits == 2) DQ_LAUNCH_FUSED_PART3(2);
-      else if (fmt->bits == 4) DQ_LAUNCH_FUSED_PART3(4);
-      else DQ_LAUNCH_FUSED_PART3(8);
+      const bool direct = fused_groups >= kLeastDirect && fused_groups <= kMostDirect;
+      if (fmt->bits == 2 && direct) DQ_LAUNCH_FUSED_PART3(2, true);
+      else if (fmt->bits == 2) DQ_LAUNCH_FUSED_PART3(2, false);
+      else if (fmt->bits == 4 && direct) DQ_LAUNCH_FUSED_PART3(4, true);
+      else if (fmt->bits == 4) DQ_LAUNCH_FUSED_PART3(4, false);
+      else DQ_LAUNCH_FUSED_PART3(8, false);
     } else if (fused_waves == 4) {
       if (fmt->bits == 2) DQ_LAUNCH_FUSED(4, 2);
       else if (fmt->bits == 4) DQ_LAUNCH_FUSED(4, 4);

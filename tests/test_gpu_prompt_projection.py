@@ -95,3 +95,27 @@ def test_prompt_projection_on_blocks_that_strain_its_bound(kind, bits, group, di
         caches.append(cache)
     for name in caches[0].t:
         assert torch.equal(caches[1].t[name].view(torch.uint8), caches[0].t[name].view(torch.uint8)), name
+
+
+@pytest.mark.parametrize("groups", [2048, 2050, 2816, 2818, 6144, 6146, 8192, 8194])
+@pytest.mark.parametrize("bits,group,dim,levels", [(4, 128, 128, 0), (2, 64, 128, 1), (4, 64, 64, 1), (2, 64, 64, 0)])
+def test_prompt_projection_on_both_sides_of_its_launch_rules(bits, group, dim, levels, groups):
+    """Calls of up to 2048, 2816, 6144, 8192 and more workgroups take different builds: sequences of whole
+    and of ragged length, easy tokens and blocks that are settled in fp64 as a whole, against the rows kept."""
+    print("projection launch rules: %s" % ((bits, group, dim, levels, groups),), flush=True)
+    fmt = dq.Format(bits, group, dim, dim // 8, 8, 128, 1, levels)
+    g = torch.Generator(device=DEV).manual_seed(11)
+    nb, b, h = groups // 2, 1, 1 if dim == 128 else 2   # keys and values; a workgroup takes a pair of 64-channel heads
+    n = nb * 128
+    k = torch.cat([_rows("normal", b, h, n - 256 * 128, dim, g), _hard_rows("mixed3", b, h, 256 * 128, dim, g)], 2)
+    v = torch.cat([_hard_rows("channels3", b, h, 256 * 128, dim, g), _rows("outliers", b, h, n - 256 * 128, dim, g)], 2)
+    first = torch.zeros(b, dtype=torch.int32, device=DEV)
+    for valid in (n, n - 128 * 3 - 37):
+        caches = []
+        for keep in (True, False):
+            cache = dq.alloc_cache(fmt, b, h, nb, DEV, fill=0xA5)
+            ws = dq.compress_workspace(fmt, b, h, DEV, t_new=n)
+            dq.compress_kv_blocks(cache, k, v, first, torch.tensor([valid], dtype=torch.int32, device=DEV), ws, keep_large=keep)
+            caches.append(cache)
+        for name in caches[0].t:
+            assert torch.equal(caches[1].t[name].view(torch.uint8), caches[0].t[name].view(torch.uint8)), name
