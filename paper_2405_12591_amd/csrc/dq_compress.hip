@@ -1336,19 +1336,22 @@ struct GramSums {
       i32x4 q4;
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
-        int v[4], top[4];
+        int v[4];
+        uint32_t top[4];   // d4 in the low byte
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const float h = (float)__builtin_bit_cast(f16x2, (uint32_t)x[w >> 1][2 * (w & 1) + (i >> 1)])[i & 1];
-          const float t = __builtin_rintf(h * (1.f / 254.f));   // 0 up to 127, |h - 254 t| <= 127.1 beyond
-          const float big = fabsf(h) > kPlainMost ? t : 0.f;
-          v[i] = (int)(fmaf(-254.f, big, h) * 0x1p24f);
-          top[i] = (int)big;
+          // all exact: where d4 is not zero, x is a multiple of 2^-4, and |x - 254 d4| <= 127
+          constexpr float kRound = 12582912.f;   // 1.5 * 2^23: the nearest integer appears in the low bits
+          const float h = fmaf((float)__builtin_bit_cast(f16x2, (uint32_t)x[w >> 1][2 * (w & 1) + (i >> 1)])[i & 1], 0x1p24f, 0.f);
+          const float t = fmaf(h, 0x1p-24f / 254.f, kRound);
+          v[i] = (int)fmaf(t - kRound, -254.f * 0x1p24f, h);
+          top[i] = __builtin_bit_cast(uint32_t, t);
         }
         int d0, d1, d2, d3;
         cut(v, d0, d1, d2, d3);
         q[0][w] = d0; q[1][w] = d1; q[2][w] = d2; q[3][w] = d3;
-        q4[w] = (top[0] & 0xFF) | (top[1] & 0xFF) << 8 | (top[2] & 0xFF) << 16 | top[3] << 24;
+        q4[w] = (int)__builtin_amdgcn_perm(__builtin_amdgcn_perm(top[3], top[2], 0x0C0C0400u),
+                                           __builtin_amdgcn_perm(top[1], top[0], 0x0C0C0400u), 0x05040100u);
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i) f[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(q4, q[i], f[i], 0, 0, 0);
