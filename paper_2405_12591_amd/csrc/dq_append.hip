@@ -172,9 +172,13 @@ extern "C" int32_t dq_cache_append(const dq_format* fmt, dq_cache* cache, const 
   const int chunks = (n_rows + rpb - 1) / rpb;
   const dim3 grid((unsigned)(B * H * chunks));
   const int may_compress = (flags & DQ_APPEND_NO_COMPRESS) ? 0 : 1;
-  // A sequence's rows in one workgroup as long as a thread's share of them fits its registers: 8 pieces each of keys
-  // and values, i.e. one row of up to 128 heads of 128 channels.
-  if ((long)H * n_rows * (fmt->head_dim / 8) <= kFewPieces * kAppendThreads) {
+  // A sequence's rows in one workgroup: up to 1024 pieces always, up to what its registers hold (kFewPieces a thread: one row
+  // of 128 heads of 128 channels) where the other kernel would be 128 workgroups or more, whose tickets take longer than
+  // the copy.  Kernel times, ticket / one workgroup: 1 sequence of 8 heads and 1 row 3.1 / 1.9 us, of 64 heads 3.2 / 2.8, 64
+  // sequences of 32 heads 16.3 / 4.0; 2048 pieces in 16 workgroups 2.9 / 3.6, 32 3.4 / 4.1, 64 3.6 / 4.5, 128 4.2 / 4.6 to
+  // 5.3 / 4.6, 256 5.6 / 4.6 (8 tickets a sequence 4.4 / 4.8), 2048 16.0 / 5.5.
+  const long pieces = (long)H * n_rows * (fmt->head_dim / 8);
+  if (pieces <= 4 * kAppendThreads || (pieces <= kFewPieces * kAppendThreads && grid.x >= 128)) {
     if (fmt->head_dim == 128)
       hipLaunchKernelGGL(append_few_kernel<128>, dim3(B), dim3(kAppendThreads), 0, st, *fmt, H, cache->block_capacity,
                          state->k_tail, state->v_tail, state->tail_lens, state->seq_lens, k_rows, v_rows, n_rows,

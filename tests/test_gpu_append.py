@@ -263,10 +263,11 @@ def test_idle_and_filling_steps_of_any_size(bits, group, d, i3, batch, kvh):
 
 
 @pytest.mark.parametrize("heads,n,d", [(8, 1, 128), (128, 1, 128), (130, 1, 128), (8, 16, 128), (8, 17, 128), (3, 7, 64),
-                                       (1, 1, 64), (2, 128, 64), (2, 129, 64)])
+                                       (1, 1, 64), (2, 128, 64), (2, 129, 64), (8, 8, 128), (13, 5, 128), (16, 5, 128),
+                                       (15, 8, 128), (16, 8, 128), (32, 16, 64)])
 def test_rows_and_lengths_on_both_sides_of_the_one_workgroup_limit(heads, n, d):
-    """One workgroup per sequence copies up to 2048 pieces of 16 bytes (heads * n * d / 8), larger calls take a
-    workgroup per head and chunk: tails, lengths and status of either, from empty, ordinary, nearly full and
+    """One workgroup per sequence copies up to 1024 pieces of 16 bytes (heads * n * d / 8), or 2048 where the other way would
+    be 128 workgroups or more (here: 16 heads); other calls take a workgroup per head and chunk: tails, lengths and status of either, from empty, ordinary, nearly full and
     full tails, with and without a free slot, against the policy written out on the host."""
     tb, nb = 256, 2
     _say("append: %d heads, %d rows, d=%d" % (heads, n, d))
