@@ -648,8 +648,8 @@ __device__ __forceinline__ void jacobi_rotation(double app, double aqq, double a
 // normalised columns are the eigenvectors and the columns' norms the eigenvalues; no matrix of
 // accumulated rotations is needed.  A lane holds a pair of columns (x, y) and derives their
 // rotation once; eight lanes hold the sixteen columns.  ROWS of the sixteen rows sit in a lane:
-// ROWS = 2 spreads one block over the wave (lane = pair + 8 * row group; the shortest chain),
-// ROWS = 16 works eight blocks per wave (lane = pair + 8 * block; no sum over lanes, every
+// ROWS = 2 spreads one block over the wave (lane = pair + 8 * row group; the shortest chain), ROWS = 4 and 8 two and
+// four, ROWS = 16 works eight blocks per wave (lane = pair + 8 * block; no sum over lanes, every
 // rotation derived once per block).  Between rounds the y columns move to another lane of the eight
 // by a data-parallel-primitive pattern, so a round touches no LDS at all: on one wave per SIMD, which
 // issues an instruction every 5.3 cycles whatever it is, a round of about 55 instructions takes 320
@@ -1550,7 +1550,7 @@ __device__ __forceinline__ int dealt_unit(int wg, int n) {
 // write-back or invalidation is needed between the XCDs.
 // PART: calls of thousands of blocks (a prompt) are bound by throughput, not by one block's latency, and
 // run as three launches, each with one wave per block or less and several waves per SIMD: PART 1 is the
-// Gram matrix alone (left in the block's region of the workspace), then solve16_kernel, eight blocks
+// Gram matrix alone (left in the block's region of the workspace), then solve16_kernel, two to eight blocks
 // per wave, then PART 3, the projection and quantizer.  In one launch every block derives each of its
 // rotations in eight lanes at once and its solver, a chain of dependent instructions, holds the
 // registers of the contractions.  The arithmetic, and so every bit written, is that of the other builds.
@@ -2634,6 +2634,13 @@ static int waves_per_block(int groups, int want_waves) {
   return groups <= 512 ? 4 : groups <= 1024 ? 2 : 0;
 }
 
+// Blocks per wave of the eigen-solver's launch: two up to kMostTwoBlocks blocks, four up to kMostFourBlocks, eight beyond.  More
+// blocks share a wave's instructions, fewer give more waves, and the launch takes whole rounds of the chip's 1024 SIMDs.
+// Whole call in us, 4 bits, two / four blocks per wave: 4352 blocks 133.3 / 132.3, 7168 184.7 / 172.3, 8192 204.5 / 192.0,
+// graded over three decades 428 / 401, 4096 pairs of heads 226 / 214, 8192 blocks in 8 bits 284 / 269; four / eight: 8448
+// 224 / 237, 9216 237 / 254, 12288 286 / 303, 14336 333 / 333, 16384 364 / 369, 32768 686 / 682, graded 1462 / 1387.
+constexpr int kMostTwoBlocks = 4096, kMostFourBlocks = 16384;
+
 // Blocks (of sixteen rows of channels: pairs of 64-channel heads count once) up to which the Gram matrices' launch requests
 // its rows with plain loads: the projection then finds them in the 256 MB last-level cache, 32 KB a block (kMostCachedFast: 2- and
 // 4-bit codes).  Where the rows do not fit, or the fp32 rows, 64 KB a block, displace them (kMostCached: kept large tensors;
@@ -2707,11 +2714,7 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
   // quantizer); larger calls, and a forced wave count of one, take the one-kernel build.
   const bool fused3 = fmt->i3 == kRun && fmt->i1 == 1 && !force_general && fmt->head_dim == 128 && fmt->j1 == 16 &&
                       (fmt->group == 128 || fmt->group == 64) && (want_waves == 1 || (want_waves == 0 && units > 512));
-  // The first two launches of a call of thousands of blocks: Gram matrices, eigen-solver.  Eight blocks per
-  // solver wave need 8192 blocks to put a wave on every SIMD; up to there two blocks per wave are as fast
-  // or faster (whole call, two / eight blocks per wave: 1280 blocks 90 / 121 us, 2560 129 / 138, 8192
-  // 291 / 292, 16384 545 / 517).
-  // `fast`: the fp16 projection follows and wants its constants.
+  // The first two launches of a call of thousands of blocks: Gram matrices, eigen-solver.  `fast`: the fp16 projection follows and wants its constants.
   auto launch_factor = [&](bool fast) {
     const int groups = pair_heads ? units / 2 : units;
     const bool cached = groups <= (fast ? kMostCachedFast : kMostCached);
@@ -2732,9 +2735,12 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
     if (fast) DQ_LAUNCH_SOLVE(R_, P_, true); \
     else DQ_LAUNCH_SOLVE(R_, P_, false);   \
   } while (0)
-    if (groups > 8192) {
+    if (groups > kMostFourBlocks) {
       if (pair_heads) DQ_LAUNCH_SOLVE_F(16, true);
       else DQ_LAUNCH_SOLVE_F(16, false);
+    } else if (groups > kMostTwoBlocks) {
+      if (pair_heads) DQ_LAUNCH_SOLVE_F(8, true);
+      else DQ_LAUNCH_SOLVE_F(8, false);
     } else {
       if (pair_heads) DQ_LAUNCH_SOLVE_F(4, true);
       else DQ_LAUNCH_SOLVE_F(4, false);

@@ -167,20 +167,21 @@ def test_the_lean_build_for_large_calls_writes_the_same_bits(bits, group, levels
         assert torch.equal(status, out[0][1])
 
 
+@pytest.mark.parametrize("nb", [9, 17, 34])
 @pytest.mark.parametrize("bits,group,levels,d,keep", [(4, 128, 0, 128, False), (2, 64, 1, 128, True), (4, 64, 0, 64, False)])
-def test_calls_of_more_than_8192_blocks_write_the_bits_of_small_ones(bits, group, levels, d, keep):
-    """Above 8192 blocks (pairs of 64-channel heads) the eigen-solver works eight blocks per wave.  8330 of them, not a
-    multiple of what a workgroup takes, ragged rows and skipped sequences among them: cache and status
-    words must be those of one small call per block position (four waves per block)."""
-    batch, kvh, nb = 5, 98 if d == 64 else 49, 17
+def test_calls_of_more_than_8192_blocks_write_the_bits_of_small_ones(bits, group, levels, d, keep, nb):
+    """Above 4096 blocks (pairs of 64-channel heads) the eigen-solver works four blocks per wave, above 16384 eight.  4410, 8330
+    and 16660 of them, not a multiple of what a workgroup takes, ragged rows and skipped sequences among them: cache and
+    status words must be those of one small call per block position (four waves per block)."""
+    batch, kvh = 5, 98 if d == 64 else 49
     n = nb * 128 - 50
-    _say("8330 blocks: bits=%d G=%d levels=%d d=%d keep=%s" % (bits, group, levels, d, keep))
+    _say("490 x %d blocks: bits=%d G=%d levels=%d d=%d keep=%s" % (nb, bits, group, levels, d, keep))
     fmt = dq.Format(bits, group, d, d // 8, 8, 128, 1, levels)
     gen = torch.Generator(device=DEV).manual_seed(12)
     k, v = (torch.randn((batch, kvh, n, d), device=DEV, generator=gen).half() for _ in "kv")
     for x in (k, v):
         x[..., 7] *= 20
-    rows = [n, 9 * 128 + 1, n, 3 * 128, n - 100]
+    rows = [n, min(9 * 128 + 1, n), n, 3 * 128, n - 100]
     first = [0, 1, -1, 0, 0]
     valid, slot = (torch.tensor(t, dtype=torch.int32, device=DEV) for t in (rows, first))
     large, small = (dq.alloc_cache(fmt, batch, kvh, nb, DEV, fill=0xA5) for _ in range(2))

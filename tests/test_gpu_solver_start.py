@@ -43,8 +43,8 @@ def test_blocks_come_out_orthonormal_whatever_they_start_from(kind, dim):
     k, v = _rows(kind, h, dim, g), _rows(kind, h, dim, g)
     first = torch.zeros(1, dtype=torch.int32, device=DEV)
     seen = []
-    # 2 and 4 waves: one block per solver wave; 1: two; many copies of the heads (8220 blocks): eight
-    for waves, copies in ((4, 1), (2, 1), (1, 1), (0, 411)):
+    # 2 and 4 waves: one block per solver wave; 1: two; many copies of the heads: four (8220 blocks) and eight (16400)
+    for waves, copies in ((4, 1), (2, 1), (1, 1), (0, 411), (0, 820)):
         kk, vv = (t.repeat(copies, 1, 1)[None].contiguous() for t in (k, v))
         if dim == 64 and copies > 1:
             kk, vv = (t.repeat(1, 2, 1, 1) for t in (kk, vv))
