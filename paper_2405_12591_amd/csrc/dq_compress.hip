@@ -1768,17 +1768,25 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? (!CACHED && (
           listed += __builtin_popcount(tokens);
         };
         u32x4 next[4];
-        fp.load(next, tile);
+        auto request = [&](int t) __attribute__((always_inline)) {   // sixteen tokens of the tile, if there are any
+          if (t < min(tile + kTileTokens, nv)) {
+            fp.load(next, t);
+          } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) next[u] = u32x4{0u, 0u, 0u, 0u};
+          }
+        };
+        request(tile);
 #pragma unroll 1
         for (int t0 = 0; t0 < kTileTokens; t0 += 16) {
           u32x4 x[4] = {next[0], next[1], next[2], next[3]};
-          if (!CACHED && tile + t0 + 16 > nv) {   // (rows that are not there are zero)
+          if (!CACHED && tile + t0 + 16 > nv) {   // (the last row stands in for those that are not there: they are zero)
 #pragma unroll
             for (int u = 0; u < 4; ++u)
               if (tile + t0 + 4 * u + q4 >= nv) x[u] = u32x4{0u, 0u, 0u, 0u};
           }
           if (!CACHED) FP::turn(x, stage + FP::kStageBytes);
-          fp.load(next, tile + t0 + 16);   // (past the tile's end: read and dropped; past the rows: nothing is read)
+          request(tile + t0 + 16);
           f32x4 acc[8];
           uint16_t sb;
           if (!which) {
