@@ -267,7 +267,7 @@ int32_t dq_compress_kv(const dq_format* fmt, dq_cache* cache, const uint16_t* k_
  * the cache is quantized block by block; every block is decomposed on its own): t_new >= 1 rows,
  * cut into ceil(t_new / T_b) blocks of T_b rows, block j going to slot blk_idx[b] + j.  Same
  * arguments and results as dq_compress_kv, whose kernels it shares (a block's bits do not depend on
- * the call that wrote it), with these differences: the workspace holds the fp32 large tensors of
+ * the call that wrote it; where values beyond 32256 make the Gram matrix a rounded sum, its last bits may), with these differences: the workspace holds the fp32 large tensors of
  * all blocks ([B*H*blocks*2, T_b, d], K block j of (b, h) at index 2*((b*H+h)*blocks + j)) and is
  * sized by dq_compress_blocks_workspace_bytes; a block whose slot falls outside the cache or none
  * of whose rows is valid (rows >= n_valid[b]) is not written.  At most 2^22 blocks per call, keys

@@ -1280,7 +1280,8 @@ struct FastProject {
 // once, and G does not depend on the number of waves or the order of the sums, whatever the size of the block (a sum of
 // squares beyond 2^30 whose rows hold values of 127.5 and more has more bits than the high half holds: it takes up to
 // three roundings more each time the accumulators are drained).  A block that holds values
-// beyond kMostDigits (infinities and NaN among them) takes the fp64 matrix instructions below.
+// beyond kMostDigits (infinities and NaN among them) takes the fp64 matrix instructions below, whose sums round, in an
+// order that depends on the number of waves.
 // Bound by vector instructions: six and a half an element, and 160 matrix instructions of 16 cycles a block, where
 // the fp64 matrix cores take two an element and 256 of 64 cycles (and round their sums).
 typedef int i32x4 __attribute__((ext_vector_type(4)));
@@ -1526,7 +1527,7 @@ __device__ __forceinline__ void gram16(const uint16_t* __restrict__ X, int nv, l
 // its four shader engines, whatever these have left to do, so workgroup wg runs on engine wg % 32.  Keys and values
 // (units 2 i and 2 i + 1), which take 25 and 32 us a wave, and the blocks past a sequence's end would each fall to the
 // same few engines; a group of 32 units is dealt five places further on than the one before it.
-// 14720 of 16384 blocks valid: Gram matrices 99 us, 103 in plain order.
+// 14720 of 16384 blocks valid: projection 149 us, 160 in plain order.
 __device__ __forceinline__ int dealt_unit(int wg, int n) {
   return wg < (n & ~31) ? (wg & ~31) | ((wg + 5 * (wg >> 5)) & 31) : wg;
 }
@@ -1554,8 +1555,8 @@ __device__ __forceinline__ int dealt_unit(int wg, int n) {
 // per wave, then PART 3, the projection and quantizer.  In one launch every block derives each of its
 // rotations in eight lanes at once and its solver, a chain of dependent instructions, holds the
 // registers of the contractions.  The arithmetic, and so every bit written, is that of the other builds.
-// 14720 blocks (4-bit, d = 128): 670 us in one launch, 163 + 100 + 280 us in three when both contractions were fp64 and the
-// sweeps double, 103 + 103 + 148 now (steady clocks).
+// 14720 blocks (4-bit, d = 128): 670 us in one launch, 163 + 100 + 280 us in three when both contractions were fp64, 98 + 100 +
+// 146 now (steady clocks).
 // Launch bounds: one launch (PART 0) asks for two waves per SIMD, or its products' accumulators go to registers of
 // their own and calls of more than one workgroup a compute unit hold one (1024 blocks of 64 channels, 8 bits: 56 us, 37).
 // N3 (PART 3 with the quantizer, d = 128): three local tensors (Eq. 2 with n = 3, factor shapes

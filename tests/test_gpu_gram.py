@@ -22,7 +22,7 @@ def _rows(kind, shape, g):
     elif kind == "edges":
         pick = torch.tensor(EDGES, device=DEV)[torch.randint(len(EDGES), shape, device=DEV, generator=g)]
         x = pick * x.sign()
-    elif kind == "equal":          # every sum of products of digits at its largest
+    elif kind == "equal":          # the largest value without a fifth digit, everywhere: a block of rank one
         x = torch.full(shape, -127.4375, device=DEV)
     elif kind == "last":
         x[..., 5] = 32256
@@ -101,7 +101,7 @@ def _exact_long(x, j1):
 
 
 @pytest.mark.parametrize("tokens", [257, 8191, 16512])
-@pytest.mark.parametrize("kind", ["half", "tiny", "wide", "small_by_large", "normal", "edges"])
+@pytest.mark.parametrize("kind", ["half", "tiny", "wide", "top", "small_by_large", "normal", "edges"])
 def test_gram_matrix_of_long_blocks(kind, tokens):
     """The products of digits are summed in 32 bits.  One digit of -128 throughout (a half) passes 2^31 at 16384
     tokens of a wave, other values later; a block may have any multiple of 128 tokens.  257 tokens: the first that a
@@ -113,7 +113,8 @@ def test_gram_matrix_of_long_blocks(kind, tokens):
     shape = (1, 2, tokens, 128)
     fill = {"half": 0.5,                      # the third digit is -128
             "tiny": -32896 * 2.0 ** -24,      # the two lowest digits are
-            "wide": 126.5}                    # the third -128, the fourth 127
+            "wide": 126.5,                    # the third -128, the fourth 127
+            "top": 31872.0}                   # the fifth 125, the fourth 122
     if kind in fill:
         k = torch.full(shape, fill[kind], device=DEV)
     elif kind == "small_by_large":            # the two products of the middle weight at their largest together
@@ -137,7 +138,7 @@ def test_gram_matrix_of_long_blocks(kind, tokens):
         for which, src in enumerate((k, v)):
             want = _exact_long(src[0, h].cpu().numpy(), 16)
             got = part[h, which].reshape(16, 16)
-            if kind == "edges":   # rows with values beyond 127.5: every part of 256 tokens may round three times
+            if kind in ("edges", "top"):   # rows with values beyond 127.5: every part of 256 tokens may round three times
                 size = np.sqrt(np.outer(np.diag(want), np.diag(want)))
                 assert (np.abs(got - want) <= (3 * -(-tokens // 256) + 1) * 2.0 ** -53 * size).all(), (h, which)
             else:
