@@ -98,15 +98,19 @@ __host__ __device__ inline uint16_t f64_to_f16_rne(double x, bool saturate, bool
   const float f = (float)x;
   const double e = x - (double)f;                       // what the first rounding dropped
   uint32_t bits = __builtin_bit_cast(uint32_t, f);
-  const bool away = (e > 0.0) == (f > 0.f);             // x lies further from zero than f
-  const bool inexact = e > 0.0 || e < 0.0;              // (false for infinities, whose e is a NaN)
-  if (inexact && f != 0.f && !(bits & 1u)) bits += away ? 1u : 0xFFFFFFFFu;
+  // even and not exact (an infinity, whose e is a NaN, is): one further from zero where x is (e and f, a zero too, have the same
+  // sign), one nearer otherwise.  No branches: a solver's lane converts 32 values in a row.
+  const uint32_t unlike = (uint32_t)(__builtin_bit_cast(uint64_t, e) >> 32) ^ bits;
+  const bool move = ((e > 0.0) | (e < 0.0)) & !(bits & 1u);
+  bits += move ? (uint32_t)((int32_t)unlike >> 31) | 1u : 0u;
   const float odd = __builtin_bit_cast(float, bits);
-  if (saturate && __builtin_fabsf(odd) >= 65520.f) {    // rounds to infinity
-    if (saturated) *saturated = true;
-    return (uint16_t)(((bits >> 16) & 0x8000u) | 0x7BFFu);
+  uint16_t h = f2h_rne(odd);
+  if (saturate) {
+    const bool over = __builtin_fabsf(odd) >= 65520.f;  // rounds to infinity
+    if (saturated) *saturated |= over;
+    h = over ? (uint16_t)((h & 0x8000u) | 0x7BFFu) : h;
   }
-  return f2h_rne(odd);
+  return h;
 }
 
 }  // namespace dq

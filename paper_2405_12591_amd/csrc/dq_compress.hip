@@ -706,64 +706,90 @@ __device__ __forceinline__ double dot16(const double (&u)[ROWS], const double (&
 
 constexpr int kMostSweeps = 24;
 
+// Make a pair's columns orthogonal.  tan of the angle is 2 x.y over d + sign(d) sqrt(d^2 + (2 x.y)^2)
+// with d the difference of the squared norms a, b; hardware estimates (about 1e-7) do for it: what is
+// left of x.y shrinks by that factor and the next sweep deals with it.  cos gets a Newton step, so that
+// rotations stay orthogonal to 1e-14.  The tiny addend keeps a pair of zero columns (0 / 0) from
+// producing a NaN and is far below any pair that matters.  TEST: report whether the pair was
+// still apart (the first sweeps do not ask); `floor`: squared norm below which that does not matter.
+template <int ROWS, bool TEST>
+__device__ __forceinline__ void rotate_pair(double (&x)[ROWS], double (&y)[ROWS], double& a, double& b, double floor, bool& unsettled) {
+  const double g = dot16<ROWS>(x, y);
+  if (TEST) unsettled |= (g * g > kSettled2 * (a * b)) & (a > floor) & (b > floor);
+  const double d = b - a, g2 = g + g;
+  const double root = __builtin_amdgcn_sqrt(fma(g2, g2, fma(d, d, 1e-240)));
+  const double t = g2 * __builtin_amdgcn_rcp(d + copysign(root, d));
+  const double w = fma(t, t, 1.0);
+  const double r0 = __builtin_amdgcn_rsq(w);
+  const double c = r0 * fma(-0.5 * w, r0 * r0, 1.5);
+  const double tc = t * c;
+#pragma unroll
+  for (int i = 0; i < ROWS; ++i) {
+    const double xi = x[i], yi = y[i];
+    x[i] = fma(-tc, yi, c * xi);
+    y[i] = fma(tc, xi, c * yi);
+  }
+  a = fma(-t, g, a);
+  b = fma(t, g, b);
+}
+
+// The sum over the eight places of a column pair (DPP lanes 0..7 of each eight).
+__device__ __forceinline__ double over_eight(double v) {
+  v += dpp_d<kDppXor1>(v);
+  v += dpp_d<kDppXor2>(v);
+  return v + dpp_d<kDppXor7>(v);
+}
+
+// a, or b where the lane's bit of `mask` is set.  The select that names VCC takes 9.5 ns where several follow each other (1.85 in
+// the form with a pair of scalar registers, which the compiler gives up for the shorter one wherever it can).
+__device__ __forceinline__ int select_i(unsigned long long mask, int a, int b) {
+  int r;
+  asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(mask));
+  return r;
+}
+__device__ __forceinline__ double select_d(unsigned long long mask, double a, double b) {
+  const u32x2 u = __builtin_bit_cast(u32x2, a), v = __builtin_bit_cast(u32x2, b);
+  return __builtin_bit_cast(double, u32x2{(unsigned)select_i(mask, (int)u.x, (int)v.x), (unsigned)select_i(mask, (int)u.y, (int)v.y)});
+}
+
 template <int ROWS>
 struct Jacobi16 {
   double x[ROWS], y[ROWS];   // the lane's rows of its two columns
   double a, b;               // their squared norms
-  int ix, iy;                // which columns they are
+  int ix, iy;                // what they are ranked by: where they end up or (a pair of heads) where they began, which tells the head
 
-  template <int CTRL>
+  template <int CTRL, bool PAIR>
   __device__ __forceinline__ void move() {   // the y columns to lane ^ mask
 #pragma unroll
     for (int i = 0; i < ROWS; ++i) y[i] = dpp_d<CTRL>(y[i]);
     b = dpp_d<CTRL>(b);
-    iy = __builtin_amdgcn_update_dpp(0, iy, CTRL, 0xF, 0xF, true);
+    if (PAIR) iy = __builtin_amdgcn_update_dpp(0, iy, CTRL, 0xF, 0xF, true);
   }
-  // The lanes whose `upper` is false collect the x columns of both partners (lane, lane ^ mask), the
+  // The lanes whose bit of `upper` is not set collect the x columns of both partners (lane, lane ^ mask), the
   // others the y columns.
-  template <int CTRL>
-  __device__ __forceinline__ void split(bool upper) {
+  template <int CTRL, bool PAIR>
+  __device__ __forceinline__ void split(unsigned long long upper) {
+    auto cross = [&](double& u, double& v) __attribute__((always_inline)) {
+      const double uo = dpp_d<CTRL>(u), vo = dpp_d<CTRL>(v);
+      u = select_d(upper, u, vo);
+      v = select_d(upper, uo, v);
+    };
 #pragma unroll
-    for (int i = 0; i < ROWS; ++i) {
-      const double xo = dpp_d<CTRL>(x[i]), yo = dpp_d<CTRL>(y[i]);
-      x[i] = upper ? yo : x[i];
-      y[i] = upper ? y[i] : xo;
+    for (int i = 0; i < ROWS; ++i) cross(x[i], y[i]);
+    cross(a, b);
+    if (PAIR) {
+      const int ixo = __builtin_amdgcn_update_dpp(0, ix, CTRL, 0xF, 0xF, true);
+      const int iyo = __builtin_amdgcn_update_dpp(0, iy, CTRL, 0xF, 0xF, true);
+      ix = select_i(upper, ix, iyo);
+      iy = select_i(upper, ixo, iy);
     }
-    const double ao = dpp_d<CTRL>(a), bo = dpp_d<CTRL>(b);
-    a = upper ? bo : a;
-    b = upper ? b : ao;
-    const int ixo = __builtin_amdgcn_update_dpp(0, ix, CTRL, 0xF, 0xF, true);
-    const int iyo = __builtin_amdgcn_update_dpp(0, iy, CTRL, 0xF, 0xF, true);
-    ix = upper ? iyo : ix;
-    iy = upper ? iy : ixo;
   }
 
-  // Make the pair's columns orthogonal.  tan of the angle is 2 x.y over d + sign(d) sqrt(d^2 + (2 x.y)^2)
-  // with d the difference of the squared norms; hardware estimates (about 1e-7) do for it: what is
-  // left of x.y shrinks by that factor and the next sweep deals with it.  cos gets a Newton step, so that
-  // rotations stay orthogonal to 1e-14.  The tiny addend keeps a pair of zero columns (0 / 0) from
-  // producing a NaN and is far below any pair that matters.  TEST: report whether the pair was
-  // still apart (the first sweeps do not ask).  PAIR: the floor of the columns' own head counts (two
-  // columns of different heads have no row in common: g is zero and nothing is to settle).
+  // PAIR: the floor of the columns' own head counts (two columns of different heads have no row in common: their
+  // product is zero and nothing is to settle).
   template <bool TEST, bool PAIR>
   __device__ __forceinline__ void rotate(double floor_lo, double floor_hi, bool& unsettled) {
-    const double g = dot16<ROWS>(x, y);
-    if (TEST) unsettled |= (g * g > kSettled2 * (a * b)) && (fmin(a, b) > ((PAIR && ix >= 8) ? floor_hi : floor_lo));
-    const double d = b - a, g2 = g + g;
-    const double root = __builtin_amdgcn_sqrt(fma(g2, g2, fma(d, d, 1e-240)));
-    const double t = g2 * __builtin_amdgcn_rcp(d + copysign(root, d));
-    const double w = fma(t, t, 1.0);
-    const double r0 = __builtin_amdgcn_rsq(w);
-    const double c = r0 * fma(-0.5 * w, r0 * r0, 1.5);
-    const double tc = t * c;
-#pragma unroll
-    for (int i = 0; i < ROWS; ++i) {
-      const double xi = x[i], yi = y[i];
-      x[i] = fma(-tc, yi, c * xi);
-      y[i] = fma(tc, xi, c * yi);
-    }
-    a = fma(-t, g, a);
-    b = fma(t, g, b);
+    rotate_pair<ROWS, TEST>(x, y, a, b, (PAIR && ix >= 8) ? floor_hi : floor_lo, unsettled);
   }
 
   // Fifteen rounds of eight disjoint pairs: x columns against y columns, then the two halves of each
@@ -771,22 +797,22 @@ struct Jacobi16 {
   // that leave the columns where the next sweep can start from them, this one converges soonest (5.9
   // sweeps on the synthetic workloads' blocks; with the first eight rounds the other way round, 6.9).
   template <bool TEST, bool PAIR>
-  __device__ __forceinline__ void sweep(int j, double floor_lo, double floor_hi, bool& unsettled) {
-    move<kDppXor7>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
-    move<kDppXor3>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
-    move<kDppXor1>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
-    move<kDppXor3>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
-    move<kDppXor7>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
-    move<kDppXor3>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
-    move<kDppXor1>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
-    move<kDppXor3>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
-    split<kDppXor7>((j & 4) != 0); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
-    move<kDppXor1>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
-    move<kDppXor2>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
-    move<kDppXor1>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
-    split<kDppXor3>((j & 2) != 0); move<kDppXor1>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
-    move<kDppXor1>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
-    split<kDppXor1>((j & 1) != 0); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+  __device__ __forceinline__ void sweep(double floor_lo, double floor_hi, bool& unsettled) {
+    move<kDppXor7, PAIR>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    move<kDppXor3, PAIR>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    move<kDppXor1, PAIR>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    move<kDppXor3, PAIR>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    move<kDppXor7, PAIR>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    move<kDppXor3, PAIR>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    move<kDppXor1, PAIR>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    move<kDppXor3, PAIR>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    split<kDppXor7, PAIR>(0xF0F0F0F0F0F0F0F0ull); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    move<kDppXor1, PAIR>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    move<kDppXor2, PAIR>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    move<kDppXor1, PAIR>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    split<kDppXor3, PAIR>(0xCCCCCCCCCCCCCCCCull); move<kDppXor1, PAIR>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    move<kDppXor1, PAIR>(); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
+    split<kDppXor1, PAIR>(0xAAAAAAAAAAAAAAAAull); rotate<TEST, PAIR>(floor_lo, floor_hi, unsettled);
   }
 
   // Called with x = column j, y = column j + 8 of the matrix, j = lane % 8.  Returns the sweeps used.  All
@@ -801,22 +827,13 @@ struct Jacobi16 {
     // does not matter.  (A pair: of the largest of the same head, as order() drops them.  x are the first
     // head's columns here, y the second's.  One floor over both left a head a thousand times smaller
     // than its partner unsettled: up to 88 % of its block lost where its singular values span 1e5.)
-    double tr_lo = PAIR ? a : a + b, tr_hi = b;
-    tr_lo += dpp_d<kDppXor1>(tr_lo);
-    tr_lo += dpp_d<kDppXor2>(tr_lo);
-    tr_lo += dpp_d<kDppXor7>(tr_lo);
-    if (PAIR) {
-      tr_hi += dpp_d<kDppXor1>(tr_hi);
-      tr_hi += dpp_d<kDppXor2>(tr_hi);
-      tr_hi += dpp_d<kDppXor7>(tr_hi);
-    }
-    const double floor_lo = tr_lo * 1e-28, floor_hi = tr_hi * 1e-28;
+    const double floor_lo = over_eight(PAIR ? a : a + b) * 1e-28, floor_hi = PAIR ? over_eight(b) * 1e-28 : 0.0;
     bool unsettled = true;
     int sweeps = 0;
     // no block with anything off the diagonal settles in three sweeps: they do not test
     while (sweeps < 3) {
       ++sweeps;
-      sweep<false, PAIR>(j, floor_lo, floor_hi, unsettled);
+      sweep<false, PAIR>(floor_lo, floor_hi, unsettled);
       a = dot16<ROWS>(x, x);
       b = dot16<ROWS>(y, y);
     }
@@ -824,7 +841,7 @@ struct Jacobi16 {
     while (unsettled && sweeps < kMostSweeps) {
       ++sweeps;
       unsettled = false;
-      sweep<true, PAIR>(j, floor_lo, floor_hi, unsettled);
+      sweep<true, PAIR>(floor_lo, floor_hi, unsettled);
       a = dot16<ROWS>(x, x);
       b = dot16<ROWS>(y, y);
       // every pair of this sweep was within 3e-5 of orthogonal when it was rotated, so the sweep (one
@@ -860,8 +877,8 @@ struct Jacobi16 {
       const int s = row0 + i;
       const double o = lam[s];
       const bool sx = !PAIR || (s >> 3) == (ix >> 3), sy = !PAIR || (s >> 3) == (iy >> 3);
-      places += (sx && (o > lx || (o == lx && s < ix))) ? 1 : 0;
-      places += (sy && (o > ly || (o == ly && s < iy))) ? 0x10000 : 0;
+      places += (sx & ((o > lx) | ((o == lx) & (s < ix)))) ? 1 : 0;
+      places += (sy & ((o > ly) | ((o == ly) & (s < iy)))) ? 0x10000 : 0;
       mx = sx ? fmax(mx, o) : mx;
       if (PAIR) my = sy ? fmax(my, o) : my;
     }
@@ -870,20 +887,16 @@ struct Jacobi16 {
       mx = fmax(mx, dpp_d<kDppXor8>(mx));
       if (PAIR) my = fmax(my, dpp_d<kDppXor8>(my));
     }
-    if (ROWS <= 4) {
-      places += __shfl_xor(places, 16);
-      mx = fmax(mx, __shfl_xor(mx, 16));
-      if (PAIR) my = fmax(my, __shfl_xor(my, 16));
-    }
-    if (ROWS <= 2) {
-      places += __shfl_xor(places, 32);
-      mx = fmax(mx, __shfl_xor(mx, 32));
-      if (PAIR) my = fmax(my, __shfl_xor(my, 32));
+#pragma unroll
+    for (int o = 16; o < 128 / ROWS; o <<= 1) {
+      places += __shfl_xor(places, o);
+      mx = fmax(mx, __shfl_xor(mx, o));
+      if (PAIR) my = fmax(my, __shfl_xor(my, o));
     }
     if (!PAIR) my = mx;
     px = (places & 0xFFFF) + (PAIR ? (ix & 8) : 0);
     py = (places >> 16) + (PAIR ? (iy & 8) : 0);
-    const bool kx = lx > 1e-12 * mx && lx > 0.0, ky = ly > 1e-12 * my && ly > 0.0;
+    const bool kx = (lx > 1e-12 * mx) & (lx > 0.0), ky = (ly > 1e-12 * my) & (ly > 0.0);
     rx = kx ? fast_rsqrt(lx) : 0.0;
     ry = ky ? fast_rsqrt(ly) : 0.0;
     if (!kx) lx = 0.0;
@@ -2204,15 +2217,17 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? (!CACHED && (
 
 // The constants of FastProject, from the solver's registers (a lane: ROWS of the rows b1 of two columns of W^T, places
 // px and py; their sums cross eight lanes at most, where the projection's wave, one block in 64 lanes, took 850
-// instructions for them, a fifth of its own: 14720 blocks 177 us for the projection, 193 before, and 7 more here): the three fp16 pieces
-// of W scaled by 2^(15 - e), |W[r]| < 2^e, as [piece][b1 % 4][r][b1 / 4]; 2^(e - 15) of every row; eps, eps_abs, hard.
+// instructions for them, a fifth of its own: 14720 blocks 177 us for the projection, 193 before, and 7 more here then): the three fp16 pieces
+// of W scaled by 2^(15 - e), |W[r]| < 2^e, as [piece][b1 % 4][r][b1 / 4]; 2^(e - 15) of every row; eps, eps_abs, hard.  They go
+// to the block's place in LDS, on their way to G + kFastPieces.
+constexpr int kFastPieceBytes = 3 * 256 * 2, kFastBytes = kFastPieceBytes + 20 * 4;   // (of the latter 19 floats are used)
 template <int ROWS, bool PAIR>
 __device__ __forceinline__ void store_fast_factors(const Jacobi16<ROWS>& jac, const double (&wx)[ROWS], const double (&wy)[ROWS],
-                                                   int px, int py, double lx, double ly, bool live, double* G) {
+                                                   int px, int py, double lx, double ly, unsigned char* dst) {
   static_assert(ROWS % 4 == 0, "a lane's rows are whole pieces");
   const int lane = threadIdx.x & 63, row0 = jac.first_row(lane);
-  uint16_t* const pieces = reinterpret_cast<uint16_t*>(G + kFastPieces);
-  float* const scales = reinterpret_cast<float*>(G + kFastScales);
+  uint16_t* const pieces = reinterpret_cast<uint16_t*>(dst);
+  float* const scales = reinterpret_cast<float*>(dst + kFastPieceBytes);
   auto over_rows = [&](float v, auto op) __attribute__((always_inline)) {   // the lanes that hold the column's other rows
     if (ROWS <= 8) v = op(v, lane_exchange<kDppXor8>(v));
     if (ROWS <= 4) v = op(v, __shfl_xor(v, 16));
@@ -2289,20 +2304,11 @@ __device__ __forceinline__ void store_fast_factors(const Jacobi16<ROWS>& jac, co
       // (a subnormal piece counts with exponent -14 as well: the addend)
       rest = fmaf((fabsf((float)left) + 0x1p-35f) * scale, s[i], rest);
     }
-    if (live) {
 #pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        if (ROWS == 16) {
+    for (int k = 0; k < 3; ++k)
 #pragma unroll
-          for (int g = 0; g < 4; ++g)
-            *reinterpret_cast<f16x4*>(pieces + 256 * k + (g * 16 + r) * 4) = f16x4{h[k][g], h[k][(4 + g) % ROWS], h[k][(8 + g) % ROWS], h[k][(12 + g) % ROWS]};
-        } else {
-#pragma unroll
-          for (int i = 0; i < ROWS; ++i)
-            reinterpret_cast<_Float16*>(pieces)[256 * k + ((i & 3) * 16 + r) * 4 + ((row0 + i) >> 2)] = h[k][i];
-        }
-      }
-    }
+      for (int i = 0; i < ROWS; ++i)
+        reinterpret_cast<_Float16*>(pieces)[256 * k + ((i & 3) * 16 + r) * 4 + ((row0 + i) >> 2)] = h[k][i];
     one = over_rows(one, add);
     two = over_rows(two, add);
     cs = over_rows(cs, add);
@@ -2315,34 +2321,42 @@ __device__ __forceinline__ void store_fast_factors(const Jacobi16<ROWS>& jac, co
     soft = soft && re + 32.f * ae <= kHardEps;   // all of the block's rows; false for a NaN (a block that holds one)
     rel = fmaxf(rel, re);
     abs = fmaxf(abs, ae);
-    if (live && row0 == 0) scales[r] = scale;
+    if (row0 == 0) scales[r] = scale;
   }
   rel = over_columns(rel, most);
   abs = over_columns(abs, most);
   const float all_soft = -over_columns(soft ? -1.f : 0.f, most);
-  if (live && row0 == 0 && (lane & 7) == 0) {
+  if (row0 == 0 && (lane & 7) == 0) {
     scales[16] = rel;
     scales[17] = abs;
     scales[18] = all_soft != 0.f ? 0.f : 1.f;
   }
 }
 
-// The eigen-solver of a call of thousands of blocks: 64 * ROWS / 128 blocks per wave (eight at ROWS = 16:
-// every rotation is derived once, no sum crosses lanes, nothing touches LDS but the ordering).  Reads the
-// Gram matrices and writes W behind them, the small tensors into the cache, the blocks' status words.
-// Bound by instruction issue: about 145 instructions per round for eight blocks.
+// The eigen-solver of a call of thousands of blocks: ROWS / 2 blocks per wave (eight at ROWS = 16:
+// every rotation is derived once, no sum crosses lanes, nothing touches LDS in the sweeps).  Reads the
+// Gram matrices and writes W, the eigenvalues and FastProject's constants behind them, the small tensors into the cache, the
+// blocks' status words.
+// Bound by instruction issue in its sweeps; what comes before and after them is a burst of all waves at once, bound by requests:
+// a lane's rows lie 64 bytes apart from its neighbour's, and from the registers they would take an instruction of 64 lines for
+// every 16 bytes.  They pass through LDS and cross as they lie in memory, 1 KB an instruction.
+// 14720 blocks, eight a wave: 87 us, 99 with four a wave, factors stored from the registers and selects by VCC.  Tried: four
+// columns a lane (the same pairs and bits, a third of the exchanges, 2 x 1260 instead of 2 x 1440 instructions a sweep of
+// eight blocks): 94, too few waves to cover one another's waits.
 // Workgroups of four waves, so that the waves spread evenly over the SIMDs.
 constexpr int kSolveWaves = 4;
 template <int ROWS, bool PAIR, bool FAST>
-__global__ __launch_bounds__(64 * kSolveWaves) void solve16_kernel(dq_format fmt, dq_cache cache, CompressJob job,
+__global__ __launch_bounds__(64 * kSolveWaves, ROWS == 16 ? 2 : 4) void solve16_kernel(dq_format fmt, dq_cache cache, CompressJob job,
                                                      float* __restrict__ large_ws, int32_t* __restrict__ unit_status,
                                                      int n_groups) {
-  constexpr int LPB = 128 / ROWS, BPG = 64 * kSolveWaves / LPB;   // lanes per block, blocks per workgroup
+  constexpr int LPB = 128 / ROWS, BPW = 64 / LPB, BPG = kSolveWaves * BPW;   // lanes per block, blocks per wave and workgroup
   constexpr int j1 = 16, d = PAIR ? 64 : 128;
+  constexpr int kFactorBytes = (j1 * j1 + j1) * 8;           // W and the eigenvalues
+  static_assert(kFactorBytes == (kFastPieces - j1 * j1) * 8 && kFactorBytes >= kFastBytes, "a block's place in LDS");
   const Geometry g = make_geometry(fmt, cache.kv_heads, cache.block_capacity);
-  __shared__ double s_lam[BPG][j1];
-  __shared__ __attribute__((aligned(16))) uint16_t s_small[BPG][j1 * j1];
-  const int lane = threadIdx.x & 63, blk = threadIdx.x / LPB, j = lane & 7;
+  __shared__ __attribute__((aligned(16))) unsigned char s_stage[BPG][kFactorBytes];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, blk = threadIdx.x / LPB, j = lane & 7;
+  unsigned char* const stage = s_stage[blk];
   const int gi = blockIdx.x * BPG + blk;
   int unit = min(gi, n_groups - 1);
   const int unit_gap = 2 * job.n_blocks;
@@ -2361,47 +2375,88 @@ __global__ __launch_bounds__(64 * kSolveWaves) void solve16_kernel(dq_format fmt
     }
     return;
   }
-  double* const G = reinterpret_cast<double*>(large_ws + (long)unit * g.Tb * d);
+  // the wave's b-th block: its part of the workspace (a block that is skipped has no matrix)
+  auto there = [&](int b) __attribute__((always_inline)) { return __builtin_amdgcn_readlane((int)live, b * LPB) != 0; };
+  auto region = [&](int b) __attribute__((always_inline)) {
+    return reinterpret_cast<unsigned char*>(large_ws + (long)__builtin_amdgcn_readlane(unit, b * LPB) * g.Tb * d);
+  };
   Jacobi16<ROWS> jac;
   const int row0 = jac.first_row(lane);
+  {
+    u32x4 x[2 * BPW];
 #pragma unroll
-  for (int i = 0; i < ROWS; ++i) {   // (symmetric: column j is row j; a block that is skipped has no matrix)
-    jac.x[i] = live ? G[j * j1 + row0 + i] : 0.0;
-    jac.y[i] = live ? G[(j + 8) * j1 + row0 + i] : 0.0;
+    for (int b = 0; b < BPW; ++b) {
+      const bool any = there(b);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        x[2 * b + k] = u32x4{0u, 0u, 0u, 0u};
+        if (any) x[2 * b + k] = *reinterpret_cast<const u32x4*>(region(b) + 1024 * k + 16 * lane);
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < 2 * BPW; ++b) *reinterpret_cast<u32x4*>(s_stage[BPW * wave + b / 2] + 1024 * (b & 1) + 16 * lane) = x[b];
+    team_barrier<1>();
+    const double* const G = reinterpret_cast<const double*>(stage);
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {   // (symmetric: column j is row j)
+      jac.x[i] = G[j * j1 + row0 + i];
+      jac.y[i] = G[(j + 8) * j1 + row0 + i];
+    }
+    team_barrier<1>();
   }
   const int sweeps = jac.template run<PAIR>();
   int px, py;
   double rx, ry, lx, ly;
-  jac.template order<PAIR>(s_lam[blk], px, py, rx, ry, lx, ly);
+  jac.template order<PAIR>(reinterpret_cast<double*>(stage), px, py, rx, ry, lx, ly);
+  team_barrier<1>();
+  // `bytes` of every block, from its place in LDS to `at` bytes behind its Gram matrix' begin
+  auto flush = [&](int bytes, int at) __attribute__((always_inline)) {
+    team_barrier<1>();
+#pragma unroll 1
+    for (int b = 0; b < BPW; ++b) {
+      if (!there(b)) continue;
+      unsigned char* const to = region(b) + at;
+      for (int i = 16 * lane; i < bytes; i += 16 * 64)
+        *reinterpret_cast<u32x4*>(to + i) = *reinterpret_cast<const u32x4*>(s_stage[BPW * wave + b] + i);
+    }
+    team_barrier<1>();
+  };
   const double fx = rx * rx * rx, fy = ry * ry * ry;
-  if (live) {
-    G[2 * j1 * j1 + px] = lx;
-    G[2 * j1 * j1 + py] = ly;
+  double wx[ROWS], wy[ROWS];   // columns px and py of W^T
+  {
+    double* const to = reinterpret_cast<double*>(stage);
+    to[j1 * j1 + px] = lx;
+    to[j1 * j1 + py] = ly;
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+      wx[i] = rx > 0.0 ? jac.x[i] * fx : 0.0;
+      wy[i] = ry > 0.0 ? jac.y[i] * fy : 0.0;
+      to[px * j1 + row0 + i] = wx[i];
+      to[py * j1 + row0 + i] = wy[i];
+    }
+  }
+  flush(kFactorBytes, j1 * j1 * 8);
+  if constexpr (FAST) {
+    store_fast_factors<ROWS, PAIR>(jac, wx, wy, px, py, lx, ly, stage);
+    flush(kFastBytes, kFastPieces * 8);
   }
   bool sat = false;
-  double wx[ROWS], wy[ROWS];   // columns px and py of W^T
 #pragma unroll
   for (int i = 0; i < ROWS; ++i) {
     const int b1 = row0 + i;
-    wx[i] = rx > 0.0 ? jac.x[i] * fx : 0.0;
-    wy[i] = ry > 0.0 ? jac.y[i] * fy : 0.0;
-    if (live) {
-      G[j1 * j1 + px * j1 + b1] = wx[i];
-      G[j1 * j1 + py * j1 + b1] = wy[i];
-    }
     auto put = [&](int r, double ts) __attribute__((always_inline)) {
+      uint16_t* const to = reinterpret_cast<uint16_t*>(stage);
       if (PAIR) {   // the heads' 8 x 8 tensors one after the other; across heads there is nothing
         if ((b1 >> 3) != (r >> 3)) return;
-        s_small[blk][(b1 >> 3) * 64 + (ur.which ? (b1 & 7) * 8 + (r & 7) : (r & 7) * 8 + (b1 & 7))] = f64_to_f16_rne(ts, true, &sat);
+        to[(b1 >> 3) * 64 + (ur.which ? (b1 & 7) * 8 + (r & 7) : (r & 7) * 8 + (b1 & 7))] = f64_to_f16_rne(ts, true, &sat);
       } else {      // values: [b1][r]; keys: transposed [r][b1]
-        s_small[blk][ur.which ? b1 * j1 + r : r * j1 + b1] = f64_to_f16_rne(ts, true, &sat);
+        to[ur.which ? b1 * j1 + r : r * j1 + b1] = f64_to_f16_rne(ts, true, &sat);
       }
     };
     put(px, wx[i] * lx);   // T_S = U Sigma = W Lambda
     put(py, wy[i] * ly);
   }
-  if constexpr (FAST) store_fast_factors<ROWS, PAIR>(jac, wx, wy, px, py, lx, ly, live, G);
-  __builtin_amdgcn_wave_barrier();
+  team_barrier<1>();
   const unsigned long long sat_lanes = __ballot(sat);
   if (live) {
     const int lb = lane % LPB;
@@ -2410,7 +2465,7 @@ __global__ __launch_bounds__(64 * kSolveWaves) void solve16_kernel(dq_format fmt
 #pragma unroll
     for (int c = lb; c < CHUNKS; c += LPB) {
       uint16_t* dst = PAIR ? small + (long)(c / 8) * g.NB * g.small_per_block + (c % 8) * 8 : small + c * 8;
-      *reinterpret_cast<u32x4*>(dst) = *reinterpret_cast<const u32x4*>(&s_small[blk][c * 8]);
+      *reinterpret_cast<u32x4*>(dst) = *reinterpret_cast<const u32x4*>(stage + c * 16);
     }
   }
   if (gi < n_groups && lane % LPB == 0) {
@@ -2644,11 +2699,12 @@ static int waves_per_block(int groups, int want_waves) {
 }
 
 // Blocks per wave of the eigen-solver's launch: two up to kMostTwoBlocks blocks, four up to kMostFourBlocks, eight beyond.  More
-// blocks share a wave's instructions, fewer give more waves, and the launch takes whole rounds of the chip's 1024 SIMDs.
-// Whole call in us, 4 bits, two / four blocks per wave: 4352 blocks 133.3 / 132.3, 7168 184.7 / 172.3, 8192 204.5 / 192.0,
-// graded over three decades 428 / 401, 4096 pairs of heads 226 / 214, 8192 blocks in 8 bits 284 / 269; four / eight: 8448
-// 224 / 237, 9216 237 / 254, 12288 286 / 303, 14336 333 / 333, 16384 364 / 369, 32768 686 / 682, graded 1462 / 1387.
-constexpr int kMostTwoBlocks = 4096, kMostFourBlocks = 16384;
+// blocks share a wave's instructions, fewer give more waves, and the launch takes whole rounds of the chip's 1024 SIMDs: the
+// lines lie where a SIMD would get a second wave of two blocks, and a fourth of four.
+// Whole call in us, 4 bits, two / four blocks per wave: 2048 blocks 63.9 / 71.8, 3072 95.5 / 87.9, 4096 111.0 / 106.8, graded over
+// three decades 207 / 193; four / eight: 4096 107 / 127, 8192 184.1 / 185.5, 9216 228 / 242, 12288 271 / 286, 14720 326.7 / 320.3, graded
+// 669 / 657, 32768 665 / 648; 8192 pairs of heads 210 / 214, 16384 401 / 398.
+constexpr int kMostTwoBlocks = 2048, kMostFourBlocks = 12288;
 
 // Blocks (of sixteen rows of channels: pairs of 64-channel heads count once) up to which the Gram matrices' launch requests
 // its rows with plain loads: the projection then finds them in the 256 MB last-level cache, 32 KB a block (kMostCachedFast: 2- and
