@@ -23,11 +23,11 @@
 //      accumulators' starting value);
 //   3. online softmax with two tokens per lane (scores cross from the MFMA layout through
 //      wave-private LDS); w_t = p_t * step^V_t is cut into limbs, again B columns;
-//   4. streams the value codes (stored token-contiguous): o'[r, b2] = sum_t u[t, r, b2] limb[t];
+//   4. streams the value codes (stored token-contiguous): o'[r, b2] = sum_t u[t, r, b2] limb[t]
+//      (several heads, two tensors: with the limbs as the left operand, which leaves a head's limbs in one lane);
 //   5. applies the values' small tensor with fp32 16x16x4 MFMAs,
 //      acc[b1, b2] = alpha * acc + sum_r T_S^V[b1, r] o'[r, b2]
-//      (the limb columns of several b2 packed side by side first, so that the sixteen columns
-//      of these MFMAs are all in use).
+//      (several b2 side by side first, so that the sixteen columns of these MFMAs are all in use).
 // With two step groups per token row (group = 64: rows r < 8 and r >= 8 of the large tensor)
 // every limb gets one B column per group: the key side zeroes the limbs of the other group's
 // channels, the value side takes each row of o' from the column of that row's group.
@@ -199,17 +199,18 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   static_assert(NC <= 16, "too many heads for sixteen B columns");
   constexpr int F = (R + 1) / 2;              // fold MFMAs (two heads each)
   constexpr int D = 128, J1 = 16, J2 = 8;
-  // The epilogue multiplies o'[r][column] by the values' small tensor, sixteen columns at a time,
-  // but one b2 fills only 3 R of them (one limb triple per head, once the two step groups' columns
-  // have been merged): the columns of PK = 4 / R successive b2 are packed side by side first.
-  // With four heads (R = 4) that packing would leave one b2 per set and 32 fp32 matrix instructions
-  // per tile, which on this chip cost what ten vector instructions each cost (matrix and vector
-  // instructions of one SIMD do not run side by side).  There the three limbs of a head are joined
-  // first, as floats, by lane shifts (column 4*head + limb holds limb `limb`, most significant first),
-  // and the joined columns of four successive b2 are packed side by side: 8 matrix instructions
-  // per tile, and a quarter of the accumulators.
-  constexpr bool JOIN = (R == 4 && CG == 1 && !N3);
-  constexpr int PK = JOIN ? 4 : 4 / R, NSET = J2 / PK;
+  // The epilogue multiplies o'[r] of every head and b2 by the values' small tensor, sixteen (head, b2) columns at a time.
+  // With one head, or three tensors, one b2 fills only 3 R of the columns (one limb triple per head, once the two step groups'
+  // columns have been merged): the columns of PK = 4 / R successive b2 are packed side by side first.
+  // With several heads the value product has its operands the other way round (see step 4): a lane's result
+  // registers are then the limbs of one head, which it joins as floats, two multiply-adds, and the rows r, now down the lanes, are
+  // turned through LDS: 16 / R b2 of a head fill a set, 4 R / 2 matrix instructions per tile.  (Limbs joined by lane shifts, from
+  // columns, took 176 vector instructions a tile with four heads where this takes 40; with two heads it was 16 matrix instructions
+  // instead of 4.  64 query on 8 kv heads, 8 x 32768 tokens: 72.2 us, 66.0 so; 32 on 8, mixed lengths with tails: whole step 34.2,
+  // 33.1; four 64-channel heads of 256 tokens: 6.0, 5.7.)
+  constexpr bool JOIN = (R >= 2 && !N3);
+  constexpr int PK = JOIN ? 16 / R : 4 / R, NSET = J2 / PK;
+  constexpr int TS = 20;                      // floats per (head, b2) of the joined values on their way through LDS (16 rows + pad)
   constexpr int RD = P2 ? 64 : D;             // channels of a real head (output, partials, cache rows)
   constexpr int RJ1 = P2 ? 8 : J1;            // rows of a real head's large tensors
   constexpr int ROWB = RD * BITS / 8;         // bytes of a key row in memory
@@ -219,6 +220,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   constexpr int QS_BYTES = NC * 128, PS_BYTES = NC * 128, SS_BYTES = NC * SS * 4;
   constexpr int WAVE_LDS = QS_BYTES + PS_BYTES + SS_BYTES;
   static_assert(WAVE_LDS >= NC * D * 4 + 2 * R * 4, "merge area must fit the wave's LDS");
+  static_assert(!JOIN || R * J2 * TS * 4 <= SS_BYTES, "the joined values take the scores' place");
   __shared__ __attribute__((aligned(16))) unsigned char smem[NW * WAVE_LDS];
   // the waves' partial results over the fp16 tail
   // (128 rows requested up front, by two workgroups if TM == 2; fewer where the heads leave fewer registers)
@@ -379,8 +381,13 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   const bool col_live = (n < NC) && (N3 || (n & 3) != 3);   // value side: three limbs per group of four columns (four with three local tensors)
   const bool col_live_k = n < NC;                      // key side: four
   // the epilogue's packed columns (see PK): column n holds head packed_head, slot packed_slot of its set
-  const int packed_head = (R == 1) ? 0 : (R == 4) ? (n >> 2) : (CG == 1) ? ((n >> 2) & 1) : (n >> 3);
-  const int packed_slot = JOIN ? (n & 3) : (R == 1) ? (n >> 2) : (R == 4) ? 0 : (CG == 1) ? (n >> 3) : ((n >> 2) & 1);
+  const int packed_head = JOIN ? n / PK : (R == 1) ? 0 : (R == 4) ? (n >> 2) : (CG == 1) ? ((n >> 2) & 1) : (n >> 3);
+  const int packed_slot = JOIN ? n % PK : (R == 1) ? (n >> 2) : (R == 4) ? 0 : (CG == 1) ? (n >> 3) : ((n >> 2) & 1);
+  // JOIN: lane (row r = n, g) holds the limbs of head g (two step groups: of head g / 2, rows of group g % 2)
+  const bool join_live = (CG == 1) ? g < R : (g & 1) == (n >> 3);
+  float* const Ts = reinterpret_cast<float*>(Ss);                // [R * 8][TS]
+  float* const join_to = Ts + (g / CG) * (J2 * TS) + n;
+  const float* const join_from = Ts + (packed_head * J2 + packed_slot) * TS + 4 * g;
 
   // softmax layout: lane = 8*G16 + pi owns the two tokens of token group G16 whose weights sit in
   // B slots 2*pi and 2*pi + 1
@@ -784,8 +791,8 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
     for (int i = 0; i < 4; ++i) aT[i] = (float)vsm_h[i] * v_unscale;
     i32x4 cinitv = izero;
     if (C::kOffset != 0) {
-      cinitv = __builtin_amdgcn_mfma_i32_16x16x64_i8(a_minus, bp[0], izero, 0, 0, 0);
-      cinitv = __builtin_amdgcn_mfma_i32_16x16x64_i8(a_minus, bp[1], cinitv, 0, 0, 0);
+      cinitv = JOIN ? __builtin_amdgcn_mfma_i32_16x16x64_i8(bp[0], a_minus, izero, 0, 0, 0) : __builtin_amdgcn_mfma_i32_16x16x64_i8(a_minus, bp[0], izero, 0, 0, 0);
+      cinitv = JOIN ? __builtin_amdgcn_mfma_i32_16x16x64_i8(bp[1], a_minus, cinitv, 0, 0, 0) : __builtin_amdgcn_mfma_i32_16x16x64_i8(a_minus, bp[1], cinitv, 0, 0, 0);
     }
     if (__any(alpha_col != 1.f)) {   // the running maximum moved: rare after the first tiles
 #pragma unroll
@@ -812,32 +819,22 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
         }
       }
     };
-    // JOIN: the limbs of o' joined as floats.  In the lane of column 4*head + k the three limbs of
-    // that head sit k, k - 1 and k - 2 lanes below; every lane computes the combination with the
-    // same shifts and the lanes of slot k = b2 % 4 keep it.  The joined value (|o'| < 2^32) takes one
-    // fp32 rounding, of the size of the accumulation's own.
-    auto pack_joined = [&](i32x4& pk, i32x4 o, auto k_tag) __attribute__((always_inline)) {
-      constexpr int K = decltype(k_tag)::value % 4;
+    // JOIN: the limbs of o' joined as floats (|o'| < 2^32: one fp32 rounding, of the size of the accumulation's own)
+    auto join = [&](int b2, const i32x4& o) __attribute__((always_inline)) {
+      const float v = fmaf((float)o[0], 16384.f, fmaf((float)o[1], 128.f, (float)o[2]));
+      if (join_live) join_to[b2 * TS] = v;
+    };
+    auto epilogue_joined = [&](int st) __attribute__((always_inline)) {   // b2 = st * PK .. + PK - 1 of every head
+      const f32x4 v = *reinterpret_cast<const f32x4*>(join_from + st * (PK * TS));   // rows r = 4 g + i
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float f = (float)o[i];
-        const int fb = __builtin_bit_cast(int, f);
-        // (shift by zero lanes: the value itself)
-        const float l0 = K == 0 ? f : __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, fb, 0x110 + K /* row_shr:K */, 0xF, 0xF, true));
-        const float l1 = K == 1 ? f : K == 0 ? __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, fb, 0x101 /* row_shl:1 */, 0xF, 0xF, true))
-                                             : __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, fb, 0x110 + (K - 1), 0xF, 0xF, true));
-        const float l2 = K == 2 ? f : K == 3 ? __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, fb, 0x111 /* row_shr:1 */, 0xF, 0xF, true))
-                                             : __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, fb, 0x100 + (2 - K) /* row_shl */, 0xF, 0xF, true));
-        const float joined = fmaf(l0, 16384.f, fmaf(l1, 128.f, l2));
-        pk[i] = ((n & 3) == K) ? __builtin_bit_cast(int, joined) : pk[i];
-      }
+      for (int i = 0; i < 4; ++i) acc[st] = __builtin_amdgcn_mfma_f32_16x16x4f32(aT[i], v[i], acc[st], 0, 0, 0);
     };
     auto epilogue = [&](int st, const i32x4& pk) __attribute__((always_inline)) {
       f32x4 c = acc[st];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int word = pk[i];   // (a copy: the bit cast below wants an object, not an element of a vector)
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(aT[i], JOIN ? __builtin_bit_cast(float, word) : (float)word, c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(aT[i], (float)word, c, 0, 0, 0);
       }
       acc[st] = c;
     };
@@ -848,22 +845,32 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
       __builtin_amdgcn_sched_barrier(0);
       if (HAS_NEXT) ring[8 + b2] = __builtin_nontemporal_load(reinterpret_cast<const chunk_t*>(vc_next + b2 * (RJ1 * VROWB)));
       __builtin_amdgcn_sched_barrier(0);
-      i32x4 o = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0, bp[0], cinitv, 0, 0, 0);
-      o = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1, bp[1], o, 0, 0, 0);
-      // the previous set's epilogue runs while this b2's integer MFMAs do
-      if (b2 > 0 && b2 % PK == 0) epilogue(b2 / PK - 1, pk_done);
       if constexpr (JOIN) {
-        if (b2 % 4 == 0) pack_joined(pk_cur, o, std::integral_constant<int, 0>{});
-        else if (b2 % 4 == 1) pack_joined(pk_cur, o, std::integral_constant<int, 1>{});
-        else if (b2 % 4 == 2) pack_joined(pk_cur, o, std::integral_constant<int, 2>{});
-        else pack_joined(pk_cur, o, std::integral_constant<int, 3>{});
-      } else if (b2 % PK == 0) pack(pk_cur, o, std::integral_constant<int, 0>{});
-      else if (b2 % PK == 1) pack(pk_cur, o, std::integral_constant<int, 1>{});
-      else if (b2 % PK == 2) pack(pk_cur, o, std::integral_constant<int, 2>{});
-      else pack(pk_cur, o, std::integral_constant<int, 3>{});
-      if (b2 % PK == PK - 1) pk_done = pk_cur;
+        i32x4 o = __builtin_amdgcn_mfma_i32_16x16x64_i8(bp[0], a0, cinitv, 0, 0, 0);
+        o = __builtin_amdgcn_mfma_i32_16x16x64_i8(bp[1], a1, o, 0, 0, 0);
+        // the b2 before this one is joined, and a set that has gone through LDS multiplied, while this b2's integer MFMAs run
+        if (b2 > 0) join(b2 - 1, pk_cur);
+        if (b2 > PK && (b2 - 1) % PK == 0) epilogue_joined((b2 - 1) / PK - 1);
+        pk_cur = o;
+      } else {
+        i32x4 o = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0, bp[0], cinitv, 0, 0, 0);
+        o = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1, bp[1], o, 0, 0, 0);
+        // the previous set's epilogue runs while this b2's integer MFMAs do
+        if (b2 > 0 && b2 % PK == 0) epilogue(b2 / PK - 1, pk_done);
+        if (b2 % PK == 0) pack(pk_cur, o, std::integral_constant<int, 0>{});
+        else if (b2 % PK == 1) pack(pk_cur, o, std::integral_constant<int, 1>{});
+        else if (b2 % PK == 2) pack(pk_cur, o, std::integral_constant<int, 2>{});
+        else pack(pk_cur, o, std::integral_constant<int, 3>{});
+        if (b2 % PK == PK - 1) pk_done = pk_cur;
+      }
     }
-    epilogue(NSET - 1, pk_done);
+    if constexpr (JOIN) {
+      join(J2 - 1, pk_cur);
+      __builtin_amdgcn_wave_barrier();
+      epilogue_joined(NSET - 1);
+    } else {
+      epilogue(NSET - 1, pk_done);
+    }
     cur = nxt;
     if (N3) cur3 = nxt3;
     if (P2) curP = nxtP;
