@@ -18,7 +18,7 @@
 //   1. folds the keys' small tensor into the query,  q'[r, b2] = sum_b1 T_S^K[b1, r] q[b1, b2]
 //      (one 16x16x16 f16 MFMA per two heads; T_S and q are fp16, so the products are exact),
 //      and writes the limbs of q' * scale * log2(e) as B operands;
-//   2. streams the key codes: S[t][limb] = sum_c (u[t, c] - offset) limb[c]  (16x16x64 i8 MFMA,
+//   2. streams the key codes: S[t][limb] = sum_c (u[t, c] - offset) limb[c]  (16x16x64 i8 MFMA; four heads: the limbs on the left,
 //      u = code + offset as stored; the offset's share comes from a constant-A MFMA and is the
 //      accumulators' starting value);
 //   3. online softmax with two tokens per lane (scores cross from the MFMA layout through
@@ -162,6 +162,25 @@ __device__ __forceinline__ float wave_allsum(float v) {
   return (lane_f(v, 0) + lane_f(v, 16)) + (lane_f(v, 32) + lane_f(v, 48));
 }
 
+// The same over the sixteen lanes of a row.
+__device__ __forceinline__ float row_allmax(float v) {
+  int x = __builtin_bit_cast(int, v);
+  x ^= (x >> 31) & 0x7FFFFFFF;
+  x = max(x, dpp_i<0xB1>(x));
+  x = max(x, dpp_i<0x4E>(x));
+  x = max(x, dpp_i<0x141>(x));
+  x = max(x, dpp_i<0x140>(x));
+  x ^= (x >> 31) & 0x7FFFFFFF;
+  return __builtin_bit_cast(float, x);
+}
+__device__ __forceinline__ float row_allsum(float v) {
+  v += dpp_f<0xB1>(v);
+  v += dpp_f<0x4E>(v);
+  v += dpp_f<0x141>(v);
+  v += dpp_f<0x140>(v);
+  return v;
+}
+
 // 2^e as a float for -126 <= e <= 127
 __device__ __forceinline__ float pow2i(int e) {
   return __builtin_bit_cast(float, (uint32_t)(e + 127) << 23);
@@ -213,6 +232,13 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   // instead of 4.  64 query on 8 kv heads, 8 x 32768 tokens: 72.2 us, 66.0 so; 32 on 8, mixed lengths with tails: whole step 34.2,
   // 33.1; four 64-channel heads of 256 tokens: 6.0, 5.7.)
   constexpr bool JOIN = (R >= 2 && !N3);
+  // Four heads fill all sixteen columns: the score product has its operands the other way round as well.  A lane then holds the limbs
+  // of one head's scores of eight tokens, joins them in registers and goes on with them; the steps reach it from the lanes
+  // that asked for them by lane swaps.  Through LDS (8 writes and 32 reads a tile, four reductions' checks instead of one) the wave
+  // waited for them: 16 x 32 heads (8 kv heads) x 32768 tokens 92.2 -> 90.5 us, so turned and with the folded query in 8 writes instead of
+  // 32; a serving step of 16 sequences of 3000 to 8000 tokens 32.5 -> 31.4; 8 x 32 on 8 heads of 64 channels, 2048 to 4096 tokens
+  // 11.5 -> 11.0.  (Two heads would leave half the lanes idle in the softmax.)
+  constexpr bool TURN = (R == 4 && !N3);
   constexpr int PK = JOIN ? 16 / R : 4 / R, NSET = J2 / PK;
   constexpr int TS = 20;                      // floats per (head, b2) of the joined values on their way through LDS (16 rows + pad)
   constexpr int RD = P2 ? 64 : D;             // channels of a real head (output, partials, cache rows)
@@ -221,9 +247,11 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   constexpr int VROWB = kTileTokens * BITS / 8;   // bytes of a value row (one r, one b2) in a tile
   constexpr int CHUNKB = sizeof(chunk_t);
   constexpr int SS = 132;                     // ints per column of the score staging (128 tokens + pad)
-  constexpr int QS_BYTES = NC * 128, PS_BYTES = NC * 128, SS_BYTES = NC * SS * 4;
+  constexpr int LS = 144;                     // bytes from column to column of the limbs (128 and a pad that keeps the b128 reads off each other's banks)
+  constexpr int QS_BYTES = NC * LS, PS_BYTES = NC * LS, SS_BYTES = TURN ? R * J2 * TS * 4 : NC * SS * 4;
+  constexpr int MC = JOIN ? R : NC;           // columns of a wave's result in the merge (JOIN: the limbs are joined already)
   constexpr int WAVE_LDS = QS_BYTES + PS_BYTES + SS_BYTES;
-  static_assert(WAVE_LDS >= NC * D * 4 + 2 * R * 4, "merge area must fit the wave's LDS");
+  static_assert(WAVE_LDS >= MC * D * 4 + 2 * R * 4, "merge area must fit the wave's LDS");
   static_assert(!JOIN || R * J2 * TS * 4 <= SS_BYTES, "the joined values take the scores' place");
   __shared__ __attribute__((aligned(16))) unsigned char smem[NW * WAVE_LDS];
   // the waves' partial results over the fp16 tail
@@ -403,14 +431,25 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   else if (BITS == 2) { tA = 16 * G16 + 8 * (pi & 1) + (pi >> 1); tB = tA + 4; }
   else { tA = 16 * G16 + 2 * pi; tB = tA + 1; }
 
-  // loop-invariant B operands of the fold, q[k = b1][n' = (b2, head)].  The loads go out first (the
+  // key rows of the chunks.  TURN: chunks 2 k and 2 k + 1 hold the lane's tokens tA and tB of the k-th 32, the pair whose weights
+  // share a 16-bit word of B slots; a chunk still asks for whole lines (two rows at 4 bits, four at 2, one at 8)
+  const int key_row = TURN ? tA - 32 * g : n;
+  constexpr int kPairRows = BITS == 4 ? 2 : BITS == 2 ? 4 : 1;   // tB - tA
+  auto chunk_rows = [](int j) constexpr -> int { return TURN ? 32 * (j >> 1) + (j & 1) * kPairRows : 16 * j; };
+
+  // The fold's columns are dealt so that the four a lane gets lie side by side in B slots (2-bit codes: two and two).
+  auto fold_b2 = [](int c) constexpr -> int {   // the b2 of column c (mod 8)
+    return BITS == 4 ? 2 * (c & 3) + (c >> 2) : BITS == 2 ? (c >> 2) * 2 + ((c >> 1) & 1) + 4 * (c & 1) : c;
+  };
+
+  // loop-invariant operands of the fold, q[(b2, head)][k = b1].  The loads go out first (the
   // memory counter retires in issue order and q is needed before the first codes); the values are
   // packed further down, after the first tile's codes have been requested, so that the wait for q
   // does not sit in front of those requests.
   half4 bq[F];
   uint32_t q_raw[F][4];
   {
-    const int b2 = n & 7;
+    const int b2 = fold_b2(n & 7);
 #pragma unroll
     for (int f = 0; f < F; ++f) {
       const int hd = 2 * f + (n >> 3);
@@ -424,9 +463,9 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
     }
   }
 
-  float m_run[R], l_run[R];
+  float m_run[TURN ? 1 : R], l_run[TURN ? 1 : R];   // TURN: of head g, the sum over the lane's own tokens
 #pragma unroll
-  for (int hd = 0; hd < R; ++hd) { m_run[hd] = -INFINITY; l_run[hd] = 0.f; }
+  for (int hd = 0; hd < (TURN ? 1 : R); ++hd) { m_run[hd] = -INFINITY; l_run[hd] = 0.f; }
   f32x4 acc[NSET];
 #pragma unroll
   for (int st = 0; st < NSET; ++st) acc[st] = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -457,6 +496,8 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   // the kv head (0 or 1) of the head in the lane's column of fold f, and whether the lane's rows are its own
   auto fold_half = [&](int f) -> int { return (2 * f + (n >> 3)) / HPK; };
   auto fold_live = [&](int f) -> bool { return !P2 || (g >> 1) == fold_half(f); };
+  // the same of the fold's result: columns 4 g + i, row n
+  auto folded_half = [&](int f) -> int { return (2 * f + (g >> 1)) / HPK; };
 
   auto tile_ptrs = [&](int tile, const unsigned char*& kc, const unsigned char*& vc, long& blkid, int& tib) {
     blkid = bh0 * NB + tile / tpb;
@@ -464,10 +505,10 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
     if (P2) {
       // keys: a virtual row is the two heads' rows side by side, two chunks each; values: virtual
       // row r of a b2 is row r % 8 of head r / 8 (the second head's blocks lie NB blocks further on)
-      kc = a.cache.k_codes + (blkid + (g >> 1) * NB) * codes_per_block + (long)tib * kTileTokens * ROWB + n * ROWB + CHUNKB * (g & 1);
+      kc = a.cache.k_codes + (blkid + (g >> 1) * NB) * codes_per_block + (long)tib * kTileTokens * ROWB + key_row * ROWB + CHUNKB * (g & 1);
       vc = a.cache.v_codes + (blkid + (n >> 3) * NB) * codes_per_block + (long)tib * kTileTokens * ROWB + (n & 7) * VROWB + CHUNKB * g;
     } else {
-      kc = a.cache.k_codes + blkid * codes_per_block + (long)tib * kTileTokens * ROWB + n * ROWB + CHUNKB * g;
+      kc = a.cache.k_codes + blkid * codes_per_block + (long)tib * kTileTokens * ROWB + key_row * ROWB + CHUNKB * g;
       vc = a.cache.v_codes + blkid * codes_per_block + (long)tib * kTileTokens * ROWB + n * VROWB + CHUNKB * g;
     }
   };
@@ -514,7 +555,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
     if (P2) load_sideP(curP, blkid, tib);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) ring[j] = __builtin_nontemporal_load(reinterpret_cast<const chunk_t*>(kc + j * (16 * ROWB)));
+    for (int j = 0; j < 8; ++j) ring[j] = __builtin_nontemporal_load(reinterpret_cast<const chunk_t*>(kc + chunk_rows(j) * ROWB));
 #pragma unroll
     for (int b2 = 0; b2 < 8; ++b2) ring[8 + b2] = __builtin_nontemporal_load(reinterpret_cast<const chunk_t*>(vc + b2 * (RJ1 * VROWB)));
   };
@@ -570,9 +611,10 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
       if (HAS_NEXT) load_sideP(nxtP, blkid_next, tib_next);
     }
     __builtin_amdgcn_sched_barrier(0);
-    const bool okA = (tok0 + tA) < S, okB = (tok0 + tB) < S;
+    // (a tile with another one after it is full)
+    const bool okA = HAS_NEXT || (tok0 + tA) < S, okB = HAS_NEXT || (tok0 + tB) < S;
     // three tensors: a row counts as soon as its run of eight holds a valid token
-    const bool rowA = N3 ? (tok0 + (tA & ~7)) < S : okA, rowB = N3 ? (tok0 + (tB & ~7)) < S : okB;
+    const bool rowA = N3 && !HAS_NEXT ? (tok0 + (tA & ~7)) < S : okA, rowB = N3 && !HAS_NEXT ? (tok0 + (tB & ~7)) < S : okB;
     float dvA[NG], dvB[NG], dkA[NG], dkB[NG];
 #pragma unroll
     for (int gr = 0; gr < NG; ++gr) {
@@ -592,14 +634,14 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
       float amax = 0.f, amax_second = 0.f;
 #pragma unroll
       for (int f = 0; f < F; ++f) {
-        fd[f] = __builtin_amdgcn_mfma_f32_16x16x16f16(aK, bq[f], (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-        // a pair of heads: rows r = 4g + i of the other head's half are zero by construction; they
+        fd[f] = __builtin_amdgcn_mfma_f32_16x16x16f16(bq[f], aK, (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        // a pair of heads: rows r = n of the other head's half are zero by construction; they
         // are set to zero outright so that nothing the other head holds (a NaN, say) gets across
-        if (P2 && !fold_live(f)) fd[f] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        if (P2 && (n >> 3) != folded_half(f)) fd[f] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          if (P2) amax_second = fmaxf(amax_second, fold_half(f) ? fabsf(fd[f][i]) : 0.f);
-          amax = fmaxf(amax, (P2 && fold_half(f)) ? 0.f : fabsf(fd[f][i]));
+          if (P2) amax_second = fmaxf(amax_second, folded_half(f) ? fabsf(fd[f][i]) : 0.f);
+          amax = fmaxf(amax, (P2 && folded_half(f)) ? 0.f : fabsf(fd[f][i]));
         }
       }
       auto exponent_of = [&](float m) -> int {
@@ -616,24 +658,36 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
         q_unscale_second = pow2i(e_second - (kQueryBits - 1));
         qn_second = qk_scale * pow2i(kQueryBits - 1 - e_second);
       }
-      // the fold's D layout: lane (n' = b2 + 8*head, g) holds rows r = 4g + i.  Channel (r, b2) is
-      // code number (r & 1)*8 + b2 of the 16 codes that row pair r >> 1 contributes to one MFMA.
+      // the fold's D layout: lane (n, g) holds row r = n of the columns 4 g + i, four b2 of head 2 f + (g >> 1).  Channel (r, b2) is
+      // code number (r & 1)*8 + b2 of the 16 codes that row pair r >> 1 contributes to one MFMA: four channels side by side in
+      // B slots go out in one word per limb (byte by byte: 32 writes instead of 8 with four heads).
 #pragma unroll
       for (int f = 0; f < F; ++f) {
-        const int hd = 2 * f + (n >> 3);
-        const float qn = (P2 && fold_half(f)) ? qn_second : qn_first;
-        if (hd < R) {
+        const int hd = 2 * f + (g >> 1);
+        const float qn = (P2 && folded_half(f)) ? qn_second : qn_first;
+        uint32_t w[4];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const uint32_t w = ((uint32_t)(int)__builtin_rintf(fd[f][i] * qn) + kDigitBias) ^ kDigitBias;
-            const int r = 4 * g + i;
-            const int grp = (CG == 2) ? (r >> 3) : 0;
-            const int pos = (r >> 1) * 16 + C::slot((r & 1) * 8 + (n & 7));
-            unsigned char* dst = Qs + (CPH * hd + 4 * grp) * 128 + pos;
-            dst[0] = (unsigned char)(w >> 24);
-            dst[128] = (unsigned char)(w >> 16);
-            dst[256] = (unsigned char)(w >> 8);
-            dst[384] = (unsigned char)w;
+        for (int i = 0; i < 4; ++i) w[i] = ((uint32_t)(int)__builtin_rintf(fd[f][i] * qn) + kDigitBias) ^ kDigitBias;
+        // the four words' bytes by limb
+        const uint32_t low01 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u), high01 = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u);
+        const uint32_t low23 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u), high23 = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
+        if (hd < R) {
+          const int grp = (CG == 2) ? (n >> 3) : 0;
+          unsigned char* dst = Qs + (CPH * hd + 4 * grp) * LS + (n >> 1) * 16 + C::slot((n & 1) * 8 + fold_b2(4 * (g & 1)));
+          if (BITS == 2) {   // two and two: b2, b2 + 4 and b2 + 1, b2 + 5
+            *reinterpret_cast<uint16_t*>(dst) = (uint16_t)(high01 >> 16);
+            *reinterpret_cast<uint16_t*>(dst + LS) = (uint16_t)high01;
+            *reinterpret_cast<uint16_t*>(dst + 2 * LS) = (uint16_t)(low01 >> 16);
+            *reinterpret_cast<uint16_t*>(dst + 3 * LS) = (uint16_t)low01;
+            *reinterpret_cast<uint16_t*>(dst + 4) = (uint16_t)(high23 >> 16);
+            *reinterpret_cast<uint16_t*>(dst + 4 + LS) = (uint16_t)high23;
+            *reinterpret_cast<uint16_t*>(dst + 4 + 2 * LS) = (uint16_t)(low23 >> 16);
+            *reinterpret_cast<uint16_t*>(dst + 4 + 3 * LS) = (uint16_t)low23;
+          } else {
+            *reinterpret_cast<uint32_t*>(dst) = __builtin_amdgcn_perm(high23, high01, 0x07060302u);
+            *reinterpret_cast<uint32_t*>(dst + LS) = __builtin_amdgcn_perm(high23, high01, 0x05040100u);
+            *reinterpret_cast<uint32_t*>(dst + 2 * LS) = __builtin_amdgcn_perm(low23, low01, 0x07060302u);
+            *reinterpret_cast<uint32_t*>(dst + 3 * LS) = __builtin_amdgcn_perm(low23, low01, 0x05040100u);
           }
         }
       }
@@ -652,36 +706,45 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
 #pragma unroll
     for (int w = 0; w < 2; ++w) {
       i32x4 t = izero;
-      if (col_live_k) t = *reinterpret_cast<const i32x4*>(Qs + n * 128 + (2 * g + w) * 16);
+      if (col_live_k) t = *reinterpret_cast<const i32x4*>(Qs + n * LS + (2 * g + w) * 16);
       bqs[w] = t;
     }
 
     // ---- 2. scores: S[t][col] = sum_c (u[t, c] - offset) limb[col][c] ----
+    [[maybe_unused]] float sc[8];   // TURN: of head g, the lane's tokens tA and tB of each 32
     // (the offset's share, the same for every token, is the accumulators' starting value)
     {
       i32x4 cinitk = izero;
+      auto product = [&](const i32x4& codes, const i32x4& limbs, const i32x4& c) __attribute__((always_inline)) {
+        return TURN ? __builtin_amdgcn_mfma_i32_16x16x64_i8(limbs, codes, c, 0, 0, 0) : __builtin_amdgcn_mfma_i32_16x16x64_i8(codes, limbs, c, 0, 0, 0);
+      };
       if (C::kOffset != 0) {
-        cinitk = __builtin_amdgcn_mfma_i32_16x16x64_i8(a_minus, bqs[0], izero, 0, 0, 0);
-        cinitk = __builtin_amdgcn_mfma_i32_16x16x64_i8(a_minus, bqs[1], cinitk, 0, 0, 0);
+        cinitk = product(a_minus, bqs[0], izero);
+        cinitk = product(a_minus, bqs[1], cinitk);
       }
+      // limb pairs are joined as integers (|S| <= 2^21 per limb: 128 channels x 128 x 128), then as floats
+      auto keep = [&](int j, const i32x4& v) __attribute__((always_inline)) {
+        if (TURN) sc[j] = fmaf((float)(v[0] * 256 + v[1]), 65536.f, (float)(v[2] * 256 + v[3]));
+        else if (col_live_k) *reinterpret_cast<i32x4*>(Ss + n * SS + 16 * j + 4 * g) = v;
+      };
       i32x4 s_prev = izero;
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const i32x4 a0 = C::half(ring[j], 0), a1 = C::half(ring[j], 1);
         __builtin_amdgcn_sched_barrier(0);   // the slot is dead from here on: refill it in place
-        if (HAS_NEXT) ring[j] = __builtin_nontemporal_load(reinterpret_cast<const chunk_t*>(kc_next + j * (16 * ROWB)));
+        if (HAS_NEXT) ring[j] = __builtin_nontemporal_load(reinterpret_cast<const chunk_t*>(kc_next + chunk_rows(j) * ROWB));
         __builtin_amdgcn_sched_barrier(0);
-        i32x4 s = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0, bqs[0], cinitk, 0, 0, 0);
-        s = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1, bqs[1], s, 0, 0, 0);
-        // the previous chunk's scores are stored while this chunk's MFMAs run
-        if (j > 0 && col_live_k) *reinterpret_cast<i32x4*>(Ss + n * SS + 16 * (j - 1) + 4 * g) = s_prev;
+        i32x4 s = product(a0, bqs[0], cinitk);
+        s = product(a1, bqs[1], s);
+        // the previous chunk's scores are taken while this chunk's MFMAs run
+        if (j > 0) keep(j - 1, s_prev);
         s_prev = s;
       }
-      if (col_live_k) *reinterpret_cast<i32x4*>(Ss + n * SS + 16 * 7 + 4 * g) = s_prev;
+      keep(7, s_prev);
     }
-    __builtin_amdgcn_wave_barrier();
+    if (!TURN) __builtin_amdgcn_wave_barrier();
 
-    // ---- 3. online softmax, tokens tA and tB per lane ----
+    // ---- 3. online softmax, tokens tA and tB per lane (TURN: of head g, the pair of each 32 tokens) ----
     float v_unscale, vs = 0.f;
     float vs_second = 0.f;   // a pair of heads: the second head's steps get a scale of their own
     if (!N3) {
@@ -712,11 +775,62 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
       dvsA[gr] = dvsA[gr] > kMost ? kMost : dvsA[gr];
       dvsB[gr] = dvsB[gr] > kMost ? kMost : dvsB[gr];
     }
+    if constexpr (TURN) {
+      // lane (n, g) has its pair's steps of the g-th 32 tokens; it needs those of all four for its own head (a pair of heads:
+      // its kv head's).  Three swaps deal a register of each row of lanes to all of them.
+      float kA[4], kB[4], wA[4], wB[4];
+      auto deal = [&](const float (&x)[NG], float (&to)[4]) __attribute__((always_inline)) {
+        const uint32_t x0 = __builtin_bit_cast(uint32_t, x[0]), x1 = __builtin_bit_cast(uint32_t, x[NG - 1]);
+        const auto h = __builtin_amdgcn_permlane32_swap(x0, x1, false, false);   // rows 0, 1 twice; rows 2, 3 twice
+        const auto lo = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false), hi = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);
+        to[0] = __builtin_bit_cast(float, (uint32_t)lo[0]); to[1] = __builtin_bit_cast(float, (uint32_t)lo[1]);
+        to[2] = __builtin_bit_cast(float, (uint32_t)hi[0]); to[3] = __builtin_bit_cast(float, (uint32_t)hi[1]);
+      };
+      deal(dkA, kA);
+      deal(dkB, kB);
+      deal(dvsA, wA);
+      deal(dvsB, wB);
+      float mt_lane = -INFINITY;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        // a token past the end scores minus infinity (its step counts as zero)
+        const int t = tok0 + 32 * k + key_row;
+        sc[2 * k] = fmaf(sc[2 * k], kA[k], (HAS_NEXT || t < S) ? 0.f : -INFINITY);
+        sc[2 * k + 1] = fmaf(sc[2 * k + 1], kB[k], (HAS_NEXT || t + kPairRows < S) ? 0.f : -INFINITY);
+        mt_lane = fmaxf(mt_lane, fmaxf(sc[2 * k], sc[2 * k + 1]));
+      }
+      // the running maxima move in a sequence's first tiles and rarely afterwards: they are reduced only when some lane
+      // holds a score above its head's
+      if (__any(mt_lane > m_run[0])) {
+        const float m_new = fmaxf(m_run[0], row_allmax(mt_lane));   // finite after the first tile (it has a valid token)
+        const float alpha = __builtin_amdgcn_exp2f(m_run[0] - m_new);
+        m_run[0] = m_new;
+        l_run[0] *= alpha;
+        const float alpha_col = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(64 * packed_head, __builtin_bit_cast(int, alpha)));
+#pragma unroll
+        for (int st = 0; st < NSET; ++st) acc[st] *= alpha_col;
+      }
+      float p_sum = 0.f;
+      unsigned char* const dst0 = Ps + CPH * g * LS + (n >> 3) * 16 + 2 * (n & 7);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float pA = __builtin_amdgcn_exp2f(sc[2 * k] - m_run[0]), pB = __builtin_amdgcn_exp2f(sc[2 * k + 1] - m_run[0]);
+        p_sum += pA + pB;
+        const uint32_t iA = ((uint32_t)fmaf(pA, wA[k], 0.5f) + kDigitBias) ^ kDigitBias;
+        const uint32_t iB = ((uint32_t)fmaf(pB, wB[k], 0.5f) + kDigitBias) ^ kDigitBias;
+        const uint32_t low = __builtin_amdgcn_perm(iB, iA, 0x05010400u);   // the two lowest limbs of both tokens
+        unsigned char* const dst = dst0 + 32 * k;
+        *reinterpret_cast<uint16_t*>(dst) = (uint16_t)__builtin_amdgcn_perm(iB, iA, 0x0C0C0602u);
+        *reinterpret_cast<uint16_t*>(dst + LS) = (uint16_t)(low >> 16);
+        *reinterpret_cast<uint16_t*>(dst + 2 * LS) = (uint16_t)low;
+      }
+      l_run[0] += p_sum;
+    }
     float alpha[R];
     float wA[R][NG], wB[R][NG];   // three tensors: the weights, kept until their common scale is known
     float wmax = 0.f;
 #pragma unroll
-    for (int hd = 0; hd < R; ++hd) {
+    for (int hd = 0; hd < (TURN ? 0 : R); ++hd) {
       float sA = pastA, sB = pastB;
 #pragma unroll
       for (int gr = 0; gr < NG; ++gr) {
@@ -725,7 +839,6 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
         const int* s1 = s0 + SS;
         const int* s2 = s1 + SS;
         const int* s3 = s2 + SS;
-        // limb pairs are joined as integers (|S| <= 2^21 per limb: 128 channels x 128 x 128), then as floats
         sA = fmaf(fmaf((float)(s0[tA] * 256 + s1[tA]), 65536.f, (float)(s2[tA] * 256 + s3[tA])), dkA[gr], sA);
         sB = fmaf(fmaf((float)(s0[tB] * 256 + s1[tB]), 65536.f, (float)(s2[tB] * 256 + s3[tB])), dkB[gr], sB);
       }
@@ -766,10 +879,10 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
           const uint32_t iA = ((uint32_t)fmaf(pA, dvsA[gr], 0.5f) + kDigitBias) ^ kDigitBias;
           const uint32_t iB = ((uint32_t)fmaf(pB, dvsB[gr], 0.5f) + kDigitBias) ^ kDigitBias;
           const uint32_t low = __builtin_amdgcn_perm(iB, iA, 0x05010400u);   // the two lowest limbs of both tokens
-          unsigned char* dst = Ps + (CPH * hd + (P2 ? 0 : 4 * gr)) * 128 + G16 * 16 + 2 * pi;
+          unsigned char* dst = Ps + (CPH * hd + (P2 ? 0 : 4 * gr)) * LS + G16 * 16 + 2 * pi;
           *reinterpret_cast<uint16_t*>(dst) = (uint16_t)__builtin_amdgcn_perm(iB, iA, 0x0C0C0602u);
-          *reinterpret_cast<uint16_t*>(dst + 128) = (uint16_t)(low >> 16);
-          *reinterpret_cast<uint16_t*>(dst + 256) = (uint16_t)low;
+          *reinterpret_cast<uint16_t*>(dst + LS) = (uint16_t)(low >> 16);
+          *reinterpret_cast<uint16_t*>(dst + 2 * LS) = (uint16_t)low;
         }
       }
     }
@@ -788,11 +901,11 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
           const uint32_t iA = ((uint32_t)(int)__builtin_rintf(wA[hd][gr] * vs) + kDigitBias) ^ kDigitBias;
           const uint32_t iB = ((uint32_t)(int)__builtin_rintf(wB[hd][gr] * vs) + kDigitBias) ^ kDigitBias;
           const uint32_t low = __builtin_amdgcn_perm(iB, iA, 0x05010400u), high = __builtin_amdgcn_perm(iB, iA, 0x07030602u);
-          unsigned char* dst = Ps + (CPH * hd + 4 * gr) * 128 + G16 * 16 + 2 * pi;
+          unsigned char* dst = Ps + (CPH * hd + 4 * gr) * LS + G16 * 16 + 2 * pi;
           *reinterpret_cast<uint16_t*>(dst) = (uint16_t)(high >> 16);
-          *reinterpret_cast<uint16_t*>(dst + 128) = (uint16_t)high;
-          *reinterpret_cast<uint16_t*>(dst + 256) = (uint16_t)(low >> 16);
-          *reinterpret_cast<uint16_t*>(dst + 384) = (uint16_t)low;
+          *reinterpret_cast<uint16_t*>(dst + LS) = (uint16_t)high;
+          *reinterpret_cast<uint16_t*>(dst + 2 * LS) = (uint16_t)(low >> 16);
+          *reinterpret_cast<uint16_t*>(dst + 3 * LS) = (uint16_t)low;
         }
       }
     }
@@ -803,12 +916,12 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
 #pragma unroll
     for (int v = 0; v < 2; ++v) {
       i32x4 t = izero;
-      if (col_live) t = *reinterpret_cast<const i32x4*>(Ps + n * 128 + (2 * g + v) * 16);
+      if (col_live) t = *reinterpret_cast<const i32x4*>(Ps + n * LS + (2 * g + v) * 16);
       bp[v] = t;
     }
     float alpha_col = 1.f;
 #pragma unroll
-    for (int hd = 0; hd < R; ++hd) alpha_col = (packed_head == hd) ? alpha[hd] : alpha_col;
+    for (int hd = 0; hd < (TURN ? 0 : R); ++hd) alpha_col = (packed_head == hd) ? alpha[hd] : alpha_col;
     float aT[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) aT[i] = (float)vsm_h[i] * v_unscale;
@@ -817,7 +930,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
       cinitv = JOIN ? __builtin_amdgcn_mfma_i32_16x16x64_i8(bp[0], a_minus, izero, 0, 0, 0) : __builtin_amdgcn_mfma_i32_16x16x64_i8(a_minus, bp[0], izero, 0, 0, 0);
       cinitv = JOIN ? __builtin_amdgcn_mfma_i32_16x16x64_i8(bp[1], a_minus, cinitv, 0, 0, 0) : __builtin_amdgcn_mfma_i32_16x16x64_i8(a_minus, bp[1], cinitv, 0, 0, 0);
     }
-    if (__any(alpha_col != 1.f)) {   // the running maximum moved: rare after the first tiles
+    if (!TURN && __any(alpha_col != 1.f)) {   // the running maximum moved: rare after the first tiles
 #pragma unroll
       for (int st = 0; st < NSET; ++st) acc[st] *= alpha_col;
     }
@@ -953,15 +1066,15 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   DQ_STAMP(18);
 
   // ---- merge the waves of the workgroup ----
-  float* Macc = reinterpret_cast<float*>(wl);            // [NC][128] per wave (reuses the wave's LDS)
-  float* Mml = Macc + NC * D;                            // [R] m, [R] l
+  float* Macc = reinterpret_cast<float*>(wl);            // [MC][128] per wave (reuses the wave's LDS)
+  float* Mml = Macc + MC * D;                            // [R] m, [R] l
 #pragma unroll
-  for (int hd = 0; hd < R; ++hd) l_run[hd] = wave_allsum(l_run[hd]);
-  if (JOIN) {                 // [head][0][channel b1 * 8 + b2]: the limbs are joined already
+  for (int hd = 0; hd < (TURN ? 1 : R); ++hd) l_run[hd] = TURN ? row_allsum(l_run[hd]) : wave_allsum(l_run[hd]);
+  if (JOIN) {                 // [head][channel b1 * 8 + b2]
 #pragma unroll
     for (int st = 0; st < NSET; ++st) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) Macc[4 * packed_head * D + (4 * g + i) * J2 + st * PK + packed_slot] = acc[st][i];
+      for (int i = 0; i < 4; ++i) Macc[packed_head * D + (4 * g + i) * J2 + st * PK + packed_slot] = acc[st][i];
     }
   } else if (N3 || (n & 3) != 3) {   // [head][limb][channel b1 * 8 + b2]
 #pragma unroll
@@ -970,7 +1083,9 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
       for (int i = 0; i < 4; ++i) Macc[(4 * packed_head + (n & 3)) * D + (4 * g + i) * J2 + st * PK + packed_slot] = acc[st][i];
     }
   }
-  if (lane == 0) {
+  if (TURN) {
+    if (n == 0) { Mml[g] = m_run[0]; Mml[R + g] = l_run[0]; }
+  } else if (lane == 0) {
 #pragma unroll
     for (int hd = 0; hd < R; ++hd) { Mml[hd] = m_run[hd]; Mml[R + hd] = l_run[hd]; }
   }
@@ -982,21 +1097,21 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
     float M = -INFINITY;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      M = fmaxf(M, reinterpret_cast<const float*>(smem + w * WAVE_LDS)[NC * D + hd]);
+      M = fmaxf(M, reinterpret_cast<const float*>(smem + w * WAVE_LDS)[MC * D + hd]);
       if (TM) M = fmaxf(M, s_tail[w * Tail::kResultFloats + hd * (D + 2) + D]);
     }
     float o = 0.f, L = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
       const float* base = reinterpret_cast<const float*>(smem + w * WAVE_LDS);
-      const float mw = base[NC * D + hd];
+      const float mw = base[MC * D + hd];
       const float wgt = (mw == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mw - M);
-      const float* col = base + 4 * hd * D + cv;
+      const float* col = base + (JOIN ? hd : 4 * hd) * D + cv;
       const float v = JOIN ? col[0]
                       : N3 ? ((col[0] * 256.f + col[D]) * 256.f + col[2 * D]) * 256.f + col[3 * D]
                            : col[0] * 65536.f + col[D] * 256.f + col[2 * D];
       o = fmaf(v, wgt, o);
-      L = fmaf(base[NC * D + R + hd], wgt, L);
+      L = fmaf(base[MC * D + R + hd], wgt, L);
       if (TM) {   // the wave's share of the fp16 tail
         const float* tp = s_tail + w * Tail::kResultFloats + hd * (D + 2);
         const float wt = (tp[D] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(tp[D] - M);
