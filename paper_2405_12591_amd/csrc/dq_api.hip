@@ -37,9 +37,12 @@ static void choose_mfma_shape(int units, int max_tiles, int heads, int bits, boo
   else if (bits == 4) resident = (!three && (heads == 1 || (heads == 2 && !tail && !two_groups))) ? 3 : 2;
   else resident = heads == 1 ? (three ? 3 : 4) : heads == 2 ? (three ? 2 : 3) : 2;
   const float h = (float)(heads - 1), n3 = three ? 1.f : 0.f;
-  const float chain = 1.955f + 0.626f * h + 2.847f * n3 - (pair ? 0.2f : 0.f);
-  const float issue = 0.018f + 0.483f * bits + 0.008f * h + 0.758f * n3;
-  const float per_wave = 2.172f + (tail ? 0.024f * (1 + heads) : 0.f);
+  // (eight heads, two sets of columns: fitted by themselves, 276 sizes in three code widths; the picks are 0.25 % behind the fastest
+  // shape on average, 7.5 % at worst, and with the constants of the others, extended to eight heads, 0.8 % and 28 %)
+  const bool eight = heads == 8;
+  const float chain = eight ? 3.623f : 1.955f + 0.626f * h + 2.847f * n3 - (pair ? 0.2f : 0.f);
+  const float issue = eight ? 1.247f : 0.018f + 0.483f * bits + 0.008f * h + 0.758f * n3;
+  const float per_wave = eight ? 2.087f : 2.172f + (tail ? 0.024f * (1 + heads) : 0.f);
   float best = 3.0e38f;
   for (const int n : kSplits) {
     if (n > kMaxSplits || n > max_tiles) break;
@@ -50,12 +53,12 @@ static void choose_mfma_shape(int units, int max_tiles, int heads, int bits, boo
       auto round = [&](int groups) -> float {                          // so many workgroups on a compute unit at a time
         if (groups == 0) return 0.f;
         const float waves = 0.25f * (float)(groups * nw);               // per SIMD
-        return tiles * (fmaxf(chain, waves * issue) + 0.289f * waves) + per_wave * waves + 0.072f;
+        return tiles * (fmaxf(chain, waves * issue) + (eight ? 0.911f : 0.289f) * waves) + per_wave * waves + 0.072f;
       };
       const int together = resident * 4 / nw > 1 ? resident * 4 / nw : 1;
       const long per_cu = ((long)units * n + 255) / 256;
       float t = (float)(per_cu / together) * round(together) + round((int)(per_cu % together));
-      if (n > 1) t += 1.606f + 0.112f * n;
+      if (n > 1) t += eight ? 2.038f + 0.233f * n : 1.606f + 0.112f * n;
       if (tail) t += 0.136f * (float)((16 + n * nw - 1) / (n * nw));    // (64 rows, four a load)
       if (t < 0.914f * best) { best = t; *n_out = n; *nw_out = nw; }
     }
@@ -63,13 +66,14 @@ static void choose_mfma_shape(int units, int max_tiles, int heads, int bits, boo
 }
 
 int choose_splits(const dq_format* f, int batch, int q_heads, int kv_heads, int max_seq_len, bool mfma, bool tail,
-                  uint32_t flags, int* nw_out) {
+                  uint32_t flags, int* nw_out, int* head_groups_out, int* heads_per_group_out) {
   const int max_tiles = (max_seq_len + kTileTokens - 1) / kTileTokens;
   int n = 1, nw = 4;
+  int per_group = q_heads / kv_heads;
+  int hg = mfma ? mfma_head_groups(f, q_heads, kv_heads, &per_group) : 1;   // each head group is a workgroup of its own
+  if (mfma && mfma_eight_heads(f, batch, q_heads, kv_heads, max_tiles, tail)) { hg /= 2; per_group = 8; }
   if (max_tiles > 0) {
     if (mfma) {
-      int per_group = 1;
-      const int hg = mfma_head_groups(f, q_heads, kv_heads, &per_group);   // each head group is a workgroup of its own
       if (mfma_pair_heads(f, q_heads, kv_heads))   // two kv heads per workgroup
         choose_mfma_shape(batch * kv_heads / 2 * hg, max_tiles, 2 * per_group, f->bits, true, false, true, tail, &n, &nw);
       else
@@ -88,7 +92,9 @@ int choose_splits(const dq_format* f, int batch, int q_heads, int kv_heads, int 
   if (n < 1) n = 1;
   if (n > kMaxSplits) n = kMaxSplits;
   if (max_tiles > 0 && n > max_tiles) n = max_tiles;
-  if (nw_out) *nw_out = nw;
+  *nw_out = nw;
+  *head_groups_out = hg;
+  *heads_per_group_out = per_group;
   return n;
 }
 
@@ -223,9 +229,8 @@ static int32_t decode_impl(const dq_format* fmt, const dq_cache* cache, const ui
   char* ws = reinterpret_cast<char*>(workspace);
   a.counters = reinterpret_cast<int32_t*>(ws + kWsHeaderBytes);
   a.partials = reinterpret_cast<float*>(ws + kWsHeaderBytes + decode_counter_bytes(cache->batch, q_heads));
-  a.heads_per_group = q_heads / cache->kv_heads;
-  a.head_groups = use_mfma ? mfma_head_groups(fmt, q_heads, cache->kv_heads, &a.heads_per_group) : 1;
-  a.n_split = choose_splits(fmt, cache->batch, q_heads, cache->kv_heads, max_seq_len, use_mfma, tail != nullptr, flags, &a.nw);
+  a.n_split = choose_splits(fmt, cache->batch, q_heads, cache->kv_heads, max_seq_len, use_mfma, tail != nullptr, flags, &a.nw,
+                            &a.head_groups, &a.heads_per_group);
   // With one workgroup per compute unit and equal shares, a launch ends with its slowest XCD.
   // Dealing the units so that every XCD sees every residue class of them (mod 8) brings the XCDs
   // closer together: measured 4 - 5 % faster on the 256-unit benchmark shapes (4- and 8-bit), neutral

@@ -21,7 +21,7 @@ struct DecodeArgs {
   dq_tail tail;            // k_tail == nullptr: no tail
   int nw;                  // waves per workgroup of the matrix-core kernel (4 or 8)
   int head_groups;         // matrix-core kernel: workgroups per (sequence, kv head, split) ...
-  int heads_per_group;     // ... each with this many query heads (1, 2 or 4; the last one what is left)
+  int heads_per_group;     // ... each with this many query heads (1, 2, 4 or 8; the last one what is left)
   int pair_heads;          // matrix-core kernel: 1 = two kv heads of 64 channels per workgroup (heads_per_group query heads of each)
   int unit_map;            // which (sequence, kv head) a workgroup row takes: 0 = its own index, see unit_of_row()
   int rows_on_x;           // 0: grid (splits, rows); 1: grid (rows, splits), for more rows than a grid's y extent takes
@@ -73,7 +73,8 @@ bool mfma_supported(const dq_format* f, int q_heads, int kv_heads);
 bool mfma_takes(const dq_format* f, int q_heads, int kv_heads);
 bool mfma_pair_heads(const dq_format* f, int q_heads, int kv_heads);
 int mfma_head_groups(const dq_format* f, int q_heads, int kv_heads, int* heads_per_group);
+bool mfma_eight_heads(const dq_format* f, int batch, int q_heads, int kv_heads, int max_tiles, bool tail);
 int choose_splits(const dq_format* f, int batch, int q_heads, int kv_heads, int max_seq_len, bool mfma,
-                  bool tail, uint32_t flags, int* nw_out);
+                  bool tail, uint32_t flags, int* nw_out, int* head_groups_out, int* heads_per_group_out);
 
 }  // namespace dq

@@ -210,17 +210,25 @@ __device__ __forceinline__ float pow2i(int e) {
 // step group, so two query heads of each kv head share a code stream; more come in head groups of
 // two.  Batch 8, 32 query on 8 kv heads, 2048 to 4096 tokens (15 MB): 74 + 7 us in the plain kernel
 // these shapes used to take, 12 us here.
-template <int BITS, int NG, int R, int NW, int TM, bool N3, bool P2>
+//
+// HP = 2: two sets of four heads in one workgroup, each with sixteen columns of its own.  What bounded more than four heads per kv head
+// was the stream: every head group asked for the same codes (8 x 64 heads, 8 kv heads, x 32768 tokens: 587 MB through the L2s for 294 MB
+// of cache; 68.5 us with one wave a SIMD, 66.2 with two) and unpacked them.  Here a chunk is asked for and unpacked once and multiplied with both
+// sets: 221 registers, two waves a SIMD.  4 bits 65.4 -> 55 us, 2 bits 52.9 -> 45.5, 8 bits x 8192 tokens 47.4 -> 32.7.
+// Which launches take it: mfma_eight_heads (dq_decode_mfma.hip).
+template <int BITS, int NG, int R, int NW, int TM, bool N3, bool P2, int HP = 1>
 __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode_mfma_kernel(DecodeArgs a) {
   static_assert(!P2 || (NG == 2 && (R == 2 || R == 4) && !N3), "a pair of heads is two step groups and two or four query heads");
+  static_assert(HP == 1 || (HP == 2 && R == 4 && NG == 1 && TM == 0 && !N3), "sets of four heads: no tail, two tensors, one step group");
+  constexpr int RW = R * HP;                  // query heads per workgroup, in HP sets of sixteen columns
   typedef Codec<BITS> C;
   typedef typename C::chunk_t chunk_t;
   constexpr int CG = P2 ? 1 : NG;             // column groups per head (a pair: a head has channels of one step group only)
-  constexpr int HPK = P2 ? R / 2 : R;         // query heads per kv head of the workgroup
+  constexpr int HPK = P2 ? R / 2 : RW;        // query heads per kv head of the workgroup
   constexpr int CPH = 4 * CG;                 // B columns per head: column CPH*head + 4*group + limb
   constexpr int NC = CPH * R;
   static_assert(NC <= 16, "too many heads for sixteen B columns");
-  constexpr int F = (R + 1) / 2;              // fold MFMAs (two heads each)
+  constexpr int F = (RW + 1) / 2;             // fold MFMAs (two heads each)
   constexpr int D = 128, J1 = 16, J2 = 8;
   // The epilogue multiplies o'[r] of every head and b2 by the values' small tensor, sixteen (head, b2) columns at a time.
   // With one head, or three tensors, one b2 fills only 3 R of the columns (one limb triple per head, once the two step groups'
@@ -248,11 +256,11 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   constexpr int CHUNKB = sizeof(chunk_t);
   constexpr int SS = 132;                     // ints per column of the score staging (128 tokens + pad)
   constexpr int LS = 144;                     // bytes from column to column of the limbs (128 and a pad that keeps the b128 reads off each other's banks)
-  constexpr int QS_BYTES = NC * LS, PS_BYTES = NC * LS, SS_BYTES = TURN ? R * J2 * TS * 4 : NC * SS * 4;
-  constexpr int MC = JOIN ? R : NC;           // columns of a wave's result in the merge (JOIN: the limbs are joined already)
+  constexpr int QS_BYTES = HP * NC * LS, PS_BYTES = HP * NC * LS, SS_BYTES = TURN ? RW * J2 * TS * 4 : NC * SS * 4;
+  constexpr int MC = JOIN ? RW : NC;           // columns of a wave's result in the merge (JOIN: the limbs are joined already)
   constexpr int WAVE_LDS = QS_BYTES + PS_BYTES + SS_BYTES;
-  static_assert(WAVE_LDS >= MC * D * 4 + 2 * R * 4, "merge area must fit the wave's LDS");
-  static_assert(!JOIN || R * J2 * TS * 4 <= SS_BYTES, "the joined values take the scores' place");
+  static_assert(WAVE_LDS >= MC * D * 4 + 2 * RW * 4, "merge area must fit the wave's LDS");
+  static_assert(!JOIN || RW * J2 * TS * 4 <= SS_BYTES, "the joined values take the scores' place");
   __shared__ __attribute__((aligned(16))) unsigned char smem[NW * WAVE_LDS];
   // the waves' partial results over the fp16 tail
   // (128 rows requested up front, by two workgroups if TM == 2; fewer where the heads leave fewer registers)
@@ -260,8 +268,8 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   typedef TailWave<R, kTailBatch < kTailMost ? kTailBatch : kTailMost, P2> Tail;
   __shared__ float s_tail[TM ? NW * Tail::kResultFloats : 1];
   __shared__ int s_last;
-  __shared__ float s_wgt[4][kMaxSplits];
-  __shared__ float s_sum[4];
+  __shared__ float s_wgt[HP * 4][kMaxSplits];
+  __shared__ float s_sum[HP * 4];
 
   const int tid = threadIdx.x, lane = tid & 63;
 #ifdef DQ_TIMELINE
@@ -362,24 +370,34 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
         v[k] = (sp + k < ns) ? __hip_atomic_load(col + (sp + k) * (RD + 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.f;
     };
     float v_first[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    float m0 = -INFINITY, l0 = 0.f;
-    if (wave < R && head_live(wave)) {
-      const float* base = a.partials + head_row(wave) * ns * (RD + 2);
-      if (lane < ns) {
-        m0 = __hip_atomic_load(base + lane * (RD + 2) + RD, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        l0 = __hip_atomic_load(base + lane * (RD + 2) + RD + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    constexpr int kHeadsAWave = (RW + NW - 1) / NW;
+    float m0[kHeadsAWave], l0[kHeadsAWave];
+#pragma unroll
+    for (int k = 0; k < kHeadsAWave; ++k) {
+      const int hd = wave + k * NW;
+      m0[k] = -INFINITY; l0[k] = 0.f;
+      if (hd < RW && head_live(hd)) {
+        const float* base = a.partials + head_row(hd) * ns * (RD + 2);
+        if (lane < ns) {
+          m0[k] = __hip_atomic_load(base + lane * (RD + 2) + RD, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          l0[k] = __hip_atomic_load(base + lane * (RD + 2) + RD + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
       }
     }
-    if (tid < R * RD && head_live(tid / RD)) load_slots(a.partials + head_row(tid / RD) * ns * (RD + 2) + tid % RD, 0, v_first);
-    if (wave < R && head_live(wave)) {
-      const float M = wave_allmax(m0);
-      const float w0 = (m0 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m0 - M);
-      if (lane < ns) s_wgt[wave][lane] = w0;
-      const float L = wave_allsum(l0 * w0);
-      if (lane == 0) s_sum[wave] = L;
+    if (tid < RW * RD && head_live(tid / RD)) load_slots(a.partials + head_row(tid / RD) * ns * (RD + 2) + tid % RD, 0, v_first);
+#pragma unroll
+    for (int k = 0; k < kHeadsAWave; ++k) {
+      const int hd = wave + k * NW;
+      if (hd < RW && head_live(hd)) {
+        const float M = wave_allmax(m0[k]);
+        const float w0 = (m0[k] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m0[k] - M);
+        if (lane < ns) s_wgt[hd][lane] = w0;
+        const float L = wave_allsum(l0[k] * w0);
+        if (lane == 0) s_sum[hd] = L;
+      }
     }
     __syncthreads();
-    for (int idx = tid; idx < R * RD; idx += 64 * NW) {
+    for (int idx = tid; idx < RW * RD; idx += 64 * NW) {
       const int hd = idx / RD, c = idx % RD;
       if (!head_live(hd)) continue;
       const float* col = a.partials + head_row(hd) * ns * (RD + 2) + c;
@@ -457,18 +475,18 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
       // across a branch the compiler loses count of the loads in flight and waits for all of them
       // (a pair of heads: virtual row b1 = 4g + i of virtual head hd is row b1 % 8 of the real head;
       // the rows of the other head's half are zeroed when packed)
-      const uint16_t* qp = a.q + head_row(min(hd, R - 1)) * RD;
+      const uint16_t* qp = a.q + head_row(min(hd, RW - 1)) * RD;
 #pragma unroll
       for (int i = 0; i < 4; ++i) q_raw[f][i] = qp[((4 * g + i) & (RJ1 - 1)) * J2 + b2];
     }
   }
 
-  float m_run[TURN ? 1 : R], l_run[TURN ? 1 : R];   // TURN: of head g, the sum over the lane's own tokens
+  float m_run[TURN ? HP : R], l_run[TURN ? HP : R];   // TURN: of head g, the sum over the lane's own tokens
 #pragma unroll
-  for (int hd = 0; hd < (TURN ? 1 : R); ++hd) { m_run[hd] = -INFINITY; l_run[hd] = 0.f; }
-  f32x4 acc[NSET];
+  for (int hd = 0; hd < (TURN ? HP : R); ++hd) { m_run[hd] = -INFINITY; l_run[hd] = 0.f; }
+  f32x4 acc[HP * NSET];
 #pragma unroll
-  for (int st = 0; st < NSET; ++st) acc[st] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  for (int st = 0; st < HP * NSET; ++st) acc[st] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
   const float qk_scale = a.scale * kLog2e;
   constexpr int kMinusWord = (int)((uint32_t)((256 - C::kOffset) & 255) * 0x01010101u);  // four bytes of -offset
@@ -671,7 +689,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
         // the four words' bytes by limb
         const uint32_t low01 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u), high01 = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u);
         const uint32_t low23 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u), high23 = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
-        if (hd < R) {
+        if (hd < RW) {
           const int grp = (CG == 2) ? (n >> 3) : 0;
           unsigned char* dst = Qs + (CPH * hd + 4 * grp) * LS + (n >> 1) * 16 + C::slot((n & 1) * 8 + fold_b2(4 * (g & 1)));
           if (BITS == 2) {   // two and two: b2, b2 + 4 and b2 + 1, b2 + 5
@@ -702,45 +720,56 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
     // a token past the end scores minus infinity (its step, which may be anything, counts as zero)
     const float pastA = (N3 || okA) ? 0.f : -INFINITY, pastB = (N3 || okB) ? 0.f : -INFINITY;
     __builtin_amdgcn_wave_barrier();
-    i32x4 bqs[2];
+    i32x4 bqs[HP][2];
 #pragma unroll
-    for (int w = 0; w < 2; ++w) {
-      i32x4 t = izero;
-      if (col_live_k) t = *reinterpret_cast<const i32x4*>(Qs + n * LS + (2 * g + w) * 16);
-      bqs[w] = t;
+    for (int hp = 0; hp < HP; ++hp) {
+#pragma unroll
+      for (int w = 0; w < 2; ++w) {
+        i32x4 t = izero;
+        if (col_live_k) t = *reinterpret_cast<const i32x4*>(Qs + (hp * NC + n) * LS + (2 * g + w) * 16);
+        bqs[hp][w] = t;
+      }
     }
 
     // ---- 2. scores: S[t][col] = sum_c (u[t, c] - offset) limb[col][c] ----
-    [[maybe_unused]] float sc[8];   // TURN: of head g, the lane's tokens tA and tB of each 32
+    [[maybe_unused]] float sc[HP][8];   // TURN: of head g, the lane's tokens tA and tB of each 32
     // (the offset's share, the same for every token, is the accumulators' starting value)
     {
-      i32x4 cinitk = izero;
+      i32x4 cinitk[HP];
       auto product = [&](const i32x4& codes, const i32x4& limbs, const i32x4& c) __attribute__((always_inline)) {
         return TURN ? __builtin_amdgcn_mfma_i32_16x16x64_i8(limbs, codes, c, 0, 0, 0) : __builtin_amdgcn_mfma_i32_16x16x64_i8(codes, limbs, c, 0, 0, 0);
       };
-      if (C::kOffset != 0) {
-        cinitk = product(a_minus, bqs[0], izero);
-        cinitk = product(a_minus, bqs[1], cinitk);
+#pragma unroll
+      for (int hp = 0; hp < HP; ++hp) {
+        cinitk[hp] = izero;
+        if (C::kOffset != 0) {
+          cinitk[hp] = product(a_minus, bqs[hp][0], izero);
+          cinitk[hp] = product(a_minus, bqs[hp][1], cinitk[hp]);
+        }
       }
       // limb pairs are joined as integers (|S| <= 2^21 per limb: 128 channels x 128 x 128), then as floats
-      auto keep = [&](int j, const i32x4& v) __attribute__((always_inline)) {
-        if (TURN) sc[j] = fmaf((float)(v[0] * 256 + v[1]), 65536.f, (float)(v[2] * 256 + v[3]));
+      auto keep = [&](int hp, int j, const i32x4& v) __attribute__((always_inline)) {
+        if (TURN) sc[hp][j] = fmaf((float)(v[0] * 256 + v[1]), 65536.f, (float)(v[2] * 256 + v[3]));
         else if (col_live_k) *reinterpret_cast<i32x4*>(Ss + n * SS + 16 * j + 4 * g) = v;
       };
-      i32x4 s_prev = izero;
+      i32x4 s_prev[HP];
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const i32x4 a0 = C::half(ring[j], 0), a1 = C::half(ring[j], 1);
         __builtin_amdgcn_sched_barrier(0);   // the slot is dead from here on: refill it in place
         if (HAS_NEXT) ring[j] = __builtin_nontemporal_load(reinterpret_cast<const chunk_t*>(kc_next + chunk_rows(j) * ROWB));
         __builtin_amdgcn_sched_barrier(0);
-        i32x4 s = product(a0, bqs[0], cinitk);
-        s = product(a1, bqs[1], s);
-        // the previous chunk's scores are taken while this chunk's MFMAs run
-        if (j > 0) keep(j - 1, s_prev);
-        s_prev = s;
+#pragma unroll
+        for (int hp = 0; hp < HP; ++hp) {
+          i32x4 s = product(a0, bqs[hp][0], cinitk[hp]);
+          s = product(a1, bqs[hp][1], s);
+          // the previous chunk's scores are taken while this chunk's MFMAs run
+          if (j > 0) keep(hp, j - 1, s_prev[hp]);
+          s_prev[hp] = s;
+        }
       }
-      keep(7, s_prev);
+#pragma unroll
+      for (int hp = 0; hp < HP; ++hp) keep(hp, 7, s_prev[hp]);
     }
     if (!TURN) __builtin_amdgcn_wave_barrier();
 
@@ -790,41 +819,44 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
       deal(dkB, kB);
       deal(dvsA, wA);
       deal(dvsB, wB);
-      float mt_lane = -INFINITY;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        // a token past the end scores minus infinity (its step counts as zero)
-        const int t = tok0 + 32 * k + key_row;
-        sc[2 * k] = fmaf(sc[2 * k], kA[k], (HAS_NEXT || t < S) ? 0.f : -INFINITY);
-        sc[2 * k + 1] = fmaf(sc[2 * k + 1], kB[k], (HAS_NEXT || t + kPairRows < S) ? 0.f : -INFINITY);
-        mt_lane = fmaxf(mt_lane, fmaxf(sc[2 * k], sc[2 * k + 1]));
-      }
-      // the running maxima move in a sequence's first tiles and rarely afterwards: they are reduced only when some lane
-      // holds a score above its head's
-      if (__any(mt_lane > m_run[0])) {
-        const float m_new = fmaxf(m_run[0], row_allmax(mt_lane));   // finite after the first tile (it has a valid token)
-        const float alpha = __builtin_amdgcn_exp2f(m_run[0] - m_new);
-        m_run[0] = m_new;
-        l_run[0] *= alpha;
-        const float alpha_col = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(64 * packed_head, __builtin_bit_cast(int, alpha)));
+      for (int hp = 0; hp < HP; ++hp) {
+        float mt_lane = -INFINITY;
 #pragma unroll
-        for (int st = 0; st < NSET; ++st) acc[st] *= alpha_col;
-      }
-      float p_sum = 0.f;
-      unsigned char* const dst0 = Ps + CPH * g * LS + (n >> 3) * 16 + 2 * (n & 7);
+        for (int k = 0; k < 4; ++k) {
+          // a token past the end scores minus infinity (its step counts as zero)
+          const int t = tok0 + 32 * k + key_row;
+          sc[hp][2 * k] = fmaf(sc[hp][2 * k], kA[k], (HAS_NEXT || t < S) ? 0.f : -INFINITY);
+          sc[hp][2 * k + 1] = fmaf(sc[hp][2 * k + 1], kB[k], (HAS_NEXT || t + kPairRows < S) ? 0.f : -INFINITY);
+          mt_lane = fmaxf(mt_lane, fmaxf(sc[hp][2 * k], sc[hp][2 * k + 1]));
+        }
+        // the running maxima move in a sequence's first tiles and rarely afterwards: they are reduced only when some lane
+        // holds a score above its head's
+        if (__any(mt_lane > m_run[hp])) {
+          const float m_new = fmaxf(m_run[hp], row_allmax(mt_lane));   // finite after the first tile (it has a valid token)
+          const float alpha = __builtin_amdgcn_exp2f(m_run[hp] - m_new);
+          m_run[hp] = m_new;
+          l_run[hp] *= alpha;
+          const float alpha_col = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(64 * packed_head, __builtin_bit_cast(int, alpha)));
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float pA = __builtin_amdgcn_exp2f(sc[2 * k] - m_run[0]), pB = __builtin_amdgcn_exp2f(sc[2 * k + 1] - m_run[0]);
-        p_sum += pA + pB;
-        const uint32_t iA = ((uint32_t)fmaf(pA, wA[k], 0.5f) + kDigitBias) ^ kDigitBias;
-        const uint32_t iB = ((uint32_t)fmaf(pB, wB[k], 0.5f) + kDigitBias) ^ kDigitBias;
-        const uint32_t low = __builtin_amdgcn_perm(iB, iA, 0x05010400u);   // the two lowest limbs of both tokens
-        unsigned char* const dst = dst0 + 32 * k;
-        *reinterpret_cast<uint16_t*>(dst) = (uint16_t)__builtin_amdgcn_perm(iB, iA, 0x0C0C0602u);
-        *reinterpret_cast<uint16_t*>(dst + LS) = (uint16_t)(low >> 16);
-        *reinterpret_cast<uint16_t*>(dst + 2 * LS) = (uint16_t)low;
+          for (int st = 0; st < NSET; ++st) acc[hp * NSET + st] *= alpha_col;
+        }
+        float p_sum = 0.f;
+        unsigned char* const dst0 = Ps + (hp * NC + CPH * g) * LS + (n >> 3) * 16 + 2 * (n & 7);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float pA = __builtin_amdgcn_exp2f(sc[hp][2 * k] - m_run[hp]), pB = __builtin_amdgcn_exp2f(sc[hp][2 * k + 1] - m_run[hp]);
+          p_sum += pA + pB;
+          const uint32_t iA = ((uint32_t)fmaf(pA, wA[k], 0.5f) + kDigitBias) ^ kDigitBias;
+          const uint32_t iB = ((uint32_t)fmaf(pB, wB[k], 0.5f) + kDigitBias) ^ kDigitBias;
+          const uint32_t low = __builtin_amdgcn_perm(iB, iA, 0x05010400u);   // the two lowest limbs of both tokens
+          unsigned char* const dst = dst0 + 32 * k;
+          *reinterpret_cast<uint16_t*>(dst) = (uint16_t)__builtin_amdgcn_perm(iB, iA, 0x0C0C0602u);
+          *reinterpret_cast<uint16_t*>(dst + LS) = (uint16_t)(low >> 16);
+          *reinterpret_cast<uint16_t*>(dst + 2 * LS) = (uint16_t)low;
+        }
+        l_run[hp] += p_sum;
       }
-      l_run[0] += p_sum;
     }
     float alpha[R];
     float wA[R][NG], wB[R][NG];   // three tensors: the weights, kept until their common scale is known
@@ -912,12 +944,15 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
     __builtin_amdgcn_wave_barrier();
 
     // ---- 4 + 5. o' = sum_t u limb per b2, then the small-tensor epilogue ----
-    i32x4 bp[2];
+    i32x4 bp[HP][2];
 #pragma unroll
-    for (int v = 0; v < 2; ++v) {
-      i32x4 t = izero;
-      if (col_live) t = *reinterpret_cast<const i32x4*>(Ps + n * LS + (2 * g + v) * 16);
-      bp[v] = t;
+    for (int hp = 0; hp < HP; ++hp) {
+#pragma unroll
+      for (int v = 0; v < 2; ++v) {
+        i32x4 t = izero;
+        if (col_live) t = *reinterpret_cast<const i32x4*>(Ps + (hp * NC + n) * LS + (2 * g + v) * 16);
+        bp[hp][v] = t;
+      }
     }
     float alpha_col = 1.f;
 #pragma unroll
@@ -925,10 +960,14 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
     float aT[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) aT[i] = (float)vsm_h[i] * v_unscale;
-    i32x4 cinitv = izero;
-    if (C::kOffset != 0) {
-      cinitv = JOIN ? __builtin_amdgcn_mfma_i32_16x16x64_i8(bp[0], a_minus, izero, 0, 0, 0) : __builtin_amdgcn_mfma_i32_16x16x64_i8(a_minus, bp[0], izero, 0, 0, 0);
-      cinitv = JOIN ? __builtin_amdgcn_mfma_i32_16x16x64_i8(bp[1], a_minus, cinitv, 0, 0, 0) : __builtin_amdgcn_mfma_i32_16x16x64_i8(a_minus, bp[1], cinitv, 0, 0, 0);
+    i32x4 cinitv[HP];
+#pragma unroll
+    for (int hp = 0; hp < HP; ++hp) {
+      cinitv[hp] = izero;
+      if (C::kOffset != 0) {
+        cinitv[hp] = JOIN ? __builtin_amdgcn_mfma_i32_16x16x64_i8(bp[hp][0], a_minus, izero, 0, 0, 0) : __builtin_amdgcn_mfma_i32_16x16x64_i8(a_minus, bp[hp][0], izero, 0, 0, 0);
+        cinitv[hp] = JOIN ? __builtin_amdgcn_mfma_i32_16x16x64_i8(bp[hp][1], a_minus, cinitv[hp], 0, 0, 0) : __builtin_amdgcn_mfma_i32_16x16x64_i8(a_minus, bp[hp][1], cinitv[hp], 0, 0, 0);
+      }
     }
     if (!TURN && __any(alpha_col != 1.f)) {   // the running maximum moved: rare after the first tiles
 #pragma unroll
@@ -956,14 +995,14 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
       }
     };
     // JOIN: the limbs of o' joined as floats (one fp32 rounding, of the size of the accumulation's own)
-    auto join = [&](int b2, const i32x4& o) __attribute__((always_inline)) {
+    auto join = [&](int hp, int b2, const i32x4& o) __attribute__((always_inline)) {
       const float v = fmaf((float)o[0], 65536.f, fmaf((float)o[1], 256.f, (float)o[2]));
-      if (join_live) join_to[b2 * TS] = v;
+      if (join_live) join_to[(hp * R * J2 + b2) * TS] = v;
     };
-    auto epilogue_joined = [&](int st) __attribute__((always_inline)) {   // b2 = st * PK .. + PK - 1 of every head
-      const f32x4 v = *reinterpret_cast<const f32x4*>(join_from + st * (PK * TS));   // rows r = 4 g + i
+    auto epilogue_joined = [&](int hp, int st) __attribute__((always_inline)) {   // b2 = st * PK .. + PK - 1 of every head
+      const f32x4 v = *reinterpret_cast<const f32x4*>(join_from + (hp * R * J2 + st * PK) * TS);   // rows r = 4 g + i
 #pragma unroll
-      for (int i = 0; i < 4; ++i) acc[st] = __builtin_amdgcn_mfma_f32_16x16x4f32(aT[i], v[i], acc[st], 0, 0, 0);
+      for (int i = 0; i < 4; ++i) acc[hp * NSET + st] = __builtin_amdgcn_mfma_f32_16x16x4f32(aT[i], v[i], acc[hp * NSET + st], 0, 0, 0);
     };
     auto epilogue = [&](int st, const i32x4& pk) __attribute__((always_inline)) {
       f32x4 c = acc[st];
@@ -974,7 +1013,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
       }
       acc[st] = c;
     };
-    i32x4 pk_cur = izero, pk_done = izero;
+    i32x4 pk_cur = izero, pk_done = izero, o_prev[HP];
 #pragma unroll
     for (int b2 = 0; b2 < J2; ++b2) {
       const i32x4 a0 = C::half(ring[8 + b2], 0), a1 = C::half(ring[8 + b2], 1);
@@ -982,15 +1021,18 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
       if (HAS_NEXT) ring[8 + b2] = __builtin_nontemporal_load(reinterpret_cast<const chunk_t*>(vc_next + b2 * (RJ1 * VROWB)));
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (JOIN) {
-        i32x4 o = __builtin_amdgcn_mfma_i32_16x16x64_i8(bp[0], a0, cinitv, 0, 0, 0);
-        o = __builtin_amdgcn_mfma_i32_16x16x64_i8(bp[1], a1, o, 0, 0, 0);
-        // the b2 before this one is joined, and a set that has gone through LDS multiplied, while this b2's integer MFMAs run
-        if (b2 > 0) join(b2 - 1, pk_cur);
-        if (b2 > PK && (b2 - 1) % PK == 0) epilogue_joined((b2 - 1) / PK - 1);
-        pk_cur = o;
+#pragma unroll
+        for (int hp = 0; hp < HP; ++hp) {
+          i32x4 o = __builtin_amdgcn_mfma_i32_16x16x64_i8(bp[hp][0], a0, cinitv[hp], 0, 0, 0);
+          o = __builtin_amdgcn_mfma_i32_16x16x64_i8(bp[hp][1], a1, o, 0, 0, 0);
+          // the b2 before this one is joined, and a set that has gone through LDS multiplied, while this b2's integer MFMAs run
+          if (b2 > 0) join(hp, b2 - 1, o_prev[hp]);
+          if (b2 > PK && (b2 - 1) % PK == 0) epilogue_joined(hp, (b2 - 1) / PK - 1);
+          o_prev[hp] = o;
+        }
       } else {
-        i32x4 o = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0, bp[0], cinitv, 0, 0, 0);
-        o = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1, bp[1], o, 0, 0, 0);
+        i32x4 o = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0, bp[0][0], cinitv[0], 0, 0, 0);
+        o = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1, bp[0][1], o, 0, 0, 0);
         // the previous set's epilogue runs while this b2's integer MFMAs do
         if (b2 > 0 && b2 % PK == 0) epilogue(b2 / PK - 1, pk_done);
         if (b2 % PK == 0) pack(pk_cur, o, std::integral_constant<int, 0>{});
@@ -1001,9 +1043,11 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
       }
     }
     if constexpr (JOIN) {
-      join(J2 - 1, pk_cur);
+#pragma unroll
+      for (int hp = 0; hp < HP; ++hp) join(hp, J2 - 1, o_prev[hp]);
       __builtin_amdgcn_wave_barrier();
-      epilogue_joined(NSET - 1);
+#pragma unroll
+      for (int hp = 0; hp < HP; ++hp) epilogue_joined(hp, NSET - 1);
     } else {
       epilogue(NSET - 1, pk_done);
     }
@@ -1031,7 +1075,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
 #pragma unroll
   for (int f = 0; f < F; ++f) {
     const int fold_head = 2 * f + (n >> 3);
-    const bool live = fold_head < R && head_live(fold_head) && fold_live(f);
+    const bool live = fold_head < RW && head_live(fold_head) && fold_live(f);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       asm volatile("" : "+v"(q_raw[f][i]));   // nothing derived from q may move above the requests
@@ -1067,14 +1111,14 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
 
   // ---- merge the waves of the workgroup ----
   float* Macc = reinterpret_cast<float*>(wl);            // [MC][128] per wave (reuses the wave's LDS)
-  float* Mml = Macc + MC * D;                            // [R] m, [R] l
+  float* Mml = Macc + MC * D;                            // [RW] m, [RW] l
 #pragma unroll
-  for (int hd = 0; hd < (TURN ? 1 : R); ++hd) l_run[hd] = TURN ? row_allsum(l_run[hd]) : wave_allsum(l_run[hd]);
+  for (int hd = 0; hd < (TURN ? HP : R); ++hd) l_run[hd] = TURN ? row_allsum(l_run[hd]) : wave_allsum(l_run[hd]);
   if (JOIN) {                 // [head][channel b1 * 8 + b2]
 #pragma unroll
-    for (int st = 0; st < NSET; ++st) {
+    for (int st = 0; st < HP * NSET; ++st) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) Macc[packed_head * D + (4 * g + i) * J2 + st * PK + packed_slot] = acc[st][i];
+      for (int i = 0; i < 4; ++i) Macc[(st / NSET * R + packed_head) * D + (4 * g + i) * J2 + st % NSET * PK + packed_slot] = acc[st][i];
     }
   } else if (N3 || (n & 3) != 3) {   // [head][limb][channel b1 * 8 + b2]
 #pragma unroll
@@ -1084,13 +1128,16 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
     }
   }
   if (TURN) {
-    if (n == 0) { Mml[g] = m_run[0]; Mml[R + g] = l_run[0]; }
+#pragma unroll
+    for (int hp = 0; hp < HP; ++hp) {
+      if (n == 0) { Mml[hp * R + g] = m_run[hp]; Mml[RW + hp * R + g] = l_run[hp]; }
+    }
   } else if (lane == 0) {
 #pragma unroll
-    for (int hd = 0; hd < R; ++hd) { Mml[hd] = m_run[hd]; Mml[R + hd] = l_run[hd]; }
+    for (int hd = 0; hd < R; ++hd) { Mml[hd] = m_run[hd]; Mml[RW + hd] = l_run[hd]; }
   }
   __syncthreads();
-  for (int idx = tid; idx < R * RD; idx += 64 * NW) {
+  for (int idx = tid; idx < RW * RD; idx += 64 * NW) {
     // c: the real head's channel; cv: where it sits among the 128 channels the waves worked on
     const int hd = idx / RD, c = idx % RD, cv = P2 ? c + RD * (hd / HPK) : c;
     if (!head_live(hd)) continue;
@@ -1111,7 +1158,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
                       : N3 ? ((col[0] * 256.f + col[D]) * 256.f + col[2 * D]) * 256.f + col[3 * D]
                            : col[0] * 65536.f + col[D] * 256.f + col[2 * D];
       o = fmaf(v, wgt, o);
-      L = fmaf(base[MC * D + R + hd], wgt, L);
+      L = fmaf(base[MC * D + RW + hd], wgt, L);
       if (TM) {   // the wave's share of the fp16 tail
         const float* tp = s_tail + w * Tail::kResultFloats + hd * (D + 2);
         const float wt = (tp[D] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(tp[D] - M);
@@ -1143,7 +1190,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   DQ_STAMP(19);
 }
 #undef DQ_STAMP
-template <int BITS, int NG, int R, int TM, bool N3, bool P2>
+template <int BITS, int NG, int R, int TM, bool N3, bool P2, int HP = 1>
 inline void launch_tm(const DecodeArgs& a, hipStream_t st) {
   const int units = a.cache.batch * a.cache.kv_heads / (P2 ? 2 : 1);
   const dim3 grid = a.rows_on_x ? dim3(units * a.head_groups, a.n_split) : dim3(a.n_split, units * a.head_groups);
@@ -1152,11 +1199,11 @@ inline void launch_tm(const DecodeArgs& a, hipStream_t st) {
   // registers, so that width always takes 4 waves)
   if constexpr (BITS < 8) {
     if (a.nw == 8) {
-      hipExtLaunchKernelGGL((decode_mfma_kernel<BITS, NG, R, 8, TM, N3, P2>), grid, dim3(512), 0, st, a.ev_start, a.ev_stop, 0, a);
+      hipExtLaunchKernelGGL((decode_mfma_kernel<BITS, NG, R, 8, TM, N3, P2, HP>), grid, dim3(512), 0, st, a.ev_start, a.ev_stop, 0, a);
       return;
     }
   }
-  hipExtLaunchKernelGGL((decode_mfma_kernel<BITS, NG, R, 4, TM, N3, P2>), grid, dim3(256), 0, st, a.ev_start, a.ev_stop, 0, a);
+  hipExtLaunchKernelGGL((decode_mfma_kernel<BITS, NG, R, 4, TM, N3, P2, HP>), grid, dim3(256), 0, st, a.ev_start, a.ev_stop, 0, a);
 }
 
 template <int BITS, int NG, int R, bool N3, bool P2 = false>
@@ -1185,6 +1232,7 @@ int32_t launch_bits(const DecodeArgs& a, hipStream_t st) {
       case 1: launch_r<BITS, 1, 1>(a, st); break;
       case 2: launch_r<BITS, 1, 2>(a, st); break;
       case 4: launch_r<BITS, 1, 4>(a, st); break;
+      case 8: launch_tm<BITS, 1, 4, 0, false, false, 2>(a, st); break;
       default: return DQ_EINVAL;
     }
   } else {
