@@ -29,7 +29,7 @@ void set_last_hip_error(hipError_t e) { g_last_hip_error.store((int)e); }
 // 33.6 us in its 8 splits of 4 waves, 26.8 in the 2 of 8 taken here), and over 3 % slower in 133 of the
 // 2302 cases than the rule of fixed depths before it (33 now); that rule was 4.5 % off and 73 %.
 static void choose_mfma_shape(int units, int max_tiles, int heads, int bits, bool two_groups, bool three, bool pair,
-                              bool tail, int* n_out, int* nw_out) {
+                              bool two_sets, bool tail, int* n_out, int* nw_out) {
   static const int kSplits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
   // waves a SIMD's registers hold (the heads' accumulators, the ring of chunks and the tail's rows decide)
   int resident;
@@ -37,12 +37,12 @@ static void choose_mfma_shape(int units, int max_tiles, int heads, int bits, boo
   else if (bits == 4) resident = (!three && (heads == 1 || (heads == 2 && !tail && !two_groups))) ? 3 : 2;
   else resident = heads == 1 ? (three ? 3 : 4) : heads == 2 ? (three ? 2 : 3) : 2;
   const float h = (float)(heads - 1), n3 = three ? 1.f : 0.f;
-  // (eight heads, two sets of columns: fitted by themselves, 276 sizes in three code widths; the picks are 0.25 % behind the fastest
-  // shape on average, 7.5 % at worst, and with the constants of the others, extended to eight heads, 0.8 % and 28 %)
-  const bool eight = heads == 8;
-  const float chain = eight ? 3.623f : 1.955f + 0.626f * h + 2.847f * n3 - (pair ? 0.2f : 0.f);
-  const float issue = eight ? 1.247f : 0.018f + 0.483f * bits + 0.008f * h + 0.758f * n3;
-  const float per_wave = eight ? 2.087f : 2.172f + (tail ? 0.024f * (1 + heads) : 0.f);
+  // (two sets of columns: fitted by themselves, 276 sizes in three code widths; the picks are 0.25 % behind the fastest
+  // shape on average, 7.5 % at worst, and with the constants of the others, extended to eight heads, 0.8 % and 28 %;
+  // two step groups, four heads, 219 sizes: 1.1 % and 11 %)
+  const float chain = two_sets ? 3.623f : 1.955f + 0.626f * h + 2.847f * n3 - (pair ? 0.2f : 0.f);
+  const float issue = two_sets ? 1.247f : 0.018f + 0.483f * bits + 0.008f * h + 0.758f * n3;
+  const float per_wave = two_sets ? 2.087f : 2.172f + (tail ? 0.024f * (1 + heads) : 0.f);
   float best = 3.0e38f;
   for (const int n : kSplits) {
     if (n > kMaxSplits || n > max_tiles) break;
@@ -53,12 +53,12 @@ static void choose_mfma_shape(int units, int max_tiles, int heads, int bits, boo
       auto round = [&](int groups) -> float {                          // so many workgroups on a compute unit at a time
         if (groups == 0) return 0.f;
         const float waves = 0.25f * (float)(groups * nw);               // per SIMD
-        return tiles * (fmaxf(chain, waves * issue) + (eight ? 0.911f : 0.289f) * waves) + per_wave * waves + 0.072f;
+        return tiles * (fmaxf(chain, waves * issue) + (two_sets ? 0.911f : 0.289f) * waves) + per_wave * waves + 0.072f;
       };
       const int together = resident * 4 / nw > 1 ? resident * 4 / nw : 1;
       const long per_cu = ((long)units * n + 255) / 256;
       float t = (float)(per_cu / together) * round(together) + round((int)(per_cu % together));
-      if (n > 1) t += eight ? 2.038f + 0.233f * n : 1.606f + 0.112f * n;
+      if (n > 1) t += two_sets ? 2.038f + 0.233f * n : 1.606f + 0.112f * n;
       if (tail) t += 0.136f * (float)((16 + n * nw - 1) / (n * nw));    // (64 rows, four a load)
       if (t < 0.914f * best) { best = t; *n_out = n; *nw_out = nw; }
     }
@@ -71,14 +71,15 @@ int choose_splits(const dq_format* f, int batch, int q_heads, int kv_heads, int 
   int n = 1, nw = 4;
   int per_group = q_heads / kv_heads;
   int hg = mfma ? mfma_head_groups(f, q_heads, kv_heads, &per_group) : 1;   // each head group is a workgroup of its own
-  if (mfma && mfma_eight_heads(f, batch, q_heads, kv_heads, max_tiles, tail)) { hg /= 2; per_group = 8; }
+  const bool two_sets = mfma && mfma_two_groups(f, batch, q_heads, kv_heads, max_tiles, tail);   // ... or two of them are
+  if (two_sets) { hg /= 2; per_group *= 2; }
   if (max_tiles > 0) {
     if (mfma) {
       if (mfma_pair_heads(f, q_heads, kv_heads))   // two kv heads per workgroup
-        choose_mfma_shape(batch * kv_heads / 2 * hg, max_tiles, 2 * per_group, f->bits, true, false, true, tail, &n, &nw);
+        choose_mfma_shape(batch * kv_heads / 2 * hg, max_tiles, 2 * per_group, f->bits, true, false, true, false, tail, &n, &nw);
       else
-        choose_mfma_shape(batch * kv_heads * hg, max_tiles, per_group, f->bits, f->group == 64, f->i3 == kRun, false, tail,
-                          &n, &nw);
+        choose_mfma_shape(batch * kv_heads * hg, max_tiles, per_group, f->bits, f->group == 64, f->i3 == kRun, false, two_sets,
+                          tail, &n, &nw);
     } else {
       const int units = batch * q_heads;
       n = (2048 + units - 1) / units;

@@ -6,7 +6,7 @@
 namespace dq {
 
 // Query heads per kv head that one workgroup takes: four B columns per head and step group of the
-// sixteen, so at most 4 (one step group) or 2 (two); the kernel is built for 1, 2 and 4.  More heads
+// sixteen, so at most 4 (one step group) or 2 (two); the kernel is built for 1, 2 and 4 in a set of columns.  More heads
 // are served in groups of that many, the last group taking what is left (7 = 4 + 3); a number that
 // is not a power of two takes the next size up (3 heads run in a workgroup built for 4).
 static int heads_per_workgroup(const dq_format* f, int rep) {
@@ -55,19 +55,20 @@ int mfma_head_groups(const dq_format* f, int q_heads, int kv_heads, int* heads_p
   return (rep + r - 1) / r;
 }
 
-// Whether the head groups of four go two to a workgroup (the kernel with two sets of columns, for an even number of groups, one step
-// group, two local tensors and no fp16 tail).  The codes are then requested and unpacked once for eight heads, but a wave's chain over a
+// Whether the head groups (of four heads, with two step groups of two) go two to a workgroup: the kernel with two sets of columns, for an even
+// number of groups, two local tensors and no fp16 tail.  The codes are then requested and unpacked once for both, but a wave's chain over a
 // tile is longer and there are half the workgroups, so a launch that leaves the chip part idle loses by it.  The line lies where
-// groups of four take more than one workgroup a compute unit already (kv heads of all sequences x 8 query heads x tokens, 4 bits: 256 x 8 x 512
-// 9.7 us in fours, 8.6 in eights; 128 x 8 x 1024: 8.2, 11.3), or there are tiles enough to fill the chip either way (64 x 8 x 32768:
-// 64.5, 55; 64 x 8 x 8192: 22.2, 22.8; 8 bits, whose stream, twice through the L2, bounds it sooner: 64 x 8 x 3072: 22.3, 20.7; 64 x 8 x
-// 1024: 12.4, 15.1).  Over 300 sizes measured in both: none slower than fours by 2 %, at most 8 % behind the better of the two.
-bool mfma_eight_heads(const dq_format* f, int batch, int q_heads, int kv_heads, int max_tiles, bool tail) {
+// single groups take more than one workgroup a compute unit already (kv heads of all sequences x 8 query heads x tokens, 4 bits: 256 x 8 x
+// 512 9.7 us one by one, 8.6 by two; 128 x 8 x 1024: 8.2, 11.3), or there are tiles enough to fill the chip either way (64 x 8 x 32768:
+// 64.5, 55; 64 x 8 x 8192: 22.2, 22.8; two step groups 64 x 4 x 16384: 35.0, 32.1; 96 x 4 x 8192: 31.8, 28.1; 128 x 4 x 4096: 20.2,
+// 21.0; 8 bits, whose stream, twice through the L2, bounds it sooner: 64 x 8 x 3072: 22.3, 20.7; 64 x 8 x 1024: 12.4, 15.1).  Over 500
+// sizes measured in both: none slower than one by one by 2 %, at most 11 % behind the better of the two.
+bool mfma_two_groups(const dq_format* f, int batch, int q_heads, int kv_heads, int max_tiles, bool tail) {
   int per_group = 0;
   const int groups = mfma_head_groups(f, q_heads, kv_heads, &per_group);
-  if (tail || per_group != 4 || groups % 2 || f->i3 != 1 || f->group != 128) return false;
+  if (tail || mfma_pair_heads(f, q_heads, kv_heads) || per_group != (f->group == 128 ? 4 : 2) || groups % 2 || f->i3 != 1) return false;
   const long units = (long)batch * kv_heads * (groups / 2);
-  return (2 * units > 256 && (max_tiles >= 4 || f->bits == 8)) || units * max_tiles > (f->bits == 8 ? 1024 : 8192);
+  return (2 * units > 256 && (max_tiles >= 4 || f->bits == 8)) || units * max_tiles > (f->bits == 8 ? 1024 : f->group == 64 ? 5000 : 8192);
 }
 
 // defined in dq_decode_mfma_b8.hip, _b4.hip, _b2.hip

@@ -211,15 +211,17 @@ __device__ __forceinline__ float pow2i(int e) {
 // two.  Batch 8, 32 query on 8 kv heads, 2048 to 4096 tokens (15 MB): 74 + 7 us in the plain kernel
 // these shapes used to take, 12 us here.
 //
-// HP = 2: two sets of four heads in one workgroup, each with sixteen columns of its own.  What bounded more than four heads per kv head
+// HP = 2: two sets of four heads (two step groups: of two) in one workgroup, each with sixteen columns of its own.  What bounded more than four heads per kv head
 // was the stream: every head group asked for the same codes (8 x 64 heads, 8 kv heads, x 32768 tokens: 587 MB through the L2s for 294 MB
 // of cache; 68.5 us with one wave a SIMD, 66.2 with two) and unpacked them.  Here a chunk is asked for and unpacked once and multiplied with both
-// sets: 221 registers, two waves a SIMD.  4 bits 65.4 -> 55 us, 2 bits 52.9 -> 45.5, 8 bits x 8192 tokens 47.4 -> 32.7.
-// Which launches take it: mfma_eight_heads (dq_decode_mfma.hip).
-template <int BITS, int NG, int R, int NW, int TM, bool N3, bool P2, int HP = 1>
+// sets: 221 registers, two waves a SIMD.  4 bits 65.4 -> 55 us, 2 bits 52.9 -> 45.5, 8 bits x 8192 tokens 47.4 -> 32.7; two step
+// groups, 64 x 4 heads x 32768 tokens, 4 bits 65.5 -> 55.2.  Which launches take it: mfma_two_groups (dq_decode_mfma.hip).
+// (two step groups: R counts the heads of both sets)
+template <int BITS, int NG, int RQ, int NW, int TM, bool N3, bool P2, int HP = 1>
 __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode_mfma_kernel(DecodeArgs a) {
+  constexpr int R = (NG == 2 && HP == 2) ? RQ / 2 : RQ;   // query heads of a set of columns
   static_assert(!P2 || (NG == 2 && (R == 2 || R == 4) && !N3), "a pair of heads is two step groups and two or four query heads");
-  static_assert(HP == 1 || (HP == 2 && R == 4 && NG == 1 && TM == 0 && !N3), "sets of four heads: no tail, two tensors, one step group");
+  static_assert(HP == 1 || (HP == 2 && NG * R == 4 && R >= 2 && TM == 0 && !N3 && !P2), "sets of sixteen columns: no tail, two tensors");
   constexpr int RW = R * HP;                  // query heads per workgroup, in HP sets of sixteen columns
   typedef Codec<BITS> C;
   typedef typename C::chunk_t chunk_t;
@@ -240,13 +242,14 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   // instead of 4.  64 query on 8 kv heads, 8 x 32768 tokens: 72.2 us, 66.0 so; 32 on 8, mixed lengths with tails: whole step 34.2,
   // 33.1; four 64-channel heads of 256 tokens: 6.0, 5.7.)
   constexpr bool JOIN = (R >= 2 && !N3);
-  // Four heads fill all sixteen columns: the score product has its operands the other way round as well.  A lane then holds the limbs
+  // Four heads, or two of two step groups, fill all sixteen columns: the score product has its operands the other way round as well.  A lane then holds the limbs
   // of one head's scores of eight tokens, joins them in registers and goes on with them; the steps reach it from the lanes
   // that asked for them by lane swaps.  Through LDS (8 writes and 32 reads a tile, four reductions' checks instead of one) the wave
   // waited for them: 16 x 32 heads (8 kv heads) x 32768 tokens 92.2 -> 90.5 us, so turned and with the folded query in 8 writes instead of
   // 32; a serving step of 16 sequences of 3000 to 8000 tokens 32.5 -> 31.4; 8 x 32 on 8 heads of 64 channels, 2048 to 4096 tokens
-  // 11.5 -> 11.0.  (Two heads would leave half the lanes idle in the softmax.)
-  constexpr bool TURN = (R == 4 && !N3);
+  // 11.5 -> 11.0.  (Two heads of one step group would leave half the lanes idle in the softmax.)  Two step groups add a swap a token, for the
+  // other group's share: 64 x 2 heads x 8192 tokens of two step groups, 4 bits, 24.1 -> 22.1, 64 x 2 x 128 6.1 -> 5.4.
+  constexpr bool TURN = (NC == 16 && R >= 2 && !N3);
   constexpr int PK = JOIN ? 16 / R : 4 / R, NSET = J2 / PK;
   constexpr int TS = 20;                      // floats per (head, b2) of the joined values on their way through LDS (16 rows + pad)
   constexpr int RD = P2 ? 64 : D;             // channels of a real head (output, partials, cache rows)
@@ -732,7 +735,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
     }
 
     // ---- 2. scores: S[t][col] = sum_c (u[t, c] - offset) limb[col][c] ----
-    [[maybe_unused]] float sc[HP][8];   // TURN: of head g, the lane's tokens tA and tB of each 32
+    [[maybe_unused]] float sc[HP][8];   // TURN: of head g (two step groups: of head g / 2, the share of group g % 2), the lane's tokens tA and tB of each 32
     // (the offset's share, the same for every token, is the accumulators' starting value)
     {
       i32x4 cinitk[HP];
@@ -806,14 +809,21 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
     }
     if constexpr (TURN) {
       // lane (n, g) has its pair's steps of the g-th 32 tokens; it needs those of all four for its own head (a pair of heads:
-      // its kv head's).  Three swaps deal a register of each row of lanes to all of them.
+      // its kv head's; two step groups: of its own group).  Three swaps deal a register of each row of lanes to all of them.
       float kA[4], kB[4], wA[4], wB[4];
       auto deal = [&](const float (&x)[NG], float (&to)[4]) __attribute__((always_inline)) {
         const uint32_t x0 = __builtin_bit_cast(uint32_t, x[0]), x1 = __builtin_bit_cast(uint32_t, x[NG - 1]);
-        const auto h = __builtin_amdgcn_permlane32_swap(x0, x1, false, false);   // rows 0, 1 twice; rows 2, 3 twice
-        const auto lo = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false), hi = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);
-        to[0] = __builtin_bit_cast(float, (uint32_t)lo[0]); to[1] = __builtin_bit_cast(float, (uint32_t)lo[1]);
-        to[2] = __builtin_bit_cast(float, (uint32_t)hi[0]); to[3] = __builtin_bit_cast(float, (uint32_t)hi[1]);
+        if (CG == 2) {   // (odd rows of lanes take the second step group's)
+          const auto h = __builtin_amdgcn_permlane16_swap(x0, x1, false, false);   // rows 0, 2; rows 1, 3
+          const auto lo = __builtin_amdgcn_permlane32_swap(h[0], h[0], false, false), hi = __builtin_amdgcn_permlane32_swap(h[1], h[1], false, false);
+          to[0] = __builtin_bit_cast(float, (uint32_t)lo[0]); to[2] = __builtin_bit_cast(float, (uint32_t)lo[1]);
+          to[1] = __builtin_bit_cast(float, (uint32_t)hi[0]); to[3] = __builtin_bit_cast(float, (uint32_t)hi[1]);
+        } else {
+          const auto h = __builtin_amdgcn_permlane32_swap(x0, x1, false, false);   // rows 0, 1 twice; rows 2, 3 twice
+          const auto lo = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false), hi = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);
+          to[0] = __builtin_bit_cast(float, (uint32_t)lo[0]); to[1] = __builtin_bit_cast(float, (uint32_t)lo[1]);
+          to[2] = __builtin_bit_cast(float, (uint32_t)hi[0]); to[3] = __builtin_bit_cast(float, (uint32_t)hi[1]);
+        }
       };
       deal(dkA, kA);
       deal(dkB, kB);
@@ -828,6 +838,14 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
           const int t = tok0 + 32 * k + key_row;
           sc[hp][2 * k] = fmaf(sc[hp][2 * k], kA[k], (HAS_NEXT || t < S) ? 0.f : -INFINITY);
           sc[hp][2 * k + 1] = fmaf(sc[hp][2 * k + 1], kB[k], (HAS_NEXT || t + kPairRows < S) ? 0.f : -INFINITY);
+          if (CG == 2) {   // the head's other step group is in the neighbouring row of lanes
+#pragma unroll
+            for (int i = 2 * k; i < 2 * k + 2; ++i) {
+              const uint32_t w = __builtin_bit_cast(uint32_t, sc[hp][i]);
+              const auto both = __builtin_amdgcn_permlane16_swap(w, w, false, false);
+              sc[hp][i] = __builtin_bit_cast(float, (uint32_t)both[0]) + __builtin_bit_cast(float, (uint32_t)both[1]);
+            }
+          }
           mt_lane = fmaxf(mt_lane, fmaxf(sc[hp][2 * k], sc[hp][2 * k + 1]));
         }
         // the running maxima move in a sequence's first tiles and rarely afterwards: they are reduced only when some lane
@@ -837,12 +855,12 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
           const float alpha = __builtin_amdgcn_exp2f(m_run[hp] - m_new);
           m_run[hp] = m_new;
           l_run[hp] *= alpha;
-          const float alpha_col = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(64 * packed_head, __builtin_bit_cast(int, alpha)));
+          const float alpha_col = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(64 * CG * packed_head, __builtin_bit_cast(int, alpha)));
 #pragma unroll
           for (int st = 0; st < NSET; ++st) acc[hp * NSET + st] *= alpha_col;
         }
         float p_sum = 0.f;
-        unsigned char* const dst0 = Ps + (hp * NC + CPH * g) * LS + (n >> 3) * 16 + 2 * (n & 7);
+        unsigned char* const dst0 = Ps + (hp * NC + 4 * g) * LS + (n >> 3) * 16 + 2 * (n & 7);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           const float pA = __builtin_amdgcn_exp2f(sc[hp][2 * k] - m_run[hp]), pB = __builtin_amdgcn_exp2f(sc[hp][2 * k + 1] - m_run[hp]);
@@ -1130,7 +1148,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   if (TURN) {
 #pragma unroll
     for (int hp = 0; hp < HP; ++hp) {
-      if (n == 0) { Mml[hp * R + g] = m_run[hp]; Mml[RW + hp * R + g] = l_run[hp]; }
+      if (n == 0 && g % CG == 0) { Mml[hp * R + g / CG] = m_run[hp]; Mml[RW + hp * R + g / CG] = l_run[hp]; }
     }
   } else if (lane == 0) {
 #pragma unroll
@@ -1239,6 +1257,7 @@ int32_t launch_bits(const DecodeArgs& a, hipStream_t st) {
     switch (rep) {
       case 1: launch_r<BITS, 2, 1>(a, st); break;
       case 2: launch_r<BITS, 2, 2>(a, st); break;
+      case 4: launch_tm<BITS, 2, 4, 0, false, false, 2>(a, st); break;
       default: return DQ_EINVAL;
     }
   }

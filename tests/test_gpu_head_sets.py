@@ -1,6 +1,6 @@
-"""Launches of more than four query heads per kv head that are large enough go to the matrix-core kernel in eights, two sets of
-columns a workgroup.  It is compared with the plain kernel: on both sides of the line, with missing heads in either set (5 = 4 + 1, 13 =
-8 + 4 + 1 of sixteen), every merge path, lengths at the edges of tiles, and codes, steps and small tensors of any content past the end."""
+"""Launches of more than four query heads per kv head (more than two with two step groups) that are large enough go to the matrix-core
+kernel with two sets of columns a workgroup.  It is compared with the plain kernel: on both sides of the line, with missing heads in
+either set (5 = 4 + 1, 13 = 8 + 4 + 1 of sixteen; 3 = 2 + 1, 7 = 4 + 2 + 1), every merge path, lengths at the edges of tiles, and codes, steps and small tensors of any content past the end."""
 import pytest
 import torch
 
@@ -10,12 +10,15 @@ from gpu_util import DEV
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("bits,rep,batch,tiles", [(4, 8, 17, 4), (4, 8, 16, 4), (4, 5, 17, 5), (4, 13, 17, 4), (4, 8, 33, 3), (2, 8, 17, 4),
-                                                  (2, 7, 17, 4), (8, 8, 17, 1), (8, 8, 17, 4), (8, 6, 5, 33), (4, 8, 2, 513)])
-def test_eight_heads_a_workgroup(bits, rep, batch, tiles):
-    print("eight heads: %s" % ((bits, rep, batch, tiles),), flush=True)
+@pytest.mark.parametrize("bits,group,rep,batch,tiles", [
+    (4, 128, 8, 17, 4), (4, 128, 8, 16, 4), (4, 128, 5, 17, 5), (4, 128, 13, 17, 4), (4, 128, 8, 33, 3), (2, 128, 8, 17, 4),
+    (2, 128, 7, 17, 4), (8, 128, 8, 17, 1), (8, 128, 8, 17, 4), (8, 128, 6, 5, 33), (4, 128, 8, 2, 513),
+    (4, 64, 4, 17, 4), (4, 64, 4, 16, 4), (4, 64, 3, 17, 5), (4, 64, 7, 17, 4), (2, 64, 4, 17, 4), (2, 64, 8, 17, 4), (8, 64, 4, 17, 1),
+    (8, 64, 3, 17, 4), (4, 64, 4, 2, 313), (4, 64, 2, 5, 5), (2, 64, 2, 5, 5), (8, 64, 2, 5, 5)])
+def test_two_sets_of_heads_a_workgroup(bits, group, rep, batch, tiles):
+    print("two sets of heads: %s" % ((bits, group, rep, batch, tiles),), flush=True)
     heads, dim = 8, 128
-    fmt = dq.Format(bits, 128, dim, 16, 8, 128)
+    fmt = dq.Format(bits, group, dim, 16, 8, 128)
     g = torch.Generator(device=DEV).manual_seed(100 * bits + rep)
     cache = dq.alloc_cache(fmt, batch, heads, tiles, DEV, fill=None)
     for name, x in cache.t.items():
@@ -30,8 +33,8 @@ def test_eight_heads_a_workgroup(bits, rep, batch, tiles):
     # steps past the end: NaN (what lies there counts for nothing)
     past = torch.arange(n, device=DEV)[None, :] >= lens[:, None]
     for name in ("k_scales", "v_scales"):
-        x = cache.t[name].view(batch, heads, n)
-        x.masked_fill_(past[:, None, :], float("nan"))
+        x = cache.t[name].view(batch, heads, n, 128 // group)
+        x.masked_fill_(past[:, None, :, None], float("nan"))
     q = torch.randn(batch, heads * rep, dim, device=DEV, generator=g).half()
     ws = dq.decode_workspace(fmt, batch, heads * rep, heads, n, DEV)
     want = torch.empty(batch, heads * rep, dim, dtype=torch.float32, device=DEV)
