@@ -39,7 +39,7 @@ static void choose_mfma_shape(int units, int max_tiles, int heads, int bits, boo
   const float h = (float)(heads - 1), n3 = three ? 1.f : 0.f;
   // (two sets of columns: fitted by themselves, 276 sizes in three code widths; the picks are 0.25 % behind the fastest
   // shape on average, 7.5 % at worst, and with the constants of the others, extended to eight heads, 0.8 % and 28 %;
-  // two step groups, four heads, 219 sizes: 1.1 % and 11 %)
+  // two step groups, the 74 of 219 sizes that take it: 3.8 % at worst)
   const float chain = two_sets ? 3.623f : 1.955f + 0.626f * h + 2.847f * n3 - (pair ? 0.2f : 0.f);
   const float issue = two_sets ? 1.247f : 0.018f + 0.483f * bits + 0.008f * h + 0.758f * n3;
   const float per_wave = two_sets ? 2.087f : 2.172f + (tail ? 0.024f * (1 + heads) : 0.f);

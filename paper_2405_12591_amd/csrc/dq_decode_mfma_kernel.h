@@ -250,6 +250,9 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   // 11.5 -> 11.0.  (Two heads of one step group would leave half the lanes idle in the softmax.)  Two step groups add a swap a token, for the
   // other group's share: 64 x 2 heads x 8192 tokens of two step groups, 4 bits, 24.1 -> 22.1, 64 x 2 x 128 6.1 -> 5.4.
   constexpr bool TURN = (NC == 16 && R >= 2 && !N3);
+  // One head of one step group fills four of the sixteen columns.  Its limbs stand in all four groups of columns, so that with the score product
+  // turned every lane holds the limbs of every eighth token's score, and keeps those of its own two.  (Three tensors: 8-bit codes would drop to one wave a SIMD.)
+  constexpr bool SPREAD = (NC == 4 && !N3);
   constexpr int PK = JOIN ? 16 / R : 4 / R, NSET = J2 / PK;
   constexpr int TS = 20;                      // floats per (head, b2) of the joined values on their way through LDS (16 rows + pad)
   constexpr int RD = P2 ? 64 : D;             // channels of a real head (output, partials, cache rows)
@@ -259,7 +262,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   constexpr int CHUNKB = sizeof(chunk_t);
   constexpr int SS = 132;                     // ints per column of the score staging (128 tokens + pad)
   constexpr int LS = 144;                     // bytes from column to column of the limbs (128 and a pad that keeps the b128 reads off each other's banks)
-  constexpr int QS_BYTES = HP * NC * LS, PS_BYTES = HP * NC * LS, SS_BYTES = TURN ? RW * J2 * TS * 4 : NC * SS * 4;
+  constexpr int QS_BYTES = HP * NC * LS, PS_BYTES = HP * NC * LS, SS_BYTES = TURN ? RW * J2 * TS * 4 : SPREAD ? 1024 : NC * SS * 4;
   constexpr int MC = JOIN ? RW : NC;           // columns of a wave's result in the merge (JOIN: the limbs are joined already)
   constexpr int WAVE_LDS = QS_BYTES + PS_BYTES + SS_BYTES;
   static_assert(WAVE_LDS >= MC * D * 4 + 2 * RW * 4, "merge area must fit the wave's LDS");
@@ -454,9 +457,9 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
 
   // key rows of the chunks.  TURN: chunks 2 k and 2 k + 1 hold the lane's tokens tA and tB of the k-th 32, the pair whose weights
   // share a 16-bit word of B slots; a chunk still asks for whole lines (two rows at 4 bits, four at 2, one at 8)
-  const int key_row = TURN ? tA - 32 * g : n;
+  const int key_row = (TURN || SPREAD) ? tA - 32 * g : n;
   constexpr int kPairRows = BITS == 4 ? 2 : BITS == 2 ? 4 : 1;   // tB - tA
-  auto chunk_rows = [](int j) constexpr -> int { return TURN ? 32 * (j >> 1) + (j & 1) * kPairRows : 16 * j; };
+  auto chunk_rows = [](int j) constexpr -> int { return (TURN || SPREAD) ? 32 * (j >> 1) + (j & 1) * kPairRows : 16 * j; };
 
   // The fold's columns are dealt so that the four a lane gets lie side by side in B slots (2-bit codes: two and two).
   auto fold_b2 = [](int c) constexpr -> int {   // the b2 of column c (mod 8)
@@ -729,18 +732,19 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
 #pragma unroll
       for (int w = 0; w < 2; ++w) {
         i32x4 t = izero;
-        if (col_live_k) t = *reinterpret_cast<const i32x4*>(Qs + (hp * NC + n) * LS + (2 * g + w) * 16);
+        if (col_live_k || SPREAD) t = *reinterpret_cast<const i32x4*>(Qs + (hp * NC + (SPREAD ? n & 3 : n)) * LS + (2 * g + w) * 16);
         bqs[hp][w] = t;
       }
     }
 
     // ---- 2. scores: S[t][col] = sum_c (u[t, c] - offset) limb[col][c] ----
+    [[maybe_unused]] int highA = 0, lowA = 0, highB = 0, lowB = 0;   // SPREAD: the limb pairs of the lane's two tokens
     [[maybe_unused]] float sc[HP][8];   // TURN: of head g (two step groups: of head g / 2, the share of group g % 2), the lane's tokens tA and tB of each 32
     // (the offset's share, the same for every token, is the accumulators' starting value)
     {
       i32x4 cinitk[HP];
       auto product = [&](const i32x4& codes, const i32x4& limbs, const i32x4& c) __attribute__((always_inline)) {
-        return TURN ? __builtin_amdgcn_mfma_i32_16x16x64_i8(limbs, codes, c, 0, 0, 0) : __builtin_amdgcn_mfma_i32_16x16x64_i8(codes, limbs, c, 0, 0, 0);
+        return (TURN || SPREAD) ? __builtin_amdgcn_mfma_i32_16x16x64_i8(limbs, codes, c, 0, 0, 0) : __builtin_amdgcn_mfma_i32_16x16x64_i8(codes, limbs, c, 0, 0, 0);
       };
 #pragma unroll
       for (int hp = 0; hp < HP; ++hp) {
@@ -753,7 +757,12 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
       // limb pairs are joined as integers (|S| <= 2^21 per limb: 128 channels x 128 x 128), then as floats
       auto keep = [&](int hp, int j, const i32x4& v) __attribute__((always_inline)) {
         if (TURN) sc[hp][j] = fmaf((float)(v[0] * 256 + v[1]), 65536.f, (float)(v[2] * 256 + v[3]));
-        else if (col_live_k) *reinterpret_cast<i32x4*>(Ss + n * SS + 16 * j + 4 * g) = v;
+        else if (SPREAD) {
+          const int high = v[0] * 256 + v[1], low = v[2] * 256 + v[3];
+          const bool own = g == (j >> 1);
+          if (j & 1) { highB = own ? high : highB; lowB = own ? low : lowB; }
+          else { highA = own ? high : highA; lowA = own ? low : lowA; }
+        } else if (col_live_k) *reinterpret_cast<i32x4*>(Ss + n * SS + 16 * j + 4 * g) = v;
       };
       i32x4 s_prev[HP];
 #pragma unroll
@@ -774,7 +783,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
 #pragma unroll
       for (int hp = 0; hp < HP; ++hp) keep(hp, 7, s_prev[hp]);
     }
-    if (!TURN) __builtin_amdgcn_wave_barrier();
+    if (!TURN && !SPREAD) __builtin_amdgcn_wave_barrier();
 
     // ---- 3. online softmax, tokens tA and tB per lane (TURN: of head g, the pair of each 32 tokens) ----
     float v_unscale, vs = 0.f;
@@ -885,6 +894,11 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
 #pragma unroll
       for (int gr = 0; gr < NG; ++gr) {
         if (P2 && gr != hd / HPK) continue;   // a head of a pair has its channels in its own step group only
+        if (SPREAD) {
+          sA = fmaf(fmaf((float)highA, 65536.f, (float)lowA), dkA[gr], sA);
+          sB = fmaf(fmaf((float)highB, 65536.f, (float)lowB), dkB[gr], sB);
+          continue;
+        }
         const int* s0 = Ss + (CPH * hd + (P2 ? 0 : 4 * gr)) * SS;
         const int* s1 = s0 + SS;
         const int* s2 = s1 + SS;
