@@ -756,7 +756,10 @@ __device__ __forceinline__ double over_eight(double v) {
 // the form with a pair of scalar registers, which the compiler gives up for the shorter one wherever it can).
 __device__ __forceinline__ int select_i(unsigned long long mask, int a, int b) {
   int r;
-  asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(mask));
+  // (the mask is a constant; said so that a build without optimization has it in scalar registers, too)
+  asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b),
+      "s"((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(mask >> 32)) << 32 |
+          (unsigned)__builtin_amdgcn_readfirstlane((int)mask)));
   return r;
 }
 __device__ __forceinline__ double select_d(unsigned long long mask, double a, double b) {
@@ -1604,8 +1607,8 @@ __device__ __forceinline__ int dealt_unit(int wg, int n) {
 // per wave, then PART 3, the projection and quantizer.  In one launch every block derives each of its
 // rotations in eight lanes at once and its solver, a chain of dependent instructions, holds the
 // registers of the contractions.  The arithmetic, and so every bit written, is that of the other builds.
-// 14720 blocks (4-bit, d = 128): 670 us in one launch, 163 + 100 + 280 us in three when both contractions were fp64, 98 + 100 +
-// 146 now (steady clocks).
+// 14720 blocks (4-bit, d = 128): 670 us in one launch, 163 + 100 + 280 us in three when both contractions were fp64, 98 + 87 +
+// 137 now (steady clocks).
 // Launch bounds: one launch (PART 0) asks for two waves per SIMD, or its products' accumulators go to registers of
 // their own and calls of more than one workgroup a compute unit hold one (1024 blocks of 64 channels, 8 bits: 56 us, 37).
 // N3 (PART 3 with the quantizer, d = 128): three local tensors (Eq. 2 with n = 3, factor shapes
