@@ -47,7 +47,7 @@ PROFILED_TRAFFIC_BYTES = {
     ("llama7b_8bit", "mfma"): (137574.3 * 1.9997 + 64.0) * 1024,
     ("llama13b_mixed", "mfma"): (152201.9 * 1.9998 + 352.5) * 1024,
     ("gqa_long", "mfma"): (287280.5 * 1.9999 + 764.0) * 1024,
-    ("gqa8_long", "mfma"): (353847.3 * 1.9999 + 256.0) * 1024,
+    ("gqa8_long", "mfma"): (287660.5 * 1.9999 + 1516.0) * 1024,
     ("opt_d64_4bit", "mfma"): (71839.5 * 1.9994 + 64.0) * 1024,
     ("llama7b_4bit_n3", "mfma"): (72857.5 * 1.9994 + 64.0) * 1024,
 }

@@ -251,7 +251,10 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   // other group's share: 64 x 2 heads x 8192 tokens of two step groups, 4 bits, 24.1 -> 22.1, 64 x 2 x 128 6.1 -> 5.4.
   constexpr bool TURN = (NC == 16 && R >= 2 && !N3);
   // One head of one step group fills four of the sixteen columns.  Its limbs stand in all four groups of columns, so that with the score product
-  // turned every lane holds the limbs of every eighth token's score, and keeps those of its own two.  (Three tensors: 8-bit codes would drop to one wave a SIMD.)
+  // turned every lane holds the limbs of every eighth token's score, and keeps those of its own two.  Through LDS (8 writes and 8 reads a
+  // tile): 1 x 32 heads x 2999 tokens 7.54 -> 7.41 us, 8 x 32 x 4096 4 bits 24.6 -> 24.4, 8 bits 48.8 -> 48.3.  (Three tensors: 8-bit codes would
+  // drop to one wave a SIMD.  Two heads, their limbs in both halves of the columns and a lane swap between them: 14 x 32 64-channel heads x
+  // 8442 tokens, 2 bits, 29.5 -> 30.1, so these go through LDS.)
   constexpr bool SPREAD = (NC == 4 && !N3);
   constexpr int PK = JOIN ? 16 / R : 4 / R, NSET = J2 / PK;
   constexpr int TS = 20;                      // floats per (head, b2) of the joined values on their way through LDS (16 rows + pad)
