@@ -242,6 +242,8 @@ size_t dq_compress_workspace_bytes(const dq_format* fmt, int32_t batch, int32_t 
  *   blk_idx       i32 [B] device, 0 <= blk_idx[b] < block_capacity; negative skips sequence b
  *   n_valid       i32 [B] device, rows >= n_valid[b] (and rows >= t_new) count as zero; may be NULL;
  *                 a sequence with no valid row is skipped like one with a negative blk_idx
+ * Rows that count as zero and rows of skipped sequences are not read: the arrays need not reach
+ * beyond the last row that counts.
  * The decomposition is an eigen-decomposition of the fp64 Gram matrix M M^T (j1 x j1) by
  * Jacobi rotations: T_S = U diag(sigma), T_L = diag(1/sigma) U^T M; directions with
  * sigma <= 1e-6 sigma_max are dropped (T_S column and T_L row zero).  T_S saturates to the

@@ -5,57 +5,9 @@
 // small tensor into the cache and the fp32 large tensor into the workspace;
 // `quantize_tiles_kernel` turns fp32 rows into packed codes and fp16 steps.
 #include "dq_common.h"
+#include "dq_unit.h"
 
 namespace dq {
-
-// What one dq_compress_kv call works on: t_new rows per (sequence, kv head), cut into n_blocks
-// blocks of T_b rows (the last one may be short); block j of sequence b goes to slot blk_idx[b] + j.
-struct CompressJob {
-  const uint16_t* k_new;     // [B, H, t_new, d] fp16 bits
-  const uint16_t* v_new;
-  int t_new;
-  int n_blocks;              // ceil(t_new / T_b)
-  const int32_t* blk_idx;    // [B]
-  const int32_t* n_valid;    // [B] or null
-  int keep_large;            // the one-kernel three-tensor build also leaves its fp32 rows in the workspace
-  int mostly_idle;           // most calls skip every sequence (a serving step whose tails rarely fill)
-  int batch;
-};
-
-// Work unit `unit` = (((b * H + h) * n_blocks) + j) * 2 + which: where it lies (no memory is read for that).
-struct UnitPlace {
-  int which, b, j, rows;     // rows: of this block, in the caller's array
-  long bh;                   // b * H + h
-  const uint16_t* X;         // the block's first row
-};
-__device__ __forceinline__ UnitPlace unit_place(const Geometry& g, const CompressJob& job, int unit) {
-  UnitPlace u;
-  u.which = unit & 1;
-  const int ub = unit >> 1;
-  u.j = ub % job.n_blocks;
-  u.bh = ub / job.n_blocks;
-  u.b = (int)(u.bh / g.H);
-  u.rows = min(job.t_new - u.j * g.Tb, g.Tb);
-  u.X = (u.which ? job.v_new : job.k_new) + (u.bh * job.t_new + (long)u.j * g.Tb) * g.d;
-  return u;
-}
-// slot < 0: nothing to do (sequence skipped, slot past the cache's capacity, or a block none of whose rows is valid).
-struct UnitRef : UnitPlace {
-  int slot, nv;              // nv: valid rows of this block (the rest count as zero)
-};
-__device__ __forceinline__ UnitRef unit_ref(const Geometry& g, const CompressJob& job, const UnitPlace& place) {
-  UnitRef u;
-  static_cast<UnitPlace&>(u) = place;
-  const int first = job.blk_idx[u.b];
-  int rows = job.t_new;
-  if (job.n_valid) rows = min(max(job.n_valid[u.b], 0), job.t_new);
-  u.nv = min(max(rows - u.j * g.Tb, 0), g.Tb);
-  u.slot = (first < 0 || first + u.j >= g.NB || u.nv == 0) ? -1 : first + u.j;
-  return u;
-}
-__device__ __forceinline__ UnitRef unit_ref(const Geometry& g, const CompressJob& job, int unit) {
-  return unit_ref(g, job, unit_place(g, job, unit));
-}
 
 // ------------------------------------------------------------------------------------------
 // Quantize + pack one tile of 128 token rows (Eq. 1 per group).  256 threads.
@@ -1032,19 +984,20 @@ struct FastProject {
   __device__ __forceinline__ const uint16_t* piece(int t, int b1) const {
     return PAIR ? X + (b1 >> 3) * head_gap + (long)t * 64 + (b1 & 7) * 8 : X + (long)t * 128 + b1 * 8;
   }
-  // Sixteen tokens' rows, as they lie in memory: lane l gets piece b1 = l % 16 of token t0 + 4 u + l / 16 (past the last of `rows`
-  // rows: that row again; the caller clears it).  What bounds a prompt's projection is memory: without its quantizer it
+  // Sixteen tokens' rows, as they lie in memory: lane l gets piece b1 = l % 16 of token t0 + 4 u + l / 16 (past the last valid
+  // row: that row again; the caller clears it).  What bounds a prompt's projection is memory: without its quantizer it
   // takes the same time.  Requested in the matrix cores' order, lanes 256 bytes apart, the rows took four times the
   // accesses to the first-level cache, and each of its lines was asked for four times; in memory order no line is,
   // so that they can pass the caches by.  14720 blocks, steady clocks: 179 us in the other order (215 non-temporal),
   // 172 so, 148 non-temporal; two groups ahead instead of one 161.
   // DIRECT: in the matrix cores' order all the same, pieces b1 = 4 j + l / 16 of token t0 + l % 16.
-  __device__ __forceinline__ void load(u32x4 (&x)[4], int t0, int rows) const {
-    const int l = threadIdx.x & 63;
+  __device__ __forceinline__ void load(u32x4 (&x)[4], int t0) const {
+    int l = threadIdx.x & 63;
+    if (DIRECT && PAIR) asm volatile("" : "+v"(l));   // (the pieces' places, kept from call to call, would be a spill)
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      if (DIRECT) x[u] = *reinterpret_cast<const u32x4*>(piece(min(t0 + (l & 15), rows - 1), 4 * u + (l >> 4)));
-      else x[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(piece(min(t0 + 4 * u + (l >> 4), rows - 1), l & 15)));
+      if (DIRECT) x[u] = *reinterpret_cast<const u32x4*>(piece(min(t0 + (l & 15), nv - 1), 4 * u + (l >> 4)));
+      else x[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(piece(min(t0 + 4 * u + (l >> 4), nv - 1), l & 15)));
     }
   }
   // ... those of tokens past the last valid one are zero
@@ -1500,29 +1453,17 @@ __device__ __forceinline__ void gram16_fp64(const uint16_t* row, int nv, double*
 
 // mats: 2 * NWV matrices of 16 x 17 doubles in LDS; s_fits: NWV words.  out may be mats (ldo 17).  All waves call it; it
 // ends with a barrier.
-// (first: the wave's first groups of tokens, from load_groups(first, gram_row(...), 0, rows there are))
-template <int NWV> constexpr int kGramGroups = NWV == 1 ? 4 : 8;   // groups requested together
-template <bool PAIR>
-__device__ __forceinline__ const uint16_t* gram_row(const uint16_t* X, long head_gap) {
-  const int b1 = threadIdx.x & 15;
-  return PAIR ? X + (b1 >> 3) * head_gap + (b1 & 7) * 8 : X + b1 * 8;
-}
 template <int NWV, bool PAIR, bool CACHED>
-__device__ __forceinline__ void gram16(const u32x4 (&first_groups)[kGramGroups<NWV>], const uint16_t* __restrict__ row, int nv, double* mats,
+__device__ __forceinline__ void gram16(const uint16_t* __restrict__ X, int nv, long head_gap, double* mats,
                                        int* s_fits, double* out, int ldo) {
   constexpr int ld = 17, kMat = 16 * ld;
-  constexpr int GP = kGramGroups<NWV>;
-  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  constexpr int GP = NWV == 1 ? 4 : 8;   // groups requested together
+  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, b1 = l & 15;
+  const uint16_t* const row = PAIR ? X + (b1 >> 3) * head_gap + (b1 & 7) * 8 : X + b1 * 8;
   static_assert(kDrainTokens % (4 * GP) == 0, "a wave's share is whole steps");
   GramSums sums;
   u32x4 x[GP], y[GP];
-#pragma unroll
-  for (int u = 0; u < GP; ++u) x[u] = first_groups[u];
-  if (4 * GP * NWV > nv) {   // (rows that are there, but not valid, count as zero)
-#pragma unroll
-    for (int u = 0; u < GP; ++u)
-      if (4 * wv + (l >> 4) + 4 * u * NWV >= nv) x[u] = u32x4{0u, 0u, 0u, 0u};
-  }
+  load_groups<NWV, PAIR, CACHED>(x, row, 0, nv);
   int t0 = 0;
   bool more = true;
 #pragma unroll 1
@@ -1675,28 +1616,7 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? (!CACHED && (
     const int half_h = g.H >> 1;
     unit = (((hp / half_h) * g.H + 2 * (hp % half_h)) * job.n_blocks + j) * 2 + (wg & 1);
   }
-  const UnitPlace up = unit_place(g, job, unit);
-  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  constexpr int j1 = 16, ld = 17;
-  constexpr int d = PAIR ? 64 : 128;     // halves per row in memory
-  const uint16_t* X = up.X;  // [nv, d] fp16 bits
-  const long head_gap = (long)job.t_new * d;   // PAIR: from a row of the first head to the same row of the second
-  double* const gram_ws = reinterpret_cast<double*>(large_ws + (long)unit * g.Tb * d);   // PART: G, then W, of this block
-  // The first rows (all the caller's rows may be read, valid or not) and the factors are requested ahead of the lengths: a round trip
-  // off the chain of a small call (256 blocks 29.3 us, 28.6 so; 1024 53.9, 52.4; a prompt's waves hide it from each other).
-  u32x4 first_groups[kGramGroups<NWV>];
-  // (not in a call that mostly skips everything: its blocks would each read 32 KB before they leave)
-  if constexpr (PART != 3)
-    if (!job.mostly_idle) load_groups<NWV, PAIR, CACHED>(first_groups, gram_row<PAIR>(X, head_gap), 0, up.rows);
-  typedef FastProject<QB == 2 ? 2 : 4, FULL, PAIR, CACHED> FP;
-  FP fp;
-  u32x4 next[4];
-  if constexpr (FAST) {
-    fp.X = X; fp.head_gap = head_gap; fp.one_group = !PAIR && g.groups == 1;
-    fp.load(next, 0, up.rows);
-    fp.setup(gram_ws);
-  }
-  const UnitRef ur = unit_ref(g, job, up);
+  const UnitRef ur = unit_ref(g, job, unit);
   const int which = ur.which, slot = ur.slot, nv = ur.nv;
   const long bh = ur.bh;
   // (the three launches of a prompt: the solver's launch has left the status words)
@@ -1721,7 +1641,13 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? (!CACHED && (
     if constexpr (QB != 0 && PART == 0) end_call();
     return;
   }
+  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int solver = blockIdx.x % NWV;   // the wave that runs the eigen-solver (spread over the SIMDs)
+  constexpr int j1 = 16, ld = 17;
+  constexpr int d = PAIR ? 64 : 128;     // halves per row in memory
+  const uint16_t* X = ur.X;  // [nv, d] fp16 bits
+  const long head_gap = (long)job.t_new * d;   // PAIR: from a row of the first head to the same row of the second
+  double* const gram_ws = reinterpret_cast<double*>(large_ws + (long)unit * g.Tb * d);   // PART: G, then W, of this block
 
   static_assert(!LEAN || NWV == 1, "one wave per block");
   static_assert(!N3 || (LEAN && !PAIR && QB != 0), "three tensors: PART 3 with the quantizer, d = 128");
@@ -1731,6 +1657,7 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? (!CACHED && (
   // (a pair: one such area per head, of 64 channels each)
   constexpr int QT = LEAN ? 32 : kTileTokens;                // rows quantized and packed at a time
   constexpr int kHeadArea = QT * d + d * (pack_parts(QB ? QB : 8, QT) * QT * (QB ? QB : 8) / 32 + 1) * 4;
+  typedef FastProject<QB == 2 ? 2 : 4, FULL, PAIR, CACHED> FP;
   constexpr int kFieldBytes = FAST ? FP::kStageBytes + FP::kRowBytes : QB ? (PAIR ? 2 : 1) * kHeadArea : 16;
   // (the three launches: no matrices in LDS, but the second cut's)
   constexpr int kPoolBytes = LEAN ? (kMatBytes > kFieldBytes ? kMatBytes : kFieldBytes) : kMatBytes + kFieldBytes;
@@ -1744,8 +1671,7 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? (!CACHED && (
   // ---- Gram matrix G[p][q] = sum_{t, b2} X[t, p*8+b2] X[t, q*8+b2] ----
   if constexpr (PART != 3) {
     __shared__ int s_fits[NWV];
-    if (job.mostly_idle) load_groups<NWV, PAIR, CACHED>(first_groups, gram_row<PAIR>(X, head_gap), 0, nv);
-    gram16<NWV, PAIR, CACHED>(first_groups, gram_row<PAIR>(X, head_gap), nv, A, s_fits, PART == 1 ? gram_ws : A, PART == 1 ? j1 : ld);
+    gram16<NWV, PAIR, CACHED>(X, nv, head_gap, A, s_fits, PART == 1 ? gram_ws : A, PART == 1 ? j1 : ld);
   }
   if constexpr (PART == 1) return;
   if constexpr (PART == 0) {
@@ -1801,7 +1727,9 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? (!CACHED && (
   }
 
   if constexpr (FAST) {
-    fp.nv = nv;
+    FP fp;
+    fp.X = X; fp.nv = nv; fp.head_gap = head_gap; fp.one_group = !PAIR && g.groups == 1;
+    fp.setup(gram_ws);
     const int n = l & 15, q4 = l >> 4;
     const long blk = bh * g.NB + slot;
     uint8_t* const codes = (which ? cache.v_codes : cache.k_codes) + blk * g.codes_per_block;
@@ -1869,6 +1797,8 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? (!CACHED && (
         }
       }
     };
+    u32x4 next[4];
+    fp.load(next, 0);
     for (int tile = 0; tile < g.Tb; tile += kTileTokens) {
       int listed = fp.hard ? kTileTokens : 0;   // DIRECT: tokens of the tile in s_list (a hard block: all of them)
 #pragma unroll 1
@@ -1877,7 +1807,7 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? (!CACHED && (
         fp.clear(x, tile + t0);
         if (!CACHED) FP::turn(x, stage + FP::kStageBytes);
         if (tile + t0 + 16 < nv) {   // (the next sixteen tokens of the block, if there are any)
-          fp.load(next, tile + t0 + 16, nv);
+          fp.load(next, tile + t0 + 16);
         } else {
 #pragma unroll
           for (int u = 0; u < 4; ++u) next[u] = u32x4{0u, 0u, 0u, 0u};
@@ -2762,6 +2692,8 @@ static int waves_per_block(int groups, int want_waves) {
 // Whole call in us, 4 bits, two / four blocks per wave: 2048 blocks 63.9 / 71.8, 3072 95.5 / 87.9, 4096 111.0 / 106.8, graded over
 // three decades 207 / 193; four / eight: 4096 107 / 127, 8192 184.1 / 185.5, 9216 228 / 242, 12288 271 / 286, 14720 326.7 / 320.3, graded
 // 669 / 657, 32768 665 / 648; 8192 pairs of heads 210 / 214, 16384 401 / 398.
+// The host does not know which sequences are skipped.  Where most are, the chain of one wave is what counts: the launch alone for 16384
+// blocks, four / eight a wave, one sequence of sixteen left 30.6 / 47, four 53 / 50, eight 71 / 53.
 constexpr int kMostTwoBlocks = 2048, kMostFourBlocks = 12288;
 
 // Blocks (of sixteen rows of channels: pairs of 64-channel heads count once) up to which the Gram matrices' launch requests
