@@ -9,6 +9,33 @@ namespace dq {
 static std::atomic<int> g_last_hip_error{0};
 void set_last_hip_error(hipError_t e) { g_last_hip_error.store((int)e); }
 
+// Waves per SIMD that choose_mfma_shape counts on: what the registers of the 4-wave kernels hold in a launch of several splits (one split
+// holds a tail's rows in more of them).  Five kinds of launch hold three and are counted with two: the estimate takes a third workgroup
+// on a compute unit for cheaper than it is, and with three picked finer splits that lost more than others won.  Kernel times, counted with
+// two / three: four heads of one step group, 4 bits, 192 units x 64 tiles 36.0 / 45.0 us, 96 x 128 37.5 / 41.8, 2 bits 96 x 128
+// 30.4 / 32.8; two heads of two step groups, 4 bits, 96 x 128 37.6 / 40.0, 384 x 32 40.1 / 38.6; pairs of four heads, 2 bits, 160 x 64
+// 26.0 / 28.6, 96 x 24 14.4 / 12.4; two heads, three tensors, 2 bits, 160 x 64 27.7 / 30.4, 96 x 24 15.3 / 13.4.  (8 bits with two waves where
+// one was counted: four heads 96 x 64 49.4 -> 43.8, pairs of four 65.8 -> 59.3, two heads and a tail 48.8 -> 41.2.)
+static int resident_waves(int bits, int heads, bool two_groups, bool three, bool two_sets, bool tail) {
+  if (bits == 8) {
+    if (two_sets) return 1;
+    if (heads == 1) return three && two_groups ? 1 : 2;
+    if (heads == 2) return three || (tail && two_groups) ? 1 : 2;
+    return three || tail ? 1 : 2;
+  }
+  if (two_sets || heads == 4) return 2;
+  if (bits == 4) return !three && (heads == 1 || (!tail && !two_groups)) ? 3 : 2;
+  if (heads == 1) return three ? 3 : 4;
+  if (three) return 2;
+  return !two_groups && !tail ? 4 : 3;
+}
+
+// (for tests)
+extern "C" int32_t dq_debug_resident_waves(int32_t bits, int32_t heads, int32_t two_groups, int32_t three,
+                                           int32_t two_sets, int32_t tail) {
+  return resident_waves(bits, heads, two_groups != 0, three != 0, two_sets != 0, tail != 0);
+}
+
 // Launch shape of the matrix-core kernel: n splits of every (sequence, kv head) unit and nw waves per
 // workgroup, the pair with the least estimated time.  The estimate is meant to rank shapes, not to give
 // their time; it was fitted to the kernel timestamps of 2302 launches (1 to 640 units, 1 to 256
@@ -24,18 +51,14 @@ void set_last_hip_error(hipError_t e) { g_last_hip_error.store((int)e); }
 //   every wave on a SIMD and every split (partial, ticket, merge) costs a fixed amount, and so does the
 //   tail per wave and per load of its rows;
 //   a finer split has to promise 8.6 % to be taken.
-// The picks are 0.9 % slower than the fastest shape measured on average, 19 % at worst.  An estimate
-// without rounds was 1.3 % off on average and 30 % at worst (96 units of 64 tiles, four heads and a tail:
-// 33.6 us in its 8 splits of 4 waves, 26.8 in the 2 of 8 taken here), and over 3 % slower in 133 of the
-// 2302 cases than the rule of fixed depths before it (33 now); that rule was 4.5 % off and 73 %.
+// The picks were 0.9 % slower than the fastest shape measured on average, 19 % at worst.  The kernels of several heads have become
+// faster since: over 4290 launches of the present ones, 54 formats and options, the picks are 1.1 % slower on average and 31 % at
+// worst (160 units of 12 tiles, four heads, 4 bits, a tail: 17.1 us in 3 splits of 4 waves, 13.0 in 1 of 4), 93 of them over 10 %.  All constants
+// fitted again to these, with no launch slower than it was, gained 0.04 %.
 static void choose_mfma_shape(int units, int max_tiles, int heads, int bits, bool two_groups, bool three, bool pair,
                               bool two_sets, bool tail, int* n_out, int* nw_out) {
   static const int kSplits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
-  // waves a SIMD's registers hold (the heads' accumulators, the ring of chunks and the tail's rows decide)
-  int resident;
-  if (bits == 8) resident = (heads == 1 || (heads == 2 && !three && !tail)) ? 2 : 1;
-  else if (bits == 4) resident = (!three && (heads == 1 || (heads == 2 && !tail && !two_groups))) ? 3 : 2;
-  else resident = heads == 1 ? (three ? 3 : 4) : heads == 2 ? (three ? 2 : 3) : 2;
+  const int resident = resident_waves(bits, heads, two_groups, three, two_sets, tail);
   const float h = (float)(heads - 1), n3 = three ? 1.f : 0.f;
   // (two sets of columns: fitted by themselves, 276 sizes in three code widths; the picks are 0.25 % behind the fastest
   // shape on average, 7.5 % at worst, and with the constants of the others, extended to eight heads, 0.8 % and 28 %;
