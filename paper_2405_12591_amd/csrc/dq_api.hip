@@ -276,6 +276,19 @@ static int32_t decode_impl(const dq_format* fmt, const dq_cache* cache, const ui
   return use_mfma ? launch_decode_mfma(a, st) : launch_decode_generic(a, st);
 }
 
+// (for tests) How decode_impl would launch these sizes: out = {matrix-core kernel or not, splits, waves, query heads per workgroup}.
+extern "C" int32_t dq_debug_decode_shape(const dq_format* fmt, int32_t batch, int32_t q_heads, int32_t kv_heads, int32_t max_seq_len,
+                                         int32_t tail, uint32_t flags, int32_t* out) {
+  if (!format_ok(fmt) || batch <= 0 || kv_heads <= 0 || q_heads <= 0 || q_heads % kv_heads || max_seq_len < 0 || !out) return DQ_EINVAL;
+  const bool mfma = mfma_takes(fmt, q_heads, kv_heads) && !(flags & DQ_DECODE_FORCE_GENERIC);
+  int nw = 0, groups = 0, heads = 0;
+  out[1] = choose_splits(fmt, batch, q_heads, kv_heads, max_seq_len, mfma, tail != 0, flags, &nw, &groups, &heads);
+  out[0] = mfma;
+  out[2] = nw;
+  out[3] = heads;
+  return DQ_OK;
+}
+
 extern "C" int32_t dq_attn_decode_timed(const dq_format* fmt, const dq_cache* cache, const uint16_t* q,
                                         int32_t q_heads, const int32_t* seq_lens, int32_t max_seq_len,
                                         float softmax_scale, uint16_t* out, float* out_f32, void* workspace,

@@ -1262,19 +1262,27 @@ int32_t launch_bits(const DecodeArgs& a, hipStream_t st) {
     return DQ_OK;
   }
   const int rep = a.heads_per_group;   // query heads per workgroup (the last group may hold fewer)
+  // two sets of columns know neither a tail nor a third tensor: a rule that sent such a call there must not be answered without them
+  const bool two_sets_ok = !a.tail.k_tail && a.fmt.i3 == 1;
   if (a.fmt.group == 128) {
     switch (rep) {
       case 1: launch_r<BITS, 1, 1>(a, st); break;
       case 2: launch_r<BITS, 1, 2>(a, st); break;
       case 4: launch_r<BITS, 1, 4>(a, st); break;
-      case 8: launch_tm<BITS, 1, 4, 0, false, false, 2>(a, st); break;
+      case 8:
+        if (!two_sets_ok) return DQ_EINVAL;
+        launch_tm<BITS, 1, 4, 0, false, false, 2>(a, st);
+        break;
       default: return DQ_EINVAL;
     }
   } else {
     switch (rep) {
       case 1: launch_r<BITS, 2, 1>(a, st); break;
       case 2: launch_r<BITS, 2, 2>(a, st); break;
-      case 4: launch_tm<BITS, 2, 4, 0, false, false, 2>(a, st); break;
+      case 4:
+        if (!two_sets_ok) return DQ_EINVAL;
+        launch_tm<BITS, 2, 4, 0, false, false, 2>(a, st);
+        break;
       default: return DQ_EINVAL;
     }
   }
