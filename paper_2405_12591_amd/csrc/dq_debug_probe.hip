@@ -1,9 +1,28 @@
-// Instrumented build only (-DDQ_TIMELINE; the product library holds nothing of this file): a probe
-// of how matrix and vector instructions of one SIMD share its issue.  Four waves per SIMD run a
+// Probes of the matrix instructions.
+// For tests: products of the 16x16x32 fp16 instruction, on which the error bound of the prompt's projection rests.
+// Instrumented build only (-DDQ_TIMELINE): a probe of how matrix and vector instructions of one SIMD share its issue.  Four waves per SIMD run a
 // loop of four independent matrix instructions of one kind, sixteen independent fp32 FMAs, or
 // both; the time per loop body tells whether the two kinds run side by side.  The decode kernel's
 // choice between matrix and vector instructions for its small-tensor epilogue rests on the figures.
 #include "dq_common.h"
+
+namespace dq {
+typedef _Float16 pf16x8 __attribute__((ext_vector_type(8)));
+typedef float pfx4 __attribute__((ext_vector_type(4)));
+__global__ __launch_bounds__(64) void mfma_f16_kernel(const pf16x8* a, const pf16x8* b, pfx4* out) {
+  const long at = (long)blockIdx.x * 64 + threadIdx.x;
+  out[at] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[at], b[at], pfx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+}
+}  // namespace dq
+
+// `count` products of their own: operands fp16 [count, 64, 8] and results fp32 [count, 64, 4], as the 64 lanes hold them (16-byte aligned).
+extern "C" int32_t dq_debug_mfma_f16(const uint16_t* a, const uint16_t* b, float* out, int32_t count, void* hip_stream) {
+  if (!a || !b || !out || count < 1 || (((uintptr_t)a | (uintptr_t)b | (uintptr_t)out) & 15)) return DQ_EINVAL;
+  hipLaunchKernelGGL(dq::mfma_f16_kernel, dim3(count), dim3(64), 0, (hipStream_t)hip_stream, reinterpret_cast<const dq::pf16x8*>(a),
+                     reinterpret_cast<const dq::pf16x8*>(b), reinterpret_cast<dq::pfx4*>(out));
+  DQ_HIP_CHECK(hipGetLastError());
+  return DQ_OK;
+}
 
 #ifdef DQ_TIMELINE
 namespace dq {
