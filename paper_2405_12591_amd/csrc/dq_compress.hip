@@ -1858,7 +1858,7 @@ __global__ __launch_bounds__(64 * NWV, PART == 1 ? 3 : PART == 3 ? (!CACHED && (
       __builtin_amdgcn_wave_barrier();
       if (listed > 0) {
         // (the lane's number anew: addresses formed from it ahead of the first pass would cost that pass its
-        // registers, 152 instead of 114)
+        // registers, of which it has 122 to 128 for four waves a SIMD)
         int lane = l;
         asm volatile("" : "+v"(lane));
         const int n = lane & 15;
@@ -2710,20 +2710,22 @@ constexpr int kMostCachedFast = 8192, kMostCached = 2048;
 // SIMD, of those that turn their rows in LDS three, which takes launches of more than 2816 in two rounds instead of one.  It
 // matters where many tokens are settled in fp64 and a wave takes long; the rows still come from the last-level cache (see
 // kMostCachedFast), whose lines are asked for four times in this order.  Whole call in us, turned / direct, blocks with outlier
-// channels and blocks graded over three decades: 2048 blocks 67.5 / 68.1 and 131 / 130, 2816 94.1 / 94.1 and 183 / 183, 3072
-// 99.3 / 98.8 and 221 / 184, 4096 117 / 116 and 252 / 213, 6144 158 / 154 and 343 / 308, 8192 202 / 211 and 439 / 398;
-// pairs of heads, 4096 135 / 132 and 238 / 201, 5120 155 / 157 and 348 / 254.
+// channels and blocks graded over three decades, 4 bits: 2048 blocks 67.6 / 69.4 and 125 / 128, 2816 85.1 / 87.0 and 166 / 167, 2944
+// 87.4 / 88.9 and 191 / 165, 4096 105 / 108 and 228 / 195, 5120 137 / 132 and 287 / 264, 6144 153 / 153 and 322 / 289, 7168 166 / 175
+// and 357 / 323, 14720 315 / 354 and 630 / 604; 2 bits 2944 86.5 / 89.4 and 161 / 161, 4096 106 / 108 and 200 / 190, 5120 140 / 134 and
+// 261 / 258, 7168 168 / 172 and 326 / 314; pairs of heads, 4 bits, 4096 121 / 128 and 213 / 187, 5120 154 / 154 and 259 / 247, 2 bits 4096 120 / 124
+// and 186 / 183.
 constexpr int kLeastDirect = 2817, kMostDirect = 6144;
 
-// LDS that a prompt's projection (2 or 4 bits) is given beyond what it uses, to hold fewer waves than its
-// registers would let onto a SIMD: beyond 6144 workgroups more rows on their way are slower, not faster.  Pairs of heads
-// are held to six workgroups per compute unit (whole call, without / with: 8192 pairs 236 / 232 us in 4 bits, 231 / 225 in
-// 2; 16384 pairs 423 / 416 and 419 / 408; 6000 pairs 190 / 184), 2-bit codes of 128 channels to twelve (32768 blocks 696 /
-// 683; 4-bit ones use that much LDS as it is).
+// LDS that the projection of pairs of heads (2 or 4 bits) is given beyond what it uses from 6145 workgroups on, to hold six of them
+// per compute unit instead of the twelve its registers would let in: more rows on their way are slower, not faster.  Whole call
+// without / with, outlier channels: 8192 pairs 212 / 205 us in 4 bits, 212 / 206 in 2; 14720 pairs 370 / 362 and 364 / 353; 32768
+// 763 / 742 and 763 / 725.  Blocks graded over three decades, most of whose tokens are settled in fp64, lose by it: 8192 pairs 356 / 442 and
+// 329 / 432, 14720 581 / 745 and 557 / 727.
 static size_t prompt_projection_pad(int groups, bool pair_heads, int bits) {
-  if (groups <= kMostDirect || bits == 8) return 0;
-  const size_t per_cu = pair_heads ? 6 : 12, used = 128 * (16 * bits + 4) + 4096 + 1024;
-  return 160 * 1024 / per_cu > used ? 160 * 1024 / per_cu - used : 0;
+  if (groups <= kMostDirect || !pair_heads || bits == 8) return 0;
+  const size_t used = 128 * (16 * bits + 4) + 4096 + 1024;
+  return 160 * 1024 / 6 > used ? 160 * 1024 / 6 - used : 0;
 }
 
 static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16_t* k_new,
