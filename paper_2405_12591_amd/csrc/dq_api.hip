@@ -15,13 +15,13 @@ void set_last_hip_error(hipError_t e) { g_last_hip_error.store((int)e); }
 // two / three: four heads of one step group, 4 bits, 192 units x 64 tiles 36.0 / 45.0 us, 96 x 128 37.5 / 41.8, 2 bits 96 x 128
 // 30.4 / 32.8; two heads of two step groups, 4 bits, 96 x 128 37.6 / 40.0, 384 x 32 40.1 / 38.6; pairs of four heads, 2 bits, 160 x 64
 // 26.0 / 28.6, 96 x 24 14.4 / 12.4; two heads, three tensors, 2 bits, 160 x 64 27.7 / 30.4, 96 x 24 15.3 / 13.4.  (8 bits with two waves where
-// one was counted: four heads 96 x 64 49.4 -> 43.8, pairs of four 65.8 -> 59.3, two heads and a tail 48.8 -> 41.2.)
+// one was counted: four heads 96 x 64 49.4 -> 43.8, two heads and a tail 48.8 -> 41.2.)
 static int resident_waves(int bits, int heads, bool two_groups, bool three, bool two_sets, bool tail) {
   if (bits == 8) {
     if (two_sets) return 1;
     if (heads == 1) return three && two_groups ? 1 : 2;
     if (heads == 2) return three || (tail && two_groups) ? 1 : 2;
-    return three || tail ? 1 : 2;
+    return three || tail || two_groups ? 1 : 2;   // (four heads; of two step groups: pairs)
   }
   if (two_sets || heads == 4) return 2;
   if (bits == 4) return !three && (heads == 1 || (!tail && !two_groups)) ? 3 : 2;
@@ -52,7 +52,7 @@ extern "C" int32_t dq_debug_resident_waves(int32_t bits, int32_t heads, int32_t 
 //   tail per wave and per load of its rows;
 //   a finer split has to promise 8.6 % to be taken.
 // The picks were 0.9 % slower than the fastest shape measured on average, 19 % at worst.  The kernels of several heads have become
-// faster since: over 4290 launches of the present ones, 54 formats and options, the picks are 1.1 % slower on average and 31 % at
+// faster since: over 4361 launches of the present ones, 55 formats and options, the picks are 1.1 % slower on average and 31 % at
 // worst (160 units of 12 tiles, four heads, 4 bits, a tail: 17.1 us in 3 splits of 4 waves, 13.0 in 1 of 4), 93 of them over 10 %.  All constants
 // fitted again to these, with no launch slower than it was, gained 0.04 %.
 static void choose_mfma_shape(int units, int max_tiles, int heads, int bits, bool two_groups, bool three, bool pair,

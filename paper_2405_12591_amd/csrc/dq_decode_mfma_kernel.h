@@ -249,7 +249,9 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   // 32; a serving step of 16 sequences of 3000 to 8000 tokens 32.5 -> 31.4; 8 x 32 on 8 heads of 64 channels, 2048 to 4096 tokens
   // 11.5 -> 11.0.  (Two heads of one step group would leave half the lanes idle in the softmax.)  Two step groups add a swap a token, for the
   // other group's share: 64 x 2 heads x 8192 tokens of two step groups, 4 bits, 24.1 -> 22.1, 64 x 2 x 128 6.1 -> 5.4.
-  constexpr bool TURN = (NC == 16 && R >= 2 && !N3);
+  // (Pairs in 8 bits keep the other order: a lane's two tokens are neighbours there and lie in one line of two 64-byte rows, which two chunks would each ask for half
+  // of: 128 units x 64 tiles 66.8 us turned, 50.6 so, 64 x 128 61.1, 47.5.  In 4 and 2 bits the same costs less than turning gains.)
+  constexpr bool TURN = (NC == 16 && R >= 2 && !N3 && !(P2 && BITS == 8));
   // One head of one step group fills four of the sixteen columns.  Its limbs stand in all four groups of columns, so that with the score product
   // turned every lane holds the limbs of every eighth token's score, and keeps those of its own two.  Through LDS (8 writes and 8 reads a
   // tile): 1 x 32 heads x 2999 tokens 7.54 -> 7.41 us, 8 x 32 x 4096 4 bits 24.6 -> 24.4, 8 bits 48.8 -> 48.3.  (Three tensors: 8-bit codes would
@@ -462,6 +464,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   // share a 16-bit word of B slots; a chunk still asks for whole lines (two rows at 4 bits, four at 2, one at 8)
   const int key_row = (TURN || SPREAD) ? tA - 32 * g : n;
   constexpr int kPairRows = BITS == 4 ? 2 : BITS == 2 ? 4 : 1;   // tB - tA
+  static_assert(!(TURN || SPREAD) || BITS < 8 || kPairRows * ROWB == 128, "8 bits: a chunk asks for whole lines");
   auto chunk_rows = [](int j) constexpr -> int { return (TURN || SPREAD) ? 32 * (j >> 1) + (j & 1) * kPairRows : 16 * j; };
 
   // The fold's columns are dealt so that the four a lane gets lie side by side in B slots (2-bit codes: two and two).
