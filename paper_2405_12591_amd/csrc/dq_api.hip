@@ -10,11 +10,13 @@ static std::atomic<int> g_last_hip_error{0};
 void set_last_hip_error(hipError_t e) { g_last_hip_error.store((int)e); }
 
 // Waves per SIMD that choose_mfma_shape counts on: what the registers of the 4-wave kernels hold in a launch of several splits (one split
-// holds a tail's rows in more of them).  Five kinds of launch hold three and are counted with two: the estimate takes a third workgroup
+// holds a tail's rows in more of them).  Six kinds of launch are counted with one fewer than they hold.  Five hold three and are counted with two: the estimate takes a third workgroup
 // on a compute unit for cheaper than it is, and with three picked finer splits that lost more than others won.  Kernel times, counted with
 // two / three: four heads of one step group, 4 bits, 192 units x 64 tiles 36.0 / 45.0 us, 96 x 128 37.5 / 41.8, 2 bits 96 x 128
 // 30.4 / 32.8; two heads of two step groups, 4 bits, 96 x 128 37.6 / 40.0, 384 x 32 40.1 / 38.6; pairs of four heads, 2 bits, 160 x 64
-// 26.0 / 28.6, 96 x 24 14.4 / 12.4; two heads, three tensors, 2 bits, 160 x 64 27.7 / 30.4, 96 x 24 15.3 / 13.4.  (8 bits with two waves where
+// 26.0 / 28.6, 96 x 24 14.4 / 12.4; two heads, three tensors, 2 bits, 160 x 64 27.7 / 30.4, 96 x 24 15.3 / 13.4.  Two heads of one step group in 2 bits
+// hold four and are counted with three: 128 x 256 55.1 / 64.6, 392 x 124 83.4 / 89.4 (416 x 152 100 / 107), but 272 x 168 92.0 / 76.4; the 90 of 670 launches
+// that differ, measured in both, 1 % slower on average.  (8 bits with two waves where
 // one was counted: four heads 96 x 64 49.4 -> 43.8, two heads and a tail 48.8 -> 41.2.)
 static int resident_waves(int bits, int heads, bool two_groups, bool three, bool two_sets, bool tail) {
   if (bits == 8) {
@@ -27,7 +29,7 @@ static int resident_waves(int bits, int heads, bool two_groups, bool three, bool
   if (bits == 4) return !three && (heads == 1 || (!tail && !two_groups)) ? 3 : 2;
   if (heads == 1) return three ? 3 : 4;
   if (three) return 2;
-  return !two_groups && !tail ? 4 : 3;
+  return 3;
 }
 
 // (for tests)
