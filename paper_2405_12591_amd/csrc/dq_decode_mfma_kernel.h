@@ -217,7 +217,7 @@ __device__ __forceinline__ float pow2i(int e) {
 // sets: 221 registers, two waves a SIMD.  4 bits 65.4 -> 55 us, 2 bits 52.9 -> 45.5, 8 bits x 8192 tokens 47.4 -> 32.7; two step
 // groups, 64 x 4 heads x 32768 tokens, 4 bits 65.5 -> 55.2.  Which launches take it: mfma_two_groups (dq_decode_mfma.hip).
 // (two step groups: R counts the heads of both sets)
-template <int BITS, int NG, int RQ, int NW, int TM, bool N3, bool P2, int HP = 1>
+template <int BITS, int NG, int RQ, int NW, int TM, bool N3, bool P2, int HP = 1, bool KEEP = false>
 __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode_mfma_kernel(DecodeArgs a) {
   constexpr int R = (NG == 2 && HP == 2) ? RQ / 2 : RQ;   // query heads of a set of columns
   static_assert(!P2 || (NG == 2 && (R == 2 || R == 4) && !N3), "a pair of heads is two step groups and two or four query heads");
@@ -250,7 +250,8 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   // 11.5 -> 11.0.  (Two heads of one step group would leave half the lanes idle in the softmax.)  Two step groups add a swap a token, for the
   // other group's share: 64 x 2 heads x 8192 tokens of two step groups, 4 bits, 24.1 -> 22.1, 64 x 2 x 128 6.1 -> 5.4.
   // (Pairs in 8 bits keep the other order: a lane's two tokens are neighbours there and lie in one line of two 64-byte rows, which two chunks would each ask for half
-  // of: 128 units x 64 tiles 66.8 us turned, 50.6 so, 64 x 128 61.1, 47.5.  In 4 and 2 bits the same costs less than turning gains.)
+  // of: 128 units x 64 tiles 66.8 us turned, 50.6 so, 64 x 128 61.1, 47.5.  In 4 and 2 bits turning gains more than that costs, in 4 bits with several
+  // head groups only if the halves meet in the caches: see KEEP.)
   constexpr bool TURN = (NC == 16 && R >= 2 && !N3 && !(P2 && BITS == 8));
   // One head of one step group fills four of the sixteen columns.  Its limbs stand in all four groups of columns, so that with the score product
   // turned every lane holds the limbs of every eighth token's score, and keeps those of its own two.  Through LDS (8 writes and 8 reads a
@@ -467,6 +468,12 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   static_assert(!(TURN || SPREAD) || BITS < 8 || kPairRows * ROWB == 128, "8 bits: a chunk asks for whole lines");
   auto chunk_rows = [](int j) constexpr -> int { return (TURN || SPREAD) ? 32 * (j >> 1) + (j & 1) * kPairRows : 16 * j; };
 
+  // KEEP: not past the caches (see launch_bits)
+  auto load_key = [](const unsigned char* from) __attribute__((always_inline)) {
+    const chunk_t* const at = reinterpret_cast<const chunk_t*>(from);
+    return KEEP ? *at : __builtin_nontemporal_load(at);
+  };
+
   // The fold's columns are dealt so that the four a lane gets lie side by side in B slots (2-bit codes: two and two).
   auto fold_b2 = [](int c) constexpr -> int {   // the b2 of column c (mod 8)
     return BITS == 4 ? 2 * (c & 3) + (c >> 2) : BITS == 2 ? (c >> 2) * 2 + ((c >> 1) & 1) + 4 * (c & 1) : c;
@@ -585,7 +592,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
     if (P2) load_sideP(curP, blkid, tib);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) ring[j] = __builtin_nontemporal_load(reinterpret_cast<const chunk_t*>(kc + chunk_rows(j) * ROWB));
+    for (int j = 0; j < 8; ++j) ring[j] = load_key(kc + chunk_rows(j) * ROWB);
 #pragma unroll
     for (int b2 = 0; b2 < 8; ++b2) ring[8 + b2] = __builtin_nontemporal_load(reinterpret_cast<const chunk_t*>(vc + b2 * (RJ1 * VROWB)));
   };
@@ -775,7 +782,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
       for (int j = 0; j < 8; ++j) {
         const i32x4 a0 = C::half(ring[j], 0), a1 = C::half(ring[j], 1);
         __builtin_amdgcn_sched_barrier(0);   // the slot is dead from here on: refill it in place
-        if (HAS_NEXT) ring[j] = __builtin_nontemporal_load(reinterpret_cast<const chunk_t*>(kc_next + chunk_rows(j) * ROWB));
+        if (HAS_NEXT) ring[j] = load_key(kc_next + chunk_rows(j) * ROWB);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int hp = 0; hp < HP; ++hp) {
@@ -1228,7 +1235,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   DQ_STAMP(19);
 }
 #undef DQ_STAMP
-template <int BITS, int NG, int R, int TM, bool N3, bool P2, int HP = 1>
+template <int BITS, int NG, int R, int TM, bool N3, bool P2, int HP = 1, bool KEEP = false>
 inline void launch_tm(const DecodeArgs& a, hipStream_t st) {
   const int units = a.cache.batch * a.cache.kv_heads / (P2 ? 2 : 1);
   const dim3 grid = a.rows_on_x ? dim3(units * a.head_groups, a.n_split) : dim3(a.n_split, units * a.head_groups);
@@ -1237,18 +1244,18 @@ inline void launch_tm(const DecodeArgs& a, hipStream_t st) {
   // registers, so that width always takes 4 waves)
   if constexpr (BITS < 8) {
     if (a.nw == 8) {
-      hipExtLaunchKernelGGL((decode_mfma_kernel<BITS, NG, R, 8, TM, N3, P2, HP>), grid, dim3(512), 0, st, a.ev_start, a.ev_stop, 0, a);
+      hipExtLaunchKernelGGL((decode_mfma_kernel<BITS, NG, R, 8, TM, N3, P2, HP, KEEP>), grid, dim3(512), 0, st, a.ev_start, a.ev_stop, 0, a);
       return;
     }
   }
-  hipExtLaunchKernelGGL((decode_mfma_kernel<BITS, NG, R, 4, TM, N3, P2, HP>), grid, dim3(256), 0, st, a.ev_start, a.ev_stop, 0, a);
+  hipExtLaunchKernelGGL((decode_mfma_kernel<BITS, NG, R, 4, TM, N3, P2, HP, KEEP>), grid, dim3(256), 0, st, a.ev_start, a.ev_stop, 0, a);
 }
 
-template <int BITS, int NG, int R, bool N3, bool P2 = false>
+template <int BITS, int NG, int R, bool N3, bool P2 = false, bool KEEP = false>
 inline void launch_n3(const DecodeArgs& a, hipStream_t st) {
-  if (!a.tail.k_tail) launch_tm<BITS, NG, R, 0, N3, P2>(a, st);
-  else if (a.n_split == 1) launch_tm<BITS, NG, R, 1, N3, P2>(a, st);
-  else launch_tm<BITS, NG, R, 2, N3, P2>(a, st);
+  if (!a.tail.k_tail) launch_tm<BITS, NG, R, 0, N3, P2, 1, KEEP>(a, st);
+  else if (a.n_split == 1) launch_tm<BITS, NG, R, 1, N3, P2, 1, KEEP>(a, st);
+  else launch_tm<BITS, NG, R, 2, N3, P2, 1, KEEP>(a, st);
 }
 
 template <int BITS, int NG, int R>
@@ -1261,6 +1268,10 @@ template <int BITS>
 int32_t launch_bits(const DecodeArgs& a, hipStream_t st) {
   if (a.pair_heads) {   // two kv heads of 64 channels per workgroup, one or two query heads of each
     if (a.heads_per_group == 1) launch_n3<BITS, 2, 2, false, true>(a, st);
+    // 4 bits, turned: two chunks ask for half of every line of keys.  Requested past the caches, a line was fetched for each half; where several
+    // head groups read it as well, plain loads are never slower (17 x 48 heads on 8 x 32768 tokens 143 us, 118 so; 8 x 96 on 32
+    // x 2048 15.3, 14.2), with one group they lose up to 4 % beyond 64 MB of codes (8 x 64 on 32 x 32768 87.3, 90.9).  2 bits: the same within 1 %.
+    else if (BITS == 4 && a.head_groups > 1) launch_n3<BITS, 2, 4, false, true, BITS == 4>(a, st);
     else launch_n3<BITS, 2, 4, false, true>(a, st);
     return DQ_OK;
   }
