@@ -2334,16 +2334,14 @@ __device__ __forceinline__ void store_fast_factors(const Jacobi16<ROWS>& jac, co
 // eight blocks): 94, too few waves to cover one another's waits.
 // Workgroups of four waves, so that the waves spread evenly over the SIMDs.
 constexpr int kSolveWaves = 4;
+constexpr int kFactorBytes = (16 * 16 + 16) * 8;             // a block's place in LDS: W and the eigenvalues
+static_assert(kFactorBytes == (kFastPieces - 16 * 16) * 8 && kFactorBytes >= kFastBytes, "a block's place in LDS");
 template <int ROWS, bool PAIR, bool FAST>
-__global__ __launch_bounds__(64 * kSolveWaves, ROWS == 16 ? 2 : 4) void solve16_kernel(dq_format fmt, dq_cache cache, CompressJob job,
-                                                     float* __restrict__ large_ws, int32_t* __restrict__ unit_status,
-                                                     int n_groups) {
+__device__ __forceinline__ void solve16(const dq_format& fmt, const dq_cache& cache, const CompressJob& job, float* __restrict__ large_ws,
+                                        int32_t* __restrict__ unit_status, int n_groups, unsigned char (*s_stage)[kFactorBytes]) {
   constexpr int LPB = 128 / ROWS, BPW = 64 / LPB, BPG = kSolveWaves * BPW;   // lanes per block, blocks per wave and workgroup
   constexpr int j1 = 16, d = PAIR ? 64 : 128;
-  constexpr int kFactorBytes = (j1 * j1 + j1) * 8;           // W and the eigenvalues
-  static_assert(kFactorBytes == (kFastPieces - j1 * j1) * 8 && kFactorBytes >= kFastBytes, "a block's place in LDS");
   const Geometry g = make_geometry(fmt, cache.kv_heads, cache.block_capacity);
-  __shared__ __attribute__((aligned(16))) unsigned char s_stage[BPG][kFactorBytes];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, blk = threadIdx.x / LPB, j = lane & 7;
   unsigned char* const stage = s_stage[blk];
   const int gi = blockIdx.x * BPG + blk;
@@ -2463,6 +2461,32 @@ __global__ __launch_bounds__(64 * kSolveWaves, ROWS == 16 ? 2 : 4) void solve16_
     unit_status[unit] = word;
     if (PAIR) unit_status[unit + unit_gap] = word;
   }
+}
+
+// ROWS / 2 blocks a wave, half as many where at most `few` of the call's blocks (pairs of them) are live: the host, which sees
+// neither the slots nor the lengths, launches workgroups for the latter, and those that are not wanted leave.
+template <int ROWS, bool PAIR, bool FAST>
+__global__ __launch_bounds__(64 * kSolveWaves, ROWS == 16 ? 2 : 4) void solve16_kernel(dq_format fmt, dq_cache cache, CompressJob job,
+                                                     float* __restrict__ large_ws, int32_t* __restrict__ unit_status,
+                                                     int n_groups, int few) {
+  __shared__ __attribute__((aligned(16))) unsigned char s_stage[kSolveWaves * ROWS / 2][kFactorBytes];
+  if constexpr (ROWS > 4) {
+    const Geometry g = make_geometry(fmt, cache.kv_heads, cache.block_capacity);
+    int live = 0;
+    for (int b = threadIdx.x & 63; b < job.batch; b += 64) live += live_blocks(g, job, b);
+    live += __builtin_amdgcn_update_dpp(0, live, kDppXor1, 0xF, 0xF, true);
+    live += __builtin_amdgcn_update_dpp(0, live, kDppXor2, 0xF, 0xF, true);
+    live += __builtin_amdgcn_update_dpp(0, live, kDppXor7, 0xF, 0xF, true);
+    live += __builtin_amdgcn_update_dpp(0, live, kDppXor8, 0xF, 0xF, true);
+    live = (__builtin_amdgcn_readlane(live, 0) + __builtin_amdgcn_readlane(live, 16)) +
+           (__builtin_amdgcn_readlane(live, 32) + __builtin_amdgcn_readlane(live, 48));
+    if (live * (PAIR ? g.H : 2 * g.H) <= few) {
+      solve16<ROWS / 2, PAIR, FAST>(fmt, cache, job, large_ws, unit_status, n_groups, s_stage);
+      return;
+    }
+    if ((int)blockIdx.x * (kSolveWaves * ROWS / 2) >= n_groups) return;
+  }
+  solve16<ROWS, PAIR, FAST>(fmt, cache, job, large_ws, unit_status, n_groups, s_stage);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2693,9 +2717,11 @@ static int waves_per_block(int groups, int want_waves) {
 // Whole call in us, 4 bits, two / four blocks per wave: 2048 blocks 63.9 / 71.8, 3072 95.5 / 87.9, 4096 111.0 / 106.8, graded over
 // three decades 207 / 193; four / eight: 4096 107 / 127, 8192 184.1 / 185.5, 9216 228 / 242, 12288 271 / 286, 14720 326.7 / 320.3, graded
 // 669 / 657, 32768 665 / 648; 8192 pairs of heads 210 / 214, 16384 401 / 398.
-// The host does not know which sequences are skipped.  Where most are, the chain of one wave is what counts: the launch alone for 16384
-// blocks, four / eight a wave, one sequence of sixteen left 30.6 / 47, four 53 / 50, eight 71 / 53.
-constexpr int kMostTwoBlocks = 2048, kMostFourBlocks = 12288;
+// Where most sequences are skipped, the chain of one wave is what counts: the launch alone for 16384 blocks, four / eight a wave, one
+// sequence of sixteen left 30.6 / 47, four 53 / 50, eight 71 / 53.  A launch of eight (four) a wave takes four (two) where at most
+// kFewFourBlocks (kFewTwoBlocks) are live, seven eighths of a wave a SIMD: the waves that are left do not spread evenly.  3328 of 14336
+// live: 79.7 us, 50.6 so, whole call 200 and 161; 1536 of 3072 78.2 and 71.5; where all are live the count costs 0.4.
+constexpr int kMostTwoBlocks = 2048, kMostFourBlocks = 12288, kFewTwoBlocks = 1792, kFewFourBlocks = 3584;
 
 // Blocks (of sixteen rows of channels: pairs of 64-channel heads count once) up to which the Gram matrices' launch requests
 // its rows with plain loads: the projection then finds them in the 256 MB last-level cache, 32 KB a block (kMostCachedFast: 2- and
@@ -2784,10 +2810,12 @@ static int32_t compress_impl(const dq_format* fmt, dq_cache* cache, const uint16
     else if (cached) DQ_LAUNCH_GRAM(false, true);
     else DQ_LAUNCH_GRAM(false, false);
 #undef DQ_LAUNCH_GRAM
+    // (workgroups for half as many blocks a wave, see solve16_kernel)
+    constexpr int kFewPerGroup16 = kSolveWaves * 4, kFewPerGroup8 = kSolveWaves * 2, kFewPerGroup4 = kSolveWaves * 2;
 #define DQ_LAUNCH_SOLVE(R_, P_, F_)                                                                               \
-  hipLaunchKernelGGL((solve16_kernel<R_, P_, F_>), dim3((groups + kSolveWaves * R_ / 2 - 1) / (kSolveWaves * R_ / 2)), \
+  hipLaunchKernelGGL((solve16_kernel<R_, P_, F_>), dim3((groups + kFewPerGroup##R_ - 1) / kFewPerGroup##R_),      \
                      dim3(64 * kSolveWaves), 0, st, *fmt,                                                         \
-                     *cache, job, large_ws, unit_status, groups)
+                     *cache, job, large_ws, unit_status, groups, R_ == 16 ? kFewFourBlocks : kFewTwoBlocks)
 #define DQ_LAUNCH_SOLVE_F(R_, P_)          \
   do {                                     \
     if (fast) DQ_LAUNCH_SOLVE(R_, P_, true); \

@@ -18,6 +18,12 @@ struct CompressJob {
   int batch;
 };
 
+__host__ __device__ __forceinline__ int valid_rows(const CompressJob& job, int b) {
+  if (!job.n_valid) return job.t_new;
+  const int valid = job.n_valid[b];
+  return valid < 0 ? 0 : valid < job.t_new ? valid : job.t_new;
+}
+
 // Work unit `unit` = (((b * H + h) * n_blocks) + j) * 2 + which.  slot < 0: nothing to do (sequence
 // skipped, slot past the cache's capacity, or a block none of whose rows is valid).
 struct UnitRef {
@@ -37,16 +43,17 @@ __host__ __device__ __forceinline__ UnitRef unit_ref(const Geometry& g, const Co
   u.bh = ub / job.n_blocks;
   u.b = (int)(u.bh / g.H);
   const int first = job.blk_idx[u.b];
-  int rows = job.t_new;
-  if (job.n_valid) {
-    const int valid = job.n_valid[u.b];
-    rows = valid < 0 ? 0 : valid < job.t_new ? valid : job.t_new;
-  }
-  const int left = rows - j * g.Tb;
+  const int left = valid_rows(job, u.b) - j * g.Tb;
   u.nv = left < 0 ? 0 : left < g.Tb ? left : g.Tb;
   u.slot = (first < 0 || first + j >= g.NB || u.nv == 0) ? -1 : first + j;
   u.X = u.slot < 0 ? nullptr : (u.which ? job.v_new : job.k_new) + (u.bh * job.t_new + (long)j * g.Tb) * g.d;
   return u;
+}
+
+// Blocks of sequence b, per head and side, for which unit_ref() has something to do.
+__host__ __device__ __forceinline__ int live_blocks(const Geometry& g, const CompressJob& job, int b) {
+  const int first = job.blk_idx[b], blocks = (valid_rows(job, b) + g.Tb - 1) / g.Tb, room = g.NB - first;
+  return first < 0 || room < 0 ? 0 : blocks < room ? blocks : room;
 }
 
 }  // namespace dq

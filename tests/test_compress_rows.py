@@ -1,6 +1,6 @@
 """Which of the caller's rows a compression call may read (dq_unit.h), on the CPU: the rows of a block come as an address and a
 number, and over all blocks of a call these are exactly the valid rows of the sequences that are not skipped; a block with
-nothing to do has no address."""
+nothing to do has no address.  The number of blocks with something to do, by which the eigen-solver's launch chooses, is theirs."""
 import os
 import subprocess
 
@@ -13,7 +13,7 @@ PROGRAM = r"""
 #include <stdio.h>
 #include <vector>
 #include "dq_unit.h"
-int main() {   // stdin: B, H, t_new, T_b, d, NB, n_valid given, blk_idx, n_valid; stdout: per unit slot, nv, 1 + row of X (0: null)
+int main() {   // stdin: B, H, t_new, T_b, d, NB, n_valid given, blk_idx, n_valid; stdout: per unit slot, nv, 1 + row of X (0: null), live blocks of its sequence
   int p[7];
   while (fread(p, sizeof p, 1, stdin) == 1) {
     std::vector<int32_t> first(p[0]), valid(p[0]);
@@ -27,7 +27,7 @@ int main() {   // stdin: B, H, t_new, T_b, d, NB, n_valid given, blk_idx, n_vali
       const dq::UnitRef r = dq::unit_ref(g, job, u);
       const long at = r.X ? r.X - (r.which ? v.data() : k.data()) : -p[4];
       if (at % p[4]) return 2;
-      const int out[3] = {r.slot, r.nv, (int)(at / p[4]) + 1};
+      const int out[4] = {r.slot, r.nv, (int)(at / p[4]) + 1, dq::live_blocks(g, job, r.b)};
       fwrite(out, sizeof out, 1, stdout);
     }
   }
@@ -54,7 +54,7 @@ def test_a_block_reads_the_valid_rows_of_sequences_that_are_not_skipped(tmp_path
         first = rng.integers(-1, nb + 1, b).astype(np.int32)
         valid = np.array([rng.choice([-1, 0, 1, t_new, t_new + 3, int(rng.integers(0, t_new + 1))]) for _ in range(b)], np.int32)
         data = np.array([b, h, t_new, tb, d, nb, given], np.int32).tobytes() + first.tobytes() + valid.tobytes()
-        out = np.frombuffer(subprocess.run([exe], input=data, capture_output=True, check=True).stdout, np.int32).reshape(b, h, n_blocks, 2, 3)
+        out = np.frombuffer(subprocess.run([exe], input=data, capture_output=True, check=True).stdout, np.int32).reshape(b, h, n_blocks, 2, 4)
         for i in range(b):
             rows = min(max(int(valid[i]), 0), t_new) if given else t_new
             for j in range(n_blocks):
@@ -63,4 +63,5 @@ def test_a_block_reads_the_valid_rows_of_sequences_that_are_not_skipped(tmp_path
                 for hd in range(h):
                     row = (i * h + hd) * t_new + j * tb
                     want = (first[i] + j, nv, 1 + row) if live else (-1, nv, 0)
-                    assert (out[i, hd, j] == want).all(), (t_new, tb, first, valid, given, i, hd, j, out[i, hd, j], want)
+                    assert (out[i, hd, j, :, :3] == want).all(), (t_new, tb, first, valid, given, i, hd, j, out[i, hd, j], want)
+            assert (out[i, :, :, :, 3] == (out[i, 0, :, 0, 0] >= 0).sum()).all(), (t_new, tb, first, valid, given, i)
