@@ -61,13 +61,16 @@ int mfma_head_groups(const dq_format* f, int q_heads, int kv_heads, int* heads_p
 // single groups take more than one workgroup a compute unit already (kv heads of all sequences x 8 query heads x tokens, 4 bits: 256 x 8 x
 // 512 9.7 us one by one, 8.6 by two; 128 x 8 x 1024: 8.2, 11.3), or there are tiles enough to fill the chip either way (64 x 8 x 32768:
 // 64.5, 55; 64 x 8 x 8192: 22.2, 22.8; two step groups 64 x 4 x 16384: 35.0, 32.1; 96 x 4 x 8192: 31.8, 28.1; 128 x 4 x 4096: 20.2,
-// 21.0; 8 bits, whose stream, twice through the L2, bounds it sooner: 64 x 8 x 3072: 22.3, 20.7; 64 x 8 x 1024: 12.4, 15.1).  Over 500
-// sizes measured in both: none slower than one by one by 2 %, at most 11 % behind the better of the two.
+// 21.0; 8 bits, whose stream, twice through the L2, bounds it sooner: 64 x 8 x 3072: 22.3, 20.7; 64 x 8 x 1024: 12.4, 15.1).  8 bits
+// hold one wave a SIMD, so 257 workgroups and more take a second round; with two step groups and up to three tiles one by one was up to
+// 5 % faster there up to 400 (136 x 8 x 256: 17.3, 18.0; 208 x 8 x 256, 416 workgroups: 22.6, 19.2).  Over 729 sizes measured in both: none
+// slower than one by one by more than 2 %, at most 11 % behind the better of the two.
 bool mfma_two_groups(const dq_format* f, int batch, int q_heads, int kv_heads, int max_tiles, bool tail) {
   int per_group = 0;
   const int groups = mfma_head_groups(f, q_heads, kv_heads, &per_group);
   if (tail || mfma_pair_heads(f, q_heads, kv_heads) || per_group != (f->group == 128 ? 4 : 2) || groups % 2 || f->i3 != 1) return false;
   const long units = (long)batch * kv_heads * (groups / 2);
+  if (f->bits == 8 && f->group == 64 && max_tiles < 4 && units > 256 && units <= 400) return false;
   return (2 * units > 256 && (max_tiles >= 4 || f->bits == 8)) || units * max_tiles > (f->bits == 8 ? 1024 : f->group == 64 ? 5000 : 8192);
 }
 

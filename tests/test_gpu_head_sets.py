@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
     (4, 128, 8, 17, 4, 1), (4, 128, 8, 16, 4, 0), (4, 128, 5, 17, 5, 1), (4, 128, 13, 17, 4, 1), (4, 128, 8, 33, 3, 0), (2, 128, 8, 17, 4, 1),
     (2, 128, 7, 17, 4, 1), (8, 128, 8, 17, 1, 1), (8, 128, 8, 17, 4, 1), (8, 128, 6, 5, 33, 1), (4, 128, 8, 2, 513, 1),
     (4, 64, 4, 17, 4, 1), (4, 64, 4, 16, 4, 0), (4, 64, 3, 17, 5, 1), (4, 64, 7, 17, 4, 1), (2, 64, 4, 17, 4, 1), (2, 64, 8, 17, 4, 1), (8, 64, 4, 17, 1, 1),
-    (8, 64, 3, 17, 4, 1), (4, 64, 4, 2, 313, 1), (4, 64, 2, 5, 5, 0), (2, 64, 2, 5, 5, 0), (8, 64, 2, 5, 5, 0)])
+    (8, 64, 3, 17, 4, 1), (8, 64, 8, 17, 2, 0), (8, 64, 8, 17, 4, 1), (4, 64, 4, 2, 313, 1), (4, 64, 2, 5, 5, 0), (2, 64, 2, 5, 5, 0), (8, 64, 2, 5, 5, 0)])
 def test_two_sets_of_heads_a_workgroup(bits, group, rep, batch, tiles, wide):
     most = 4 if group == 128 else 2
     assert shape(dq, bits, group, rep, batch, tiles)[3] == (2 * most if wide else most)
