@@ -60,7 +60,7 @@ int mfma_head_groups(const dq_format* f, int q_heads, int kv_heads, int* heads_p
 // tile is longer and there are half the workgroups, so a launch that leaves the chip part idle loses by it.  The line lies where
 // single groups take more than one workgroup a compute unit already (kv heads of all sequences x 8 query heads x tokens, 4 bits: 256 x 8 x
 // 512 9.7 us one by one, 8.6 by two; 128 x 8 x 1024: 8.2, 11.3), or there are tiles enough to fill the chip either way (64 x 8 x 32768:
-// 64.5, 55; 64 x 8 x 8192: 22.2, 22.8; two step groups 64 x 4 x 16384: 35.0, 32.1; 96 x 4 x 8192: 31.8, 28.1; 128 x 4 x 4096: 20.2,
+// 64.5, 56; 64 x 8 x 8192: 22.2, 22.8; two step groups 64 x 4 x 16384: 35.0, 32.1; 96 x 4 x 8192: 31.8, 28.1; 128 x 4 x 4096: 20.2,
 // 21.0; 8 bits, whose stream, twice through the L2, bounds it sooner: 64 x 8 x 3072: 22.3, 20.7; 64 x 8 x 1024: 12.4, 15.1).  8 bits
 // hold one wave a SIMD, so 257 workgroups and more take a second round; with two step groups and up to three tiles one by one was up to
 // 5 % faster there up to 400 (136 x 8 x 256: 17.3, 18.0; 208 x 8 x 256, 416 workgroups: 22.6, 19.2).  Over 729 sizes measured in both: none

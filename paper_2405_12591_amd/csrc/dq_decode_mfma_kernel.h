@@ -1,6 +1,6 @@
 // Matrix-core decode attention over the compressed cache for the formats
-//   bits in {2, 4, 8};  group = 128 with 1, 2 or 4 query heads of a kv head per workgroup,
-//                       group = 64  with 1 or 2
+//   bits in {2, 4, 8};  group = 128 with 1, 2 or 4 query heads of a kv head per workgroup, 8 in large launches,
+//                       group = 64  with 1 or 2, 4 in large launches (see HP below),
 // with head_dim = 128, j1 = 16, j2 = 8, block_tokens % 128 == 0, two or three local tensors.
 // More query heads per kv head are served by several workgroups (head groups) over the same codes.
 // Heads of 64 channels (j1 = 8, j2 = 8, group = 64) ride in pairs: two neighbouring kv heads are
@@ -18,11 +18,12 @@
 //   1. folds the keys' small tensor into the query,  q'[r, b2] = sum_b1 T_S^K[b1, r] q[b1, b2]
 //      (one 16x16x16 f16 MFMA per two heads; T_S and q are fp16, so the products are exact),
 //      and writes the limbs of q' * scale * log2(e) as B operands;
-//   2. streams the key codes: S[t][limb] = sum_c (u[t, c] - offset) limb[c]  (16x16x64 i8 MFMA; four heads: the limbs on the left,
+//   2. streams the key codes: S[t][limb] = sum_c (u[t, c] - offset) limb[c]  (16x16x64 i8 MFMA; limbs on the left where all sixteen
+//      columns are in use or one head's stand in all of them, see TURN and SPREAD;
 //      u = code + offset as stored; the offset's share comes from a constant-A MFMA and is the
 //      accumulators' starting value);
-//   3. online softmax with two tokens per lane (scores cross from the MFMA layout through
-//      wave-private LDS); w_t = p_t * step^V_t is cut into limbs, again B columns;
+//   3. online softmax with two tokens per lane (scores cross from the MFMA layout through wave-private LDS; SPREAD: they are
+//      there already), or with eight tokens of one head per lane (TURN); w_t = p_t * step^V_t is cut into limbs, again B columns;
 //   4. streams the value codes (stored token-contiguous): o'[r, b2] = sum_t u[t, r, b2] limb[t]
 //      (several heads, two tensors: with the limbs as the left operand, which leaves a head's limbs in one lane);
 //   5. applies the values' small tensor with fp32 16x16x4 MFMAs,
@@ -214,7 +215,7 @@ __device__ __forceinline__ float pow2i(int e) {
 // HP = 2: two sets of four heads (two step groups: of two) in one workgroup, each with sixteen columns of its own.  What bounded more than four heads per kv head
 // was the stream: every head group asked for the same codes (8 x 64 heads, 8 kv heads, x 32768 tokens: 587 MB through the L2s for 294 MB
 // of cache; 68.5 us with one wave a SIMD, 66.2 with two) and unpacked them.  Here a chunk is asked for and unpacked once and multiplied with both
-// sets: 221 registers, two waves a SIMD.  4 bits 65.4 -> 55 us, 2 bits 52.9 -> 45.5, 8 bits x 8192 tokens 47.4 -> 32.7; two step
+// sets: 221 registers, two waves a SIMD.  4 bits 65.4 -> 56 us, 2 bits 52.9 -> 45.5, 8 bits x 8192 tokens 47.4 -> 32.7; two step
 // groups, 64 x 4 heads x 32768 tokens, 4 bits 65.5 -> 55.2.  Which launches take it: mfma_two_groups (dq_decode_mfma.hip).
 // (two step groups: R counts the heads of both sets)
 template <int BITS, int NG, int RQ, int NW, int TM, bool N3, bool P2, int HP = 1, bool KEEP = false>
@@ -247,7 +248,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   // that asked for them by lane swaps.  Through LDS (8 writes and 32 reads a tile, four reductions' checks instead of one) the wave
   // waited for them: 16 x 32 heads (8 kv heads) x 32768 tokens 92.2 -> 90.5 us, so turned and with the folded query in 8 writes instead of
   // 32; a serving step of 16 sequences of 3000 to 8000 tokens 32.5 -> 31.4; 8 x 32 on 8 heads of 64 channels, 2048 to 4096 tokens
-  // 11.5 -> 11.0.  (Two heads of one step group would leave half the lanes idle in the softmax.)  Two step groups add a swap a token, for the
+  // 11.5 -> 11.0 (10.6 with KEEP).  (Two heads of one step group would leave half the lanes idle in the softmax.)  Two step groups add a swap a token, for the
   // other group's share: 64 x 2 heads x 8192 tokens of two step groups, 4 bits, 24.1 -> 22.1, 64 x 2 x 128 6.1 -> 5.4.
   // (Pairs in 8 bits keep the other order: a lane's two tokens are neighbours there and lie in one line of two 64-byte rows, which two chunks would each ask for half
   // of: 128 units x 64 tiles 66.8 us turned, 50.6 so, 64 x 128 61.1, 47.5.  In 4 and 2 bits turning gains more than that costs, in 4 bits with several
@@ -255,7 +256,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   constexpr bool TURN = (NC == 16 && R >= 2 && !N3 && !(P2 && BITS == 8));
   // One head of one step group fills four of the sixteen columns.  Its limbs stand in all four groups of columns, so that with the score product
   // turned every lane holds the limbs of every eighth token's score, and keeps those of its own two.  Through LDS (8 writes and 8 reads a
-  // tile): 1 x 32 heads x 2999 tokens 7.54 -> 7.41 us, 8 x 32 x 4096 4 bits 24.6 -> 24.4, 8 bits 48.8 -> 48.3.  (Three tensors: 8-bit codes would
+  // tile): 1 x 32 heads x 2999 tokens 7.54 -> 7.41 us, 8 x 32 x 4096 4 bits 24.6 -> 24.4, 8 bits the same.  (Three tensors: 8-bit codes would
   // drop to one wave a SIMD.  Two heads, their limbs in both halves of the columns and a lane swap between them: 14 x 32 64-channel heads x
   // 8442 tokens, 2 bits, 29.5 -> 30.1, so these go through LDS.)
   constexpr bool SPREAD = (NC == 4 && !N3);
