@@ -475,9 +475,12 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
     return KEEP ? *at : __builtin_nontemporal_load(at);
   };
 
-  // The fold's columns are dealt so that the four a lane gets lie side by side in B slots (2-bit codes: two and two).
+  // The fold has its operands the other way round as well, and its columns are dealt so that the four a lane gets lie side by side in B slots
+  // (2-bit codes: two and two).  Three tensors, four heads and a tail do without in 4 and 2 bits: turned, small calls took longer (1 x 32 heads on
+  // 4 x 640 tokens 13.6 us, 13.0 so; over 180 sizes 2.5 %), without a tail shorter (1 x 16 on 4 x 128 7.6, 7.8), in 8 bits 1.3 %.
+  constexpr bool FOLD_TURN = !(N3 && R == 4 && TM != 0 && BITS < 8);
   auto fold_b2 = [](int c) constexpr -> int {   // the b2 of column c (mod 8)
-    return BITS == 4 ? 2 * (c & 3) + (c >> 2) : BITS == 2 ? (c >> 2) * 2 + ((c >> 1) & 1) + 4 * (c & 1) : c;
+    return !FOLD_TURN ? c : BITS == 4 ? 2 * (c & 3) + (c >> 2) : BITS == 2 ? (c >> 2) * 2 + ((c >> 1) & 1) + 4 * (c & 1) : c;
   };
 
   // loop-invariant operands of the fold, q[(b2, head)][k = b1].  The loads go out first (the
@@ -672,7 +675,8 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
       float amax = 0.f, amax_second = 0.f;
 #pragma unroll
       for (int f = 0; f < F; ++f) {
-        fd[f] = __builtin_amdgcn_mfma_f32_16x16x16f16(bq[f], aK, (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        fd[f] = FOLD_TURN ? __builtin_amdgcn_mfma_f32_16x16x16f16(bq[f], aK, (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0)
+                          : __builtin_amdgcn_mfma_f32_16x16x16f16(aK, bq[f], (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
         // a pair of heads: rows r = n of the other head's half are zero by construction; they
         // are set to zero outright so that nothing the other head holds (a NaN, say) gets across
         if (P2 && (n >> 3) != folded_half(f)) fd[f] = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -701,6 +705,20 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
       // B slots go out in one word per limb (byte by byte: 32 writes instead of 8 with four heads).
 #pragma unroll
       for (int f = 0; f < F; ++f) {
+        if constexpr (!FOLD_TURN) {   // lane (n, g) holds rows r = 4 g + i of column n, b2 = n % 8
+          const int hd = 2 * f + (n >> 3);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const uint32_t v = ((uint32_t)(int)__builtin_rintf(fd[f][i] * qn_first) + kDigitBias) ^ kDigitBias;
+            const int r = 4 * g + i;
+            unsigned char* const dst = Qs + CPH * hd * LS + (r >> 1) * 16 + C::slot((r & 1) * 8 + (n & 7));
+            dst[0] = (unsigned char)(v >> 24);
+            dst[LS] = (unsigned char)(v >> 16);
+            dst[2 * LS] = (unsigned char)(v >> 8);
+            dst[3 * LS] = (unsigned char)v;
+          }
+          continue;
+        }
         const int hd = 2 * f + (g >> 1);
         const float qn = (P2 && folded_half(f)) ? qn_second : qn_first;
         uint32_t w[4];
