@@ -43,13 +43,13 @@ LARGE_CONFIGS = ["llama7b_4bit", "llama7b_2bit", "llama13b_mixed", "gqa_long"]
 # cannot host the profiler.  None where no such run exists.
 PROFILED_TRAFFIC_BYTES = {
     ("llama7b_4bit", "mfma"): (71814.0 * 1.9994 + 64.0) * 1024,
-    ("llama7b_2bit", "mfma"): (164017.5 * 1.9997 + 128.0) * 1024,
-    ("llama7b_8bit", "mfma"): (137574.3 * 1.9997 + 64.0) * 1024,
-    ("llama13b_mixed", "mfma"): (152201.9 * 1.9998 + 352.5) * 1024,
-    ("gqa_long", "mfma"): (287280.5 * 1.9999 + 764.0) * 1024,
-    ("gqa8_long", "mfma"): (287660.5 * 1.9999 + 1516.0) * 1024,
-    ("opt_d64_4bit", "mfma"): (71839.5 * 1.9994 + 64.0) * 1024,
-    ("llama7b_4bit_n3", "mfma"): (72857.5 * 1.9994 + 64.0) * 1024,
+    ("llama7b_2bit", "mfma"): (164020.0 * 1.9997 + 128.0) * 1024,
+    ("llama7b_8bit", "mfma"): (137562.2 * 1.9997 + 64.0) * 1024,
+    ("llama13b_mixed", "mfma"): (152201.1 * 1.9998 + 352.5) * 1024,
+    ("gqa_long", "mfma"): (287234.6 * 1.9999 + 764.0) * 1024,
+    ("gqa8_long", "mfma"): (287670.0 * 1.9999 + 1516.0) * 1024,
+    ("opt_d64_4bit", "mfma"): (71843.5 * 1.9994 + 64.0) * 1024,
+    ("llama7b_4bit_n3", "mfma"): (72856.0 * 1.9994 + 64.0) * 1024,
 }
 TRAFFIC_SOURCE = ("profiles/decode_mfma_llama7b_4bit.md, profiles/decode_mfma_other_workloads.md: rocprofv3 --pmc "
                   "FETCH_SIZE (scaled by the read-kernel calibration) + WRITE_SIZE per launch (a constant of the "
