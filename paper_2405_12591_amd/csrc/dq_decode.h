@@ -74,6 +74,7 @@ bool mfma_takes(const dq_format* f, int q_heads, int kv_heads);
 bool mfma_pair_heads(const dq_format* f, int q_heads, int kv_heads);
 int mfma_head_groups(const dq_format* f, int q_heads, int kv_heads, int* heads_per_group);
 bool mfma_two_groups(const dq_format* f, int batch, int q_heads, int kv_heads, int max_tiles, bool tail);
+bool mfma_spread(int units, int max_tiles);
 int choose_splits(const dq_format* f, int batch, int q_heads, int kv_heads, int max_seq_len, bool mfma,
                   bool tail, uint32_t flags, int* nw_out, int* head_groups_out, int* heads_per_group_out);
 

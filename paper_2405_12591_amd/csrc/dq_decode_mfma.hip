@@ -74,6 +74,17 @@ bool mfma_two_groups(const dq_format* f, int batch, int q_heads, int kv_heads, i
   return (2 * units > 256 && (max_tiles >= 4 || f->bits == 8)) || units * max_tiles > (f->bits == 8 ? 1024 : f->group == 64 ? 5000 : 8192);
 }
 
+// One head of one step group in 8 bits (two tensors): whether scores are joined in registers (SPREAD in dq_decode_mfma_kernel.h) or go through LDS.
+// Registers shorten a tile's chain, which counts while a wave has few of them; a launch of more than about 40 tiles a compute unit only waits for
+// memory, which answers the requests of SPREAD (a chunk's key rows are every other line) a little slower.  us, in registers / through LDS, codes from HBM:
+// 64 units x 32 tiles 18.3 / 18.7, 128 x 55 45.1 / 45.3, 256 x 32 48.5 / 48.7, 256 x 40 (10240) 0.2 % for registers; 440 x 59 149.8 / 148.7, 512 x 64
+// 185.5 / 184.5, 200 x 157, lengths from 6000 on, 204.2 / 201.7.  Of 40 sizes measured beyond the line three are slower through LDS, by 0.3 % at most.  (2 bits:
+// 440 x 59 39.4 / 38.7, but 512 x 64 49.0 / 49.6 and 256 x 32 15.3 / 15.5: in registers throughout.)
+bool mfma_spread(int units, int max_tiles) { return (long)units * max_tiles <= 10240; }
+
+// (for tests)
+extern "C" int32_t dq_debug_mfma_spread(int32_t units, int32_t max_tiles) { return mfma_spread(units, max_tiles); }
+
 // defined in dq_decode_mfma_b8.hip, _b4.hip, _b2.hip
 int32_t launch_decode_mfma_b8(const DecodeArgs& a, hipStream_t st);
 int32_t launch_decode_mfma_b4(const DecodeArgs& a, hipStream_t st);

@@ -218,7 +218,7 @@ __device__ __forceinline__ float pow2i(int e) {
 // sets: 221 registers, two waves a SIMD.  4 bits 65.4 -> 56 us, 2 bits 52.9 -> 45.5, 8 bits x 8192 tokens 47.4 -> 32.7; two step
 // groups, 64 x 4 heads x 32768 tokens, 4 bits 65.5 -> 55.2.  Which launches take it: mfma_two_groups (dq_decode_mfma.hip).
 // (two step groups: R counts the heads of both sets)
-template <int BITS, int NG, int RQ, int NW, int TM, bool N3, bool P2, int HP = 1, bool KEEP = false>
+template <int BITS, int NG, int RQ, int NW, int TM, bool N3, bool P2, int HP = 1, bool KEEP = false, bool SP = true>
 __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode_mfma_kernel(DecodeArgs a) {
   constexpr int R = (NG == 2 && HP == 2) ? RQ / 2 : RQ;   // query heads of a set of columns
   static_assert(!P2 || (NG == 2 && (R == 2 || R == 4) && !N3), "a pair of heads is two step groups and two or four query heads");
@@ -259,7 +259,8 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   // tile): 1 x 32 heads x 2999 tokens 7.54 -> 7.41 us, 8 x 32 x 4096 4 bits 24.6 -> 24.4, 8 bits the same.  (Three tensors: 8-bit codes would
   // drop to one wave a SIMD.  Two heads, their limbs in both halves of the columns and a lane swap between them: 14 x 32 64-channel heads x
   // 8442 tokens, 2 bits, 29.5 -> 30.1, so these go through LDS.)
-  constexpr bool SPREAD = (NC == 4 && !N3);
+  // (SP = false: large launches in 8 bits, see mfma_spread)
+  constexpr bool SPREAD = (NC == 4 && !N3 && SP);
   constexpr int PK = JOIN ? 16 / R : 4 / R, NSET = J2 / PK;
   constexpr int TS = 20;                      // floats per (head, b2) of the joined values on their way through LDS (16 rows + pad)
   constexpr int RD = P2 ? 64 : D;             // channels of a real head (output, partials, cache rows)
@@ -1254,7 +1255,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && BITS < 8) ? 2 : 1) void decode
   DQ_STAMP(19);
 }
 #undef DQ_STAMP
-template <int BITS, int NG, int R, int TM, bool N3, bool P2, int HP = 1, bool KEEP = false>
+template <int BITS, int NG, int R, int TM, bool N3, bool P2, int HP = 1, bool KEEP = false, bool SP = true>
 inline void launch_tm(const DecodeArgs& a, hipStream_t st) {
   const int units = a.cache.batch * a.cache.kv_heads / (P2 ? 2 : 1);
   const dim3 grid = a.rows_on_x ? dim3(units * a.head_groups, a.n_split) : dim3(a.n_split, units * a.head_groups);
@@ -1263,24 +1264,28 @@ inline void launch_tm(const DecodeArgs& a, hipStream_t st) {
   // registers, so that width always takes 4 waves)
   if constexpr (BITS < 8) {
     if (a.nw == 8) {
-      hipExtLaunchKernelGGL((decode_mfma_kernel<BITS, NG, R, 8, TM, N3, P2, HP, KEEP>), grid, dim3(512), 0, st, a.ev_start, a.ev_stop, 0, a);
+      hipExtLaunchKernelGGL((decode_mfma_kernel<BITS, NG, R, 8, TM, N3, P2, HP, KEEP, SP>), grid, dim3(512), 0, st, a.ev_start, a.ev_stop, 0, a);
       return;
     }
   }
-  hipExtLaunchKernelGGL((decode_mfma_kernel<BITS, NG, R, 4, TM, N3, P2, HP, KEEP>), grid, dim3(256), 0, st, a.ev_start, a.ev_stop, 0, a);
+  hipExtLaunchKernelGGL((decode_mfma_kernel<BITS, NG, R, 4, TM, N3, P2, HP, KEEP, SP>), grid, dim3(256), 0, st, a.ev_start, a.ev_stop, 0, a);
 }
 
-template <int BITS, int NG, int R, bool N3, bool P2 = false, bool KEEP = false>
+template <int BITS, int NG, int R, bool N3, bool P2 = false, bool KEEP = false, bool SP = true>
 inline void launch_n3(const DecodeArgs& a, hipStream_t st) {
-  if (!a.tail.k_tail) launch_tm<BITS, NG, R, 0, N3, P2, 1, KEEP>(a, st);
-  else if (a.n_split == 1) launch_tm<BITS, NG, R, 1, N3, P2, 1, KEEP>(a, st);
-  else launch_tm<BITS, NG, R, 2, N3, P2, 1, KEEP>(a, st);
+  if (!a.tail.k_tail) launch_tm<BITS, NG, R, 0, N3, P2, 1, KEEP, SP>(a, st);
+  else if (a.n_split == 1) launch_tm<BITS, NG, R, 1, N3, P2, 1, KEEP, SP>(a, st);
+  else launch_tm<BITS, NG, R, 2, N3, P2, 1, KEEP, SP>(a, st);
 }
 
 template <int BITS, int NG, int R>
 inline void launch_r(const DecodeArgs& a, hipStream_t st) {
-  if (a.fmt.i3 == kRun) launch_n3<BITS, NG, R, true>(a, st);
-  else launch_n3<BITS, NG, R, false>(a, st);
+  if (a.fmt.i3 == kRun) return launch_n3<BITS, NG, R, true>(a, st);
+  if constexpr (BITS == 8 && NG == 1 && R == 1) {
+    if (!mfma_spread(a.cache.batch * a.cache.kv_heads, (a.max_seq_len + kTileTokens - 1) / kTileTokens))
+      return launch_n3<BITS, NG, R, false, false, false, false>(a, st);
+  }
+  launch_n3<BITS, NG, R, false>(a, st);
 }
 
 template <int BITS>
